@@ -137,40 +137,42 @@ hipError_t launch_state_init(LayerState *state, int n_layers, const int32_t *ini
                              hipStream_t s);
 // ---- prompt phase (expert_batch.hip): a batch of tokens through one layer ----
 constexpr int kMaxBatch = 128;        // tokens per moe_route_batch / moe_expert_forward_batch call
-// records of one expert handled by one workgroup of the batched expert kernel: the host picks a multiple of 16 between
-// kBatchMinUnitRecords and kBatchMaxUnitRecords per launch; buffers are sized for kBatchUnitRecords and up
-constexpr int kBatchUnitRecords = 128;
-constexpr int kBatchMinUnitRecords = 32;
-constexpr int kBatchMaxUnitRecords = 512;
-// up to 16 tokens routed to one expert (or any 16 tokens, for the shared expert) and their weights for it
-struct TokenTile {
-  int32_t tok[16];
-  float w[16];
-  int32_t n, pad[3];
+// the selection of a batch as the expert kernels read it (slots and weights by selection order, 0xff = none)
+struct BatchSel {
+  uint8_t slot[kMaxBatch][MOE_MAX_TOPK];
+  float weight[kMaxBatch][MOE_MAX_TOPK];
 };
-// one workgroup's work: n_rec (a multiple of 16) records from rec0 of the expert in `slot` (-1: the shared expert),
-// applied to the tokens of tile `tile`
-struct BatchUnit {
-  int32_t slot, rec0, n_rec, tile;
+// one expert of a launch: its slot (-1: the shared expert), how many tokens of the segment take it, where its h starts
+// (in blocks of 16 tokens x 32 records x 3 bf16 = 3 KB) and its first workgroup in the two launches
+struct BatchEntry {
+  int16_t slot;
+  uint16_t n_tok;
+  uint32_t h_base, unit0_up, unit0_down;
 };
+constexpr int kMaxEntries = MOE_MAX_EXPERTS + 1;
+constexpr int kMaxPartialRows = 4096;  // rows of P of a segment (P: [rows][hidden] fp32)
 struct BatchParams {
   const uint8_t *slot_pool, *shared_blob;
-  const uint16_t *x;  // [B, d] bf16
-  float *partial;     // [n_units][16][d] fp32: every unit's output tile
-  const BatchUnit *units;
-  const TokenTile *tiles;
-  int32_t hidden, inter, shared_inter;
-  int32_t n_units, unit_base;  // the launch covers units unit_base .. unit_base + n_units - 1
+  const uint16_t *x;    // [B, d] bf16
+  const BatchSel *sel;
+  uint8_t *h;           // see up_batch_kernel
+  float *partial;       // P
   int64_t slot_bytes;
+  int32_t hidden, inter, shared_inter, top_k;
+  int32_t t0, t1;       // tokens of the segment
+  int32_t up_records;   // records per unit of up_batch_kernel (a multiple of 32)
+  int32_t down_groups;  // groups of 32 records per unit of down_batch_kernel
+  int32_t shared_row0;  // first row of the shared expert in P
+  int32_t n_entries;
+  BatchEntry e[kMaxEntries];
 };
 bool batch_shape_supported(int weight_fmt, int act_fmt, int hidden, int inter, int shared_inter);
 hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, int B, int N, int hidden, hipStream_t s);
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              hipStream_t s);
-hipError_t launch_expert_batch(const BatchParams &p, hipStream_t s);
-// y[t_first + t] = sum of the partial rows contrib[t][0 .. n_contrib[t]) in that order, for t < n_tokens
-hipError_t launch_reduce_batch(const float *partial, const int32_t *contrib, const int32_t *n_contrib, int max_contrib,
-                               void *y, int hidden, int t_first, int n_tokens, hipStream_t s);
+                              BatchSel *sel, hipStream_t s);
+hipError_t launch_up_batch(const BatchParams &p, int n_units, hipStream_t s);
+hipError_t launch_down_batch(const BatchParams &p, int n_units, hipStream_t s);
+hipError_t launch_reduce_batch(const BatchParams &p, void *y, int n_rc, int n_rc_shared, hipStream_t s);
 
 // the allocation-free entry point (expert_static.hip): device address of its fixed scratch array and the compute-unit
 // count of device `dev` (which must be current), looked up once per device

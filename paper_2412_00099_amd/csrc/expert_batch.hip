@@ -10,15 +10,9 @@
 //  route_batch_kernel  sixteen wavefronts route sixteen tokens at a time through rt::route_wave against the current
 //                      cache state; a token that misses an expert is routed alone and updates the state (see there);
 //                      one routing record per token.
-//  expert_batch_kernel one workgroup (8 wavefronts) per unit = (expert blob, up to 128 consecutive records, tile of up
-//                      to 16 tokens routed to that expert).  Per block of 16 records: all its weights are requested
-//                      at once; g, u = W_gate/up block x X tile^T with the 16x16x32 bf16 MFMA, the hidden dimension
-//                      split over the wavefronts and summed through LDS; h = silu(g) u w; then the block's columns of
-//                      W_down (the record layout keeps them as rows) are applied with the 16x16x4 fp32 MFMA, whose
-//                      operands hold one value per lane, so the rows need no transposition; each wavefront owns d/8
-//                      output columns and keeps their 16-token accumulators in registers over the whole unit.  Every
-//                      unit writes its 16 x d tile to its own rows of a partial buffer.
-//  reduce_batch_kernel adds each token's partial rows in a fixed order (deterministic y) and rounds to bf16.
+//  up_batch_kernel, down_batch_kernel, reduce_batch_kernel
+//                      the experts as two weights-stationary products over the tokens routed to them, and the sum per
+//                      token in a fixed order (deterministic y).
 #include <type_traits>
 
 #include "common.h"
@@ -34,10 +28,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 // ---- gate logits of the batch -------------------------------------------------------------------
 // grid = (token tiles of 16, expert tiles of 16), block = kGateSplit wavefronts: wavefront ks multiplies the ks-th
 // part of the hidden dimension, all its operands requested at once (one round trip); the parts are added through LDS
@@ -115,8 +105,17 @@ __device__ __forceinline__ rt::CacheRegs batch_cache_regs(const BatchCacheState 
   return cr;
 }
 
+// what the expert kernels need of a token's record: its slots and weights in selection order
+__device__ __forceinline__ void store_sel(const uint32_t *rec, int K, int lane, int t, BatchSel *sel) {
+  if (lane < MOE_MAX_TOPK) {
+    sel->slot[t][lane] = lane < K ? (uint8_t)rec[rt::W_SLOT + lane] : (uint8_t)0xff;
+    sel->weight[t][lane] = __uint_as_float(rec[rt::W_WEIGHT + lane]);
+  }
+}
+
 __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RouteParams p, const float *logits, int B,
-                                                                         LayerState *st, moe_route_out_t *out) {
+                                                                         LayerState *st, moe_route_out_t *out,
+                                                                         BatchSel *sel) {
   __shared__ float z_all[kMaxBatch * MOE_MAX_EXPERTS];
   __shared__ float range_s[kMaxBatch];
   __shared__ float dsum_s[kMaxBatch + 1];  // Eq. 10's sum before token t
@@ -181,6 +180,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
       if (lane < rt::kRecWords / 4)
         reinterpret_cast<u32x4 *>(out + t)[lane] = reinterpret_cast<const u32x4 *>(stage_s[wave])[lane];
       if (lane < N && next.stamp != cr.stamp) atomicMax(&cs.stamp[lane], (long long)next.stamp);
+      store_sel(stage_s[wave], K, lane, t, sel);
     }
     if (tid < 2) cs.counter[tid] += (long long)K * (fm - t0);  // selections and hits
     __syncthreads();
@@ -191,6 +191,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
         cr = batch_cache_regs(cs, lane, fm, dsum_s[fm]);
         rt::route_wave(p, z_all + fm * MOE_MAX_EXPERTS, cr, st, out + fm, nullptr, asm_s[0], lane,
                        rt::BoundaryFlags{nullptr, 0}, &next, false);
+        store_sel(asm_s[0], K, lane, fm, sel);
         cs.my_slot[lane] = next.my_slot;
         cs.slot_exp[lane] = next.slot_exp;
         cs.born[lane] = next.born;
@@ -219,196 +220,405 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
 }
 
 // ---- experts of the batch ---------------------------------------------------------------------------
-constexpr int kBatchWaves = 8;
-constexpr int kXPad = 8;  // bf16 elements of padding per X row in LDS (16 bytes: rows start in different banks)
+// Two weights-stationary products per expert over the tokens routed to it (tiles of 16 tokens, up to kGroupTiles of
+// them per unit), each weight read once per 64 tokens:
+//   up_batch_kernel    h[token][record] = silu(gate . x) (up . x) w           unit = (expert, block of records)
+//   down_batch_kernel  P[token, expert][column] = sum of h[token][record] down[record][column]
+//                                                                  unit = (expert, 256 columns, block of records)
+//   reduce_batch_kernel adds a token's rows of P in a fixed order and rounds to bf16.
+// What bounds them: HBM, and below it what one compute unit's L1 can keep in flight (about 58 KB, 23-38 GB/s), so
+// every compute unit has to stream evenly and nothing may be read twice.  Hence a workgroup of four wavefronts with
+// the whole register file (one wavefront per SIMD): the tokens' activations (up) and the output tile (down) of 64
+// tokens stay in registers for the unit, no weights are staged through LDS, and no barrier stands in the load
+// stream except one per 16 records of `up`.  A unit finds its tokens itself from the selected slots (1 KB): no tables
+// are made on the host or sent.  Measured (60 experts of 1408, shared 5632, top-4, d = 2048; both kernels): 19 distinct
+// experts, 128 tokens, 399 MB: 63 + 42 us, against 203 us for one fused kernel over tiles of 16 tokens with the down
+// projection on the fp32 matrix instruction; 8 experts, 8 tokens, 208 MB: 28 + 16 us against 47 us.
+constexpr int kBWaves = 4;
+constexpr int kGroupTiles = 4;  // token tiles per unit
 
-// CBW: blocks of 128 output columns per wavefront (d = 8 * 128 * CBW)
-template <int CBW>
-__global__ __launch_bounds__(kBatchWaves *kWave) void expert_batch_kernel(BatchParams p) {
-  constexpr int NW = kBatchWaves;
-  constexpr int D = NW * 128 * CBW;   // hidden size
-  constexpr int KS = D / (NW * 32);   // 32-column steps of the gate / up products per wavefront
-  constexpr int XS = D + kXPad;       // LDS row stride of the X tile, in bf16 elements
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  uint16_t *xs = reinterpret_cast<uint16_t *>(lds);                              // [16][XS] bf16
-  f32x4 *red = reinterpret_cast<f32x4 *>(lds + 16 * XS * 2);                     // [2][NW][2][64]
-  float *hs = reinterpret_cast<float *>(lds + 16 * XS * 2 + 2 * NW * 2 * 64 * 16);  // [NW][16][16]
+// LDS-only workgroup barrier: does not wait for loads or stores to memory in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int unit = p.unit_base + (int)blockIdx.x;
-  const BatchUnit u = p.units[unit];
-  const TokenTile *tile = p.tiles + u.tile;
-  const int n_tok = tile->n;
-  const uint8_t *blob = u.slot < 0 ? p.shared_blob : p.slot_pool + (int64_t)u.slot * p.slot_bytes;
-  const int64_t row_bytes = (int64_t)D * 2, rec_bytes = 3 * row_bytes;
-  const float wt = (lane & 15) < n_tok ? tile->w[lane & 15] : 0.f;  // weight of token lane % 16 for this expert
+struct UnitPos {
+  int entry, unit;  // index into BatchParams::e, and the unit's place inside that entry
+};
+// the entry a workgroup belongs to: the last one whose first unit is not beyond it
+template <bool DOWN>
+__device__ __forceinline__ UnitPos find_unit(const BatchParams &p, int block, int lane) {
+  int at = 0;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int i = lane + 64 * j;
+    const int i_c = i < p.n_entries ? i : 0;
+    const uint32_t u0 = DOWN ? p.e[i_c].unit0_down : p.e[i_c].unit0_up;
+    at += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(i < p.n_entries && (int)u0 <= block));
+  }
+  at = __builtin_amdgcn_readfirstlane(at - 1);
+  return UnitPos{at, block - (int)(DOWN ? p.e[at].unit0_down : p.e[at].unit0_up)};
+}
 
+// Position of a unit: units of an expert with several token groups are laid out in blocks of 8 x groups, so that the
+// groups reading the same weights sit 8 workgroups apart - on one XCD, where they share them in its L2.
+struct GroupPos {
+  int part, group;
+};
+__device__ __forceinline__ GroupPos group_pos(int unit, int groups) {
+  if (groups == 1) return GroupPos{unit, 0};
+  const int blk = unit / (8 * groups), r = unit - blk * 8 * groups;
+  return GroupPos{blk * 8 + (r & 7), r >> 3};
+}
 
-  f32x4 acc[CBW][8];
+// The tokens of group `group` of an expert, in token order: list[i] = token * 8 + k (k: the expert's place in the
+// token's selection), by one wavefront into LDS of its own.  list has 64 entries; unused ones repeat the first.
+__device__ __forceinline__ void token_list(const BatchParams &p, int slot, int group, int n, int lane, uint16_t *list) {
+  if (slot < 0) {
+    const int t = p.t0 + group * 64 + lane;
+    list[lane] = (uint16_t)((lane < n ? t : p.t0 + group * 64) * 8);
+  } else {
+    int seen = -64 * group;
+    uint64_t sel[2];
 #pragma unroll
-  for (int cb = 0; cb < CBW; ++cb)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[cb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int m16 = lane & 15, kq = lane >> 4;
-  float *hw = hs + wave * 256;
-  // The loads of a block: gate and up rows for this wavefront's slice of the hidden dimension, and its columns of the
-  // down rows.  They are requested as early as their registers are free - gate / up of the next block right after
-  // this block's gate / up products, down of the next block right after this block's down products - so that the
-  // barrier, the reduction and the arithmetic of a block overlap the transfer of the next.
-  u32x4 ag[KS], au[KS], dn[4][CBW];
-  auto load_gu = [&](int r0) {
-    const uint8_t *row = blob + (int64_t)(r0 + m16) * rec_bytes + ((int64_t)wave * (D / NW) + kq * 8) * 2;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      // (plain loads, not the streaming ones: a load covers 64 bytes of each of 16 rows, and the other half of every
-      // 128-byte line is wanted by the next step - with an L1 allocation it is found there; measured 10 % faster)
-      ag[s] = *reinterpret_cast<const u32x4 *>(row + s * 64);
-      au[s] = *reinterpret_cast<const u32x4 *>(row + row_bytes + s * 64);
+    for (int j = 0; j < 2; ++j) {
+      const int t = min(p.t0 + 64 * j + lane, kMaxBatch - 1);
+      sel[j] = *reinterpret_cast<const uint64_t *>(p.sel->slot[t]);
     }
-  };
-  auto load_dn = [&](int r0) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const uint8_t *drow = blob + (int64_t)(r0 + 4 * s + kq) * rec_bytes + 2 * row_bytes +
-                            ((int64_t)wave * (D / NW) + m16 * 8) * 2;
-#pragma unroll
-      for (int cb = 0; cb < CBW; ++cb) dn[s][cb] = stream_load(reinterpret_cast<const u32x4 *>(drow + cb * 256));
-    }
-  };
-  const uint16_t *xrow = xs + m16 * XS + wave * (D / NW) + kq * 8;
-  int parity = 0;
-  // one block of 16 records; NEXT: there is a block after it, whose loads are requested on the way
-  auto block = [&](int r_next, auto next_tag) {
-    constexpr bool NEXT = decltype(next_tag)::value;
-    // gate / up: this wavefront's slice of the hidden dimension
-    f32x4 g = {0.f, 0.f, 0.f, 0.f}, up = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const u32x4 b = *reinterpret_cast<const u32x4 *>(xrow + s * 32);
-      g = mfma_bf16(ag[s], b, g);
-      up = mfma_bf16(au[s], b, up);
-    }
-    if constexpr (NEXT) load_gu(r_next);
-    f32x4 *rb = red + (size_t)parity * (NW * 2 * 64);
-    parity ^= 1;
-    rb[(wave * 2 + 0) * 64 + lane] = g;
-    rb[(wave * 2 + 1) * 64 + lane] = up;
-    // (the buffer alternates between blocks, so one barrier per block is enough; it waits for LDS only, not for
-    // the weight loads in flight)
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    g = rb[lane];
-    up = rb[64 + lane];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      const f32x4 tg = rb[(w * 2 + 0) * 64 + lane], tu = rb[(w * 2 + 1) * 64 + lane];
-      g += tg;
-      up += tu;
-    }
-    // h for records 4 (lane / 16) + v and token lane % 16, stored as [record][token] for this wavefront
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const float h = g[v] / (1.f + __expf(-g[v])) * up[v] * wt;
-      hw[(4 * kq + v) * 16 + m16] = h;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    if (lane >= n) list[lane] = 0;
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // down: y[token][column] += sum over the block's records of h[record][token] * W_down[column][record]
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const float a = hw[(4 * s + kq) * 16 + m16];  // A operand: token lane % 16, record 4 s + lane / 16
+    for (int j = 0; j < 2; ++j) {
+      const int t = p.t0 + 64 * j + lane;
+      int k = -1;
 #pragma unroll
-      for (int cb = 0; cb < CBW; ++cb) {
-        const uint32_t w4[4] = {dn[s][cb].x, dn[s][cb].y, dn[s][cb].z, dn[s][cb].w};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float b = (j & 1) ? bf16_hi(w4[j >> 1]) : bf16_lo(w4[j >> 1]);
-          acc[cb][j] = mfma_f32(a, b, acc[cb][j]);
-        }
-      }
-    }
-    if constexpr (NEXT) load_dn(r_next);
-    __builtin_amdgcn_wave_barrier();
-  };
-  // the first block's weights do not depend on the tokens: requested before the X tile is staged
-  load_gu(u.rec0);
-  load_dn(u.rec0);
-  // X tile: row t = activations of the tile's t-th token (zeros past the last token); a thread's token indices first,
-  // then all its chunks of x at once (two round trips in all)
-  {
-    constexpr int PT = 16 * (D / 8) / (NW * kWave);  // 16-byte chunks per thread
-    int tok_of[PT];
-#pragma unroll
-    for (int i = 0; i < PT; ++i) {
-      const int t = (tid + i * NW * kWave) / (D / 8);
-      tok_of[i] = tile->tok[t < n_tok ? t : 0];
-    }
-    u32x4 v[PT];
-#pragma unroll
-    for (int i = 0; i < PT; ++i) {
-      const int c = tid + i * NW * kWave, t = c / (D / 8), k8 = c - t * (D / 8);
-      v[i] = *(reinterpret_cast<const u32x4 *>(p.x + (size_t)tok_of[i] * D) + k8);
-      if (t >= n_tok) v[i] = u32x4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int i = 0; i < PT; ++i) {
-      const int c = tid + i * NW * kWave, t = c / (D / 8), k8 = c - t * (D / 8);
-      *reinterpret_cast<u32x4 *>(xs + t * XS + k8 * 8) = v[i];
+      for (int i = 0; i < MOE_MAX_TOPK; ++i)
+        if (i < p.top_k && (int)((sel[j] >> (8 * i)) & 0xffu) == slot) k = i;
+      const bool mine = t < p.t1 && k >= 0;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(mine);
+      const int at = seen + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+      if (mine && at >= 0 && at < 64) list[at] = (uint16_t)(t * 8 + k);
+      seen += (int)__builtin_popcountll(m);
     }
   }
-  __syncthreads();
-  for (int blk = 16; blk < u.n_rec; blk += 16) block(u.rec0 + blk, std::true_type{});
-  block(0, std::false_type{});
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-  // The unit's tile goes to its own rows of the partial buffer (result lane l: tokens 4 (l / 16) + v, column
-  // wave * d/8 + cb * 128 + (l % 16) * 8 + j); reduce_batch_kernel adds the tiles of a token in a fixed order.
+// h as three bf16 values that add up to it exactly (8 + 8 + 8 significant bits, truncated): the down projection runs
+// on the bf16 matrix instruction with the precision of a 32-bit h (weights are bf16, products exact, fp32 sums).
+__device__ __forceinline__ void split3(float h, uint32_t &a, uint32_t &b, uint32_t &c) {
+  const uint32_t u = __float_as_uint(h);
+  if ((u & 0x7f800000u) == 0x7f800000u) {  // infinity and NaN stay what they are
+    a = (u >> 16) | ((u & 0x007fffffu) ? 0x40u : 0u);
+    b = c = 0u;
+    return;
+  }
+  const float r1 = h - __uint_as_float(u & 0xffff0000u);
+  const uint32_t u1 = __float_as_uint(r1);
+  const float r2 = r1 - __uint_as_float(u1 & 0xffff0000u);
+  a = u >> 16;
+  b = u1 >> 16;
+  c = __float_as_uint(r2) >> 16;
+}
+
+// D: hidden size.  Wavefront w owns the w-th quarter of the hidden dimension: the tokens' activations there stay in
+// registers (B operands), the gate and up rows of 16 records at a time are streamed (A operands), in two halves whose
+// loads are requested as soon as the registers are free.  The four partial sums meet in LDS (double buffer, one
+// barrier per 16 records); wavefront i then finishes token tile i: h, split in three, to memory in the order in which
+// down_batch_kernel reads it: per (token tile, 32 records) three blocks of [lane][8] bf16, lane = 16 (record / 8) +
+// token.
+template <int D, int NT>
+__device__ __forceinline__ void up_unit(const BatchParams &p, const BatchEntry &e, int part, int group, int lane, int wave,
+                                        f32x4 *red, uint16_t *list) {
+  constexpr int KQ = D / kBWaves, KS = KQ / 32, HS = KS / 2;
+  const int rows = e.slot < 0 ? p.shared_inter : p.inter;
+  const int rec0 = part * p.up_records, n_blk = (min(p.up_records, rows - rec0)) / 16;
+  const uint8_t *blob = e.slot < 0 ? p.shared_blob : p.slot_pool + (int64_t)e.slot * p.slot_bytes;
+  const int64_t row_bytes = (int64_t)D * 2, rec_bytes = 3 * row_bytes;
+  const int m16 = lane & 15, kq = lane >> 4;
+  const int n_tok = min((int)e.n_tok - 64 * group, 64);
+
+  const uint8_t *row = blob + (int64_t)(rec0 + m16) * rec_bytes + ((int64_t)wave * KQ + kq * 8) * 2;
+  u32x4 g0[HS], u0[HS], g1[HS], u1[HS];
+  auto load = [&](const uint8_t *q, u32x4 *g, u32x4 *u) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int t = 4 * kq + v;
-    if (t < n_tok) {
-      float *yrow = p.partial + ((size_t)unit * 16 + t) * D + wave * (D / NW) + m16 * 8;
+    for (int s = 0; s < HS; ++s) {
+      // (plain loads, not streaming ones: a load covers 64 bytes of each of 16 rows, the next one the other half of
+      // the same 128-byte lines)
+      g[s] = *reinterpret_cast<const u32x4 *>(q + s * 64);
+      u[s] = *reinterpret_cast<const u32x4 *>(q + row_bytes + s * 64);
+    }
+  };
+  load(row, g0, u0);
+  load(row + HS * 64, g1, u1);
+
+  token_list(p, e.slot, group, n_tok, lane, list);
+  u32x4 x[NT][KS];
 #pragma unroll
-      for (int cb = 0; cb < CBW; ++cb) {
-        *reinterpret_cast<f32x4 *>(yrow + cb * 128) = f32x4{acc[cb][0][v], acc[cb][1][v], acc[cb][2][v], acc[cb][3][v]};
-        *reinterpret_cast<f32x4 *>(yrow + cb * 128 + 4) = f32x4{acc[cb][4][v], acc[cb][5][v], acc[cb][6][v], acc[cb][7][v]};
+  for (int i = 0; i < NT; ++i) {
+    const int t = list[i * 16 + m16] >> 3;
+    const uint16_t *xr = p.x + (size_t)t * D + wave * KQ + kq * 8;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) x[i][s] = *reinterpret_cast<const u32x4 *>(xr + s * 32);
+  }
+  // what this wavefront finishes: token tile `wave` (if there is one)
+  const int my = list[min(wave, NT - 1) * 16 + m16];
+  const float wt = e.slot < 0 ? 1.f : p.sel->weight[my >> 3][my & 7];
+  const int n32 = (rows + 31) / 32;
+  uint8_t *hb = p.h + ((int64_t)e.h_base + (int64_t)(group * kGroupTiles + wave) * n32) * 3072;
+
+  int parity = 0;
+  auto block = [&](int blk, auto next_tag) {
+    constexpr bool NEXT = decltype(next_tag)::value;
+    f32x4 g[NT], u[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) g[i] = u[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < HS; ++s)
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        g[i] = mfma_bf16(g0[s], x[i][s], g[i]);
+        u[i] = mfma_bf16(u0[s], x[i][s], u[i]);
       }
+    row += 16 * rec_bytes;
+    if constexpr (NEXT) load(row, g0, u0);
+#pragma unroll
+    for (int s = 0; s < HS; ++s)
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        g[i] = mfma_bf16(g1[s], x[i][HS + s], g[i]);
+        u[i] = mfma_bf16(u1[s], x[i][HS + s], u[i]);
+      }
+    if constexpr (NEXT) load(row + HS * 64, g1, u1);
+    f32x4 *rb = red + (size_t)parity * (kBWaves * 2 * NT * 64);
+    parity ^= 1;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      rb[((wave * NT + i) * 2 + 0) * 64 + lane] = g[i];
+      rb[((wave * NT + i) * 2 + 1) * 64 + lane] = u[i];
+    }
+    lds_barrier();
+    if (wave < NT && wave * 16 < n_tok) {
+      f32x4 gs = rb[wave * 2 * 64 + lane], us = rb[(wave * 2 + 1) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < kBWaves; ++w) {
+        gs += rb[((w * NT + wave) * 2 + 0) * 64 + lane];
+        us += rb[((w * NT + wave) * 2 + 1) * 64 + lane];
+      }
+      // records 4 kq + v of the block, token m16 of the tile
+      uint32_t a[4], b[4], c[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) split3(gs[v] / (1.f + __expf(-gs[v])) * us[v] * wt, a[v], b[v], c[v]);
+      const int rec = rec0 + blk * 16;
+      uint8_t *o = hb + (int64_t)(rec >> 5) * 3072 + (((rec >> 3) & 3) + (kq >> 1)) * 256 + m16 * 16 + (kq & 1) * 8;
+      *reinterpret_cast<u32x2 *>(o) = u32x2{a[0] | (a[1] << 16), a[2] | (a[3] << 16)};
+      *reinterpret_cast<u32x2 *>(o + 1024) = u32x2{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
+      *reinterpret_cast<u32x2 *>(o + 2048) = u32x2{c[0] | (c[1] << 16), c[2] | (c[3] << 16)};
+      if (rec + 16 == rows && (rows & 31)) {  // the second half of the last 32 records does not exist: zeros
+        const u32x2 zero = {0u, 0u};
+        *reinterpret_cast<u32x2 *>(o + 512) = zero;
+        *reinterpret_cast<u32x2 *>(o + 512 + 1024) = zero;
+        *reinterpret_cast<u32x2 *>(o + 512 + 2048) = zero;
+      }
+    }
+  };
+  for (int blk = 0; blk + 1 < n_blk; ++blk) block(blk, std::true_type{});
+  block(n_blk - 1, std::false_type{});
+}
+
+template <int D>
+__global__ __launch_bounds__(kBWaves *kWave, 1) void up_batch_kernel(BatchParams p) {
+  __shared__ f32x4 red[2 * kBWaves * 2 * kGroupTiles * 64];
+  __shared__ uint16_t list_s[kBWaves][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const UnitPos up = find_unit<false>(p, blockIdx.x, lane);
+  const BatchEntry e = p.e[up.entry];
+  const int groups = (e.n_tok + 63) / 64;
+  const GroupPos gp = group_pos(up.unit, groups);
+  if (gp.part * p.up_records >= (e.slot < 0 ? p.shared_inter : p.inter)) return;  // padding of the unit grid
+  const int tiles = (min((int)e.n_tok - 64 * gp.group, 64) + 15) / 16;
+  if (tiles == 1) up_unit<D, 1>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+  else if (tiles == 2) up_unit<D, 2>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+  else up_unit<D, 4>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+}
+
+// Eight rows of eight bf16 columns -> eight columns of eight rows, inside a lane: the record layout keeps the columns of
+// W_down as rows, the matrix instruction wants eight consecutive records of one column.
+__device__ __forceinline__ void transpose8(const u32x4 (&r)[8], u32x4 (&c)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c[j][q] = __builtin_amdgcn_perm(r[2 * q + 1][j >> 1], r[2 * q][j >> 1], sel);
+  }
+}
+
+// Wavefront w takes every fourth group of 32 records of the unit's block and accumulates the unit's [tokens][256
+// columns] tile over them in registers; the four tiles are added through LDS at the end.  Lane l loads columns
+// 8 (l % 16) .. + 8 of records 8 (l / 16) + i: full 128-byte lines, each lane an 8 x 8 block that it transposes.
+template <int D, int NT>
+__device__ __forceinline__ void down_unit(const BatchParams &p, const BatchEntry &e, int part, int group, int lane, int wave,
+                                          float *red, uint16_t *list) {
+  constexpr int CBLKS = D / 256;
+  const int rows = e.slot < 0 ? p.shared_inter : p.inter;
+  const int cblk = part % CBLKS, rc = part / CBLKS;
+  const int n32 = (rows + 31) / 32;
+  const int g_begin = rc * p.down_groups, g_end = min(n32, g_begin + p.down_groups);
+  const uint8_t *blob = e.slot < 0 ? p.shared_blob : p.slot_pool + (int64_t)e.slot * p.slot_bytes;
+  const int64_t row_bytes = (int64_t)D * 2, rec_bytes = 3 * row_bytes;
+  const int m16 = lane & 15, kq = lane >> 4;
+  const int n_tok = min((int)e.n_tok - 64 * group, 64), tiles = (n_tok + 15) / 16;
+  const uint8_t *wbase = blob + 2 * row_bytes + (int64_t)cblk * 512;  // the same in every lane
+  const uint8_t *hbase = p.h + ((int64_t)e.h_base + (int64_t)group * kGroupTiles * n32) * 3072;
+
+  u32x4 w0[8], w1[8];  // columns 0..127 and 128..255 of 32 records
+  auto load_w = [&](int g, int c, u32x4 (&w)[8]) {
+    // (in a last group of 16 records the lanes of the missing half read the first half again; zeroed before use)
+    const uint8_t *q = wbase + (int64_t)g * 32 * rec_bytes + c * 256;
+    const uint32_t off = (uint32_t)(g * 32 + 32 > rows ? kq & 1 : kq) * (uint32_t)(8 * rec_bytes) + (uint32_t)m16 * 16u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] = stream_load(reinterpret_cast<const u32x4 *>(q + i * rec_bytes + off));
+  };
+  u32x4 ha[NT][3], hb[NT][3];
+  auto load_h = [&](int g, int q, u32x4 (&h)[NT][3]) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i)  // (tiles past the last repeat it; their rows are not stored)
+      h[i][q] = *reinterpret_cast<const u32x4 *>(hbase + ((int64_t)min(i, tiles - 1) * n32 + g) * 3072 + q * 1024 +
+                                                 (uint32_t)lane * 16u);
+  };
+  f32x4 acc[NT][2][8];
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[i][c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // One group of 32 records; NEXT: there is a group after it, whose loads are requested as registers become free.  The
+  // next h goes to a second set of registers ahead of the next weights (loads complete in order, and h is wanted
+  // first); with four token tiles there is no room for a second set, and h is requested again part by part.
+  constexpr bool TWO = NT <= 2;
+  auto step = [&](int g, u32x4 (&h)[NT][3], u32x4 (&h_next)[NT][3], auto next_tag) {
+    constexpr bool NEXT = decltype(next_tag)::value;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      u32x4 (&w)[8] = c == 0 ? w0 : w1;
+      if (g * 32 + 32 > rows) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (kq >= 2) w[i] = u32x4{0u, 0u, 0u, 0u};
+      }
+      u32x4 col[8];
+      transpose8(w, col);
+      if constexpr (NEXT) {
+        if (TWO && c == 0) {
+#pragma unroll
+          for (int q = 2; q >= 0; --q) load_h(g + kBWaves, q, h_next);
+        }
+        load_w(g + kBWaves, c, w);
+      }
+#pragma unroll
+      for (int q = 2; q >= 0; --q) {  // the small parts first
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) acc[i][c][j] = mfma_bf16(h[i][q], col[j], acc[i][c][j]);
+        if constexpr (NEXT && !TWO)
+          if (c == 1) load_h(g + kBWaves, q, h);
+      }
+    }
+  };
+  int g = g_begin + wave, left = g < g_end ? (g_end - g + kBWaves - 1) / kBWaves : 0;
+  if (left > 0) {
+#pragma unroll
+    for (int q = 2; q >= 0; --q) load_h(g, q, ha);
+    load_w(g, 0, w0);
+    load_w(g, 1, w1);
+    if constexpr (TWO) {
+      for (; left > 2; left -= 2, g += 2 * kBWaves) {
+        step(g, ha, hb, std::true_type{});
+        step(g + kBWaves, hb, ha, std::true_type{});
+      }
+      if (left == 2) {
+        step(g, ha, hb, std::true_type{});
+        step(g + kBWaves, hb, ha, std::false_type{});
+      } else {
+        step(g, ha, hb, std::false_type{});
+      }
+    } else {
+      for (; left > 1; --left, g += kBWaves) step(g, ha, ha, std::true_type{});
+      step(g, ha, ha, std::false_type{});
+    }
+  }
+  // the tiles of the four wavefronts, one token tile at a time: [wave][16 rows][256 columns]
+  token_list(p, e.slot, group, n_tok, lane, list);
+  const int n_seg = p.t1 - p.t0;
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    if (i * 16 >= n_tok) break;
+    if (i > 0) lds_barrier();
+    float *mine = red + wave * 4096;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float *o = mine + (4 * kq + v) * 256 + c * 128 + m16 * 8;
+        *reinterpret_cast<f32x4 *>(o) = f32x4{acc[i][c][0][v], acc[i][c][1][v], acc[i][c][2][v], acc[i][c][3][v]};
+        *reinterpret_cast<f32x4 *>(o + 4) = f32x4{acc[i][c][4][v], acc[i][c][5][v], acc[i][c][6][v], acc[i][c][7][v]};
+      }
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {  // wavefront w: rows w, w + 4, ...
+      const int t16 = r * 4 + wave;
+      if (i * 16 + t16 >= n_tok) break;
+      f32x4 v = *reinterpret_cast<const f32x4 *>(red + t16 * 256 + lane * 4);
+#pragma unroll
+      for (int w = 1; w < kBWaves; ++w) v += *reinterpret_cast<const f32x4 *>(red + w * 4096 + t16 * 256 + lane * 4);
+      const int tk = list[i * 16 + t16], t = (tk >> 3) - p.t0;
+      const int64_t at = e.slot < 0 ? (int64_t)p.shared_row0 + (int64_t)rc * n_seg + t
+                                    : ((int64_t)rc * n_seg + t) * p.top_k + (tk & 7);
+      *reinterpret_cast<f32x4 *>(p.partial + at * D + cblk * 256 + lane * 4) = v;
     }
   }
 }
 
-// y[t] = the sum of token t's partial rows, rounded to bf16.  contrib[t * max_contrib + i] is a row index into the
-// partial buffer (unit * 16 + row of the token in the unit's tile); grid = (tokens, d / 256), eight wavefronts per
-// workgroup: wavefront g adds the g-th eighth of the list in list order (several loads in flight), the eight sums are
-// added in order of g - a fixed tree, so y does not change from run to run.
-constexpr int kReduceGroups = 8;
-__global__ __launch_bounds__(kReduceGroups *kWave) void reduce_batch_kernel(const float *partial, const int32_t *contrib,
-                                                                           const int32_t *n_contrib, int max_contrib,
-                                                                           uint16_t *y, int d, int t_first) {
-  __shared__ f32x4 part_s[kReduceGroups][kWave];
-  const int t = blockIdx.x, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int col = blockIdx.y * 256 + lane * 4;
-  const int32_t *list = contrib + (size_t)t * max_contrib;
-  const int n = n_contrib[t], chunk = (n + kReduceGroups - 1) / kReduceGroups;
-  const int i0 = g * chunk, i1 = min(n, i0 + chunk);
+template <int D>
+__global__ __launch_bounds__(kBWaves *kWave, 1) void down_batch_kernel(BatchParams p) {
+  __shared__ __attribute__((aligned(16))) float red[kBWaves * 4096];
+  __shared__ uint16_t list_s[kBWaves][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const UnitPos up = find_unit<true>(p, blockIdx.x, lane);
+  const BatchEntry e = p.e[up.entry];
+  const int groups = (e.n_tok + 63) / 64;
+  const GroupPos gp = group_pos(up.unit, groups);
+  const int rows = e.slot < 0 ? p.shared_inter : p.inter;
+  if (gp.part / (D / 256) * p.down_groups * 32 >= rows) return;  // padding of the unit grid
+  const int tiles = (min((int)e.n_tok - 64 * gp.group, 64) + 15) / 16;
+  if (tiles == 1) down_unit<D, 1>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+  else if (tiles == 2) down_unit<D, 2>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+  else down_unit<D, 4>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+}
+
+// y[t] = the sum of token t's rows of P - its experts in selection order, each block of records in turn, then the
+// shared expert's blocks - rounded to bf16.  grid = (tokens, d / 256), one wavefront: all of a token's rows are
+// requested eight at a time.
+__global__ __launch_bounds__(kWave) void reduce_batch_kernel(const float *partial, uint16_t *y, int d, int t0, int n_seg, int top_k,
+                                                             int n_rc, int shared_row0, int n_rc_shared) {
+  const int t = blockIdx.x, col = blockIdx.y * 256 + threadIdx.x * 4;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  for (int rc = 0; rc < n_rc; ++rc) {
+    const float *q = partial + ((size_t)(rc * n_seg + t) * top_k) * d + col;
 #pragma unroll 8
-  for (int i = i0; i < i1; ++i) s += *reinterpret_cast<const f32x4 *>(partial + (size_t)list[i] * d + col);
-  part_s[g][lane] = s;
-  __syncthreads();
-  if (g != 0) return;
-#pragma unroll
-  for (int k = 1; k < kReduceGroups; ++k) s += part_s[k][lane];
+    for (int k = 0; k < top_k; ++k) s += *reinterpret_cast<const f32x4 *>(q + (size_t)k * d);
+  }
+  const float *q = partial + ((size_t)shared_row0 + t) * d + col;
+#pragma unroll 8
+  for (int rc = 0; rc < n_rc_shared; ++rc) s += *reinterpret_cast<const f32x4 *>(q + (size_t)rc * n_seg * d);
   u32x2 o;
   o.x = (uint32_t)f32_to_bf16_rne(s[0]) | ((uint32_t)f32_to_bf16_rne(s[1]) << 16);
   o.y = (uint32_t)f32_to_bf16_rne(s[2]) | ((uint32_t)f32_to_bf16_rne(s[3]) << 16);
-  *reinterpret_cast<u32x2 *>(y + (size_t)(t_first + t) * d + col) = o;
-}
-
-template <int CBW>
-constexpr size_t batch_lds_bytes() {
-  return (size_t)16 * (kBatchWaves * 128 * CBW + kXPad) * 2 + 2 * kBatchWaves * 2 * 64 * 16 + kBatchWaves * 256 * 4;
+  *reinterpret_cast<u32x2 *>(y + (size_t)(t0 + t) * d + col) = o;
 }
 
 }  // namespace
@@ -432,38 +642,33 @@ hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, in
 }
 
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              hipStream_t s) {
+                              BatchSel *sel, hipStream_t s) {
   if (B <= 0 || B > kMaxBatch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(route_batch_kernel, dim3(1), dim3(kRouteWaves * kWave), 0, s, p, logits, B, state, out);
+  hipLaunchKernelGGL(route_batch_kernel, dim3(1), dim3(kRouteWaves * kWave), 0, s, p, logits, B, state, out, sel);
   return hipGetLastError();
 }
 
-// the kernel's LDS (X tile, partial sums, h) exceeds the default limit of a launch: raised once per instantiation
-template <int CBW>
-hipError_t launch_expert_batch_t(const BatchParams &p, hipStream_t s) {
-  static bool raised = false;
-  if (!raised) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&expert_batch_kernel<CBW>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)batch_lds_bytes<CBW>());
-    if (e != hipSuccess) return e;
-    raised = true;
-  }
-  hipLaunchKernelGGL(expert_batch_kernel<CBW>, dim3(p.n_units), dim3(kBatchWaves * kWave), batch_lds_bytes<CBW>(), s, p);
+hipError_t launch_up_batch(const BatchParams &p, int n_units, hipStream_t s) {
+  if (n_units <= 0) return hipSuccess;
+  if (p.hidden == 2048) hipLaunchKernelGGL(up_batch_kernel<2048>, dim3(n_units), dim3(kBWaves * kWave), 0, s, p);
+  else if (p.hidden == 1024) hipLaunchKernelGGL(up_batch_kernel<1024>, dim3(n_units), dim3(kBWaves * kWave), 0, s, p);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_expert_batch(const BatchParams &p, hipStream_t s) {
-  if (p.n_units <= 0) return hipSuccess;
-  if (p.hidden == 2048) return launch_expert_batch_t<2>(p, s);
-  if (p.hidden == 1024) return launch_expert_batch_t<1>(p, s);
-  return hipErrorInvalidValue;
+hipError_t launch_down_batch(const BatchParams &p, int n_units, hipStream_t s) {
+  if (n_units <= 0) return hipSuccess;
+  if (p.hidden == 2048) hipLaunchKernelGGL(down_batch_kernel<2048>, dim3(n_units), dim3(kBWaves * kWave), 0, s, p);
+  else if (p.hidden == 1024) hipLaunchKernelGGL(down_batch_kernel<1024>, dim3(n_units), dim3(kBWaves * kWave), 0, s, p);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
-hipError_t launch_reduce_batch(const float *partial, const int32_t *contrib, const int32_t *n_contrib, int max_contrib,
-                               void *y, int hidden, int t_first, int n_tokens, hipStream_t s) {
-  if (n_tokens <= 0) return hipSuccess;
-  hipLaunchKernelGGL(reduce_batch_kernel, dim3(n_tokens, hidden / 256), dim3(kReduceGroups * kWave), 0, s, partial, contrib, n_contrib,
-                     max_contrib, static_cast<uint16_t *>(y), hidden, t_first);
+hipError_t launch_reduce_batch(const BatchParams &p, void *y, int n_rc, int n_rc_shared, hipStream_t s) {
+  const int n_seg = p.t1 - p.t0;
+  if (n_seg <= 0) return hipSuccess;
+  hipLaunchKernelGGL(reduce_batch_kernel, dim3(n_seg, p.hidden / 256), dim3(kWave), 0, s, p.partial, static_cast<uint16_t *>(y),
+                     p.hidden, p.t0, n_seg, p.top_k, n_rc, p.shared_row0, n_rc_shared);
   return hipGetLastError();
 }
 

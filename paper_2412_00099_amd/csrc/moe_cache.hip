@@ -101,21 +101,10 @@ struct moe_cache {
   float *d_logits_batch = nullptr;          // [kMaxBatch][n_experts]
   moe_route_out_t *batch_rec = nullptr;      // [kMaxBatch] the decisions of the batch routed last: pinned host memory
   moe_route_out_t *batch_rec_dev = nullptr;  // the routing kernel's view of it (the records go straight to the host)
-  float *d_bpartial = nullptr;              // [max_units][16][hidden]: the output tile of every unit
-  // the tables of a launch, one block of pinned memory and its device copy (one transfer per launch):
-  //   [max_tiles] tiles | [max_units] units | [kMaxBatch] partial rows per token | [kMaxBatch][max_contrib] their lists
-  uint8_t *h_tables = nullptr, *d_tables = nullptr;
-  size_t off_units = 0, off_contrib = 0;
-  TokenTile *d_tiles = nullptr, *h_tiles = nullptr;
-  BatchUnit *d_units = nullptr, *h_units = nullptr;
-  int32_t *d_contrib = nullptr, *h_contrib = nullptr;
-  int max_tiles = 0, max_units = 0, max_contrib = 0;
+  BatchSel *d_bsel = nullptr;               // the same selection as the expert kernels read it
+  uint8_t *d_bh = nullptr;                  // h of a segment (see up_batch_kernel)
+  float *d_bpartial = nullptr;              // P of a segment: [kMaxPartialRows][hidden]
   int n_cus = 0;
-  std::vector<BatchUnit> units_built;       // the units of a segment in the order they are made (tile by tile)
-  std::vector<int32_t> unit_pos;            // their places in the launch
-  std::vector<int32_t> xcd_queue[8];        // units per XCD, while the launch order is worked out
-  std::vector<int32_t> unit_group_owner;    // per (blob, block of records): the XCD of its group
-  std::vector<int32_t> tile_slot, tile_first_unit;
   int batch_layer = -1, batch_n = 0;
   hipEvent_t ev_batch = nullptr;            // compute stream has finished reading the slots (before fills overwrite them)
 
@@ -314,29 +303,15 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   HIP_INIT(hipMalloc(&c->d_y, sizeof(float) * (size_t)cfg->hidden));
   c->batch_ok = batch_shape_supported(cfg->weight_fmt, cfg->act_fmt, cfg->hidden, cfg->inter, cfg->shared_inter);
   if (c->batch_ok) {
-    // (units of fewer records are only made while a launch stays within one workgroup per compute unit, below)
-    const int chunks = std::max((cfg->inter + kBatchUnitRecords - 1) / kBatchUnitRecords, 1);
-    const int schunks = std::max((cfg->shared_inter + kBatchUnitRecords - 1) / kBatchUnitRecords, cfg->shared_inter > 0 ? 1 : 0);
-    // a tile is 16 tokens of one slot: at most one partly filled tile per slot plus the full ones
-    const int routed_tiles = cfg->capacity + kMaxBatch * cfg->top_k / 16, shared_tiles = kMaxBatch / 16;
-    c->max_tiles = routed_tiles + shared_tiles;
-    c->max_units = std::max(routed_tiles * chunks + shared_tiles * schunks, cus);
+    // a tile is 16 tokens of one expert: at most one partly filled tile per slot plus the full ones
+    const int64_t routed_tiles = cfg->capacity + kMaxBatch * cfg->top_k / 16;
+    const int64_t h_blocks = routed_tiles * ((cfg->inter + 31) / 32) + kMaxBatch / 16 * ((cfg->shared_inter + 31) / 32);
     HIP_INIT(hipMalloc(&c->d_logits_batch, sizeof(float) * kMaxBatch * MOE_MAX_EXPERTS));
     HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->batch_rec), sizeof(moe_route_out_t) * kMaxBatch, hipHostMallocMapped));
     HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->batch_rec_dev), c->batch_rec, 0));
-    c->max_contrib = std::max(cfg->top_k * chunks + schunks, cus);
-    HIP_INIT(hipMalloc(&c->d_bpartial, sizeof(float) * (size_t)c->max_units * 16 * cfg->hidden));
-    c->off_units = (sizeof(TokenTile) * c->max_tiles + 255) / 256 * 256;
-    c->off_contrib = (c->off_units + sizeof(BatchUnit) * c->max_units + 255) / 256 * 256;
-    const size_t table_bytes = c->off_contrib + sizeof(int32_t) * (size_t)kMaxBatch * (c->max_contrib + 1);
-    HIP_INIT(hipMalloc(&c->d_tables, table_bytes));
-    HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->h_tables), table_bytes, hipHostMallocDefault));
-    c->h_tiles = reinterpret_cast<TokenTile *>(c->h_tables);
-    c->d_tiles = reinterpret_cast<TokenTile *>(c->d_tables);
-    c->h_units = reinterpret_cast<BatchUnit *>(c->h_tables + c->off_units);
-    c->d_units = reinterpret_cast<BatchUnit *>(c->d_tables + c->off_units);
-    c->h_contrib = reinterpret_cast<int32_t *>(c->h_tables + c->off_contrib);
-    c->d_contrib = reinterpret_cast<int32_t *>(c->d_tables + c->off_contrib);
+    HIP_INIT(hipMalloc(&c->d_bsel, sizeof(BatchSel)));
+    HIP_INIT(hipMalloc(&c->d_bh, (size_t)h_blocks * 3072));
+    HIP_INIT(hipMalloc(&c->d_bpartial, sizeof(float) * (size_t)kMaxPartialRows * cfg->hidden));
     HIP_INIT(hipEventCreateWithFlags(&c->ev_batch, hipEventDisableTiming));
   }
   HIP_INIT(hipEventCreateWithFlags(&c->ev_route, hipEventDisableTiming));
@@ -364,8 +339,8 @@ void moe_cache_destroy(moe_cache_t *c) {
   if (c->d_logits_batch) (void)hipFree(c->d_logits_batch);
   if (c->batch_rec) (void)hipHostFree(c->batch_rec);
   if (c->d_bpartial) (void)hipFree(c->d_bpartial);
-  if (c->d_tables) (void)hipFree(c->d_tables);
-  if (c->h_tables) (void)hipHostFree(c->h_tables);
+  if (c->d_bsel) (void)hipFree(c->d_bsel);
+  if (c->d_bh) (void)hipFree(c->d_bh);
   if (c->ev_batch) (void)hipEventDestroy(c->ev_batch);
   if (c->ev_route) (void)hipEventDestroy(c->ev_route);
   for (hipEvent_t e : c->ev_copy)
@@ -654,7 +629,7 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
     z = c->d_logits_batch;
   }
   const RouteParams p = make_route_params(c);
-  HIP_TRY(launch_route_batch(p, z, n_tokens, c->d_state + layer, c->batch_rec_dev, c->compute));
+  HIP_TRY(launch_route_batch(p, z, n_tokens, c->d_state + layer, c->batch_rec_dev, c->d_bsel, c->compute));
   HIP_TRY(hipStreamSynchronize(c->compute));
   const moe_cache_config_t &g = c->cfg;
   for (int t = 0; t < n_tokens; ++t)
@@ -669,6 +644,37 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
   return MOE_OK;
 }
 
+namespace {
+struct BatchUnits {
+  int up_records, down_groups;  // records per unit of up_batch_kernel, groups of 32 records per unit of down_batch_kernel
+  int n_rc, n_rc_shared;        // blocks of records of down_batch_kernel per routed expert / of the shared expert
+};
+// A unit costs a start-up of about 3 us and then what its compute unit's L1 takes in (about 23 KB per us: 8 KB a
+// record in `up`, 16 KB a group of 32 records in `down`), and a launch runs in rounds of one workgroup per compute unit:
+// take the sizes with the smallest rounds x unit time, the larger ones where two are equal.  P has to hold the rows.
+BatchUnits batch_units(int groups, int inter, int shared_groups, int shared_inter, int hidden, int n_seg, int top_k, int n_cus) {
+  BatchUnits u{};
+  const auto parts = [](int n, int by) { return (n + by - 1) / by; };
+  const int longest = std::max(inter, shared_groups ? shared_inter : 0);
+  double best = 1e30;
+  for (int cand = 32; cand <= std::min(1024, parts(longest, 32) * 32); cand += 32) {
+    const int units = groups * parts(inter, cand) + shared_groups * parts(shared_inter, cand);
+    const double est = parts(units, n_cus) * (3.0 + 0.36 * hidden / 2048.0 * cand);
+    if (est <= best) best = est, u.up_records = cand;
+  }
+  const int n32 = parts(inter, 32), n32s = shared_groups ? parts(shared_inter, 32) : 0;
+  best = 1e30;
+  for (int cand = 4; cand <= parts(std::max(n32, n32s), 4) * 4; cand += 4) {
+    const int rc = parts(n32, cand), rcs = parts(n32s, cand);
+    if ((int64_t)n_seg * (top_k * rc + rcs) > kMaxPartialRows) continue;
+    const int units = (groups * rc + shared_groups * rcs) * (hidden / 256);
+    const double est = parts(units, n_cus) * (4.0 + 0.7 * cand);
+    if (est <= best) best = est, u.down_groups = cand, u.n_rc = rc, u.n_rc_shared = rcs;
+  }
+  return u;
+}
+}  // namespace
+
 int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, void *y_dev, int32_t n_tokens) {
   if (int rc = check_layer(c, layer)) return rc;
   if (!x_dev || !y_dev) return fail(MOE_EINVAL, "x_dev or y_dev is NULL");
@@ -682,26 +688,30 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
   bp.slot_pool = static_cast<const uint8_t *>(c->slot_pool[layer]);
   bp.shared_blob = g.shared_inter > 0 ? static_cast<const uint8_t *>(c->shared_blob[layer]) : nullptr;
   bp.x = static_cast<const uint16_t *>(x_dev);
+  bp.sel = c->d_bsel;
+  bp.h = c->d_bh;
   bp.partial = c->d_bpartial;
-  bp.units = c->d_units;
-  bp.tiles = c->d_tiles;
+  bp.slot_bytes = (int64_t)slot_bytes;
   bp.hidden = d;
   bp.inter = g.inter;
   bp.shared_inter = g.shared_inter;
-  bp.slot_bytes = (int64_t)slot_bytes;
+  bp.top_k = K;
   // Segments: maximal runs of tokens during which no slot is refilled after a token of the run has read it, so that
-  // all experts a segment needs are in their slots at once.  One expert launch per segment, behind its fills.
+  // all experts a segment needs are in their slots at once.
   int t0 = 0;
-  bool first = true;
   while (t0 < n_tokens) {
     uint64_t read = 0;
+    int n_of_slot[MOE_MAX_EXPERTS] = {};
     int t1 = t0;
     for (; t1 < n_tokens; ++t1) {
       const moe_route_out_t &r = c->batch_rec[t1];
       bool conflict = false;
       for (int k = 0; k < K; ++k) conflict |= r.miss[k] && ((read >> r.sel_slot[k]) & 1);
       if (conflict) break;
-      for (int k = 0; k < K; ++k) read |= 1ull << r.sel_slot[k];
+      for (int k = 0; k < K; ++k) {
+        read |= 1ull << r.sel_slot[k];
+        ++n_of_slot[r.sel_slot[k]];
+      }
     }
     // fills of the segment's misses, once the compute stream has finished with the slots' previous contents
     int n_fill = 0;
@@ -722,152 +732,53 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
       }
     }
     if (n_fill > 0) HIP_TRY(hipEventRecord(c->ev_copy[layer], c->copy));
-    // token tiles per slot and for the shared expert, units per tile; the staging buffers are free again once the
-    // previous segment's copies have been consumed
-    if (!first) HIP_TRY(hipStreamSynchronize(c->compute));
-    first = false;
-    int n_tiles = 0, n_units = 0;
-    const int n_seg = t1 - t0, mc = c->max_contrib;
-    int32_t *n_contrib = c->h_contrib;                 // [kMaxBatch] counts, then the lists
-    int32_t *contrib = c->h_contrib + kMaxBatch;       // [n_seg][mc]
-    for (int i = 0; i < n_seg; ++i) n_contrib[i] = 0;
-    // tiles first: per slot the tokens routed to it, sixteen to a tile; then the shared expert's
-    std::vector<int32_t> &tile_slot = c->tile_slot;  // -1: the shared expert
-    tile_slot.clear();
-    auto new_tile = [&](int slot) -> TokenTile * {
-      if (n_tiles >= c->max_tiles) return nullptr;
-      TokenTile *tile = &c->h_tiles[n_tiles++];
-      memset(tile, 0, sizeof *tile);
-      tile_slot.push_back(slot);
-      return tile;
-    };
-    for (int s = 0; s < g.capacity; ++s) {
-      if (!((read >> s) & 1)) continue;
-      TokenTile *tile = nullptr;
-      for (int t = t0; t < t1; ++t) {
-        const moe_route_out_t &r = c->batch_rec[t];
-        for (int k = 0; k < K; ++k) {
-          if (r.sel_slot[k] != s) continue;
-          if (!tile || tile->n == 16) tile = new_tile(s);
-          if (!tile) return fail(MOE_EHIP, "batch tables overflow (tiles)");
-          tile->tok[tile->n] = t;
-          tile->w[tile->n++] = r.sel_weight[k];
-        }
-      }
+    // Sizes of the units of the two expert kernels (see batch_units): chosen for the whole segment
+    const int n_seg = t1 - t0;
+    bp.t0 = t0;
+    bp.t1 = t1;
+    int one = 0, more = 0;  // experts with one group of 64 tokens, and the groups of those with several (padded below)
+    for (uint64_t m = read; m; m &= m - 1) {
+      const int n = n_of_slot[__builtin_ctzll(m)];
+      if (n <= 64) ++one; else more += (n + 63) / 64;
     }
-    if (g.shared_inter > 0) {
-      for (int t = t0; t < t1; t += 16) {
-        TokenTile *tile = new_tile(-1);
-        if (!tile) return fail(MOE_EHIP, "batch tables overflow (tiles)");
-        for (int i = t; i < std::min(t + 16, t1); ++i) {
-          tile->tok[tile->n] = i;
-          tile->w[tile->n++] = 1.f;
+    const BatchUnits bu = batch_units(one + more, g.inter, g.shared_inter > 0 ? (n_seg + 63) / 64 : 0, g.shared_inter, d, n_seg, K, c->n_cus);
+    bp.up_records = bu.up_records;
+    bp.down_groups = bu.down_groups;
+    bp.shared_row0 = n_seg * K * bu.n_rc;
+    // Two sets of launches: the experts that were in their slots already (and the shared expert) at once, behind them
+    // those whose slots are being filled, behind the fill event - so the first set computes while the fills stream.
+    // Experts with several token groups come first: their unit counts are padded to whole blocks of 8 x groups, which
+    // keeps the groups of a block on one XCD (see group_pos).
+    uint32_t h_base = 0;
+    for (int set = 0; set < 2; ++set) {
+      const uint64_t mine = set == 0 ? read & ~filled : read & filled;
+      int n_up = 0, n_down = 0;
+      bp.n_entries = 0;
+      auto add = [&](int slot, int n_tok, int rows) {
+        const int groups = (n_tok + 63) / 64, n32 = (rows + 31) / 32;
+        int up = (rows + bu.up_records - 1) / bu.up_records, down = (n32 + bu.down_groups - 1) / bu.down_groups * (d / 256);
+        if (groups > 1) {
+          up = (up + 7) / 8 * 8 * groups;
+          down = (down + 7) / 8 * 8 * groups;
         }
-      }
-    }
-    // Records per unit.  A unit costs about 8 us of start-up plus 0.5 us per record, and the launch runs in rounds of
-    // one workgroup per compute unit: take the size (a multiple of 16) with the smallest estimate rounds x unit time,
-    // the larger one when two are equal (fewer partial tiles to add up).  A short batch thus spreads over all
-    // compute units with small units, a long one avoids a last round that is nearly empty.
-    int unit_rec = kBatchUnitRecords;
-    {
-      double best = 1e30;
-      for (int cand = kBatchMinUnitRecords; cand <= kBatchMaxUnitRecords; cand += 16) {
-        int total = 0;
-        for (int i = 0; i < n_tiles; ++i) {
-          const int rows = tile_slot[i] < 0 ? g.shared_inter : g.inter;
-          total += (rows + cand - 1) / cand;
-        }
-        const int per_token = K * ((g.inter + cand - 1) / cand) + (g.shared_inter + cand - 1) / cand;
-        if (total > c->max_units || per_token > mc) continue;  // (what the tables are sized for)
-        const int rounds = (total + c->n_cus - 1) / c->n_cus;
-        const double est = rounds * (8.0 + 0.5 * cand);
-        if (est <= best) {
-          best = est;
-          unit_rec = cand;
-        }
-      }
-    }
-    c->units_built.clear();
-    c->tile_first_unit.assign(n_tiles + 1, 0);
-    for (int i = 0; i < n_tiles; ++i) {
-      const int rows = tile_slot[i] < 0 ? g.shared_inter : g.inter;
-      c->tile_first_unit[i] = n_units;
-      for (int r0 = 0; r0 < rows; r0 += unit_rec, ++n_units)
-        c->units_built.push_back(BatchUnit{tile_slot[i], r0, std::min(unit_rec, rows - r0), i});
-    }
-    c->tile_first_unit[n_tiles] = n_units;
-    if (n_units > c->max_units) return fail(MOE_EHIP, "batch tables overflow (%d units)", n_units);
-    // Launch order.  The units that read the same records (one blob, one block of records; one unit per token tile)
-    // should share them in an L2: workgroups go to the XCDs round-robin by index, so such a group gets consecutive
-    // places of one XCD (indices 8 apart), the groups spread over the XCDs by length.  Made tile by tile, the units
-    // of a group would sit a tile's unit count apart - at C2 on eight different XCDs, each fetching the block from HBM.
-    // Two groups: first the units whose experts were in their slots already (and the shared expert's), launched at
-    // once; behind them the units of the slots being filled, launched behind the fill event - so the first group
-    // computes while the fills stream.
-    std::vector<int32_t> &pos = c->unit_pos;
-    int n_ready = 0;
-    {
-      const int max_chunks = (std::max(g.inter, g.shared_inter) + unit_rec - 1) / unit_rec;
-      pos.assign(n_units, -1);
-      std::vector<int32_t> &owner = c->unit_group_owner;  // per (blob, block of records): the XCD of its group
-      auto key = [&](const BatchUnit &bu) { return (bu.slot + 1) * max_chunks + bu.rec0 / unit_rec; };
-      int placed = 0;
+        bp.e[bp.n_entries++] = BatchEntry{(int16_t)slot, (uint16_t)n_tok, h_base, (uint32_t)n_up, (uint32_t)n_down};
+        h_base += (uint32_t)((n_tok + 15) / 16) * (uint32_t)n32;
+        n_up += up;
+        n_down += down;
+      };
       for (int pass = 0; pass < 2; ++pass) {
-        for (auto &q : c->xcd_queue) q.clear();
-        owner.assign((size_t)(g.capacity + 1) * max_chunks, -1);
-        for (int u = 0; u < n_units; ++u) {
-          const BatchUnit &bu = c->units_built[u];
-          const bool waits = bu.slot >= 0 && ((filled >> bu.slot) & 1);
-          if (waits != (pass == 1)) continue;
-          int32_t &x = owner[(size_t)key(bu)];
-          if (x < 0) {  // a new group: to the XCD with the shortest queue
-            x = 0;
-            for (int i = 1; i < 8; ++i)
-              if (c->xcd_queue[i].size() < c->xcd_queue[x].size()) x = i;
-          }
-          c->xcd_queue[x].push_back(u);
-        }
-        for (auto &q : c->xcd_queue)  // a group's units side by side in its queue
-          std::stable_sort(q.begin(), q.end(), [&](int32_t ua, int32_t ub) { return key(c->units_built[ua]) < key(c->units_built[ub]); });
-        size_t longest = 0;
-        for (auto &q : c->xcd_queue) longest = std::max(longest, q.size());
-        for (size_t i = 0; i < longest; ++i)
-          for (int x = 0; x < 8; ++x)
-            if (i < c->xcd_queue[x].size()) {
-              const int32_t u = c->xcd_queue[x][i];
-              pos[u] = placed;
-              c->h_units[placed++] = c->units_built[u];
-            }
-        if (pass == 0) n_ready = placed;
-      }
-    }
-    // per token: the rows of the partial buffer that hold its share of y (unit place * 16 + row in the tile), in a
-    // fixed order: tiles in the order made, a tile's units by record
-    for (int i = 0; i < n_tiles; ++i) {
-      const TokenTile &tile = c->h_tiles[i];
-      for (int row = 0; row < tile.n; ++row) {
-        const int t = tile.tok[row];
-        for (int u = c->tile_first_unit[i]; u < c->tile_first_unit[i + 1]; ++u) {
-          int32_t &n = n_contrib[t - t0];
-          if (n < mc) contrib[(size_t)(t - t0) * mc + n] = pos[u] * 16 + row;
-          ++n;
+        const bool several = pass == 0;
+        if (set == 0 && g.shared_inter > 0 && (n_seg > 64) == several) add(-1, n_seg, g.shared_inter);
+        for (uint64_t m = mine; m; m &= m - 1) {
+          const int s = __builtin_ctzll(m);
+          if ((n_of_slot[s] > 64) == several) add(s, n_of_slot[s], g.inter);
         }
       }
+      if (set == 1 && n_fill > 0) HIP_TRY(hipStreamWaitEvent(c->compute, c->ev_copy[layer], 0));
+      HIP_TRY(launch_up_batch(bp, n_up, c->compute));
+      HIP_TRY(launch_down_batch(bp, n_down, c->compute));
     }
-    for (int i = 0; i < n_seg; ++i)
-      if (n_contrib[i] > mc) return fail(MOE_EHIP, "batch tables overflow (%d partial rows for one token)", n_contrib[i]);
-    HIP_TRY(hipMemcpyAsync(c->d_tables, c->h_tables, c->off_contrib + sizeof(int32_t) * ((size_t)kMaxBatch + (size_t)n_seg * mc),
-                           hipMemcpyHostToDevice, c->compute));
-    bp.unit_base = 0;
-    bp.n_units = n_ready;
-    HIP_TRY(launch_expert_batch(bp, c->compute));
-    if (n_fill > 0) HIP_TRY(hipStreamWaitEvent(c->compute, c->ev_copy[layer], 0));
-    bp.unit_base = n_ready;
-    bp.n_units = n_units - n_ready;
-    HIP_TRY(launch_expert_batch(bp, c->compute));
-    HIP_TRY(launch_reduce_batch(c->d_bpartial, c->d_contrib + kMaxBatch, c->d_contrib, mc, y_dev, d, t0, n_seg,
-                                c->compute));
+    HIP_TRY(launch_reduce_batch(bp, y_dev, bu.n_rc, bu.n_rc_shared, c->compute));
     HIP_TRY(hipEventRecord(c->ev_batch, c->compute));
     t0 = t1;
   }

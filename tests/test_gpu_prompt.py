@@ -118,6 +118,15 @@ def test_batch_outputs_reduced_shapes(hidden, inter, shared, N, K, C, lam):
     run_prompt_outputs(cfg, lam, [8, 37, 1, 128, 16])
 
 
+@pytest.mark.parametrize("hidden,inter,shared,N,K", [(1024, 48, 16, 1, 1), (2048, 16, 0, 3, 2), (2048, 80, 112, 2, 1)])
+def test_batch_outputs_token_groups(hidden, inter, shared, N, K):
+    """All experts resident, few of them: units of one, two and four token tiles, several groups of 64 tokens on one
+    expert, and records that are an odd multiple of 16 (the last 32 of the down projection half empty)."""
+    cfg = BASE.with_(n_layers=1, hidden=hidden, n_experts=N, inter=inter, shared_inter=shared, top_k=K, capacity=N,
+                     seed=7300 + inter)
+    run_prompt_outputs(cfg, 0.0, [1, 16, 17, 33, 64, 65, 128], every=3)
+
+
 def test_batch_outputs_full_layer_shape():
     """The benchmarked layer shape (60 experts of 1408, shared 5632, cache 30), batches of 32 and 128; outputs of
     every 9th token against the oracle."""
