@@ -142,6 +142,13 @@ struct BatchSel {
   uint8_t slot[kMaxBatch][MOE_MAX_TOPK];
   float weight[kMaxBatch][MOE_MAX_TOPK];
 };
+// what route_ahead_kernel leaves for route_batch_kernel: per token whether it misses an expert, its experts in touch
+// order, and Eq. 10's sum before it (and after the last one)
+struct BatchAhead {
+  uint8_t touched[kMaxBatch][MOE_MAX_TOPK];
+  uint8_t miss[kMaxBatch];
+  float dsum[kMaxBatch + 1];
+};
 // one expert of a launch: its slot (-1: the shared expert), how many tokens of the segment take it, where its h starts
 // (in blocks of 16 tokens x 32 records x 3 bf16 = 3 KB) and its first workgroup in the two launches
 struct BatchEntry {
@@ -169,7 +176,7 @@ struct BatchParams {
 bool batch_shape_supported(int weight_fmt, int act_fmt, int hidden, int inter, int shared_inter);
 hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, int B, int N, int hidden, hipStream_t s);
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              BatchSel *sel, hipStream_t s);
+                              BatchSel *sel, BatchAhead *ahead, hipStream_t s);
 hipError_t launch_up_batch(const BatchParams &p, int n_units, hipStream_t s);
 hipError_t launch_down_batch(const BatchParams &p, int n_units, hipStream_t s);
 hipError_t launch_reduce_batch(const BatchParams &p, void *y, int n_rc, int n_rc_shared, hipStream_t s);

@@ -83,6 +83,10 @@ __global__ __launch_bounds__(kGateSplit *kWave) void gate_gemm_kernel(const uint
 // merged state, which it updates, and the window moves on behind it.  What does not depend on the cache - Eq. 10's
 // running sum of logit ranges - is prepared for all tokens first (the same additions in the same order).
 // Miss-free batches cost one round per sixteen tokens; a miss costs one extra round.
+//
+// A round is issue-bound (four wavefronts a SIMD, each a long chain of dependent instructions), so longer batches are
+// first routed by route_ahead_kernel: one wavefront per token on a SIMD of its own, all against the state before the
+// batch.  Up to the first miss these are the decisions; route_batch_kernel then only merges them and walks the rest.
 constexpr int kRouteWaves = 16;
 struct BatchCacheState {  // LayerState's tables while the batch is routed (LDS)
   int32_t my_slot[MOE_MAX_EXPERTS], slot_exp[MOE_MAX_EXPERTS], born[MOE_MAX_EXPERTS];
@@ -113,9 +117,64 @@ __device__ __forceinline__ void store_sel(const uint32_t *rec, int K, int lane, 
   }
 }
 
+// barrier that waits for LDS only: the records on their way to host memory are not waited for
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+constexpr int kAheadWaves = 4;
+constexpr int kZStride = MOE_MAX_EXPERTS + 1;  // (a thread walks a row: rows start in different banks)
+
+__global__ __launch_bounds__(kAheadWaves *kWave) void route_ahead_kernel(RouteParams p, const float *logits, int B,
+                                                                         LayerState *st, moe_route_out_t *out, BatchSel *sel,
+                                                                         BatchAhead *ahead) {
+  __shared__ float z_s[kMaxBatch * kZStride];
+  __shared__ float range_s[kMaxBatch];
+  __shared__ __attribute__((aligned(16))) uint32_t rec_s[kAheadWaves][rt::kRecWords];
+  const int tid = threadIdx.x, lane = tid & 63, N = p.n_experts, K = p.top_k;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t = (int)blockIdx.x * kAheadWaves + wave;
+  const int n = min(B, ((int)blockIdx.x + 1) * kAheadWaves);  // Eq. 10's sum needs the tokens up to this workgroup's
+  rt::CacheRegs cr = rt::load_cache_regs(st, lane, N, p.capacity), next;
+  const int e_c = min(lane, N - 1);
+#pragma unroll 8
+  for (int i = wave; i < n; i += kAheadWaves) z_s[i * kZStride + lane] = logits[i * N + e_c];  // (lanes past N: a copy)
+  __syncthreads();
+  if (tid < n) {
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll 8
+    for (int e = 0; e < N; ++e) {
+      lo = fminf(lo, z_s[tid * kZStride + e]);
+      hi = fmaxf(hi, z_s[tid * kZStride + e]);
+    }
+    range_s[tid] = hi - lo;
+  }
+  __syncthreads();
+  if (t >= B) return;
+  {
+#pragma clang fp contract(off)
+    float acc = cr.dsum_prev;
+#pragma unroll 8
+    for (int i = 0; i < t; ++i) acc = acc + range_s[i];
+    cr.dsum_prev = acc;
+  }
+  const int count0 = cr.t;
+  cr.t = count0 + t;
+  int n_miss = 0;
+  rt::route_wave(p, z_s + t * kZStride, cr, st, out + t, nullptr, rec_s[wave], lane, rt::BoundaryFlags{nullptr, 0}, &next, false,
+                 &n_miss);
+  store_sel(rec_s[wave], K, lane, t, sel);
+  // the experts in touch order: their stamps are token * K + position (0xff: logits that are not numbers select fewer)
+  if (lane < MOE_MAX_TOPK) ahead->touched[t][lane] = 0xff;
+  if (lane < N && next.stamp != cr.stamp) ahead->touched[t][(int)(next.stamp - (int64_t)cr.t * K)] = (uint8_t)lane;
+  if (lane == 0) {
+    ahead->miss[t] = (uint8_t)(n_miss > 0);
+    ahead->dsum[t] = cr.dsum_prev;
+    if (t == B - 1) ahead->dsum[B] = next.dsum_prev;
+  }
+}
+
 __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RouteParams p, const float *logits, int B,
                                                                          LayerState *st, moe_route_out_t *out,
-                                                                         BatchSel *sel) {
+                                                                         BatchSel *sel, const BatchAhead *ahead) {
   __shared__ float z_all[kMaxBatch * MOE_MAX_EXPERTS];
   __shared__ float range_s[kMaxBatch];
   __shared__ float dsum_s[kMaxBatch + 1];  // Eq. 10's sum before token t
@@ -139,51 +198,73 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
       dsum_s[0] = cr.dsum_prev;
     }
   }
-  for (int i = tid; i < B * N; i += kRouteWaves * kWave) {
-    const int t = i / N;
-    z_all[t * MOE_MAX_EXPERTS + (i - t * N)] = logits[i];
+  int t0 = 0, fm;  // tokens before t0 are routed; fm: the first of the window that misses an expert
+  if (ahead != nullptr) {
+    if (tid == 0) first_miss_s = B;
+    __syncthreads();
+    if (tid < B && ahead->miss[tid]) atomicMin(&first_miss_s, tid);
+    if (tid <= B) dsum_s[tid] = ahead->dsum[tid];
+    __syncthreads();
+    fm = first_miss_s;
+    for (int i = tid; i < fm * K; i += kRouteWaves * kWave) {
+      const int t = i / K, pos = i - t * K;
+      const int e = ahead->touched[t][pos];
+      if (e < MOE_MAX_EXPERTS) atomicMax(&cs.stamp[e], (long long)(cs.count0 + t) * K + pos);
+    }
+  }
+  if (ahead == nullptr || fm < B) {
+    for (int i = tid; i < B * N; i += kRouteWaves * kWave) {
+      const int t = i / N;
+      z_all[t * MOE_MAX_EXPERTS + (i - t * N)] = logits[i];
+    }
   }
   __syncthreads();
-  for (int t = wave; t < B; t += kRouteWaves) {
-    const bool active = lane < N;
-    const float z = active ? z_all[t * MOE_MAX_EXPERTS + lane] : 0.f;
-    const float r = rt::wave_max(active ? z : -INFINITY) - rt::wave_min(active ? z : INFINITY);
-    if (lane == 0) range_s[t] = r;
-  }
-  __syncthreads();
-  if (tid == 0) {
+  if (ahead == nullptr) {
+    for (int t = wave; t < B; t += kRouteWaves) {
+      const bool active = lane < N;
+      const float z = active ? z_all[t * MOE_MAX_EXPERTS + lane] : 0.f;
+      const float r = rt::wave_max(active ? z : -INFINITY) - rt::wave_min(active ? z : INFINITY);
+      if (lane == 0) range_s[t] = r;
+    }
+    __syncthreads();
+    if (tid == 0) {
 #pragma clang fp contract(off)
-    float acc = dsum_s[0];
-    for (int t = 0; t < B; ++t) {
-      acc = acc + range_s[t];
-      dsum_s[t + 1] = acc;
+      float acc = dsum_s[0];
+      for (int t = 0; t < B; ++t) {
+        acc = acc + range_s[t];
+        dsum_s[t + 1] = acc;
+      }
     }
   }
 
-  int t0 = 0;
+  bool routed_ahead = ahead != nullptr;
   while (t0 < B) {  // (t0 and everything that steers the loop is the same in every thread)
-    if (tid == 0) first_miss_s = B;
-    __syncthreads();
-    const int t = t0 + wave;
+    int window_end = B;
     rt::CacheRegs cr, next;
-    if (t < B) {
-      cr = batch_cache_regs(cs, lane, t, dsum_s[t]);
-      int n_miss = 0;
-      rt::route_wave(p, z_all + t * MOE_MAX_EXPERTS, cr, st, reinterpret_cast<moe_route_out_t *>(stage_s[wave]), nullptr,
-                     asm_s[wave], lane, rt::BoundaryFlags{nullptr, 0}, &next, false, &n_miss);
-      if (n_miss > 0 && lane == 0) atomicMin(&first_miss_s, t);
+    if (!routed_ahead) {
+      if (tid == 0) first_miss_s = B;
+      lds_barrier();
+      const int t = t0 + wave;
+      if (t < B) {
+        cr = batch_cache_regs(cs, lane, t, dsum_s[t]);
+        int n_miss = 0;
+        rt::route_wave(p, z_all + t * MOE_MAX_EXPERTS, cr, st, reinterpret_cast<moe_route_out_t *>(stage_s[wave]), nullptr,
+                       asm_s[wave], lane, rt::BoundaryFlags{nullptr, 0}, &next, false, &n_miss);
+        if (n_miss > 0 && lane == 0) atomicMin(&first_miss_s, t);
+      }
+      lds_barrier();
+      window_end = min(t0 + kRouteWaves, B);
+      fm = min(first_miss_s, window_end);  // tokens t0 .. fm-1 stand as they are
+      if (t < fm) {
+        if (lane < rt::kRecWords / 4)
+          reinterpret_cast<u32x4 *>(out + t)[lane] = reinterpret_cast<const u32x4 *>(stage_s[wave])[lane];
+        if (lane < N && next.stamp != cr.stamp) atomicMax(&cs.stamp[lane], (long long)next.stamp);
+        store_sel(stage_s[wave], K, lane, t, sel);
+      }
     }
-    __syncthreads();
-    const int window_end = min(t0 + kRouteWaves, B);
-    const int fm = min(first_miss_s, window_end);  // tokens t0 .. fm-1 stand as they are
-    if (t < fm) {
-      if (lane < rt::kRecWords / 4)
-        reinterpret_cast<u32x4 *>(out + t)[lane] = reinterpret_cast<const u32x4 *>(stage_s[wave])[lane];
-      if (lane < N && next.stamp != cr.stamp) atomicMax(&cs.stamp[lane], (long long)next.stamp);
-      store_sel(stage_s[wave], K, lane, t, sel);
-    }
+    routed_ahead = false;
     if (tid < 2) cs.counter[tid] += (long long)K * (fm - t0);  // selections and hits
-    __syncthreads();
+    lds_barrier();
     t0 = fm;
     if (fm < window_end) {
       // token fm misses at least one expert: routed against the merged state, which it updates
@@ -236,9 +317,6 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
 // projection on the fp32 matrix instruction; 8 experts, 8 tokens, 208 MB: 28 + 16 us against 47 us.
 constexpr int kBWaves = 4;
 constexpr int kGroupTiles = 4;  // token tiles per unit
-
-// LDS-only workgroup barrier: does not wait for loads or stores to memory in flight
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 struct UnitPos {
   int entry, unit;  // index into BatchParams::e, and the unit's place inside that entry
@@ -641,10 +719,23 @@ hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, in
   return hipGetLastError();
 }
 
+// Batches of more tokens than this are routed ahead: up to one window route_batch_kernel has nothing to wait for, from
+// the second window on the extra launch pays (moe_route_batch in all, miss-free, without / with it: 24 tokens 29.6 /
+// 29.3 us, 32 tokens 31.8 / 29.5, 64 tokens 44.2 / 32.5; 128 tokens: the two kernels 8.9 + 5.1 us against 40).
+constexpr int kAheadMinTokens = kRouteWaves;
+
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              BatchSel *sel, hipStream_t s) {
+                              BatchSel *sel, BatchAhead *ahead, hipStream_t s) {
   if (B <= 0 || B > kMaxBatch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(route_batch_kernel, dim3(1), dim3(kRouteWaves * kWave), 0, s, p, logits, B, state, out, sel);
+  const bool use_ahead = B > kAheadMinTokens;
+  if (use_ahead) {
+    hipLaunchKernelGGL(route_ahead_kernel, dim3((B + kAheadWaves - 1) / kAheadWaves), dim3(kAheadWaves * kWave), 0, s, p, logits, B,
+                       state, out, sel, ahead);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(route_batch_kernel, dim3(1), dim3(kRouteWaves * kWave), 0, s, p, logits, B, state, out, sel,
+                     use_ahead ? ahead : nullptr);
   return hipGetLastError();
 }
 

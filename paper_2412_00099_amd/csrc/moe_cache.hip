@@ -102,6 +102,7 @@ struct moe_cache {
   moe_route_out_t *batch_rec = nullptr;      // [kMaxBatch] the decisions of the batch routed last: pinned host memory
   moe_route_out_t *batch_rec_dev = nullptr;  // the routing kernel's view of it (the records go straight to the host)
   BatchSel *d_bsel = nullptr;               // the same selection as the expert kernels read it
+  BatchAhead *d_bahead = nullptr;           // between the two routing kernels of a long batch
   uint8_t *d_bh = nullptr;                  // h of a segment (see up_batch_kernel)
   float *d_bpartial = nullptr;              // P of a segment: [kMaxPartialRows][hidden]
   int n_cus = 0;
@@ -310,6 +311,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
     HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->batch_rec), sizeof(moe_route_out_t) * kMaxBatch, hipHostMallocMapped));
     HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->batch_rec_dev), c->batch_rec, 0));
     HIP_INIT(hipMalloc(&c->d_bsel, sizeof(BatchSel)));
+    HIP_INIT(hipMalloc(&c->d_bahead, sizeof(BatchAhead)));
     HIP_INIT(hipMalloc(&c->d_bh, (size_t)h_blocks * 3072));
     HIP_INIT(hipMalloc(&c->d_bpartial, sizeof(float) * (size_t)kMaxPartialRows * cfg->hidden));
     HIP_INIT(hipEventCreateWithFlags(&c->ev_batch, hipEventDisableTiming));
@@ -340,6 +342,7 @@ void moe_cache_destroy(moe_cache_t *c) {
   if (c->batch_rec) (void)hipHostFree(c->batch_rec);
   if (c->d_bpartial) (void)hipFree(c->d_bpartial);
   if (c->d_bsel) (void)hipFree(c->d_bsel);
+  if (c->d_bahead) (void)hipFree(c->d_bahead);
   if (c->d_bh) (void)hipFree(c->d_bh);
   if (c->ev_batch) (void)hipEventDestroy(c->ev_batch);
   if (c->ev_route) (void)hipEventDestroy(c->ev_route);
@@ -629,7 +632,7 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
     z = c->d_logits_batch;
   }
   const RouteParams p = make_route_params(c);
-  HIP_TRY(launch_route_batch(p, z, n_tokens, c->d_state + layer, c->batch_rec_dev, c->d_bsel, c->compute));
+  HIP_TRY(launch_route_batch(p, z, n_tokens, c->d_state + layer, c->batch_rec_dev, c->d_bsel, c->d_bahead, c->compute));
   HIP_TRY(hipStreamSynchronize(c->compute));
   const moe_cache_config_t &g = c->cfg;
   for (int t = 0; t < n_tokens; ++t)

@@ -257,3 +257,39 @@ def test_batch_routing_equals_token_by_token_in_every_mode(mode, C):
     assert sa.misses >= K and (mode != "lru" or C != 3 or sa.misses > T // 4)
     one.close()
     many.close()
+
+
+@pytest.mark.parametrize("N,K,C", [(64, 8, 64), (64, 8, 9), (60, 4, 30), (9, 8, 8), (1, 1, 1)])
+def test_batch_routing_ahead_equals_token_by_token(N, K, C):
+    """Batches longer than one window are routed ahead, one wavefront per token against the state before the batch: at
+    the edges of the expert count, the selection size and the window, records, tables and counters are those of the
+    single-token steps, bit for bit."""
+    cfg = BASE.with_(n_layers=1, hidden=1024, n_experts=N, inter=16, shared_inter=0, top_k=K, capacity=C, seed=940 + N + C)
+    print(f"case routed ahead N={N} K={K} C={C}", flush=True)
+    store_a, one = build(cfg, lam=0.5)
+    store_b, many = build(cfg, lam=0.5)
+    batches = [17, 128, 33, 16, 20]
+    zs = workloads.logits_stream(cfg, sum(batches), layer=0, scale=1.5).to(DEV)
+    x = torch.zeros((128, cfg.hidden), dtype=cfg.act_dtype, device=DEV)
+    y = torch.zeros_like(x)
+    t0 = 0
+    for b in batches:
+        recs = many.route_batch(0, logits=zs[t0:t0 + b].contiguous())
+        many.expert_forward_batch(0, x[:b], y[:b])
+        for j in range(b):
+            ref = one.route_step(0, logits=zs[t0 + j])
+            one.expert_forward(0, x[0], y[0])
+            fa, fb = route_fields(ref, K), route_fields(recs[j], K)
+            for key in fa:
+                assert np.array_equal(fa[key], fb[key]), (t0 + j, key, fa[key], fb[key])
+            assert list(ref.logits[:N]) == list(recs[j].logits[:N])
+        t0 += b
+    ta, tb = one.tables(0), many.tables(0)
+    for field in ("expert_slot", "slot_expert", "stamp"):
+        assert list(getattr(ta, field)) == list(getattr(tb, field)), field
+    assert (ta.count, ta.delta_sum) == (tb.count, tb.delta_sum)
+    sa, sb = one.stats(0), many.stats(0)
+    for field in ("tokens", "selections", "hits", "misses", "cold_misses", "evictions", "lifetime_sum", "bytes_filled"):
+        assert getattr(sa, field) == getattr(sb, field), field
+    one.close()
+    many.close()
