@@ -150,7 +150,7 @@ struct BatchAhead {
   float dsum[kMaxBatch + 1];
 };
 // one expert of a launch: its slot (-1: the shared expert), how many tokens of the segment take it, where its h starts
-// (in blocks of 16 tokens x 32 records x 3 bf16 = 3 KB) and its first workgroup in the two launches
+// (in blocks of 16 tokens x 32 records in fp32 = 2 KB) and its first workgroup in the two launches
 struct BatchEntry {
   int16_t slot;
   uint16_t n_tok;

@@ -313,10 +313,12 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
 // tokens stay in registers for the unit, no weights are staged through LDS, and no barrier stands in the load
 // stream except one per 16 records of `up`.  A unit finds its tokens itself from the selected slots (1 KB): no tables
 // are made on the host or sent.  Measured (60 experts of 1408, shared 5632, top-4, d = 2048; both kernels): 19 distinct
-// experts, 128 tokens, 399 MB: 63 + 42 us, against 203 us for one fused kernel over tiles of 16 tokens with the down
+// experts, 128 tokens, 399 MB: 62 + 39 us, against 203 us for one fused kernel over tiles of 16 tokens with the down
 // projection on the fp32 matrix instruction; 8 experts, 8 tokens, 208 MB: 28 + 16 us against 47 us.
+// (h written as three bf16 planes instead of fp32, split once by `up`: 63 + 42 us; h costs `down` a third of what W does.)
 constexpr int kBWaves = 4;
 constexpr int kGroupTiles = 4;  // token tiles per unit
+constexpr int kHBlock = 16 * 32 * 4;  // bytes of h of one token tile and 32 records
 
 struct UnitPos {
   int entry, unit;  // index into BatchParams::e, and the unit's place inside that entry
@@ -382,29 +384,35 @@ __device__ __forceinline__ void token_list(const BatchParams &p, int slot, int g
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// h as three bf16 values that add up to it exactly (8 + 8 + 8 significant bits, truncated): the down projection runs
-// on the bf16 matrix instruction with the precision of a 32-bit h (weights are bf16, products exact, fp32 sums).
-__device__ __forceinline__ void split3(float h, uint32_t &a, uint32_t &b, uint32_t &c) {
-  const uint32_t u = __float_as_uint(h);
-  if ((u & 0x7f800000u) == 0x7f800000u) {  // infinity and NaN stay what they are
-    a = (u >> 16) | ((u & 0x007fffffu) ? 0x40u : 0u);
-    b = c = 0u;
-    return;
+// Eight h of one token (A operand: consecutive records) as three bf16 vectors that add up to them exactly (8 + 8 + 8
+// significant bits, truncated): the down projection runs on the bf16 matrix instruction with the precision of a 32-bit h
+// (weights are bf16, products exact, fp32 sums).
+__device__ __forceinline__ void split3(const f32x4 &lo, const f32x4 &hi, u32x4 (&out)[3]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t part[3][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float h = i < 2 ? lo[2 * i + j] : hi[2 * i + j - 4];
+      const uint32_t u = __float_as_uint(h);
+      // (infinity and NaN have no remainder)
+      const float r1 = __builtin_isfinite(h) ? h - __uint_as_float(u & 0xffff0000u) : 0.f;
+      const uint32_t u1 = __float_as_uint(r1);
+      part[0][j] = u;
+      part[1][j] = u1;
+      part[2][j] = __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u));
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) out[q][i] = __builtin_amdgcn_perm(part[q][1], part[q][0], 0x07060302u);
   }
-  const float r1 = h - __uint_as_float(u & 0xffff0000u);
-  const uint32_t u1 = __float_as_uint(r1);
-  const float r2 = r1 - __uint_as_float(u1 & 0xffff0000u);
-  a = u >> 16;
-  b = u1 >> 16;
-  c = __float_as_uint(r2) >> 16;
 }
 
 // D: hidden size.  Wavefront w owns the w-th quarter of the hidden dimension: the tokens' activations there stay in
 // registers (B operands), the gate and up rows of 16 records at a time are streamed (A operands), in two halves whose
 // loads are requested as soon as the registers are free.  The four partial sums meet in LDS (double buffer, one
-// barrier per 16 records); wavefront i then finishes token tile i: h, split in three, to memory in the order in which
-// down_batch_kernel reads it: per (token tile, 32 records) three blocks of [lane][8] bf16, lane = 16 (record / 8) +
-// token.
+// barrier per 16 records); wavefront i then finishes token tile i: h to memory in the order in which down_batch_kernel
+// reads it, per (token tile, 32 records) two blocks of [lane][4] fp32, lane = 16 (record / 8) + token: records 0..3 and
+// 4..7 of the lane's eight.
 template <int D, int NT>
 __device__ __forceinline__ void up_unit(const BatchParams &p, const BatchEntry &e, int part, int group, int lane, int wave,
                                         f32x4 *red, uint16_t *list) {
@@ -443,7 +451,7 @@ __device__ __forceinline__ void up_unit(const BatchParams &p, const BatchEntry &
   const int my = list[min(wave, NT - 1) * 16 + m16];
   const float wt = e.slot < 0 ? 1.f : p.sel->weight[my >> 3][my & 7];
   const int n32 = (rows + 31) / 32;
-  uint8_t *hb = p.h + ((int64_t)e.h_base + (int64_t)(group * kGroupTiles + wave) * n32) * 3072;
+  uint8_t *hb = p.h + ((int64_t)e.h_base + (int64_t)(group * kGroupTiles + wave) * n32) * kHBlock;
 
   int parity = 0;
   auto block = [&](int blk, auto next_tag) {
@@ -484,20 +492,14 @@ __device__ __forceinline__ void up_unit(const BatchParams &p, const BatchEntry &
         us += rb[((w * NT + wave) * 2 + 1) * 64 + lane];
       }
       // records 4 kq + v of the block, token m16 of the tile
-      uint32_t a[4], b[4], c[4];
+      f32x4 h;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) split3(gs[v] / (1.f + __expf(-gs[v])) * us[v] * wt, a[v], b[v], c[v]);
+      for (int v = 0; v < 4; ++v) h[v] = gs[v] / (1.f + __expf(-gs[v])) * us[v] * wt;
       const int rec = rec0 + blk * 16;
-      uint8_t *o = hb + (int64_t)(rec >> 5) * 3072 + (((rec >> 3) & 3) + (kq >> 1)) * 256 + m16 * 16 + (kq & 1) * 8;
-      *reinterpret_cast<u32x2 *>(o) = u32x2{a[0] | (a[1] << 16), a[2] | (a[3] << 16)};
-      *reinterpret_cast<u32x2 *>(o + 1024) = u32x2{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
-      *reinterpret_cast<u32x2 *>(o + 2048) = u32x2{c[0] | (c[1] << 16), c[2] | (c[3] << 16)};
-      if (rec + 16 == rows && (rows & 31)) {  // the second half of the last 32 records does not exist: zeros
-        const u32x2 zero = {0u, 0u};
-        *reinterpret_cast<u32x2 *>(o + 512) = zero;
-        *reinterpret_cast<u32x2 *>(o + 512 + 1024) = zero;
-        *reinterpret_cast<u32x2 *>(o + 512 + 2048) = zero;
-      }
+      uint8_t *o = hb + (int64_t)(rec >> 5) * kHBlock + (kq & 1) * (kHBlock / 2) + (((rec >> 3) & 3) + (kq >> 1)) * 256 + m16 * 16;
+      *reinterpret_cast<f32x4 *>(o) = h;
+      // the second half of the last 32 records may not exist: zeros
+      if (rec + 16 == rows && (rows & 31)) *reinterpret_cast<f32x4 *>(o + 512) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
   for (int blk = 0; blk + 1 < n_blk; ++blk) block(blk, std::true_type{});
@@ -548,7 +550,7 @@ __device__ __forceinline__ void down_unit(const BatchParams &p, const BatchEntry
   const int m16 = lane & 15, kq = lane >> 4;
   const int n_tok = min((int)e.n_tok - 64 * group, 64), tiles = (n_tok + 15) / 16;
   const uint8_t *wbase = blob + 2 * row_bytes + (int64_t)cblk * 512;  // the same in every lane
-  const uint8_t *hbase = p.h + ((int64_t)e.h_base + (int64_t)group * kGroupTiles * n32) * 3072;
+  const uint8_t *hbase = p.h + ((int64_t)e.h_base + (int64_t)group * kGroupTiles * n32) * kHBlock;
 
   u32x4 w0[8], w1[8];  // columns 0..127 and 128..255 of 32 records
   auto load_w = [&](int g, int c, u32x4 (&w)[8]) {
@@ -558,11 +560,11 @@ __device__ __forceinline__ void down_unit(const BatchParams &p, const BatchEntry
 #pragma unroll
     for (int i = 0; i < 8; ++i) w[i] = stream_load(reinterpret_cast<const u32x4 *>(q + i * rec_bytes + off));
   };
-  u32x4 ha[NT][3], hb[NT][3];
-  auto load_h = [&](int g, int q, u32x4 (&h)[NT][3]) {
+  f32x4 ha[NT][2], hb[NT][2];
+  auto load_h = [&](int g, int i, f32x4 (&h)[NT][2]) {
 #pragma unroll
-    for (int i = 0; i < NT; ++i)  // (tiles past the last repeat it; their rows are not stored)
-      h[i][q] = *reinterpret_cast<const u32x4 *>(hbase + ((int64_t)min(i, tiles - 1) * n32 + g) * 3072 + q * 1024 +
+    for (int q = 0; q < 2; ++q)  // (tiles past the last repeat it; their rows are not stored)
+      h[i][q] = *reinterpret_cast<const f32x4 *>(hbase + ((int64_t)min(i, tiles - 1) * n32 + g) * kHBlock + q * (kHBlock / 2) +
                                                  (uint32_t)lane * 16u);
   };
   f32x4 acc[NT][2][8];
@@ -572,12 +574,17 @@ __device__ __forceinline__ void down_unit(const BatchParams &p, const BatchEntry
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[i][c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // One group of 32 records; NEXT: there is a group after it, whose loads are requested as registers become free.  The
-  // next h goes to a second set of registers ahead of the next weights (loads complete in order, and h is wanted
-  // first); with four token tiles there is no room for a second set, and h is requested again part by part.
-  constexpr bool TWO = NT <= 2;
-  auto step = [&](int g, u32x4 (&h)[NT][3], u32x4 (&h_next)[NT][3], auto next_tag) {
+  // One group of 32 records; NEXT: there is a group after it, whose loads are requested as registers become free: its h
+  // into a second set ahead of its weights (loads complete in order, and h is wanted first).  With four token tiles
+  // everything but the accumulators lives in 256 registers: the order below is kept as written, or loads and splits of
+  // later tiles are moved up and spill.
+  auto step = [&](int g, const f32x4 (&h)[NT][2], f32x4 (&h_next)[NT][2], auto next_tag) {
     constexpr bool NEXT = decltype(next_tag)::value;
+    if constexpr (NEXT) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) load_h(g + kBWaves, i, h_next);
+    }
+    if constexpr (NT > 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       u32x4 (&w)[8] = c == 0 ? w0 : w1;
@@ -588,45 +595,32 @@ __device__ __forceinline__ void down_unit(const BatchParams &p, const BatchEntry
       }
       u32x4 col[8];
       transpose8(w, col);
-      if constexpr (NEXT) {
-        if (TWO && c == 0) {
+      if constexpr (NEXT) load_w(g + kBWaves, c, w);
+      if constexpr (NT > 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int q = 2; q >= 0; --q) load_h(g + kBWaves, q, h_next);
-        }
-        load_w(g + kBWaves, c, w);
-      }
+      for (int i = 0; i < NT; ++i) {
+        u32x4 a[3];
+        split3(h[i][0], h[i][1], a);
+        if constexpr (NT > 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int q = 2; q >= 0; --q) {  // the small parts first
+        for (int q = 2; q >= 0; --q)  // the small parts first
 #pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) acc[i][c][j] = mfma_bf16(h[i][q], col[j], acc[i][c][j]);
-        if constexpr (NEXT && !TWO)
-          if (c == 1) load_h(g + kBWaves, q, h);
+          for (int j = 0; j < 8; ++j) acc[i][c][j] = mfma_bf16(a[q], col[j], acc[i][c][j]);
       }
     }
   };
   int g = g_begin + wave, left = g < g_end ? (g_end - g + kBWaves - 1) / kBWaves : 0;
   if (left > 0) {
 #pragma unroll
-    for (int q = 2; q >= 0; --q) load_h(g, q, ha);
+    for (int i = 0; i < NT; ++i) load_h(g, i, ha);
     load_w(g, 0, w0);
     load_w(g, 1, w1);
-    if constexpr (TWO) {
-      for (; left > 2; left -= 2, g += 2 * kBWaves) {
-        step(g, ha, hb, std::true_type{});
-        step(g + kBWaves, hb, ha, std::true_type{});
-      }
-      if (left == 2) {
-        step(g, ha, hb, std::true_type{});
-        step(g + kBWaves, hb, ha, std::false_type{});
-      } else {
-        step(g, ha, hb, std::false_type{});
-      }
-    } else {
-      for (; left > 1; --left, g += kBWaves) step(g, ha, ha, std::true_type{});
-      step(g, ha, ha, std::false_type{});
+    for (; left > 1; --left, g += kBWaves) {
+      step(g, ha, hb, std::true_type{});
+#pragma unroll
+      for (int i = 0; i < NT; ++i) ha[i][0] = hb[i][0], ha[i][1] = hb[i][1];
     }
+    step(g, ha, hb, std::false_type{});
   }
   // the tiles of the four wavefronts, one token tile at a time: [wave][16 rows][256 columns]
   token_list(p, e.slot, group, n_tok, lane, list);

@@ -312,7 +312,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
     HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->batch_rec_dev), c->batch_rec, 0));
     HIP_INIT(hipMalloc(&c->d_bsel, sizeof(BatchSel)));
     HIP_INIT(hipMalloc(&c->d_bahead, sizeof(BatchAhead)));
-    HIP_INIT(hipMalloc(&c->d_bh, (size_t)h_blocks * 3072));
+    HIP_INIT(hipMalloc(&c->d_bh, (size_t)h_blocks * 2048));
     HIP_INIT(hipMalloc(&c->d_bpartial, sizeof(float) * (size_t)kMaxPartialRows * cfg->hidden));
     HIP_INIT(hipEventCreateWithFlags(&c->ev_batch, hipEventDisableTiming));
   }
