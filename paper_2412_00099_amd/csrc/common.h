@@ -104,10 +104,22 @@ struct HostNote {
   uint64_t w[4];
 };
 
+// The full record of a step whose decision the caller waits for, in mapped host memory: word i of the record in the
+// low half of w[i], the step's seq in the high half.  Complete once all words carry the seq (no order between the stores
+// is assumed), so nobody has to wait for the kernel's end or a copy.
+constexpr int kHostRecWords = sizeof(moe_route_out_t) / 4;
+struct HostRecord {
+  uint64_t w[kHostRecWords];
+};
+// where a routing step leaves what the host wants of it (device views of mapped host memory; nullptr: not wanted)
+struct HostOut {
+  HostNote *note;
+  HostRecord *rec;
+};
+
 // launchers (each returns the hipError_t of the launch)
 hipError_t launch_route(const RouteParams &p, const void *gate_w, const void *x, const float *logits,
-                        LayerState *state, moe_route_out_t *out_dev, HostNote *note_mapped,
-                        hipStream_t s);
+                        LayerState *state, moe_route_out_t *out_dev, HostOut host, hipStream_t s);
 // launch shape of the expert GEMV
 constexpr int kGemvWaves = 8;  // wavefronts per workgroup
 constexpr int kGemvDepth = 2;  // records in flight per wavefront (fp32 / bf16 kernels)
@@ -120,7 +132,7 @@ bool gemv_fused_supported(int weight_fmt, int act_fmt, int hidden, const GemvPla
 // f.ss != nullptr: the glue has been done by launch_reduce_glue (needs fused_route_pre_supported(hidden))
 bool fused_route_pre_supported(int hidden);
 hipError_t launch_fused_route(const RouteParams &p, const FusedParams &f, const void *gate_w, LayerState *state,
-                              moe_route_out_t *out_dev, HostNote *note_mapped, hipStream_t s);
+                              moe_route_out_t *out_dev, HostOut host, hipStream_t s);
 hipError_t launch_expert_gemv(const GemvParams &p, int weight_fmt, const GemvPlan &plan, hipStream_t s,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 hipError_t launch_partial_reduce(const float *partial, int n_partial, void *y, int hidden, int act_fmt,
@@ -176,7 +188,7 @@ struct BatchParams {
 bool batch_shape_supported(int weight_fmt, int act_fmt, int hidden, int inter, int shared_inter);
 hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, int B, int N, int hidden, hipStream_t s);
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              BatchSel *sel, BatchAhead *ahead, hipStream_t s);
+                              BatchSel *sel, BatchAhead *ahead, uint32_t *done, hipStream_t s);
 hipError_t launch_up_batch(const BatchParams &p, int n_units, hipStream_t s);
 hipError_t launch_down_batch(const BatchParams &p, int n_units, hipStream_t s);
 hipError_t launch_reduce_batch(const BatchParams &p, void *y, int n_rc, int n_rc_shared, hipStream_t s);

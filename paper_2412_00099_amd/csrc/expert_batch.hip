@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kAheadWaves *kWave) void route_ahead_kernel(RoutePa
   const int count0 = cr.t;
   cr.t = count0 + t;
   int n_miss = 0;
-  rt::route_wave(p, z_s + t * kZStride, cr, st, out + t, nullptr, rec_s[wave], lane, rt::BoundaryFlags{nullptr, 0}, &next, false,
+  rt::route_wave(p, z_s + t * kZStride, cr, st, out + t, HostOut{nullptr, nullptr}, rec_s[wave], lane, rt::BoundaryFlags{nullptr, 0}, &next, false,
                  &n_miss);
   store_sel(rec_s[wave], K, lane, t, sel);
   // the experts in touch order: their stamps are token * K + position (0xff: logits that are not numbers select fewer)
@@ -174,7 +174,8 @@ __global__ __launch_bounds__(kAheadWaves *kWave) void route_ahead_kernel(RoutePa
 
 __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RouteParams p, const float *logits, int B,
                                                                          LayerState *st, moe_route_out_t *out,
-                                                                         BatchSel *sel, const BatchAhead *ahead) {
+                                                                         BatchSel *sel, const BatchAhead *ahead,
+                                                                         uint32_t *done) {
   __shared__ float z_all[kMaxBatch * MOE_MAX_EXPERTS];
   __shared__ float range_s[kMaxBatch];
   __shared__ float dsum_s[kMaxBatch + 1];  // Eq. 10's sum before token t
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
       if (t < B) {
         cr = batch_cache_regs(cs, lane, t, dsum_s[t]);
         int n_miss = 0;
-        rt::route_wave(p, z_all + t * MOE_MAX_EXPERTS, cr, st, reinterpret_cast<moe_route_out_t *>(stage_s[wave]), nullptr,
+        rt::route_wave(p, z_all + t * MOE_MAX_EXPERTS, cr, st, reinterpret_cast<moe_route_out_t *>(stage_s[wave]), HostOut{nullptr, nullptr},
                        asm_s[wave], lane, rt::BoundaryFlags{nullptr, 0}, &next, false, &n_miss);
         if (n_miss > 0 && lane == 0) atomicMin(&first_miss_s, t);
       }
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
       // token fm misses at least one expert: routed against the merged state, which it updates
       if (wave == 0) {
         cr = batch_cache_regs(cs, lane, fm, dsum_s[fm]);
-        rt::route_wave(p, z_all + fm * MOE_MAX_EXPERTS, cr, st, out + fm, nullptr, asm_s[0], lane,
+        rt::route_wave(p, z_all + fm * MOE_MAX_EXPERTS, cr, st, out + fm, HostOut{nullptr, nullptr}, asm_s[0], lane,
                        rt::BoundaryFlags{nullptr, 0}, &next, false);
         store_sel(asm_s[0], K, lane, fm, sel);
         cs.my_slot[lane] = next.my_slot;
@@ -283,7 +284,10 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
       t0 = fm + 1;
     }
   }
+  // every record is in host memory (those of route_ahead_kernel since its end): tell the host, which polls
+  __threadfence_system();
   __syncthreads();
+  if (tid == 0) __hip_atomic_store(done, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (wave == 0) {
     if (lane < N) {
       st->expert_slot[lane] = cs.my_slot[lane];
@@ -719,7 +723,7 @@ hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, in
 constexpr int kAheadMinTokens = kRouteWaves;
 
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              BatchSel *sel, BatchAhead *ahead, hipStream_t s) {
+                              BatchSel *sel, BatchAhead *ahead, uint32_t *done, hipStream_t s) {
   if (B <= 0 || B > kMaxBatch) return hipErrorInvalidValue;
   const bool use_ahead = B > kAheadMinTokens;
   if (use_ahead) {
@@ -729,7 +733,7 @@ hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, 
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(route_batch_kernel, dim3(1), dim3(kRouteWaves * kWave), 0, s, p, logits, B, state, out, sel,
-                     use_ahead ? ahead : nullptr);
+                     use_ahead ? ahead : nullptr, done);
   return hipGetLastError();
 }
 

@@ -65,6 +65,10 @@ struct moe_cache {
   moe_route_out_t *d_route = nullptr;
   HostNote *h_note = nullptr;      // pinned, mapped: the router's message to the host, one per layer
   HostNote *h_note_dev = nullptr;  // device view of h_note
+  HostRecord *h_rec = nullptr;     // pinned, mapped: the full record of the last step that was waited for
+  HostRecord *h_rec_dev = nullptr;
+  uint32_t *h_done = nullptr;      // pinned, mapped: seq of the last batch whose records are all in batch_rec
+  uint32_t *h_done_dev = nullptr;
   struct Decision {                // h_note decoded
     int n_miss = 0;
     uint8_t miss_mask = 0;
@@ -124,6 +128,24 @@ int check_layer(const moe_cache_t *ctx, int32_t layer) {
   if (layer < 0 || layer >= ctx->cfg.n_layers) return fail(MOE_EINVAL, "layer %d out of range [0,%d)", layer, ctx->cfg.n_layers);
   if (ctx->h_gave_up && __atomic_load_n(ctx->h_gave_up, __ATOMIC_RELAXED) != 0)
     return fail(MOE_EHIP, "an expert kernel gave up waiting for the layer boundary of its own launch: outputs since then are invalid");
+  return MOE_OK;
+}
+
+// Polls until arrived() or, after 200 ms (or at once without polling: MOE_HOST_SYNC=event), the end of what has been
+// enqueued on the compute stream, which also surfaces launch errors.  Whether it has arrived then.
+template <typename F>
+int wait_for(moe_cache_t *c, F arrived, bool *ok) {
+  *ok = true;
+  if (c->poll) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t spin = 0;; ++spin) {
+      if (arrived()) return MOE_OK;
+      if ((spin & 0x3ff) == 0x3ff && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(200)) break;
+    }
+  }
+  HIP_TRY(hipEventRecord(c->ev_route, c->compute));
+  HIP_TRY(hipEventSynchronize(c->ev_route));
+  *ok = arrived();
   return MOE_OK;
 }
 
@@ -284,6 +306,9 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
                          hipHostMallocMapped | hipHostMallocCoherent));
   memset(c->h_note, 0, sizeof(HostNote) * L);
   HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->h_note_dev), c->h_note, 0));
+  HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->h_rec), sizeof(HostRecord), hipHostMallocMapped | hipHostMallocCoherent));
+  memset(c->h_rec, 0, sizeof(HostRecord));
+  HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->h_rec_dev), c->h_rec, 0));
   HIP_INIT(hipMalloc(&c->d_handover, sizeof(uint64_t) * 64 * (size_t)L));
   HIP_INIT(hipMemset(c->d_handover, 0, sizeof(uint64_t) * 64 * (size_t)L));
   HIP_INIT(hipMalloc(&c->d_ss, sizeof(float) * 128));
@@ -308,8 +333,12 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
     const int64_t routed_tiles = cfg->capacity + kMaxBatch * cfg->top_k / 16;
     const int64_t h_blocks = routed_tiles * ((cfg->inter + 31) / 32) + kMaxBatch / 16 * ((cfg->shared_inter + 31) / 32);
     HIP_INIT(hipMalloc(&c->d_logits_batch, sizeof(float) * kMaxBatch * MOE_MAX_EXPERTS));
-    HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->batch_rec), sizeof(moe_route_out_t) * kMaxBatch, hipHostMallocMapped));
+    HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->batch_rec), sizeof(moe_route_out_t) * kMaxBatch,
+                           hipHostMallocMapped | hipHostMallocCoherent));
     HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->batch_rec_dev), c->batch_rec, 0));
+    HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->h_done), sizeof(uint32_t), hipHostMallocMapped | hipHostMallocCoherent));
+    *c->h_done = 0;
+    HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->h_done_dev), c->h_done, 0));
     HIP_INIT(hipMalloc(&c->d_bsel, sizeof(BatchSel)));
     HIP_INIT(hipMalloc(&c->d_bahead, sizeof(BatchAhead)));
     HIP_INIT(hipMalloc(&c->d_bh, (size_t)h_blocks * 2048));
@@ -332,6 +361,8 @@ void moe_cache_destroy(moe_cache_t *c) {
   if (c->d_state) (void)hipFree(c->d_state);
   if (c->d_route) (void)hipFree(c->d_route);
   if (c->h_note) (void)hipHostFree(c->h_note);
+  if (c->h_rec) (void)hipHostFree(c->h_rec);
+  if (c->h_done) (void)hipHostFree(c->h_done);
   if (c->d_handover) (void)hipFree(c->d_handover);
   if (c->d_ss) (void)hipFree(c->d_ss);
   if (c->h_gave_up) (void)hipHostFree(c->h_gave_up);
@@ -368,23 +399,9 @@ static int collect_route(moe_cache_t *c, int32_t layer, uint32_t seq, int *n_mis
     w2 = __atomic_load_n(&h->w[2], __ATOMIC_ACQUIRE);
     return (uint32_t)w0 == seq && (w1 & 0xffffu) == tag && (w2 & 0xffffu) == tag;
   };
-  bool seen = false;
-  if (c->poll) {
-    const auto t0 = std::chrono::steady_clock::now();
-    for (uint32_t spin = 0;; ++spin) {
-      if (arrived()) {
-        seen = true;
-        break;
-      }
-      if ((spin & 0x3ff) == 0x3ff && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(200))
-        break;  // fall back to a stream synchronisation (also surfaces launch errors)
-    }
-  }
-  if (!seen) {
-    HIP_TRY(hipEventRecord(c->ev_route, c->compute));
-    HIP_TRY(hipEventSynchronize(c->ev_route));
-    if (!arrived()) return fail(MOE_EHIP, "route kernel of layer %d did not publish its result", layer);
-  }
+  bool ok;
+  if (int rc = wait_for(c, arrived, &ok)) return rc;
+  if (!ok) return fail(MOE_EHIP, "route kernel of layer %d did not publish its result", layer);
   moe_cache::Decision &d = c->decided[layer];
   d.n_miss = (int)((w0 >> 32) & 0xff);
   d.miss_mask = (uint8_t)((w0 >> 40) & 0xff);
@@ -452,7 +469,23 @@ static int finish_route_call(moe_cache_t *c, int32_t layer, uint32_t seq, moe_ro
   int n_miss = 0;
   if (int rc = collect_route(c, layer, seq, &n_miss)) return rc;
   c->routed[layer] = 1;
-  return fetch_record(c, layer, out_host);
+  // the record follows the decision by a microsecond
+  uint32_t w[kHostRecWords];
+  bool ok;
+  const auto arrived = [&]() {
+    bool all = true;
+    for (int i = 0; i < kHostRecWords; ++i) {
+      const uint64_t v = __atomic_load_n(&c->h_rec->w[i], __ATOMIC_ACQUIRE);
+      w[i] = (uint32_t)v;
+      all &= (uint32_t)(v >> 32) == seq;
+    }
+    return all;
+  };
+  if (int rc = wait_for(c, arrived, &ok)) return rc;
+  if (!ok) return fail(MOE_EHIP, "route kernel of layer %d did not publish its record", layer);
+  static_assert(sizeof w == sizeof *out_host, "record words");
+  memcpy(out_host, w, sizeof w);
+  return MOE_OK;
 }
 
 int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float *logits_dev,
@@ -464,7 +497,7 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
   if (c->batch_layer >= 0) return fail(MOE_ESTATE, "a routed batch is pending: call moe_expert_forward_batch first");
   const RouteParams p = make_route_params(c);
   HIP_TRY(launch_route(p, c->gate_w[layer], x_dev, logits_dev, c->d_state + layer, c->d_route + layer,
-                       c->h_note_dev + layer, c->compute));
+                       HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
   return finish_route_call(c, layer, p.seq, out_host);
 }
 
@@ -526,8 +559,8 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     f.carry = carry;
   }
   c->pending_rows = 0;
-  HIP_TRY(launch_fused_route(p, f, c->gate_w[layer], c->d_state + layer, c->d_route + layer, c->h_note_dev + layer,
-                             c->compute));
+  HIP_TRY(launch_fused_route(p, f, c->gate_w[layer], c->d_state + layer, c->d_route + layer,
+                             HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
   return finish_route_call(c, layer, p.seq, out_host);
 }
 
@@ -632,8 +665,10 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
     z = c->d_logits_batch;
   }
   const RouteParams p = make_route_params(c);
-  HIP_TRY(launch_route_batch(p, z, n_tokens, c->d_state + layer, c->batch_rec_dev, c->d_bsel, c->d_bahead, c->compute));
-  HIP_TRY(hipStreamSynchronize(c->compute));
+  HIP_TRY(launch_route_batch(p, z, n_tokens, c->d_state + layer, c->batch_rec_dev, c->d_bsel, c->d_bahead, c->h_done_dev, c->compute));
+  bool ok;
+  if (int rc = wait_for(c, [&]() { return __atomic_load_n(c->h_done, __ATOMIC_ACQUIRE) == p.seq; }, &ok)) return rc;
+  if (!ok) return fail(MOE_EHIP, "batch routing of layer %d did not publish its records", layer);
   const moe_cache_config_t &g = c->cfg;
   for (int t = 0; t < n_tokens; ++t)
     for (int k = 0; k < g.top_k; ++k) {
@@ -686,7 +721,6 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
   const moe_cache_config_t &g = c->cfg;
   const int K = g.top_k, d = g.hidden;
   const size_t slot_bytes = (size_t)c->slot_layout.total;
-  HIP_TRY(hipEventRecord(c->ev_batch, c->compute));  // whatever read the slots before this call is ahead of this point
   BatchParams bp{};
   bp.slot_pool = static_cast<const uint8_t *>(c->slot_pool[layer]);
   bp.shared_blob = g.shared_inter > 0 ? static_cast<const uint8_t *>(c->shared_blob[layer]) : nullptr;
@@ -724,7 +758,10 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
       for (int k = 0; k < K; ++k) {
         if (!r.miss[k]) continue;
         filled |= 1ull << r.sel_slot[k];
-        if (n_fill++ == 0) HIP_TRY(hipStreamWaitEvent(c->copy, c->ev_batch, 0));
+        if (n_fill++ == 0) {  // whatever reads the slots' previous contents is ahead of this point
+          HIP_TRY(hipEventRecord(c->ev_batch, c->compute));
+          HIP_TRY(hipStreamWaitEvent(c->copy, c->ev_batch, 0));
+        }
         if (c->poison_fills)
           HIP_TRY(hipMemsetAsync(static_cast<uint8_t *>(c->slot_pool[layer]) + (size_t)r.sel_slot[k] * slot_bytes, 0xff,
                                  slot_bytes, c->copy));
@@ -782,7 +819,6 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
       HIP_TRY(launch_down_batch(bp, n_down, c->compute));
     }
     HIP_TRY(launch_reduce_batch(bp, y_dev, bu.n_rc, bu.n_rc_shared, c->compute));
-    HIP_TRY(hipEventRecord(c->ev_batch, c->compute));
     t0 = t1;
   }
   HIP_TRY(hipStreamSynchronize(c->compute));

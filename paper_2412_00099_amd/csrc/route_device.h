@@ -180,12 +180,12 @@ constexpr int kHandoverCopies = 8;
 static_assert(kHandoverCopies * 8 == kWave, "one lane per word of every copy");
 
 // Everything after the logits (Eq. 3 softmax, Eq. 10, Eq. 9, Eq. 2, Eq. 4, Sec. 4.2), run by one wavefront.
-// note == nullptr: nobody on the host waits for this step (a token inside a batch).  carry != nullptr: receives the
+// host.note == nullptr: nobody on the host waits for this step (a token inside a batch).  host.rec: see HostRecord.  carry != nullptr: receives the
 // cache state as this step leaves it, so that a batch continues from registers; store_state = false then leaves the
 // state in device memory as it was.  n_miss_out, when given, receives the number of misses of the step.  out_dev may
 // point into LDS (a record that is copied out later, or dropped).
 __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_s, const CacheRegs &cr, LayerState *st,
-                                           moe_route_out_t *out_dev, HostNote *note, uint32_t *rec_s, int lane,
+                                           moe_route_out_t *out_dev, HostOut host, uint32_t *rec_s, int lane,
                                            BoundaryFlags flags = BoundaryFlags{nullptr, 0}, CacheRegs *carry = nullptr,
                                            bool store_state = true, int *n_miss_out = nullptr) {
 #pragma clang fp contract(off)
@@ -353,11 +353,11 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
       sw |= (uint64_t)(s8 & 63u) << (16 + 6 * k);
     }
   }
-  if (note != nullptr && lane < 3) {
+  if (host.note != nullptr && lane < 3) {
     const uint64_t tag = p.seq & 0xffffu;
     const uint64_t w0 = (uint64_t)p.seq | ((uint64_t)n_miss << 32) | ((uint64_t)mm << 40);
     const uint64_t v = lane == 0 ? w0 : (tag | (lane == 1 ? ew : sw));
-    __hip_atomic_store(&note->w[lane], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&host.note->w[lane], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 
   // ---- expert kernels waiting in the same launch need weights, slots and miss flags (see BoundaryFlags)
@@ -427,6 +427,15 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  if (host.rec != nullptr) {
+    static_assert(kRecWords <= 2 * kWave, "two words per lane");
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int j = lane + i * kWave;
+      if (j < kRecWords)
+        __hip_atomic_store(&host.rec->w[j], (uint64_t)rec_s[j] | ((uint64_t)p.seq << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
   if (lane < kRecWords / 4) reinterpret_cast<u32x4 *>(out_dev)[lane] = reinterpret_cast<const u32x4 *>(rec_s)[lane];
 }
 
@@ -564,7 +573,7 @@ __device__ __forceinline__ BoundaryLds carve_boundary_lds(uint32_t *base) {  // 
 // All threads of the workgroup must call it; only wavefront 0 returns late (after the routing).
 template <int NW, int CH, int PER, bool PRE = false>
 __device__ __forceinline__ void fused_boundary(const RouteParams &p, const FusedParams &f, const void *gate_w,
-                                               LayerState *st, moe_route_out_t *out_dev, HostNote *note,
+                                               LayerState *st, moe_route_out_t *out_dev, HostOut host,
                                                BoundaryFlags flags, const BoundaryLds &lds) {
 #pragma clang fp contract(off)
   constexpr int NT = NW * kWave;
@@ -714,7 +723,7 @@ __device__ __forceinline__ void fused_boundary(const RouteParams &p, const Fused
   }
   __syncthreads();
   if (wave != 0) return;
-  route_wave(p, z_s, cr, st, out_dev, note, lds.rec_s, lane, flags);
+  route_wave(p, z_s, cr, st, out_dev, host, lds.rec_s, lane, flags);
 }
 
 // Workgroup 0 of an expert launch that carries the layer boundary (NW wavefronts; d = NW*64*PER with bf16
@@ -723,7 +732,7 @@ __device__ __forceinline__ void fused_boundary(const RouteParams &p, const Fused
 template <int NW, int CH, int PER>
 __device__ __forceinline__ void boundary_workgroup(const GemvParams &p, float *red) {
   const int tid = threadIdx.x, d = p.hidden;
-  fused_boundary<NW, CH, PER, true>(p.b.route, p.b.glue, p.b.gate_w, p.b.state, p.b.out_dev, p.b.note,
+  fused_boundary<NW, CH, PER, true>(p.b.route, p.b.glue, p.b.gate_w, p.b.state, p.b.out_dev, HostOut{p.b.note, nullptr},
                                     BoundaryFlags{p.b.handover, p.b.hand_tag},
                                     carve_boundary_lds(reinterpret_cast<uint32_t *>(red)));
   float *row = p.partial + (int64_t)p.row_offset * d;  // this workgroup's partial row: nothing to add

@@ -23,7 +23,7 @@ using namespace rt;
 
 __global__ __launch_bounds__(1024) void route_kernel(RouteParams p, const void *gate_w, const void *x,
                                                      const float *logits_in, LayerState *st,
-                                                     moe_route_out_t *out_dev, HostNote *note) {
+                                                     moe_route_out_t *out_dev, HostOut host) {
   __shared__ float z_s[MOE_MAX_EXPERTS];
   __shared__ __attribute__((aligned(16))) uint32_t rec_s[kRecWords];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(1024) void route_kernel(RouteParams p, const void *
   }
   __syncthreads();
   if (wave != 0) return;
-  route_wave(p, z_s, cr, st, out_dev, note, rec_s, lane);
+  route_wave(p, z_s, cr, st, out_dev, host, rec_s, lane);
 }
 
 
@@ -50,9 +50,9 @@ __global__ __launch_bounds__(1024) void route_kernel(RouteParams p, const void *
 template <int CH, int PER, bool PRE>
 __global__ __launch_bounds__(1024) void fused_route_kernel(RouteParams p, FusedParams f, const void *gate_w,
                                                            LayerState *st, moe_route_out_t *out_dev,
-                                                           HostNote *note) {
+                                                           HostOut host) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[kBoundaryLdsWords];
-  fused_boundary<16, CH, PER, PRE>(p, f, gate_w, st, out_dev, note, BoundaryFlags{nullptr, 0},
+  fused_boundary<16, CH, PER, PRE>(p, f, gate_w, st, out_dev, host, BoundaryFlags{nullptr, 0},
                                    carve_boundary_lds(lds));
 }
 
@@ -82,14 +82,13 @@ __global__ void state_init_kernel(LayerState *state, int n_layers, const int32_t
 }  // namespace
 
 hipError_t launch_route(const RouteParams &p, const void *gate_w, const void *x, const float *logits,
-                        LayerState *state, moe_route_out_t *out_dev, HostNote *note_mapped,
-                        hipStream_t s) {
+                        LayerState *state, moe_route_out_t *out_dev, HostOut host, hipStream_t s) {
   // at most four rows of the gate matrix per wavefront, so that all of a wavefront's loads are in flight at once
   int waves = logits ? 1 : (p.n_experts + 3) / 4;
   if (waves > 16) waves = 16;
   if (waves < 1) waves = 1;
   hipLaunchKernelGGL(route_kernel, dim3(1), dim3(waves * kWave), 0, s, p, gate_w, x, logits, state, out_dev,
-                     note_mapped);
+                     host);
   return hipGetLastError();
 }
 
@@ -98,7 +97,7 @@ hipError_t launch_route(const RouteParams &p, const void *gate_w, const void *x,
 bool fused_route_pre_supported(int hidden) { return hidden == 1024 || hidden == 2048 || hidden == 4096; }
 
 hipError_t launch_fused_route(const RouteParams &p, const FusedParams &f, const void *gate_w, LayerState *state,
-                              moe_route_out_t *out_dev, HostNote *note_mapped, hipStream_t s) {
+                              moe_route_out_t *out_dev, HostOut host, hipStream_t s) {
   if (p.hidden > kFusedMaxHidden || p.hidden % 8 != 0) return hipErrorInvalidValue;
   // 16 wavefronts, at most four gate rows each (N <= 64)
   const dim3 g(1), b(1024);
@@ -110,7 +109,7 @@ hipError_t launch_fused_route(const RouteParams &p, const FusedParams &f, const 
   const bool pre = f.ss != nullptr;
   if (pre && !fused_route_pre_supported(p.hidden)) return hipErrorInvalidValue;
 #define MOE_FUSED(CH_, PER_, PRE_)                                                                              \
-  hipLaunchKernelGGL((fused_route_kernel<CH_, PER_, PRE_>), g, b, 0, s, p, f, gate_w, state, out_dev, note_mapped)
+  hipLaunchKernelGGL((fused_route_kernel<CH_, PER_, PRE_>), g, b, 0, s, p, f, gate_w, state, out_dev, host)
 #define MOE_FUSED2(CH_, PER_)                                                                                   \
   do {                                                                                                          \
     if (pre) MOE_FUSED(CH_, PER_, true);                                                                        \

@@ -293,3 +293,28 @@ def test_batch_routing_ahead_equals_token_by_token(N, K, C):
         assert getattr(sa, field) == getattr(sb, field), field
     one.close()
     many.close()
+
+
+@pytest.mark.parametrize("sync", ["poll", "event"])
+def test_record_of_a_blocking_step_is_the_device_record(sync, monkeypatch):
+    """A blocking step's record comes through mapped host memory while its kernel still runs; every field must be the
+    one the device keeps, step after step, also where the host waits for an event; and a batch's records the same."""
+    if sync == "event":
+        monkeypatch.setenv("MOE_HOST_SYNC", "event")
+    cfg = BASE.with_(n_layers=1, hidden=1024, n_experts=64, inter=16, shared_inter=0, top_k=8, capacity=12, seed=951)
+    print(f"case blocking record, {sync}", flush=True)
+    store, dec = build(cfg, lam=0.5)
+    store2, dec2 = build(cfg, lam=0.5)
+    zs = workloads.logits_stream(cfg, 40, layer=0, scale=1.5).to(DEV)
+    x = torch.zeros((40, cfg.hidden), dtype=cfg.act_dtype, device=DEV)
+    y = torch.zeros_like(x)
+    recs = dec2.route_batch(0, logits=zs)
+    for t in range(40):
+        a = dec.route_step(0, logits=zs[t])
+        b = dec.last_route(0)
+        assert bytes(a) == bytes(b)
+        assert bytes(a)[:-16] == bytes(recs[t])[:-16]  # (the library's own words carry the call's number)
+        dec.expert_forward(0, x[0], y[0])
+    dec2.expert_forward_batch(0, x, y)
+    dec.close()
+    dec2.close()
