@@ -503,9 +503,9 @@ def main():
     # on the same store, created with the in-launch boundary switched off, over the same tokens
     alone = None
     if not args.no_sweep:
-        os.environ["MOE_FUSE_BOUNDARY"] = "0"
+        os.environ["MOE_FUSE_BOUNDARY"] = os.environ["MOE_ROUTE_EVERYWHERE"] = "0"
         dec2 = pkg.MoEDecoder(store, top_k=cfg.top_k, top_j=cfg.top_j, lam=HEADLINE_LAMBDA, renormalize=cfg.renormalize)
-        del os.environ["MOE_FUSE_BOUNDARY"]
+        del os.environ["MOE_FUSE_BOUNDARY"], os.environ["MOE_ROUTE_EVERYWHERE"]
         r2 = timed_run(dec2, a, h, x, y, OWN_WARMUP, own_steps)
         us2, n2, _ = kernel_time(dec2, a, h, x, y, OWN_WARMUP, own_steps)
         dec2.close()

@@ -26,6 +26,8 @@
  *                              words the router stores into mapped host memory
  *      MOE_FUSE_BOUNDARY=0|1   overrides the rule that decides whether a non-blocking moe_stack_route_step runs
  *                              inside the layer's expert launch (see moe_cache_plan)
+ *      MOE_ROUTE_EVERYWHERE=0|1 overrides the rule that decides whether, where it does not, the routing is left to every
+ *                              workgroup of the expert launch (hidden 512, 1024, 2048, 4096; 256 with fp32)
  *      MOE_POISON_FILLS=1      debugging aid: a slot is overwritten with 0xff bytes (NaNs in every format's
  *                              scales or weights) on the copy stream right before its fill, so that anything
  *                              computed from a slot before its fill has landed shows up as NaN in the output
@@ -212,9 +214,10 @@ int moe_expert_forward_static(int32_t weight_fmt, int32_t act_fmt, int32_t hidde
  * layer's moe_expert_forward); y_dev: device act_fmt [d] or NULL, receives the finished pending output.
  * hidden must be at most 8192.  Same blocking rule and errors as moe_route_step.
  * With out_host NULL the library may defer x and the routing into the layer's expert launch (its first workgroup
- * does them while the others already stream the shared expert; see moe_cache_plan): x_dev and the routing record
- * are then written by the kernels moe_expert_forward enqueues, not by this call's, so nothing but
- * moe_expert_forward(ctx, layer, x_dev, ...) may use x_dev in between, and that call must be given the same x_dev.
+ * does them while the others already stream the shared expert; see moe_cache_plan), or the routing alone (every
+ * workgroup then works the decision out from the logits): x_dev and the routing record are then written by the kernels
+ * moe_expert_forward enqueues, not by this call's, so nothing but moe_expert_forward(ctx, layer, x_dev, ...) may use
+ * x_dev in between, that call must be given the same x_dev, and tables and counters include the step after it.
  * The other workgroups' wait for the first one is bounded; should it ever run out, they finish without the routed
  * experts, and every later call that names a layer returns MOE_EHIP until moe_cache_reset. */
 int moe_stack_route_step(moe_cache_t *ctx, int32_t layer, float *h_dev, const float *a_dev, float perturb,
@@ -276,9 +279,9 @@ int moe_trace_misses(const int32_t *trace, int64_t n_tokens, int32_t top_k, int3
                      int64_t *lifetime_sum, int64_t *evictions);
 
 /* The launch shape the context chose for the expert kernels, and whether a moe_stack_route_step without out_host
- * runs its routing inside the layer's expert launch (bf16 activations, a supported shape, and a shared expert of at
- * least a third of the layer's records; MOE_FUSE_BOUNDARY=0 or 1 in the environment at moe_cache_init overrides
- * the last condition). */
+ * runs x and its routing in the first workgroup of the layer's expert launch (bf16 activations, a supported shape, and,
+ * other than int4, a shared expert of at least a third of the layer's records in a layer-token of at least 45 MB and 41 KB
+ * per hidden column; MOE_FUSE_BOUNDARY=0 or 1 in the environment at moe_cache_init overrides the last condition). */
 typedef struct moe_cache_plan {
   int32_t grid, wavefronts, depth, packed_bf16_dot, boundary_in_expert_launch;
 } moe_cache_plan_t;

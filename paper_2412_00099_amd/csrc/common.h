@@ -66,6 +66,17 @@ struct BoundaryArgs {
   const void *next_gate_w;
   const LayerState *next_state;
   int64_t gate_bytes;
+  // routing in every workgroup: the logits, and the copy of the state that receives the step (every wavefront of the
+  // launch reads the old one)
+  const float *logits;
+  LayerState *state_out;
+};
+// how an expert launch comes by the routing decision
+enum RouteIn {
+  kRouteBefore = 0,     // from the record an earlier launch wrote
+  kRouteBoundary = 1,   // workgroup 0 runs the layer boundary `b`, hands the decision over and writes a zero partial row
+  kRouteEverywhere = 2  // every wavefront routes for itself from b.logits and b.state; one workgroup more than plan.grid,
+                        // the first, does the bookkeeping
 };
 
 struct GemvParams {
@@ -78,7 +89,7 @@ struct GemvParams {
   int64_t slot_bytes;
   int32_t pass;        // 0: shared expert + experts that were resident; 1: experts whose slot was just filled
   int32_t row_offset;  // first partial row this launch writes
-  int32_t fused;       // workgroup 0 runs the layer boundary `b` and writes a zero partial row
+  int32_t route_in;    // RouteIn
   BoundaryArgs b;
 };
 
@@ -128,6 +139,10 @@ struct GemvPlan {
   bool dot2;  // packed bf16 dot products (bf16 weights and activations)
 };
 GemvPlan gemv_plan(int n_cus, int total_records, int weight_fmt, int act_fmt);
+// logits of a layer boundary whose glue launch_reduce_glue has done: x = h / rms to f.x_out, z = W_gate x, one workgroup per
+// four experts (needs gate_rows_supported)
+bool gate_rows_supported(int hidden, int act_fmt);
+hipError_t launch_gate_rows(const RouteParams &p, const FusedParams &f, const void *gate_w, float *logits, hipStream_t s);
 bool gemv_fused_supported(int weight_fmt, int act_fmt, int hidden, const GemvPlan &plan);  // a launch variant with the boundary in workgroup 0
 // f.ss != nullptr: the glue has been done by launch_reduce_glue (needs fused_route_pre_supported(hidden))
 bool fused_route_pre_supported(int hidden);

@@ -153,13 +153,14 @@ struct RecRegs {
 
 // FMT: weight format; LPR: 16-byte loads per row per lane (d = LPR*64*VEC); NW: wavefronts per workgroup;
 // DEPTH: records in flight per wavefront; DOT2: packed bf16 dot products.
-// FUSED: workgroup 0 runs the layer boundary (x, gate GEMV, routing: rt::fused_boundary) instead of streaming
+// IN = kRouteBoundary: workgroup 0 runs the layer boundary (x, gate GEMV, routing: rt::fused_boundary) instead of streaming
 // records.  The residual glue has been done by reduce_glue_kernel; every workgroup forms x for itself from the
 // new residual stream and its sums of squares (same operations in the same order everywhere, so all copies are
 // bit-identical), starts on the shared expert's records at once, and waits for workgroup 0's decision only before
 // its first routed record (RecordWalker::load_handover), so the boundary costs the launch little.  The wait is
 // on workgroup 0 only, which is dispatched first, and is bounded.
-template <int FMT, int LPR, int NW, int DEPTH, bool DOT2, bool FUSED>
+// IN = kRouteEverywhere: see RouteIn.
+template <int FMT, int LPR, int NW, int DEPTH, bool DOT2, int IN>
 __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
   using F = Chunk<FMT, DOT2>;
   constexpr int VEC = F::VEC, XW = F::XW;
@@ -170,6 +171,13 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront-uniform: keeps record addressing scalar
   const int d = p.hidden;
+  constexpr bool FUSED = IN == kRouteBoundary;
+  if constexpr (IN == kRouteEverywhere) {
+    if (blockIdx.x == 0) {
+      rt::routing_workgroup(p, red);
+      return;
+    }
+  }
   if constexpr (FUSED) {
     if (blockIdx.x == 0) {
       // with packed bf16 arithmetic the gate matrix has LPR 16-byte chunks per row per lane, and with NW = 8 each
@@ -181,7 +189,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
   }
   const int64_t row16 = (int64_t)d / VEC;  // 16-byte chunks per row
   const int64_t rec_bytes = 3 * row16 * 16;
-  RecordWalker<NW, FUSED> walk;
+  RecordWalker<NW, IN> walk;
   walk.init(p, wave);
   // FUSED: the operands of x (this lane's columns of the residual stream, its sums of squares per 64 columns) are
   // fetched first: a few small loads that complete before the weights queued behind them
@@ -213,6 +221,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
   // all loads.  Pass 1 (only the experts just filled) skips the other records without loading them.
   const bool all = p.pass == 0;
   int todo = all ? walk.remaining() : 0;  // entries not issued yet (pass 0)
+  if constexpr (IN == kRouteEverywhere) walk.decide_now(p);
   RecRegs<LPR> ring[DEPTH];
   bool live[DEPTH], want[DEPTH];
   auto advance = [&](int j) {  // next record into ring[j], if there is one
@@ -284,7 +293,8 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     }
   }
 
-  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + blockIdx.x) * d, tid, lane, wave);
+  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
+                                tid, lane, wave);
 }
 
 // y[j] = sum over partial rows in index order, rounded to the activation type.
@@ -424,24 +434,27 @@ __global__ __launch_bounds__(256) void reduce_glue_kernel(const float *partial, 
   }
 }
 
-template <int FMT, int LPR, int NW, int DEPTH, bool DOT2, bool FUSED = false>
+template <int FMT, int LPR, int NW, int DEPTH, bool DOT2, int IN>
 void launch_one(const GemvParams &p, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  hipExtLaunchKernelGGL((expert_gemv_kernel<FMT, LPR, NW, DEPTH, DOT2, FUSED>), dim3(grid), dim3(NW * kWave), 0, s,
+  hipExtLaunchKernelGGL((expert_gemv_kernel<FMT, LPR, NW, DEPTH, DOT2, IN>), dim3(grid), dim3(NW * kWave), 0, s,
                         e0, e1, 0, p);
 }
 
 template <int FMT, int LPR, bool DOT2>
 hipError_t launch_plan(const GemvParams &p, const GemvPlan &plan, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (p.fused) {  // the variant with the boundary in workgroup 0 exists for packed bf16 arithmetic, d <= 2048
+  if (p.route_in == kRouteBoundary) {  // the variant with the boundary in workgroup 0 exists for packed bf16 arithmetic, d <= 2048
     if constexpr (LPR <= 4 && DOT2) {
       if (plan.grid < 2) return hipErrorInvalidValue;
-      launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, true>(p, plan.grid, s, e0, e1);
+      launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteBoundary>(p, plan.grid, s, e0, e1);
       return hipGetLastError();
     } else {
       return hipErrorInvalidValue;
     }
   }
-  launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2>(p, plan.grid, s, e0, e1);
+  if (p.route_in == kRouteEverywhere)
+    launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteEverywhere>(p, plan.grid + 1, s, e0, e1);
+  else
+    launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteBefore>(p, plan.grid, s, e0, e1);
   return hipGetLastError();
 }
 

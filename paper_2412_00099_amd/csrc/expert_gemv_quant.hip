@@ -119,13 +119,20 @@ struct RecI8 {
 
 // PRE: the per-column scales of W_down are fetched when the wavefront enters an expert, so that the flush at the
 // next change finds them in registers (costs 2*LPR 16-byte registers per lane)
-template <int LPR, int NW, int DEPTH, bool PRE, bool FUSED>
+template <int LPR, int NW, int DEPTH, bool PRE, int IN>
 __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams p) {
   constexpr int VEC = 16, CPL = LPR * VEC;
   __shared__ __attribute__((aligned(16))) float red[kRedFloats];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int d = p.hidden;
+  constexpr bool FUSED = IN == kRouteBoundary;
+  if constexpr (IN == kRouteEverywhere) {
+    if (blockIdx.x == 0) {
+      rt::routing_workgroup(p, red);
+      return;
+    }
+  }
   if constexpr (FUSED) {
     if (blockIdx.x == 0) {
       rt::boundary_workgroup<NW, boundary_ch(CPL * kWave), boundary_per(CPL * kWave)>(p, red);
@@ -134,7 +141,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
   }
   const int64_t row16 = d / VEC;
   const int64_t rec_bytes = 3 * row16 * 16;
-  RecordWalker<NW, FUSED> walk;
+  RecordWalker<NW, IN> walk;
   walk.init(p, wave);
 
   auto issue = [&](RecI8<LPR> &R) {
@@ -170,6 +177,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     for (int c = 0; c < LPR; ++c) fetch_x<VEC>(p.x, p.act_fmt, (c * kWave + lane) * VEC, xraw[c]);
   }
 
+  if constexpr (IN == kRouteEverywhere) walk.decide_now(p);
   RecI8<LPR> ring[DEPTH];
   bool live[DEPTH];
 #pragma unroll
@@ -291,7 +299,8 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     }
   }
   if (cur_base) flush(cur_base, cur_rows);
-  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + blockIdx.x) * d, tid, lane, wave);
+  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
+                                tid, lane, wave);
 }
 
 // =================================================================================================
@@ -321,13 +330,20 @@ struct RecI4 {
   int rows, grp;
 };
 
-template <int LPR, int NW, int DEPTH, bool PRE, bool FUSED>
+template <int LPR, int NW, int DEPTH, bool PRE, int IN>
 __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams p) {
   constexpr int VEC = 32, CPL = LPR * VEC;
   __shared__ __attribute__((aligned(16))) float red[kRedFloats];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int d = p.hidden;
+  constexpr bool FUSED = IN == kRouteBoundary;
+  if constexpr (IN == kRouteEverywhere) {
+    if (blockIdx.x == 0) {
+      rt::routing_workgroup(p, red);
+      return;
+    }
+  }
   if constexpr (FUSED) {
     if (blockIdx.x == 0) {
       rt::boundary_workgroup<NW, boundary_ch(CPL * kWave), boundary_per(CPL * kWave)>(p, red);
@@ -336,7 +352,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   }
   const int64_t row16 = d / VEC;                             // 16-byte chunks per row of nibbles
   const int64_t rec_bytes = int4_record_bytes(d);            // three rows + (gate, up) scale pairs, padded
-  RecordWalker<NW, FUSED, 1> walk;  // a contiguous block of records per wavefront: few changes of scale group
+  RecordWalker<NW, IN, 1> walk;  // a contiguous block of records per wavefront: few changes of scale group
   walk.init(p, wave);
 
   auto issue = [&](RecI4<LPR> &R) {
@@ -377,6 +393,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   // the oldest record only.  Pass 1 (the experts just filled) skips the other records without loading them.
   const bool all = p.pass == 0;
   int todo = all ? walk.remaining() : 0;
+  if constexpr (IN == kRouteEverywhere) walk.decide_now(p);
   RecI4<LPR> ring[DEPTH];
   bool live[DEPTH], want[DEPTH];
   auto advance = [&](int j) {
@@ -553,20 +570,25 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     }
   }
   if (dirty) flush(cur_base, cur_rows, cur_grp);
-  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + blockIdx.x) * d, tid, lane, wave);
+  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
+                                tid, lane, wave);
 }
 
 }  // namespace
 
 hipError_t launch_expert_gemv_quant(const GemvParams &p, int weight_fmt, const GemvPlan &plan, hipStream_t s,
                                     hipEvent_t e0, hipEvent_t e1) {
-  const dim3 g(plan.grid), b(8 * kWave);
+  const dim3 g(plan.grid + (p.route_in == kRouteEverywhere)), b(8 * kWave);
 #define MOE_Q(KERNEL, ...)                                                                      \
   do {                                                                                          \
-    if (p.fused) hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, true>), g, b, 0, s, e0, e1, 0, p);  \
-    else hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, false>), g, b, 0, s, e0, e1, 0, p);         \
+    if (p.route_in == kRouteBoundary)                                                           \
+      hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, kRouteBoundary>), g, b, 0, s, e0, e1, 0, p);   \
+    else if (p.route_in == kRouteEverywhere)                                                    \
+      hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, kRouteEverywhere>), g, b, 0, s, e0, e1, 0, p); \
+    else                                                                                        \
+      hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, kRouteBefore>), g, b, 0, s, e0, e1, 0, p);     \
   } while (0)
-  if (p.fused && (plan.grid < 2 || p.act_fmt != MOE_A_BF16)) return hipErrorInvalidValue;
+  if (p.route_in == kRouteBoundary && (plan.grid < 2 || p.act_fmt != MOE_A_BF16)) return hipErrorInvalidValue;
   if (weight_fmt == MOE_W_INT8_PC) {
     switch (p.hidden / (kWave * 16)) {
       case 1: MOE_Q(expert_gemv_int8_kernel, 1, 8, 2, true); break;

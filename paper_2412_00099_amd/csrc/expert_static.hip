@@ -116,7 +116,7 @@ hipError_t launch_expert_forward_static(int weight_fmt, int act_fmt, int hidden,
   p.slot_bytes = slot_bytes;
   p.pass = 0;
   p.row_offset = 0;
-  p.fused = 0;
+  p.route_in = kRouteBefore;
   e = launch_expert_gemv(p, weight_fmt, plan, s);
   if (e != hipSuccess) return e;
   return launch_partial_reduce(partial, plan.grid, y, hidden, act_fmt, s);

@@ -61,8 +61,10 @@ __device__ __forceinline__ void wave_sum2(float &a, float &b) {
 __device__ __forceinline__ u32x4 ld128(const void *p) { return *static_cast<const u32x4 *>(p); }
 __device__ __forceinline__ u32x2 ld64(const void *p) { return *static_cast<const u32x2 *>(p); }
 
-// FUSED: workgroup 0 of the launch runs the layer boundary; the records are shared among workgroups 1..G-1 and
-// the decision is fetched only when the first routed entry comes up, once workgroup 0 has handed it over.
+// IN (RouteIn) = kRouteBoundary: workgroup 0 of the launch runs the layer boundary; the records are shared among
+// workgroups 1..G-1 and the decision is fetched only when the first routed entry comes up, once workgroup 0 has handed it
+// over.  kRouteEverywhere: the same split, and every wavefront with routed entries works the decision out before its first
+// load of weights (decide_now: one place in the kernel, where few registers are in use).
 // STEP: distance between a wavefront's consecutive list entries.  NW (the default) interleaves the wavefronts over
 // the workgroup's list; 1 gives every wavefront one contiguous block of it, so that its records stay inside one
 // expert and, for int4, inside one scale group of 128 records as far as possible.
@@ -70,7 +72,11 @@ __device__ __forceinline__ u32x2 ld64(const void *p) { return *static_cast<const
 // The walk is organised in runs - consecutive entries of the wavefront inside one blob (the shared expert, or one
 // selected expert) - so that the per-record work is an increment and a decrement; slot, weight and the split of the
 // routed index into (expert, row) are worked out once per run.  All of it is wavefront-uniform (scalar registers).
-template <int NW, bool FUSED = false, int STEP = NW>
+namespace rt {
+__device__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane, uint64_t &slots,
+                       uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]);
+}
+template <int NW, int IN = kRouteBefore, int STEP = NW>
 struct RecordWalker {
   static_assert(STEP == NW || STEP == 1, "interleaved or blocked");
   int sh_at, n_sh;   // the wavefront's shared records: first row, how many (not yet started)
@@ -83,6 +89,8 @@ struct RecordWalker {
   u32x4 rw0, rw1, rd;  // sel_weight[0..3], sel_weight[4..7], {tag, slots lo, slots hi, miss mask}
   uint64_t slots;
   uint32_t miss_mask;
+  float z, dsum;       // kRouteEverywhere: lane's logit, Eq. 10's sum so far
+  int my_slot, count;  // lane's expert's slot, tokens so far
   // the record found by step() / next()
   const uint8_t *base;  // blob of the record's expert
   int rows, at;
@@ -145,9 +153,18 @@ struct RecordWalker {
   }
 
   __device__ __forceinline__ void init(const GemvParams &p, int wave) {
-    const int G = FUSED ? (int)gridDim.x - 1 : (int)gridDim.x, b = FUSED ? (int)blockIdx.x - 1 : (int)blockIdx.x;
-    // the routing record first: it is on its way while the shared records are set up
-    if constexpr (!FUSED) load_record(p);
+    constexpr int kFirst = IN == kRouteBefore ? 0 : 1;  // workgroups that stream nothing
+    const int G = (int)gridDim.x - kFirst, b = (int)blockIdx.x - kFirst;
+    // the routing record, or what it is worked out from, first: it is on its way while the shared records are set up
+    if constexpr (IN == kRouteBefore) load_record(p);
+    if constexpr (IN == kRouteEverywhere) {
+      const int lane = (int)(threadIdx.x & 63), e = min(lane, p.b.route.n_experts - 1);
+      z = p.b.logits[e];
+      my_slot = p.b.state->expert_slot[e];
+      dsum = p.b.state->delta_sum;
+      count = p.b.state->count;
+      __builtin_amdgcn_sched_barrier(0);
+    }
     const int routed = p.top_k * p.inter;
     const int shared = p.pass == 0 ? p.shared_inter : 0;
     // the workgroup's list: ns shared records from row s0, then nr routed entries from q0
@@ -172,6 +189,16 @@ struct RecordWalker {
     next_at = 0;
     run_wanted = true;
     decided = false;
+  }
+
+  // kRouteEverywhere, after init() and the loads that are wanted ahead of the weights
+  __device__ __forceinline__ void decide_now(const GemvParams &p) {
+    if (n_rt == 0) return;
+    float w[MOE_MAX_TOPK];
+    rt::decide(p.b.route, z, my_slot, dsum, count, (int)(threadIdx.x & 63), slots, miss_mask, w);
+    rw0 = u32x4{__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
+    rw1 = u32x4{__float_as_uint(w[4]), __float_as_uint(w[5]), __float_as_uint(w[6]), __float_as_uint(w[7])};
+    decided = true;
   }
 
   // masks instead of a select chain: a chain over adjacent members is turned into an indexed load from a
@@ -206,13 +233,15 @@ struct RecordWalker {
     }
     if (!decided) {  // first routed run: unpack the routing record
       bool ok = true;
-      if constexpr (FUSED) {
+      if constexpr (IN == kRouteBoundary) {
         // (one wavefront per workgroup fetching for all eight through LDS was measured: no faster)
         ok = load_handover(p.b.handover + 8 * ((int)blockIdx.x % 8), p.b.hand_tag, p.b.spin_limit);
       }
-      slots = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.y) |
-              ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.z) << 32);
-      miss_mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)rd.w);
+      if constexpr (IN != kRouteEverywhere) {
+        slots = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.y) |
+                ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.z) << 32);
+        miss_mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)rd.w);
+      }
       if (!ok) {  // no record: read slot 0 and use nothing of it
         slots = 0;
         miss_mask = p.pass == 1 ? 0u : ~0u;

@@ -61,7 +61,10 @@ struct moe_cache {
   BlobLayout slot_layout{};
   hipStream_t compute = nullptr, copy = nullptr;
 
-  LayerState *d_state = nullptr;
+  LayerState *d_state = nullptr;   // two copies of every layer's state: [2][n_layers]; cur[layer] says which one counts
+  std::vector<uint8_t> cur;        // (a launch that routes in every workgroup reads one and writes the other)
+  LayerState *state(int layer) const { return d_state + (size_t)cur[layer] * cfg.n_layers + layer; }
+  float *d_logits = nullptr;       // [n_layers][MOE_MAX_EXPERTS] logits of a layer boundary whose routing is still to come
   moe_route_out_t *d_route = nullptr;
   HostNote *h_note = nullptr;      // pinned, mapped: the router's message to the host, one per layer
   HostNote *h_note_dev = nullptr;  // device view of h_note
@@ -82,6 +85,7 @@ struct moe_cache {
   uint32_t *h_gave_up = nullptr;    // pinned, mapped: set by a wavefront that stopped waiting for the hand-over
   uint32_t *h_gave_up_dev = nullptr;
   bool fuse_boundary = true;        // run deferred boundaries inside the expert launch (see moe_cache_init)
+  bool route_everywhere = false;    // deferred boundaries: gate launch, routing in every workgroup of the expert launch
   bool poison_fills = false;        // debugging aid: a slot is overwritten with NaN patterns before its fill (MOE_POISON_FILLS)
   int tag_spins = 1 << 18;          // polls (about a tenth of a second) before a workgroup stops waiting for
                                     // workgroup 0; MOE_TAG_SPINS lowers it so that tests reach the error path
@@ -93,7 +97,8 @@ struct moe_cache {
   hipEvent_t ev_route = nullptr;
   std::vector<hipEvent_t> ev_copy;
   std::vector<uint8_t> routed;        // per layer: 0 idle, 1 routed (decision on the host), 2 routed (not collected
-                                      // yet), 3 boundary deferred into the expert launch
+                                      // yet), 3 boundary deferred into the expert launch,
+                                      // 4 routing deferred into every workgroup of it
   std::vector<uint32_t> route_seq;    // per layer: completion tag of the pending route step
   std::vector<uint32_t> hand_count;   // per layer: hand-overs inside an expert launch so far
   std::vector<int64_t> bytes_filled;
@@ -154,7 +159,9 @@ int do_reset(moe_cache_t *c) {
   HIP_TRY(hipStreamSynchronize(c->copy));
   if (c->n_initial > 0)
     HIP_TRY(hipMemcpy(c->d_initial, c->initial.data(), c->initial.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-  HIP_TRY(launch_state_init(c->d_state, c->cfg.n_layers, c->d_initial, c->n_initial, c->compute));
+  for (int copy = 0; copy < 2; ++copy)
+    HIP_TRY(launch_state_init(c->d_state + (size_t)copy * c->cfg.n_layers, c->cfg.n_layers, c->d_initial, c->n_initial, c->compute));
+  std::fill(c->cur.begin(), c->cur.end(), 0);
   if (c->h_gave_up) __atomic_store_n(c->h_gave_up, 0u, __ATOMIC_RELAXED);
   c->pending_rows = 0;
   c->batch_layer = -1;
@@ -267,6 +274,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   c->compute = static_cast<hipStream_t>(cfg->compute_stream);
   c->copy = static_cast<hipStream_t>(cfg->copy_stream);
   c->routed.assign(L, 0);
+  c->cur.assign(L, 0);
   c->route_seq.assign(L, 0);
   c->hand_count.assign(L, 0);
   c->decided.assign(L, {});
@@ -299,7 +307,8 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   c->poll = true;
   if (const char *s = getenv("MOE_HOST_SYNC")) c->poll = strcmp(s, "event") != 0;
 
-  HIP_INIT(hipMalloc(&c->d_state, sizeof(LayerState) * L));
+  HIP_INIT(hipMalloc(&c->d_state, sizeof(LayerState) * 2 * L));
+  HIP_INIT(hipMalloc(&c->d_logits, sizeof(float) * MOE_MAX_EXPERTS * (size_t)L));
   HIP_INIT(hipMalloc(&c->d_route, sizeof(moe_route_out_t) * L));
   HIP_INIT(hipMemset(c->d_route, 0, sizeof(moe_route_out_t) * L));
   HIP_INIT(hipHostMalloc(reinterpret_cast<void **>(&c->h_note), sizeof(HostNote) * L,
@@ -317,11 +326,27 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
                          hipHostMallocMapped | hipHostMallocCoherent));
   *c->h_gave_up = 0;
   HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->h_gave_up_dev), c->h_gave_up, 0));
-  // The boundary inside the expert launch pays off when the shared expert gives the other workgroups enough to do
-  // until the routing record exists (measured: a gain of 20 % at one half of the records, none at one quarter).
-  // MOE_FUSE_BOUNDARY=0 / 1 in the environment overrides the rule.
-  c->fuse_boundary = 3 * (int64_t)cfg->shared_inter >= (int64_t)cfg->top_k * cfg->inter + cfg->shared_inter;
+  // Three ways to run a boundary that nobody waits for, by what a layer-token streams (measured, us for 12 layer-tokens;
+  // 60 experts, top-4; one launch of the boundary before the experts / routing in every workgroup behind a gate launch /
+  // boundary inside the expert launch):
+  //   bf16 d = 512:  34.6 MB, half shared  222 / 246 / 236    57.7 MB, 0.7 shared  249 / 248 / 236    69 MB  278 / 262
+  //   bf16 d = 1024: 34.4 MB, half shared  230 / 239 / 240    53.2 MB, 0.35 shared 251 / 241 / 242    69 MB  281 / 259 / 243
+  //   bf16 d = 2048: 12 MB, 0.35 shared    236 / 235 / 257    68.8 MB, half shared 301 / 267 / 274   115 MB  375 / 345 / 303
+  //   int8 d = 2048: 34.6 MB, half shared  266 / 238 / 268    98 MB, 0.65 shared     - / 338 / 325
+  //   int8 d = 4096: 34.6 MB, half shared  315 / 252 / 356   138 MB, half shared    - / 428 / 426   197 MB   - / 529 / 502
+  //   int4 d = 2048: 36 MB, 0.25 shared      - / 284 / 351   135 MB, 0.8 shared     - / 457 / 482
+  // Inside the launch the boundary hides behind the shared expert's records, but one compute unit does all of it, and the
+  // gate matrix alone costs it time in proportion to d: the launch has to be long for that.  Routing everywhere spreads
+  // the gate matrix; it costs a launch, which a short chain of small launches (d < 2048) feels: the host is behind then.
+  // MOE_FUSE_BOUNDARY=0 / 1 in the environment overrides the first rule.
+  const int64_t records = (int64_t)cfg->top_k * cfg->inter + cfg->shared_inter, streamed = records * c->slot_layout.rec_bytes;
+  c->fuse_boundary = cfg->weight_fmt != MOE_W_INT4_G128 && 3 * (int64_t)cfg->shared_inter >= records &&
+                     streamed >= std::max((int64_t)41000 * cfg->hidden, (int64_t)45000000);
+  c->route_everywhere = gate_rows_supported(cfg->hidden, cfg->act_fmt) &&
+                        (cfg->hidden >= 2048 || streamed >= (cfg->hidden >= 1024 ? 56000000 : 64000000));
   if (const char *s = getenv("MOE_FUSE_BOUNDARY")) c->fuse_boundary = atoi(s) != 0;
+  if (const char *s = getenv("MOE_ROUTE_EVERYWHERE"))
+    c->route_everywhere = atoi(s) != 0 && gate_rows_supported(cfg->hidden, cfg->act_fmt);
   if (const char *s = getenv("MOE_POISON_FILLS")) c->poison_fills = atoi(s) != 0;
   if (const char *s = getenv("MOE_TAG_SPINS")) if (atoi(s) > 0) c->tag_spins = atoi(s);
   HIP_INIT(hipMalloc(&c->d_initial, sizeof(int32_t) * (size_t)L * (b->n_initial > 0 ? b->n_initial : 1)));
@@ -359,6 +384,7 @@ void moe_cache_destroy(moe_cache_t *c) {
   (void)hipStreamSynchronize(c->compute);
   (void)hipStreamSynchronize(c->copy);
   if (c->d_state) (void)hipFree(c->d_state);
+  if (c->d_logits) (void)hipFree(c->d_logits);
   if (c->d_route) (void)hipFree(c->d_route);
   if (c->h_note) (void)hipHostFree(c->h_note);
   if (c->h_rec) (void)hipHostFree(c->h_rec);
@@ -496,7 +522,7 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
   if (c->pending_rows) return fail(MOE_ESTATE, "an expert output is pending: the next routing call must be moe_stack_route_step");
   if (c->batch_layer >= 0) return fail(MOE_ESTATE, "a routed batch is pending: call moe_expert_forward_batch first");
   const RouteParams p = make_route_params(c);
-  HIP_TRY(launch_route(p, c->gate_w[layer], x_dev, logits_dev, c->d_state + layer, c->d_route + layer,
+  HIP_TRY(launch_route(p, c->gate_w[layer], x_dev, logits_dev, c->state(layer), c->d_route + layer,
                        HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
   return finish_route_call(c, layer, p.seq, out_host);
 }
@@ -529,7 +555,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     b.route = p;
     b.glue = f;
     b.gate_w = c->gate_w[layer];
-    b.state = c->d_state + layer;
+    b.state = c->state(layer);
     b.out_dev = c->d_route + layer;
     b.note = c->h_note_dev + layer;
     b.handover = c->d_handover + 64 * (size_t)layer;
@@ -537,10 +563,32 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     b.gave_up = c->h_gave_up_dev;
     b.spin_limit = c->tag_spins;
     b.next_gate_w = c->gate_w[(layer + 1) % c->cfg.n_layers];
-    b.next_state = c->d_state + (layer + 1) % c->cfg.n_layers;
+    b.next_state = c->state((layer + 1) % c->cfg.n_layers);
     b.gate_bytes = (int64_t)c->cfg.n_experts * c->cfg.hidden * (c->cfg.act_fmt == MOE_A_BF16 ? 2 : 4);
     c->route_seq[layer] = p.seq;
     c->routed[layer] = 3;
+    return MOE_OK;
+  }
+  if (!out_host && c->route_everywhere) {
+    // nobody waits for the decision here: only x and the logits are made by this call (over several compute units), and
+    // every wavefront of the layer's expert launch routes for itself
+    HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
+                               carry, c->d_ss, c->compute));
+    c->pending_rows = 0;
+    f.ss = c->d_ss;
+    f.n_ss = c->cfg.hidden / 64;
+    float *logits = c->d_logits + (size_t)layer * MOE_MAX_EXPERTS;
+    HIP_TRY(launch_gate_rows(p, f, c->gate_w[layer], logits, c->compute));
+    BoundaryArgs &b = c->boundary[layer];
+    b = BoundaryArgs{};
+    b.route = p;
+    b.state = c->state(layer);
+    b.state_out = c->d_state + (size_t)(1 - c->cur[layer]) * c->cfg.n_layers + layer;
+    b.logits = logits;
+    b.out_dev = c->d_route + layer;
+    b.note = c->h_note_dev + layer;
+    c->route_seq[layer] = p.seq;
+    c->routed[layer] = 4;
     return MOE_OK;
   }
   if (fused_route_pre_supported(c->cfg.hidden)) {
@@ -559,7 +607,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     f.carry = carry;
   }
   c->pending_rows = 0;
-  HIP_TRY(launch_fused_route(p, f, c->gate_w[layer], c->d_state + layer, c->d_route + layer,
+  HIP_TRY(launch_fused_route(p, f, c->gate_w[layer], c->state(layer), c->d_route + layer,
                              HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
   return finish_route_call(c, layer, p.seq, out_host);
 }
@@ -589,7 +637,10 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   if (c->routed[layer] == 3) {
     if (x_dev != c->boundary[layer].glue.x_out)
       return fail(MOE_EINVAL, "layer %d: x_dev must be the vector moe_stack_route_step wrote", layer);
-    p.fused = 1;
+    p.route_in = kRouteBoundary;
+    p.b = c->boundary[layer];
+  } else if (c->routed[layer] == 4) {
+    p.route_in = kRouteEverywhere;
     p.b = c->boundary[layer];
   }
   const bool prof = c->profiling && c->prof_tick++ % (uint64_t)c->profiling == 0 && c->prof_used < c->prof_events.size();
@@ -601,7 +652,8 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   } else {
     HIP_TRY(launch_expert_gemv(p, g.weight_fmt, c->plan, c->compute));
   }
-  p.fused = 0;
+  if (p.route_in == kRouteEverywhere) c->cur[layer] ^= 1;  // the launch writes the other copy of the state
+  p.route_in = kRouteBefore;
   int n_miss = c->decided[layer].n_miss;
   if (c->routed[layer] >= 2) {
     if (int rc = collect_route(c, layer, c->route_seq[layer], &n_miss)) return rc;
@@ -665,7 +717,7 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
     z = c->d_logits_batch;
   }
   const RouteParams p = make_route_params(c);
-  HIP_TRY(launch_route_batch(p, z, n_tokens, c->d_state + layer, c->batch_rec_dev, c->d_bsel, c->d_bahead, c->h_done_dev, c->compute));
+  HIP_TRY(launch_route_batch(p, z, n_tokens, c->state(layer), c->batch_rec_dev, c->d_bsel, c->d_bahead, c->h_done_dev, c->compute));
   bool ok;
   if (int rc = wait_for(c, [&]() { return __atomic_load_n(c->h_done, __ATOMIC_ACQUIRE) == p.seq; }, &ok)) return rc;
   if (!ok) return fail(MOE_EHIP, "batch routing of layer %d did not publish its records", layer);
@@ -838,18 +890,19 @@ int moe_cache_stats(moe_cache_t *c, int32_t layer, moe_cache_stats_t *out) {
   if (!c || !out) return fail(MOE_EINVAL, "NULL argument");
   if (int rc = check_layer(c, layer == -1 ? 0 : layer)) return rc;  // also refuses a context whose hand-over was abandoned
   HIP_TRY(hipStreamSynchronize(c->compute));
-  std::vector<LayerState> st(c->cfg.n_layers);
-  HIP_TRY(hipMemcpy(st.data(), c->d_state, sizeof(LayerState) * st.size(), hipMemcpyDeviceToHost));
+  std::vector<LayerState> both(2 * (size_t)c->cfg.n_layers);
+  HIP_TRY(hipMemcpy(both.data(), c->d_state, sizeof(LayerState) * both.size(), hipMemcpyDeviceToHost));
   memset(out, 0, sizeof *out);
   for (int l = 0; l < c->cfg.n_layers; ++l) {
     if (layer != -1 && l != layer) continue;
-    out->tokens += st[l].count;
-    out->selections += st[l].selections;
-    out->hits += st[l].hits;
-    out->misses += st[l].misses;
-    out->cold_misses += st[l].cold_misses;
-    out->evictions += st[l].evictions;
-    out->lifetime_sum += st[l].lifetime_sum;
+    const LayerState &st = both[(size_t)c->cur[l] * c->cfg.n_layers + l];
+    out->tokens += st.count;
+    out->selections += st.selections;
+    out->hits += st.hits;
+    out->misses += st.misses;
+    out->cold_misses += st.cold_misses;
+    out->evictions += st.evictions;
+    out->lifetime_sum += st.lifetime_sum;
     out->bytes_filled += c->bytes_filled[l];
   }
   return MOE_OK;
@@ -860,7 +913,7 @@ int moe_cache_tables(moe_cache_t *c, int32_t layer, moe_cache_tables_t *out) {
   if (!out) return fail(MOE_EINVAL, "out is NULL");
   HIP_TRY(hipStreamSynchronize(c->compute));
   LayerState st;
-  HIP_TRY(hipMemcpy(&st, c->d_state + layer, sizeof st, hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(&st, c->state(layer), sizeof st, hipMemcpyDeviceToHost));
   memcpy(out->expert_slot, st.expert_slot, sizeof out->expert_slot);
   memcpy(out->slot_expert, st.slot_expert, sizeof out->slot_expert);
   memcpy(out->stamp, st.stamp, sizeof out->stamp);
@@ -888,7 +941,7 @@ int moe_cache_snapshot(moe_cache_t *c, int32_t layer, void *buf, size_t *bytes) 
   HIP_TRY(hipStreamSynchronize(c->compute));
   SnapshotHeader hd{kSnapMagic, kSnapVersion, c->cfg.n_experts, c->cfg.capacity, c->cfg.top_k, 0};
   memcpy(buf, &hd, sizeof hd);
-  HIP_TRY(hipMemcpy(static_cast<uint8_t *>(buf) + sizeof hd, c->d_state + layer, sizeof(LayerState),
+  HIP_TRY(hipMemcpy(static_cast<uint8_t *>(buf) + sizeof hd, c->state(layer), sizeof(LayerState),
                     hipMemcpyDeviceToHost));
   return MOE_OK;
 }
@@ -921,7 +974,7 @@ int moe_cache_restore(moe_cache_t *c, int32_t layer, const void *buf, size_t byt
   if (st.count < 0 || st.selections < 0 || st.misses < 0) return fail(MOE_EINVAL, "snapshot counters negative");
   HIP_TRY(hipStreamSynchronize(c->compute));
   HIP_TRY(hipStreamSynchronize(c->copy));
-  HIP_TRY(hipMemcpy(c->d_state + layer, &st, sizeof st, hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(c->state(layer), &st, sizeof st, hipMemcpyHostToDevice));
   const size_t slot_bytes = (size_t)c->slot_layout.total;
   for (int s = 0; s < g.capacity; ++s) {
     const int e = st.slot_expert[s];

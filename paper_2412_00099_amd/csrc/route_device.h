@@ -179,6 +179,95 @@ struct BoundaryFlags {
 constexpr int kHandoverCopies = 8;
 static_assert(kHandoverCopies * 8 == kWave, "one lane per word of every copy");
 
+// The part of a routing step that decides which experts a token takes and with which weights (Eq. 3 softmax, Eq. 10,
+// Eq. 9, Eq. 2), by one wavefront: lane e <-> expert e.  z: this lane's logit (-inf in lanes past the last expert).
+struct Selected {
+  int rank;         // position in the altered ranking r' (exact for the first K positions, >= K otherwise)
+  float w;          // softmax of the unmodified logits, renormalised over the selected experts if asked
+  float delta, dsum;
+  float zp, kth;    // altered logit; the K-th largest of them (Cache-Prior)
+  uint64_t taken;   // Cache-Prior: the experts placed
+};
+__device__ __forceinline__ Selected route_select(const RouteParams &p, float z, bool resident, int t, float dsum_prev, int lane) {
+#pragma clang fp contract(off)
+  const int N = p.n_experts, K = p.top_k;
+  const bool active = lane < N;
+  Selected s;
+  // softmax of the unmodified logits (Eq. 3); feeds only the expert weights
+  const float zmax = wave_max(z);
+  const float zmin = wave_min(active ? z : INFINITY);
+  const float pe = active ? expf(z - zmax) : 0.f;
+  const float psum = wave_sum(pe);
+  s.w = pe / psum;
+
+  // Delta_avg (Eq. 10): cumulative mean of the logit range, current token included
+  const float range = zmax - zmin;
+  s.dsum = dsum_prev + range;
+  s.delta = p.delta_mode == MOE_DELTA_FIXED ? p.delta_fixed
+            : p.delta_mode == MOE_DELTA_TOKEN ? range
+                                              : s.dsum / (float)(t + 1);
+
+  // router's own top-J (Sec. 3.3): J rounds of arg-max, ties -> lower index
+  uint64_t topj_mask = 0;
+  for (int j = 0; j < p.top_j; ++j) {
+    const bool cand = active && !((topj_mask >> lane) & 1);
+    const float m = wave_max(cand ? z : -INFINITY);
+    topj_mask |= 1ull << __builtin_ctzll(ballot(cand && z == m));
+  }
+  const bool top_j = (topj_mask >> lane) & 1;
+
+  s.zp = z;
+  s.taken = 0;
+  s.kth = 0.f;
+  if (p.route_mode == MOE_ROUTE_CACHE_PRIOR) {
+    const float bias = p.lambda * s.delta;               // one rounding
+    if (active && (resident || top_j)) s.zp = z + bias;  // one rounding (Eq. 9)
+    // position in r': how many altered logits are larger, then ties in lane order.  (Counting against 64 lanes is 192
+    // instructions whatever K, 0.3 us; K rounds of arg-max are K chains of dependent lane exchanges, 0.13 us each.)
+    const float v = active ? s.zp : -INFINITY;
+    int larger = 0;
+#pragma unroll
+    for (int j0 = 0; j0 < kWave; j0 += 16)
+      if (j0 < N) {
+#pragma unroll
+        for (int j = j0; j < j0 + 16; ++j) larger += readlane_f(v, j) > v;
+      }
+    s.rank = N;
+    uint64_t tied = 0;
+    for (int k = 0; k < K; ++k) {
+      if (tied == 0) tied = ballot(active && larger == k);
+      if (tied == 0) break;  // (logits that are not numbers)
+      const int l = (int)__builtin_ctzll(tied);
+      tied &= tied - 1;
+      if (lane == l) s.rank = k;
+      s.kth = readlane_f(v, l);
+      s.taken |= 1ull << l;
+    }
+  } else {
+    // Max-Rank (Eq. 6-7) / Cumsum-Threshold (Eq. 8): two promote() passes = a three-class stable partition
+    const int rank_z = rank_of(rank_key(z, lane, active));
+    int M = p.max_rank;
+    if (p.route_mode == MOE_ROUTE_CUMSUM) {
+      // mass ranked before me; M = number of experts whose preceding mass is still below p
+      float before = 0.f;
+      for (int r = 0; r < N; ++r) {
+        const float wr = readlane_f(s.w, (int)__builtin_ctzll(ballot(active && rank_z == r)));
+        if (rank_z > r) before += wr;
+      }
+      M = (int)__builtin_popcountll(ballot(active && before < p.cumsum_p));
+    }
+    const int cls = top_j ? 0 : ((resident && rank_z < M) ? 1 : 2);
+    const uint64_t key = active ? (((uint64_t)(2 - cls) << 32) | (uint32_t)(63 - rank_z)) : 0ull;
+    s.rank = rank_of(key);
+  }
+  // expert weights from the unmodified logits (Sec. 3.3), optional renormalisation (Sec. 2.1)
+  if (p.renormalize) {
+    const float sum = wave_sum(active && s.rank < K ? s.w : 0.f);
+    s.w = s.w / sum;
+  }
+  return s;
+}
+
 // Everything after the logits (Eq. 3 softmax, Eq. 10, Eq. 9, Eq. 2, Eq. 4, Sec. 4.2), run by one wavefront.
 // host.note == nullptr: nobody on the host waits for this step (a token inside a batch).  host.rec: see HostRecord.  carry != nullptr: receives the
 // cache state as this step leaves it, so that a batch continues from registers; store_state = false then leaves the
@@ -200,80 +289,18 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
   const bool active = lane < N;
   const float z = active ? z_s[lane] : -INFINITY;
 
-  // softmax of the unmodified logits (Eq. 3); feeds only the expert weights
-  const float zmax = wave_max(z);
-  const float zmin = wave_min(active ? z : INFINITY);
-  const float pe = active ? expf(z - zmax) : 0.f;
-  const float psum = wave_sum(pe);
-  float w = pe / psum;
-
-  // Delta_avg (Eq. 10): cumulative mean of the logit range, current token included
-  const float range = zmax - zmin;
-  const float dsum = dsum_prev + range;
-  const int cnt = t + 1;
-  const float delta = p.delta_mode == MOE_DELTA_FIXED ? p.delta_fixed
-                      : p.delta_mode == MOE_DELTA_TOKEN ? range
-                                                        : dsum / (float)cnt;
-
   const bool resident = my_slot >= 0;
-
-  // router's own top-J (Sec. 3.3): J rounds of arg-max, ties -> lower index
-  uint64_t topj_mask = 0;
-  for (int j = 0; j < p.top_j; ++j) {
-    const bool cand = active && !((topj_mask >> lane) & 1);
-    const float m = wave_max(cand ? z : -INFINITY);
-    topj_mask |= 1ull << __builtin_ctzll(ballot(cand && z == m));
-  }
-  const bool top_j = (topj_mask >> lane) & 1;
-
-  int rank_p;    // position in the altered ranking r' (exact for the first K positions, >= K otherwise)
-  float zp = z;  // altered logits (Cache-Prior only)
-  float margin = INFINITY;  // between the K-th and (K+1)-th altered logit (tie logging)
-  uint64_t taken = 0;       // Cache-Prior: the experts placed so far
-  float kth = 0.f;
-  if (p.route_mode == MOE_ROUTE_CACHE_PRIOR) {
-    const float bias = p.lambda * delta;               // one rounding
-    if (active && (resident || top_j)) zp = z + bias;  // one rounding (Eq. 9)
-    // only the head of r' matters: K rounds of arg-max, ties -> lower index (one more round, for the margin,
-    // follows once the decision has been handed on)
-    rank_p = N;
-    for (int k = 0; k < K; ++k) {
-      const bool cand = active && !((taken >> lane) & 1);
-      const float m = wave_max(cand ? zp : -INFINITY);
-      const int l = (int)__builtin_ctzll(ballot(cand && zp == m));
-      taken |= 1ull << l;
-      if (lane == l) rank_p = k;
-      kth = m;
-    }
-  } else {
-    // Max-Rank (Eq. 6-7) / Cumsum-Threshold (Eq. 8): two promote() passes = a three-class stable partition
-    const int rank_z = rank_of(rank_key(z, lane, active));
-    int M = p.max_rank;
-    if (p.route_mode == MOE_ROUTE_CUMSUM) {
-      // mass ranked before me; M = number of experts whose preceding mass is still below p
-      float before = 0.f;
-      for (int r = 0; r < N; ++r) {
-        const float wr = readlane_f(w, (int)__builtin_ctzll(ballot(active && rank_z == r)));
-        if (rank_z > r) before += wr;
-      }
-      M = (int)__builtin_popcountll(ballot(active && before < p.cumsum_p));
-    }
-    const int cls = top_j ? 0 : ((resident && rank_z < M) ? 1 : 2);
-    const uint64_t key = active ? (((uint64_t)(2 - cls) << 32) | (uint32_t)(63 - rank_z)) : 0ull;
-    rank_p = rank_of(key);
-  }
+  const Selected pick = route_select(p, z, resident, t, dsum_prev, lane);
+  const int rank_p = pick.rank, cnt = t + 1;
+  const float w = pick.w, delta = pick.delta, dsum = pick.dsum, zp = pick.zp, kth = pick.kth;
+  const uint64_t taken = pick.taken;  // Cache-Prior: the experts placed so far
+  float margin = INFINITY;            // between the K-th and (K+1)-th altered logit (tie logging)
   const bool sel = active && rank_p < K;
   const uint64_t sel_mask = ballot(sel);
   const bool miss = sel && !resident;
   const uint64_t miss_mask = ballot(miss);
   const int n_miss = (int)__builtin_popcountll(miss_mask);
   if (n_miss_out != nullptr) *n_miss_out = n_miss;
-
-  // expert weights from the unmodified logits (Sec. 3.3), optional renormalisation (Sec. 2.1)
-  if (p.renormalize) {
-    const float s = wave_sum(sel ? w : 0.f);
-    w = w / s;
-  }
 
   // ---- LRU update (Sec. 4.2) ----------------------------------------------------------------
   // touch order inside the token: descending original logit (ties -> lower index) -> position pos
@@ -437,6 +464,36 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
     }
   }
   if (lane < kRecWords / 4) reinterpret_cast<u32x4 *>(out_dev)[lane] = reinterpret_cast<const u32x4 *>(rec_s)[lane];
+}
+
+// What a streaming wavefront needs of the decision (see RecordWalker): slots 8 bits each, weights, miss flags, all in
+// selection order.  The experts that miss have no slot yet: slot 0, whose records are loaded and not used.
+__device__ __forceinline__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane,
+                                       uint64_t &slots, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]) {
+  const Selected pick = route_select(p, lane < p.n_experts ? z : -INFINITY, my_slot >= 0, t, dsum_prev, lane);
+  slots = 0;
+  miss_mask = 0;
+#pragma unroll
+  for (int k = 0; k < MOE_MAX_TOPK; ++k) {
+    weight[k] = 0.f;
+    if (k < p.top_k) {
+      const int l = (int)__builtin_ctzll(ballot(lane < p.n_experts && pick.rank == k) | (1ull << 63));
+      const int slot = readlane_i(my_slot, l);
+      weight[k] = readlane_f(pick.w, l);
+      if (slot >= 0) slots |= (uint64_t)(uint32_t)(slot & 0xff) << (8 * k);
+      else miss_mask |= 1u << k;
+    }
+  }
+}
+
+// Workgroup 0 of an expert launch in which every wavefront routes for itself: does the same step with everything that
+// goes with it - cache update, record, the host's note - from the old state to the new one.
+__device__ __forceinline__ void routing_workgroup(const GemvParams &p, float *red) {
+  if (threadIdx.x >= kWave) return;
+  const int lane = threadIdx.x;
+  const CacheRegs cr = load_cache_regs(p.b.state, lane, p.b.route.n_experts, p.b.route.capacity);
+  route_wave(p.b.route, p.b.logits, cr, p.b.state_out, p.b.out_dev, HostOut{p.b.note, nullptr}, reinterpret_cast<uint32_t *>(red),
+             lane);
 }
 
 // Gate rows of one wavefront held in registers: loaded before x exists, used once x is in LDS.

@@ -56,6 +56,40 @@ __global__ __launch_bounds__(1024) void fused_route_kernel(RouteParams p, FusedP
                                    carve_boundary_lds(lds));
 }
 
+// The logits of a layer boundary over several compute units: four wavefronts, one gate row each (the whole gate matrix
+// through one compute unit's L1 takes 3 us of the single-workgroup boundary).  Every workgroup forms x for itself, with
+// the same operations in the same order as fused_boundary; the first writes it to memory.  The routing is left to the
+// expert launch (kRouteEverywhere).
+constexpr int kGateRowWaves = 4;
+template <int D, bool BF16>
+__global__ __launch_bounds__(kGateRowWaves *kWave) void gate_rows_kernel(RouteParams p, FusedParams f, const void *gate_w, float *logits) {
+  constexpr int PER = D / (kGateRowWaves * kWave), CH = D / (kWave * (BF16 ? 8 : 4));
+  __shared__ __attribute__((aligned(16))) uint32_t x_s[BF16 ? D / 2 : D];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int e = (int)blockIdx.x * kGateRowWaves + __builtin_amdgcn_readfirstlane(tid >> 6);
+  float hv[PER];
+  load_f32<PER>(f.h + tid * PER, hv);
+  OrderedSum<D / 64> blocks;
+  blocks.fetch(f.ss, lane);
+  __builtin_amdgcn_sched_barrier(0);  // the small loads stay ahead of the gate row
+  GateRegs<1, CH> g;
+  gate_prefetch<1, CH>(gate_w, min(e, p.n_experts - 1), 1, lane, g);
+  const float scale = 1.0f / sqrtf(blocks.total() / (float)D + 1e-6f);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) hv[i] *= scale;
+  if constexpr (BF16) {
+    store_bf16<PER>(reinterpret_cast<uint16_t *>(x_s) + tid * PER, hv);
+    if (blockIdx.x == 0) store_bf16<PER>(static_cast<uint16_t *>(f.x_out) + tid * PER, hv);
+  } else {
+    store_f32<PER>(reinterpret_cast<float *>(x_s) + tid * PER, hv);
+    if (blockIdx.x == 0) store_f32<PER>(static_cast<float *>(f.x_out) + tid * PER, hv);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  float z[1];
+  gate_dot<1, CH>(g, x_s, BF16 ? MOE_A_BF16 : MOE_A_FP32, lane, z);
+  if (lane == 0 && e < p.n_experts) logits[e] = z[0];
+}
+
 __global__ void state_init_kernel(LayerState *state, int n_layers, const int32_t *initial, int n_initial) {
   const int layer = blockIdx.x, lane = threadIdx.x;
   if (layer >= n_layers) return;
@@ -128,6 +162,32 @@ hipError_t launch_fused_route(const RouteParams &p, const FusedParams &f, const 
   }
 #undef MOE_FUSED2
 #undef MOE_FUSED
+  return hipGetLastError();
+}
+
+// a gate row is a whole number of 16-byte loads per lane
+bool gate_rows_supported(int hidden, int act_fmt) {
+  return hidden == 512 || hidden == 1024 || hidden == 2048 || hidden == 4096 || (hidden == 256 && act_fmt == MOE_A_FP32);
+}
+
+hipError_t launch_gate_rows(const RouteParams &p, const FusedParams &f, const void *gate_w, float *logits, hipStream_t s) {
+  const dim3 g((p.n_experts + kGateRowWaves - 1) / kGateRowWaves), b(kGateRowWaves * kWave);
+  const bool bf16 = p.act_fmt == MOE_A_BF16;
+  if (!gate_rows_supported(p.hidden, p.act_fmt)) return hipErrorInvalidValue;
+#define MOE_GATE(D)                                                                                            \
+  do {                                                                                                         \
+    if (bf16) hipLaunchKernelGGL((gate_rows_kernel<D, true>), g, b, 0, s, p, f, gate_w, logits);               \
+    else hipLaunchKernelGGL((gate_rows_kernel<D, false>), g, b, 0, s, p, f, gate_w, logits);                   \
+  } while (0)
+  switch (p.hidden) {
+    case 256: hipLaunchKernelGGL((gate_rows_kernel<256, false>), g, b, 0, s, p, f, gate_w, logits); break;
+    case 512: MOE_GATE(512); break;
+    case 1024: MOE_GATE(1024); break;
+    case 2048: MOE_GATE(2048); break;
+    case 4096: MOE_GATE(4096); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef MOE_GATE
   return hipGetLastError();
 }
 

@@ -250,3 +250,93 @@ def test_launch_timing_counts_and_strides():
     run()
     assert dec.profile(0, reset=True) == (0.0, 0)
     dec.close()
+
+
+@pytest.mark.parametrize("weight,act,hidden,inter,shared,N,K,C,mode", [
+    ("fp32", "fp32", 1024, 24, 0, 16, 2, 4, 0), ("bf16", "bf16", 2048, 33, 16, 64, 8, 10, 0),
+    ("bf16", "bf16", 4096, 20, 0, 9, 4, 6, 0), ("bf16", "fp32", 1024, 40, 8, 60, 5, 60, 1),
+    ("int8", "bf16", 1024, 40, 16, 16, 1, 2, 0), ("int8", "bf16", 4096, 24, 0, 8, 2, 4, 2),
+    ("int4", "bf16", 2048, 128, 128, 64, 6, 7, 0), ("int4", "fp32", 4096, 128, 0, 12, 3, 3, 0),
+    ("bf16", "bf16", 1024, 32, 300, 60, 4, 9, 0)])
+def test_routing_in_every_workgroup_equals_the_waiting_path(weight, act, hidden, inter, shared, N, K, C, mode, monkeypatch):
+    """A stack driven without waiting (every wavefront of an expert launch routes for itself, the state alternates between
+    two copies) against the same stack with a blocking boundary (one workgroup routes ahead of the launch): selections,
+    states, outputs and residual streams bit for bit, also with two layers' steps in flight, over a snapshot taken and
+    restored, and over a reset."""
+    cfg = CONFIGS["c3_olmoe_bf16"].with_(n_layers=2, hidden=hidden, n_experts=N, inter=inter, shared_inter=shared, top_k=K,
+                                         capacity=C, weight_fmt=weight, act_fmt=act, seed=5300 + hidden + N)
+    print(f"case routing everywhere {weight}/{act} d={hidden} N={N} K={K} C={C} mode={mode}", flush=True)
+    monkeypatch.setenv("MOE_ROUTE_EVERYWHERE", "1")  # also where a launch of its own is faster
+    kw = dict(lam=0.5, route_mode=mode, max_rank=min(2 * K, N), cumsum_p=0.6, top_j=min(1, K))
+    store_a, a = build(cfg, **kw)
+    store_b, b = build(cfg, **kw)
+    assert not b.plan().boundary_in_expert_launch
+    T, act_dtype = 14, cfg.act_dtype
+    stream = workloads.ar1_stream(cfg, T).to(DEV)
+    out = []
+    for dec, wait in ((a, True), (b, False)):
+        h = torch.zeros(2, T, hidden, device=DEV)
+        x = torch.zeros(2, hidden, dtype=act_dtype, device=DEV)
+        y = torch.zeros(T, hidden, dtype=act_dtype, device=DEV)
+        recs = []
+
+        def step(l, t, hh, xx, carry):
+            dec.stack_route_step(l, hh, stream[t, l], 1.0 if not carry else 0.5, xx, carry=carry, wait=wait)
+
+        for t in range(T):
+            if t == 6:
+                dec.restore(1, dec.snapshot(1))
+            if t == 9:
+                dec.reset()
+            if t % 4 == 3:  # both layers routed before either is computed
+                step(0, t, h[0, t], x[0], False)
+                step(1, t, h[1, t], x[1], False)
+                dec.expert_forward(0, x[0], y[t])
+                dec.expert_forward(1, x[1], y[t])
+            else:
+                step(0, t, h[0, t], x[0], False)
+                dec.expert_forward(0, x[0], None)
+                step(1, t, h[0, t], x[0], True)
+                dec.expert_forward(1, x[0], y[t])
+            for l in range(2):
+                recs.append(bytes(dec.last_route(l))[:-16])
+        dec.compute_stream.synchronize()
+        out.append((recs, h.cpu(), x.cpu(), y.cpu(), [bytes(dec.tables(l)) for l in range(2)], bytes(dec.stats())))
+    for u, v in zip(*out):
+        assert torch.equal(u, v) if isinstance(u, torch.Tensor) else u == v
+    assert out[0][3].float().abs().max() > 0
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("weight,act,hidden", [("fp32", "fp32", 256), ("fp32", "fp32", 512), ("bf16", "bf16", 512)])
+def test_routing_in_every_workgroup_small_hidden(weight, act, hidden, monkeypatch):
+    """Hidden sizes whose waiting boundary sums the squares of h in another order: x within one rounding of the waiting
+    path's, the same decisions, outputs and residual streams to a few roundings."""
+    cfg = CONFIGS["c3_olmoe_bf16"].with_(n_layers=1, hidden=hidden, n_experts=16, inter=40, shared_inter=8, top_k=3, capacity=16,
+                                         weight_fmt=weight, act_fmt=act, seed=5400 + hidden)
+    monkeypatch.setenv("MOE_ROUTE_EVERYWHERE", "1")
+    print(f"case routing everywhere, small hidden {weight}/{act} d={hidden}", flush=True)
+    store_a, a = build(cfg, lam=0.5)
+    store_b, b = build(cfg, lam=0.5)
+    T = 8
+    stream = workloads.ar1_stream(cfg, T).to(DEV)
+    out = []
+    for dec, wait in ((a, True), (b, False)):
+        h = torch.zeros(T, hidden, device=DEV)
+        x = torch.zeros(T, hidden, dtype=cfg.act_dtype, device=DEV)
+        y = torch.zeros_like(x)
+        sel = []
+        for t in range(T):
+            dec.stack_route_step(0, h[t], stream[t, 0], 1.0, x[t], carry=False, wait=wait)
+            dec.expert_forward(0, x[t], y[t])
+            sel.append(route_fields(dec.last_route(0), cfg.top_k)["sel"])
+        dec.compute_stream.synchronize()
+        out.append((h.cpu(), x.float().cpu(), y.float().cpu(), sel))
+    assert torch.equal(out[0][0], out[1][0]) and out[0][3] == out[1][3]
+    # the scale differs by the order of a sum of d squares (a few units of 2^-24); bf16 then rounds to 2^-9
+    tol = 1e-6 if act == "fp32" else 2 ** -8
+    for u, v in zip(out[0][1:3], out[1][1:3]):
+        assert (u - v).abs().max() <= tol * u.abs().max()
+    a.close()
+    b.close()
