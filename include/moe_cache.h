@@ -190,7 +190,7 @@ int moe_expert_forward_batch(moe_cache_t *ctx, int32_t layer, const void *x_dev,
 /* moe_expert_forward for callers that cannot allocate device memory or hold a context: code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation.  Computes y = sum_k w_k E_k(x) + shared(x) for experts that are
  * all in their slots, with the kernels moe_expert_forward uses.  The call allocates nothing (no hipMalloc / hipFree, no
- * memset): the routing record its kernels read and their fp32 partial rows live in a fixed 4 MiB + 512 B device array
+ * memset): the selection travels in the launch's arguments, and the fp32 partial rows live in a fixed 4 MiB device array
  * inside the library, one per GPU, held until the process ends.  Hence the limits: hidden <= 4096, at most 256
  * workgroups; larger shapes are refused with MOE_EINVAL.  Every call on a GPU shares that GPU's array: calls that
  * overlap in time on one GPU (different streams, different threads) race; calls on one stream are ordered.
@@ -198,7 +198,7 @@ int moe_expert_forward_batch(moe_cache_t *ctx, int32_t layer, const void *x_dev,
  *   shared_blob_dev device packed shared expert (shared_inter > 0) or NULL
  *   sel_slot_host, sel_weight_host   HOST arrays [top_k]: the slot of each selected expert and its weight (read
  *                   before the call returns; slots are checked against n_slots)
- *   x_dev, y_dev    device [hidden] in act_fmt; y is complete when `stream` reaches the end of the three kernels
+ *   x_dev, y_dev    device [hidden] in act_fmt; y is complete when `stream` reaches the end of the two kernels
  *                   this call enqueues.  The device of `stream` must be current. */
 int moe_expert_forward_static(int32_t weight_fmt, int32_t act_fmt, int32_t hidden, int32_t inter, int32_t shared_inter,
                               int32_t top_k, const void *slot_pool_dev, int32_t n_slots, const void *shared_blob_dev,

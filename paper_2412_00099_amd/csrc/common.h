@@ -75,6 +75,7 @@ struct BoundaryArgs {
 enum RouteIn {
   kRouteBefore = 0,     // from the record an earlier launch wrote
   kRouteBoundary = 1,   // workgroup 0 runs the layer boundary `b`, hands the decision over and writes a zero partial row
+  kRouteGiven = 3,      // from the launch's own arguments (given_slots, given_weight): all experts are in their slots
   kRouteEverywhere = 2  // every wavefront routes for itself from b.logits and b.state; one workgroup more than plan.grid,
                         // the first, does the bookkeeping
 };
@@ -90,6 +91,8 @@ struct GemvParams {
   int32_t pass;        // 0: shared expert + experts that were resident; 1: experts whose slot was just filled
   int32_t row_offset;  // first partial row this launch writes
   int32_t route_in;    // RouteIn
+  uint64_t given_slots;                // kRouteGiven: 8 bits each, in selection order
+  float given_weight[MOE_MAX_TOPK];
   BoundaryArgs b;
 };
 

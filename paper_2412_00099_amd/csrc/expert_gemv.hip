@@ -159,7 +159,7 @@ struct RecRegs {
 // bit-identical), starts on the shared expert's records at once, and waits for workgroup 0's decision only before
 // its first routed record (RecordWalker::load_handover), so the boundary costs the launch little.  The wait is
 // on workgroup 0 only, which is dispatched first, and is bounded.
-// IN = kRouteEverywhere: see RouteIn.
+// IN = kRouteEverywhere, kRouteGiven: see RouteIn.
 template <int FMT, int LPR, int NW, int DEPTH, bool DOT2, int IN>
 __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
   using F = Chunk<FMT, DOT2>;
@@ -453,6 +453,8 @@ hipError_t launch_plan(const GemvParams &p, const GemvPlan &plan, hipStream_t s,
   }
   if (p.route_in == kRouteEverywhere)
     launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteEverywhere>(p, plan.grid + 1, s, e0, e1);
+  else if (p.route_in == kRouteGiven)
+    launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteGiven>(p, plan.grid, s, e0, e1);
   else
     launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteBefore>(p, plan.grid, s, e0, e1);
   return hipGetLastError();

@@ -585,6 +585,8 @@ hipError_t launch_expert_gemv_quant(const GemvParams &p, int weight_fmt, const G
       hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, kRouteBoundary>), g, b, 0, s, e0, e1, 0, p);   \
     else if (p.route_in == kRouteEverywhere)                                                    \
       hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, kRouteEverywhere>), g, b, 0, s, e0, e1, 0, p); \
+    else if (p.route_in == kRouteGiven)                                                         \
+      hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, kRouteGiven>), g, b, 0, s, e0, e1, 0, p);      \
     else                                                                                        \
       hipExtLaunchKernelGGL((KERNEL<__VA_ARGS__, kRouteBefore>), g, b, 0, s, e0, e1, 0, p);     \
   } while (0)

@@ -153,7 +153,7 @@ struct RecordWalker {
   }
 
   __device__ __forceinline__ void init(const GemvParams &p, int wave) {
-    constexpr int kFirst = IN == kRouteBefore ? 0 : 1;  // workgroups that stream nothing
+    constexpr int kFirst = IN == kRouteBefore || IN == kRouteGiven ? 0 : 1;  // workgroups that stream nothing
     const int G = (int)gridDim.x - kFirst, b = (int)blockIdx.x - kFirst;
     // the routing record, or what it is worked out from, first: it is on its way while the shared records are set up
     if constexpr (IN == kRouteBefore) load_record(p);
@@ -189,6 +189,14 @@ struct RecordWalker {
     next_at = 0;
     run_wanted = true;
     decided = false;
+    if constexpr (IN == kRouteGiven) {
+      const float *w = p.given_weight;
+      slots = p.given_slots;
+      miss_mask = 0;
+      rw0 = u32x4{__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
+      rw1 = u32x4{__float_as_uint(w[4]), __float_as_uint(w[5]), __float_as_uint(w[6]), __float_as_uint(w[7])};
+      decided = true;
+    }
   }
 
   // kRouteEverywhere, after init() and the loads that are wanted ahead of the weights
@@ -237,7 +245,7 @@ struct RecordWalker {
         // (one wavefront per workgroup fetching for all eight through LDS was measured: no faster)
         ok = load_handover(p.b.handover + 8 * ((int)blockIdx.x % 8), p.b.hand_tag, p.b.spin_limit);
       }
-      if constexpr (IN != kRouteEverywhere) {
+      if constexpr (IN != kRouteEverywhere && IN != kRouteGiven) {
         slots = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.y) |
                 ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.z) << 32);
         miss_mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)rd.w);

@@ -81,3 +81,11 @@ def test_static_entry_refuses_sizes_beyond_its_scratch():
         pkg.moe_expert_forward_static(pkg.MOE_W_BF16, pkg.MOE_A_BF16, 8192, 64, 0, 1, C.c_void_p(x.data_ptr()), 1, None,
                                       [0], [1.0], C.c_void_p(x.data_ptr()), C.c_void_p(x.data_ptr()), None)
     assert e.value.code == pkg.MOE_EINVAL and "scratch" in str(e.value)
+
+
+@pytest.mark.parametrize("fmt,hidden,inter,shared,K", [("int4", 2048, 128, 128, 8), ("int4", 4096, 128, 0, 1), ("bf16", 512, 33, 0, 8),
+                                                       ("int8", 4096, 40, 16, 5)])
+def test_static_entry_selection_in_the_arguments(fmt, hidden, inter, shared, K):
+    """The selection reaches the kernels as launch arguments: every format, all eight places of it."""
+    one_case(CONFIGS["c3_olmoe_bf16"].with_(n_layers=1, hidden=hidden, n_experts=12, inter=inter, shared_inter=shared, capacity=10,
+                                            top_k=K, weight_fmt=fmt, seed=8200 + hidden + K))
