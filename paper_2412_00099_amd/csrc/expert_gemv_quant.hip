@@ -178,13 +178,26 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
   }
 
   if constexpr (IN == kRouteEverywhere) walk.decide_now(p);
+  // (pass 0 loads every list entry, see expert_gemv_int4_kernel)
+  const bool all = p.pass == 0;
+  int todo = all ? walk.remaining() : 0;
   RecI8<LPR> ring[DEPTH];
-  bool live[DEPTH];
-#pragma unroll
-  for (int j = 0; j < DEPTH; ++j) {
-    live[j] = walk.next(p);
+  bool live[DEPTH], want[DEPTH];
+  auto advance = [&](int j) {
+    if (all) {
+      live[j] = todo > 0;
+      if (live[j]) {
+        --todo;
+        want[j] = walk.step(p);
+      }
+    } else {
+      live[j] = walk.next(p);
+      want[j] = true;
+    }
     if (live[j]) issue(ring[j]);
-  }
+  };
+#pragma unroll
+  for (int j = 0; j < DEPTH; ++j) advance(j);
 
   // activations as packed fp16 pairs in column order, and their sum over this lane's columns
   uint32_t xh[CPL / 2];
@@ -288,13 +301,24 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     }
   };
 
+  // steady state of pass 0: all ring entries live and at least DEPTH more entries to fetch
+  if (all && live[DEPTH - 1]) {
+    while (todo >= DEPTH) {
+#pragma unroll
+      for (int j = 0; j < DEPTH; ++j) {
+        if (want[j]) consume(ring[j]);
+        want[j] = walk.step(p);
+        issue(ring[j]);
+      }
+      todo -= DEPTH;
+    }
+  }
   while (live[0]) {
 #pragma unroll
     for (int j = 0; j < DEPTH; ++j) {
       if (live[j]) {
-        consume(ring[j]);
-        live[j] = walk.next(p);
-        if (live[j]) issue(ring[j]);
+        if (want[j]) consume(ring[j]);
+        advance(j);
       }
     }
   }
