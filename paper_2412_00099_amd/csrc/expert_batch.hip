@@ -284,10 +284,15 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
       t0 = fm + 1;
     }
   }
-  // every record is in host memory (those of route_ahead_kernel since its end): tell the host, which polls
-  __threadfence_system();
+  // Every record is on its way to host memory (those of route_ahead_kernel are there since its end): one fence behind the
+  // barrier covers the stores of all wavefronts, then the host, which polls, is told.  (A fence in each wavefront wrote
+  // the L2 back sixteen times: 11.4 against 7.3 us for 8 tokens.)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0) __hip_atomic_store(done, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (tid == 0) {
+    __threadfence_system();
+    __hip_atomic_store(done, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   if (wave == 0) {
     if (lane < N) {
       st->expert_slot[lane] = cs.my_slot[lane];
