@@ -358,8 +358,10 @@ __device__ __forceinline__ GroupPos group_pos(int unit, int groups) {
   return GroupPos{blk * 8 + (r & 7), r >> 3};
 }
 
-// The tokens of group `group` of an expert, in token order: list[i] = token * 8 + k (k: the expert's place in the
-// token's selection), by one wavefront into LDS of its own.  list has 64 entries; unused ones repeat the first.
+// The places of group `group` of an expert, in token order: list[i] = token * 8 + k (k: the expert's place in the token's
+// selection), by one wavefront into LDS of its own.  list has 64 entries; unused ones name the segment's first token.
+// Every place that names the slot is listed, as the host counts them: a token whose logits are not numbers leaves places
+// that nothing filled, whose record reads slot 0 with weight 0, so that it may name slot 0 several times.
 __device__ __forceinline__ void token_list(const BatchParams &p, int slot, int group, int n, int lane, uint16_t *list) {
   if (slot < 0) {
     const int t = p.t0 + group * 64 + lane;
@@ -372,20 +374,27 @@ __device__ __forceinline__ void token_list(const BatchParams &p, int slot, int g
       const int t = min(p.t0 + 64 * j + lane, kMaxBatch - 1);
       sel[j] = *reinterpret_cast<const uint64_t *>(p.sel->slot[t]);
     }
-    if (lane >= n) list[lane] = 0;
+    list[lane] = (uint16_t)(p.t0 * 8);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int t = p.t0 + 64 * j + lane;
-      int k = -1;
+      uint32_t ks = 0;  // the token's places
 #pragma unroll
       for (int i = 0; i < MOE_MAX_TOPK; ++i)
-        if (i < p.top_k && (int)((sel[j] >> (8 * i)) & 0xffu) == slot) k = i;
-      const bool mine = t < p.t1 && k >= 0;
-      const uint64_t m = __builtin_amdgcn_ballot_w64(mine);
-      const int at = seen + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
-      if (mine && at >= 0 && at < 64) list[at] = (uint16_t)(t * 8 + k);
+        if (i < p.top_k && (int)((sel[j] >> (8 * i)) & 0xffu) == slot) ks |= 1u << i;
+      if (t >= p.t1) ks = 0;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(ks != 0);
+      int at = seen + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
       seen += (int)__builtin_popcountll(m);
+      for (uint64_t q = __builtin_amdgcn_ballot_w64((ks & (ks - 1u)) != 0); q; q &= q - 1) {  // (rare: several places)
+        const int l = (int)__builtin_ctzll(q);
+        const int extra = (int)__builtin_popcount((uint32_t)__builtin_amdgcn_readlane((int)ks, l)) - 1;
+        if (lane > l) at += extra;
+        seen += extra;
+      }
+      for (; ks; ks &= ks - 1u, ++at)
+        if (at >= 0 && at < 64) list[at] = (uint16_t)(t * 8 + (int)__builtin_ctz(ks));
     }
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

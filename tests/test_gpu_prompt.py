@@ -318,3 +318,94 @@ def test_record_of_a_blocking_step_is_the_device_record(sync, monkeypatch):
     dec2.expert_forward_batch(0, x, y)
     dec.close()
     dec2.close()
+
+
+def odd_logits(zs, K):
+    """Some rows of zs become rows that routing meets when activations overflow: no number at all, one NaN, fewer numbers
+    than places, equal values, experts masked by -inf, infinities of both signs."""
+    N, nan, inf = zs.shape[1], float("nan"), float("inf")
+    zs[2] = nan
+    if zs.shape[0] > 5:
+        zs[3, N // 2] = nan
+        zs[4, : N - K + 1] = nan
+        zs[5, 1:] = zs[5, 1]
+        zs[5, 0] = nan
+    if zs.shape[0] > 20:
+        zs[17] = nan
+        zs[18, ::2] = -inf
+        zs[19, ::3] = inf
+        zs[19, 1::3] = -inf
+    return zs
+
+
+@pytest.mark.parametrize("batches", [[8, 5], [40, 3]])
+@pytest.mark.parametrize("N,K,C,lam,shared", [(12, 4, 12, 0.0, 32), (12, 4, 5, 0.5, 0), (60, 2, 60, 0.5, 32), (16, 6, 16, 0.0, 0),
+                                              (8, 8, 8, 0.0, 32), (20, 5, 7, 0.5, 0), (3, 1, 2, 0.0, 0)])
+def test_batch_with_logits_that_are_not_numbers(N, K, C, lam, shared, batches):
+    """Places that nothing fills name slot 0 with weight 0, several times for one token: the batch kernels have to list and
+    compute each of them, as the single-token steps do.  Records, tables and counters of the batches (with finite ones
+    behind, whose Delta_avg is not a number any more) equal the single steps' bit for bit, outputs to bf16 rounding."""
+    cfg = BASE.with_(n_layers=1, hidden=1024, n_experts=N, inter=48, shared_inter=shared, top_k=K, capacity=C, seed=7600 + N)
+    print(f"case batch of odd logits N={N} K={K} C={C} lam={lam} batches={batches}", flush=True)
+    store_a, one = build(cfg, lam=lam)
+    store_b, many = build(cfg, lam=lam)
+    T = sum(batches)
+    zs = workloads.logits_stream(cfg, T, layer=0, scale=1.5)
+    zs[:batches[0]] = odd_logits(zs[:batches[0]].clone(), K)
+    zs = zs.to(DEV)
+    xs = workloads.ar1_stream(cfg, T)[:, 0].to(cfg.act_dtype).to(DEV)
+    xs[2, 7] = float("nan")  # (the logits are given: x is what the experts compute with)
+    yb, y1 = torch.zeros_like(xs), torch.zeros_like(xs)
+    torch.cuda.synchronize()
+    t0 = 0
+    for b in batches:
+        recs = many.route_batch(0, logits=zs[t0:t0 + b].contiguous())
+        many.expert_forward_batch(0, xs[t0:t0 + b], yb[t0:t0 + b])
+        for j in range(b):
+            ref = one.route_step(0, logits=zs[t0 + j])
+            one.expert_forward(0, xs[t0 + j], y1[t0 + j])
+            fa, fb = route_fields(ref, K), route_fields(recs[j], K)
+            for key in fa:
+                assert np.array_equal(fa[key], fb[key], equal_nan=key in ("weight", "delta", "margin")), (t0 + j, key, fa[key], fb[key])
+        t0 += b
+    one.compute_stream.synchronize()
+    ta, tb = one.tables(0), many.tables(0)
+    for field in ("expert_slot", "slot_expert", "stamp", "count"):
+        u, v = getattr(ta, field), getattr(tb, field)
+        assert (u == v) if field == "count" else (list(u) == list(v)), field
+    assert np.array_equal(ta.delta_sum, tb.delta_sum, equal_nan=True)
+    sa, sb = one.stats(0), many.stats(0)
+    for field in ("tokens", "selections", "hits", "misses", "cold_misses", "evictions", "lifetime_sum", "bytes_filled"):
+        assert getattr(sa, field) == getattr(sb, field), field
+    for t in range(T):
+        u, v = y1[t].float().cpu().numpy(), yb[t].float().cpu().numpy()
+        assert np.array_equal(np.isnan(u), np.isnan(v)), t
+        if not np.isnan(u).any():
+            assert np.array_equal(u, v) or oexp.rel_err(v, u) <= 1e-2, t
+    one.close()
+    many.close()
+
+
+def test_one_bad_token_leaves_the_others_alone():
+    """One NaN in one token's x, the gate logits computed on the device: every other token's output is what it is in the
+    same batch with a finite token in that place (all experts resident, Delta fixed: decisions do not depend on it)."""
+    cfg = BASE.with_(n_layers=1, hidden=1024, n_experts=12, inter=80, shared_inter=48, top_k=4, capacity=12, seed=7700)
+    store, dec = build(cfg, lam=0.5, delta_fixed=1.0, initial=[list(range(12))])
+    xs = workloads.ar1_stream(cfg, 100)[:, 0].to(cfg.act_dtype).to(DEV)
+    torch.cuda.synchronize()
+    for bad in (0, 50, 99):
+        print(f"case one bad token: {bad}", flush=True)
+        ys = []
+        for poisoned in (False, True):
+            x = xs.clone()
+            if poisoned:
+                x[bad, 33] = float("nan")
+            y = torch.zeros_like(x)
+            torch.cuda.synchronize()
+            dec.route_batch(0, x=x)
+            dec.expert_forward_batch(0, x, y)
+            ys.append(y)
+        others = [t for t in range(100) if t != bad]
+        assert torch.equal(ys[0][others], ys[1][others]) and torch.isfinite(ys[0]).all()
+        assert torch.isnan(ys[1][bad].float()).all()
+    dec.close()
