@@ -239,8 +239,10 @@ __device__ __forceinline__ Selected route_select(const RouteParams &p, float z, 
         s.kth = m;
       }
     } else {
-      // the same by counting how many altered logits are larger, then ties in lane order
+      // the same by counting how many altered logits are larger, then ties in lane order.  What is not a number has no
+      // place (no arg-max round finds it either): with fewer numbers than places the last ones stay empty
       const float v = active ? s.zp : -INFINITY;
+      const bool cand = active && v == v;
       int larger = 0;
 #pragma unroll
       for (int j0 = 0; j0 < kWave; j0 += 16)
@@ -250,8 +252,11 @@ __device__ __forceinline__ Selected route_select(const RouteParams &p, float z, 
         }
       uint64_t tied = 0;
       for (int k = 0; k < K; ++k) {
-        if (tied == 0) tied = ballot(active && larger == k);
-        if (tied == 0) break;  // (logits that are not numbers)
+        if (tied == 0) tied = ballot(cand && larger == k);
+        if (tied == 0) {
+          s.kth = -INFINITY;
+          break;
+        }
         const int l = (int)__builtin_ctzll(tied);
         tied &= tied - 1;
         if (lane == l) s.rank = k;

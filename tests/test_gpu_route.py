@@ -401,3 +401,39 @@ def test_pruning_baseline_on_device(h):
             ref.step(z)
         assert ref.stats.misses == st.misses
     dec.close()
+
+
+@pytest.mark.parametrize("fixed,lam", [(None, 0.5), (None, 0.0), (0.75, 0.5)])
+@pytest.mark.parametrize("N,K,C", [(20, 3, 8), (20, 5, 8), (64, 8, 16), (16, 6, 7)])
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+def test_experts_without_a_number_are_placed_last(N, K, C, fixed, lam):
+    """Masked experts (-inf), infinities and NaNs among the logits, however the places are found (rounds of arg-max up to
+    four, counting above): an altered logit that is not a number - a NaN, or -inf with an infinite bias - is never taken
+    while numbers are left, as in a sort."""
+    print(f"case odd logits N={N} K={K} C={C} fixed={fixed} lam={lam}", flush=True)
+    cfg = TINY.with_(n_experts=N, top_k=K, capacity=C, seed=191 + N)
+    store, dec = build(cfg, lam=lam, delta_fixed=fixed)
+    cache, delta_avg = routing.ExpertCache(N, C), routing.LogitRange(fixed)
+    x = torch.zeros(cfg.hidden, dtype=cfg.act_dtype, device=DEV)
+    y = torch.zeros_like(x)
+    T = 40
+    zs = workloads.logits_stream(cfg, T, scale=1.5)
+    zs[5::3, 1::7] = -float("inf")
+    zs[7::6, 3::7] = float("inf")
+    zs[8::9, 2] = zs[8::9, 4]
+    if fixed is not None:  # (a NaN among the logits: their range is taken over the numbers, which the oracle's is not)
+        zs[6::4, ::6] = float("nan")
+        zs[6::8, 4] = zs[6::8, 2]
+    zs_dev = zs.to(DEV)
+    torch.cuda.synchronize()
+    for t in range(T):
+        out = route_fields(dec.route_step(0, logits=zs_dev[t]), K)
+        dec.expert_forward(0, x, y)
+        z = zs[t].numpy()
+        zp = routing.cache_prior_logits(z, cache.resident_mask(), lam, delta_avg.update(z))
+        sel = routing.ranking(zp)[:K]
+        assert not np.isnan(zp[sel]).any()  # the numbers suffice
+        miss, slot, evicted = cache.access(sel, z)
+        assert out["sel"] == sel.tolist(), t
+        assert out["slot"] == slot and out["miss"] == miss and out["evicted"] == evicted, t
+    dec.close()
