@@ -139,11 +139,13 @@ __global__ __launch_bounds__(kAheadWaves *kWave) void route_ahead_kernel(RoutePa
   for (int i = wave; i < n; i += kAheadWaves) z_s[i * kZStride + lane] = logits[i * N + e_c];  // (lanes past N: a copy)
   __syncthreads();
   if (tid < n) {
-    float lo = INFINITY, hi = -INFINITY;
+    // (over the numbers among the logits, as a wavefront's maximum is; where 64 logits are none, it is none either)
+    const float *row = z_s + tid * kZStride;
+    float lo = N < kWave ? INFINITY : row[0], hi = N < kWave ? -INFINITY : row[0];
 #pragma unroll 8
     for (int e = 0; e < N; ++e) {
-      lo = fminf(lo, z_s[tid * kZStride + e]);
-      hi = fmaxf(hi, z_s[tid * kZStride + e]);
+      lo = fminf(lo, row[e]);
+      hi = fmaxf(hi, row[e]);
     }
     range_s[tid] = hi - lo;
   }

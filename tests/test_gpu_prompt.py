@@ -340,7 +340,8 @@ def odd_logits(zs, K):
 
 @pytest.mark.parametrize("batches", [[8, 5], [40, 3]])
 @pytest.mark.parametrize("N,K,C,lam,shared", [(12, 4, 12, 0.0, 32), (12, 4, 5, 0.5, 0), (60, 2, 60, 0.5, 32), (16, 6, 16, 0.0, 0),
-                                              (8, 8, 8, 0.0, 32), (20, 5, 7, 0.5, 0), (3, 1, 2, 0.0, 0)])
+                                              (8, 8, 8, 0.0, 32), (20, 5, 7, 0.5, 0), (3, 1, 2, 0.0, 0),
+                                              (64, 2, 40, 0.5, 0), (64, 8, 64, 0.5, 32)])
 def test_batch_with_logits_that_are_not_numbers(N, K, C, lam, shared, batches):
     """Places that nothing fills name slot 0 with weight 0, several times for one token: the batch kernels have to list and
     compute each of them, as the single-token steps do.  Records, tables and counters of the batches (with finite ones
