@@ -498,9 +498,11 @@ __device__ __forceinline__ void decide(const RouteParams &p, float z, int my_slo
   for (int k = 0; k < MOE_MAX_TOPK; ++k) {
     weight[k] = 0.f;
     if (k < p.top_k) {
-      const int l = (int)__builtin_ctzll(ballot(lane < p.n_experts && pick.rank == k) | (1ull << 63));
-      const int slot = readlane_i(my_slot, l);
-      weight[k] = readlane_f(pick.w, l);
+      // (a place that nothing fills - logits that are not numbers - is slot 0 with weight 0, as in the record)
+      const uint64_t at = ballot(lane < p.n_experts && pick.rank == k);
+      const int l = (int)__builtin_ctzll(at | (1ull << 63));
+      const int slot = at != 0 ? readlane_i(my_slot, l) : 0;
+      weight[k] = at != 0 ? readlane_f(pick.w, l) : 0.f;
       if (slot >= 0) slots |= (uint64_t)(uint32_t)(slot & 0xff) << (8 * k);
       else miss_mask |= 1u << k;
     }
