@@ -120,10 +120,12 @@ struct HostNote {
 
 // The full record of a step whose decision the caller waits for, in mapped host memory: word i of the record in the
 // low half of w[i], the step's seq in the high half.  Complete once all words carry the seq (no order between the stores
-// is assumed), so nobody has to wait for the kernel's end or a copy.
+// is assumed), so nobody has to wait for the kernel's end or a copy.  `outputs` carries the seq once everything that a
+// layer boundary writes for the caller (h, x) has reached memory, where any stream and the host find it.
 constexpr int kHostRecWords = sizeof(moe_route_out_t) / 4;
 struct HostRecord {
   uint64_t w[kHostRecWords];
+  uint64_t outputs;
 };
 // where a routing step leaves what the host wants of it (device views of mapped host memory; nullptr: not wanted)
 struct HostOut {

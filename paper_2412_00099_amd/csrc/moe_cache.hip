@@ -486,7 +486,8 @@ static RouteParams make_route_params(moe_cache_t *c) {
 }
 
 // after the router launch: either leave the decision for moe_expert_forward, or wait for it now
-static int finish_route_call(moe_cache_t *c, int32_t layer, uint32_t seq, moe_route_out_t *out_host) {
+// (with_outputs: the launch writes h and x for the caller, who may use them on any stream once the call returns)
+static int finish_route_call(moe_cache_t *c, int32_t layer, uint32_t seq, moe_route_out_t *out_host, bool with_outputs) {
   c->route_seq[layer] = seq;
   if (!out_host) {
     c->routed[layer] = 2;  // decision collected by moe_expert_forward, behind the first expert launch
@@ -505,7 +506,7 @@ static int finish_route_call(moe_cache_t *c, int32_t layer, uint32_t seq, moe_ro
       w[i] = (uint32_t)v;
       all &= (uint32_t)(v >> 32) == seq;
     }
-    return all;
+    return all && (!with_outputs || (uint32_t)__atomic_load_n(&c->h_rec->outputs, __ATOMIC_ACQUIRE) == seq);
   };
   if (int rc = wait_for(c, arrived, &ok)) return rc;
   if (!ok) return fail(MOE_EHIP, "route kernel of layer %d did not publish its record", layer);
@@ -524,7 +525,7 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
   const RouteParams p = make_route_params(c);
   HIP_TRY(launch_route(p, c->gate_w[layer], x_dev, logits_dev, c->state(layer), c->d_route + layer,
                        HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
-  return finish_route_call(c, layer, p.seq, out_host);
+  return finish_route_call(c, layer, p.seq, out_host, false);
 }
 
 int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const float *a_dev, float perturb,
@@ -609,7 +610,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   c->pending_rows = 0;
   HIP_TRY(launch_fused_route(p, f, c->gate_w[layer], c->state(layer), c->d_route + layer,
                              HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
-  return finish_route_call(c, layer, p.seq, out_host);
+  return finish_route_call(c, layer, p.seq, out_host, true);
 }
 
 int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y_dev) {

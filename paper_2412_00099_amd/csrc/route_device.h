@@ -801,7 +801,14 @@ __device__ __forceinline__ void fused_boundary(const RouteParams &p, const Fused
     for (int r = 0; r < R; ++r)
       if (lane == 0 && r < nrows) z_s[row0 + r] = v[r];
   }
+  // a caller that waits may use h and x on any stream once it has the record: every wavefront's stores are waited for
+  // ahead of the barrier, behind it the second wavefront writes them back and says so while the first one routes
+  if (host.rec != nullptr) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
+  if (wave == 1 && host.rec != nullptr) {
+    __threadfence_system();
+    if (lane == 0) __hip_atomic_store(&host.rec->outputs, (uint64_t)p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   if (wave != 0) return;
   route_wave(p, z_s, cr, st, out_dev, host, lds.rec_s, lane, flags);
 }

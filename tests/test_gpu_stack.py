@@ -385,3 +385,36 @@ def test_routing_in_every_workgroup_without_numbers(weight, N, K, C, lam, shared
     assert np.isfinite(out[0][1][2][3:]).all()
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("sync", ["poll", "event"])
+@pytest.mark.parametrize("weight,act,hidden", [("bf16", "bf16", 2048), ("bf16", "bf16", 512), ("fp32", "fp32", 1024),
+                                               ("bf16", "bf16", 4096)])
+def test_blocking_boundary_returns_with_its_outputs(weight, act, hidden, sync, monkeypatch):
+    """A blocking boundary polls for its record while the launch still runs; h, x and the finished y of the layer before
+    are complete all the same when it returns: another stream that is not ordered behind compute_stream copies them."""
+    if sync == "event":
+        monkeypatch.setenv("MOE_HOST_SYNC", "event")
+    cfg = CONFIGS["c3_olmoe_bf16"].with_(n_layers=1, hidden=hidden, n_experts=16, inter=24, shared_inter=8, top_k=2, capacity=16,
+                                         weight_fmt=weight, act_fmt=act, seed=5700 + hidden)
+    print(f"case blocking boundary {weight} d={hidden} {sync}", flush=True)
+    store, dec = build(cfg, lam=0.5)
+    T = 60
+    stream = workloads.ar1_stream(cfg, T)[:, 0].contiguous().to(DEV)
+    h = torch.zeros(hidden, device=DEV)
+    x = torch.zeros(hidden, dtype=cfg.act_dtype, device=DEV)
+    y = torch.zeros_like(x)
+    other = torch.cuda.Stream()
+    for t in range(T):
+        dec.compute_stream.synchronize()  # (the experts have read x)
+        x.fill_(float("nan"))
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        dec.stack_route_step(0, h, stream[t], 1.0 if t == 0 else stack.PERTURB, x, carry=t > 0, y=y if t > 0 else None)
+        with torch.cuda.stream(other):
+            seen = [v.clone() for v in (h, x, y)]
+        torch.cuda.synchronize()
+        for u, v in zip(seen[: 3 if t > 0 else 2], (h, x, y)):
+            assert torch.equal(u, v) and torch.isfinite(u.float()).all(), t
+        dec.expert_forward(0, x, None)
+    dec.close()
