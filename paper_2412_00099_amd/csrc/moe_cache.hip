@@ -99,6 +99,7 @@ struct moe_cache {
   std::vector<uint8_t> routed;        // per layer: 0 idle, 1 routed (decision on the host), 2 routed (not collected
                                       // yet), 3 boundary deferred into the expert launch,
                                       // 4 routing deferred into every workgroup of it
+  int deferred = -1;                  // the layer in state 3: its launch forms x from the caller's h and d_ss
   std::vector<uint32_t> route_seq;    // per layer: completion tag of the pending route step
   std::vector<uint32_t> hand_count;   // per layer: hand-overs inside an expert launch so far
   std::vector<int64_t> bytes_filled;
@@ -164,6 +165,7 @@ int do_reset(moe_cache_t *c) {
   std::fill(c->cur.begin(), c->cur.end(), 0);
   if (c->h_gave_up) __atomic_store_n(c->h_gave_up, 0u, __ATOMIC_RELAXED);
   c->pending_rows = 0;
+  c->deferred = -1;
   c->batch_layer = -1;
   c->batch_n = 0;
   const int N = c->cfg.n_experts;
@@ -485,6 +487,21 @@ static RouteParams make_route_params(moe_cache_t *c) {
   return p;
 }
 
+// Runs what is left of a layer's deferred boundary now, in launches of its own (the same operations in the same order: x,
+// logits and decision are those of the launch it was deferred into); the layer's step is then one like any other whose
+// decision is not collected yet.
+static int settle(moe_cache_t *c, int32_t layer) {
+  if (c->routed[layer] < 3) return MOE_OK;
+  const BoundaryArgs &b = c->boundary[layer];
+  float *logits = c->d_logits + (size_t)layer * MOE_MAX_EXPERTS;
+  if (c->routed[layer] == 3) HIP_TRY(launch_gate_rows(b.route, b.glue, c->gate_w[layer], logits, c->compute));
+  HIP_TRY(launch_route(b.route, nullptr, nullptr, logits, c->state(layer), c->d_route + layer,
+                       HostOut{c->h_note_dev + layer, nullptr}, c->compute));
+  if (c->deferred == layer) c->deferred = -1;
+  c->routed[layer] = 2;
+  return MOE_OK;
+}
+
 // after the router launch: either leave the decision for moe_expert_forward, or wait for it now
 // (with_outputs: the launch writes h and x for the caller, who may use them on any stream once the call returns)
 static int finish_route_call(moe_cache_t *c, int32_t layer, uint32_t seq, moe_route_out_t *out_host, bool with_outputs) {
@@ -535,6 +552,9 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   if (c->cfg.hidden > kFusedMaxHidden) return fail(MOE_EINVAL, "hidden exceeds %d", kFusedMaxHidden);
   if (c->routed[layer]) return fail(MOE_ESTATE, "layer %d: previous route step not followed by moe_expert_forward", layer);
   if (c->batch_layer >= 0) return fail(MOE_ESTATE, "a routed batch is pending: call moe_expert_forward_batch first");
+  // h may be the one another layer's deferred boundary is still to be formed from, d_ss is
+  if (c->deferred >= 0)
+    if (int rc = settle(c, c->deferred)) return rc;
   const RouteParams p = make_route_params(c);
   const bool in_launch = !out_host && c->fuse_boundary &&
                          gemv_fused_supported(c->cfg.weight_fmt, c->cfg.act_fmt, c->cfg.hidden, c->plan) && c->cfg.hidden % 64 == 0;
@@ -568,6 +588,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     b.gate_bytes = (int64_t)c->cfg.n_experts * c->cfg.hidden * (c->cfg.act_fmt == MOE_A_BF16 ? 2 : 4);
     c->route_seq[layer] = p.seq;
     c->routed[layer] = 3;
+    c->deferred = layer;
     return MOE_OK;
   }
   if (!out_host && c->route_everywhere) {
@@ -653,6 +674,7 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   } else {
     HIP_TRY(launch_expert_gemv(p, g.weight_fmt, c->plan, c->compute));
   }
+  if (c->deferred == layer) c->deferred = -1;
   if (p.route_in == kRouteEverywhere) c->cur[layer] ^= 1;  // the launch writes the other copy of the state
   p.route_in = kRouteBefore;
   int n_miss = c->decided[layer].n_miss;
