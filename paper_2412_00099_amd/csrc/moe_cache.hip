@@ -912,6 +912,9 @@ int moe_cache_last_route(moe_cache_t *c, int32_t layer, moe_route_out_t *out) {
 int moe_cache_stats(moe_cache_t *c, int32_t layer, moe_cache_stats_t *out) {
   if (!c || !out) return fail(MOE_EINVAL, "NULL argument");
   if (int rc = check_layer(c, layer == -1 ? 0 : layer)) return rc;  // also refuses a context whose hand-over was abandoned
+  for (int l = 0; l < c->cfg.n_layers; ++l)
+    if (layer == -1 || l == layer)
+      if (int rc = settle(c, l)) return rc;
   HIP_TRY(hipStreamSynchronize(c->compute));
   std::vector<LayerState> both(2 * (size_t)c->cfg.n_layers);
   HIP_TRY(hipMemcpy(both.data(), c->d_state, sizeof(LayerState) * both.size(), hipMemcpyDeviceToHost));
@@ -934,6 +937,7 @@ int moe_cache_stats(moe_cache_t *c, int32_t layer, moe_cache_stats_t *out) {
 int moe_cache_tables(moe_cache_t *c, int32_t layer, moe_cache_tables_t *out) {
   if (int rc = check_layer(c, layer)) return rc;
   if (!out) return fail(MOE_EINVAL, "out is NULL");
+  if (int rc = settle(c, layer)) return rc;
   HIP_TRY(hipStreamSynchronize(c->compute));
   LayerState st;
   HIP_TRY(hipMemcpy(&st, c->state(layer), sizeof st, hipMemcpyDeviceToHost));
@@ -961,6 +965,7 @@ int moe_cache_snapshot(moe_cache_t *c, int32_t layer, void *buf, size_t *bytes) 
   *bytes = kSnapBytes;
   if (!buf) return MOE_OK;
   if (have < kSnapBytes) return fail(MOE_EINVAL, "snapshot needs %zu bytes, buffer has %zu", kSnapBytes, have);
+  if (int rc = settle(c, layer)) return rc;
   HIP_TRY(hipStreamSynchronize(c->compute));
   SnapshotHeader hd{kSnapMagic, kSnapVersion, c->cfg.n_experts, c->cfg.capacity, c->cfg.top_k, 0};
   memcpy(buf, &hd, sizeof hd);

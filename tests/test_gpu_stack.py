@@ -458,3 +458,42 @@ def test_steps_of_two_layers_in_flight(weight, hidden, inter, shared, form, monk
             assert (u - v).abs().max() <= 2 ** -8 * u.abs().max() and u.abs().max() > 0
         else:
             assert torch.equal(u, v) if isinstance(u, torch.Tensor) else u == v
+
+
+@pytest.mark.parametrize("form", ["MOE_FUSE_BOUNDARY", "MOE_ROUTE_EVERYWHERE", "neither"])
+@pytest.mark.parametrize("weight,hidden,inter,shared", [("bf16", 1024, 33, 16), ("int8", 2048, 24, 16), ("int4", 4096, 128, 0)])
+def test_tables_counters_and_snapshots_include_the_step_in_flight(weight, hidden, inter, shared, form, monkeypatch):
+    """Between a non-blocking boundary and its moe_expert_forward the tables, the counters and a snapshot show the step, in
+    whichever form the boundary is run; the experts then compute with the same decision."""
+    cfg = CONFIGS["c2_qwen_bf16"].with_(n_layers=2, hidden=hidden, n_experts=12, inter=inter, shared_inter=shared, top_k=3,
+                                        capacity=5, weight_fmt=weight, act_fmt="bf16", seed=5900 + hidden)
+    print(f"case looking at a step in flight {weight} d={hidden} {form}", flush=True)
+    for name in ("MOE_FUSE_BOUNDARY", "MOE_ROUTE_EVERYWHERE"):
+        monkeypatch.setenv(name, "1" if name == form else "0")
+    T = 8
+    stream = workloads.ar1_stream(cfg, T).to(DEV)
+    out = []
+    for wait in (True, False):
+        store, dec = build(cfg, lam=0.5)
+        h = torch.zeros(hidden, device=DEV)
+        x = torch.zeros(hidden, dtype=cfg.act_dtype, device=DEV)
+        y = torch.zeros(T, 2, hidden, dtype=cfg.act_dtype, device=DEV)
+        torch.cuda.synchronize()
+        seen = []
+        for t in range(T):
+            for l in range(2):
+                dec.stack_route_step(l, h, stream[t, l], 1.0 if l == 0 else 0.5, x, carry=l > 0, wait=wait)
+                if t % 4 == 0:
+                    seen.append(bytes(dec.tables(l)))
+                elif t % 4 == 1:
+                    seen.append(bytes(dec.stats(l))[:48])  # (bytes_filled: counted once the decision is collected)
+                elif t % 4 == 2:
+                    seen.append(dec.snapshot(l))
+                dec.expert_forward(l, x, y[t, l])
+                seen.append(bytes(dec.last_route(l))[:-16])
+        seen += [dec.snapshot(l) for l in range(2)] + [bytes(dec.stats())]
+        out.append((seen, h.cpu(), y.float().cpu()))
+        dec.close()
+    assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1])
+    # (in one form a workgroup fewer streams records: the rounding of a sum in another order)
+    assert (out[0][2] - out[1][2]).abs().max() <= 2 ** -8 * out[0][2].abs().max()
