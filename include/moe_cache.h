@@ -217,8 +217,9 @@ int moe_expert_forward_static(int32_t weight_fmt, int32_t act_fmt, int32_t hidde
  * does them while the others already stream the shared expert; see moe_cache_plan), or the routing alone (every
  * workgroup then works the decision out from the logits): x_dev and the routing record may then be written by the kernels
  * moe_expert_forward enqueues, not by this call's, so nothing but moe_expert_forward(ctx, layer, x_dev, ...) and
- * further calls of moe_stack_route_step may use h_dev and x_dev in between, and that call must be given the same x_dev.
- * Counters, tables and snapshots taken in between include the step.
+ * further calls of moe_stack_route_step may use h_dev and x_dev in between, and that call must be given the same x_dev
+ * (another one is refused with MOE_EINVAL where the shape has the first form and a third of a layer's records or more are
+ * the shared expert's).  Counters, tables and snapshots taken in between include the step.
  * The other workgroups' wait for the first one is bounded; should it ever run out, they finish without the routed
  * experts, and every later call that names a layer returns MOE_EHIP until moe_cache_reset. */
 int moe_stack_route_step(moe_cache_t *ctx, int32_t layer, float *h_dev, const float *a_dev, float perturb,

@@ -99,6 +99,8 @@ struct moe_cache {
   std::vector<uint8_t> routed;        // per layer: 0 idle, 1 routed (decision on the host), 2 routed (not collected
                                       // yet), 3 boundary deferred into the expert launch,
                                       // 4 routing deferred into every workgroup of it
+  bool x_fixed = false;               // a non-blocking boundary's x_dev is the only one its moe_expert_forward takes
+  std::vector<const void *> x_given;  // per layer: that x_dev, or nullptr
   int deferred = -1;                  // the layer in state 3: its launch forms x from the caller's h and d_ss
   std::vector<uint32_t> route_seq;    // per layer: completion tag of the pending route step
   std::vector<uint32_t> hand_count;   // per layer: hand-overs inside an expert launch so far
@@ -281,6 +283,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   c->hand_count.assign(L, 0);
   c->decided.assign(L, {});
   c->boundary.assign(L, BoundaryArgs{});
+  c->x_given.assign(L, nullptr);
   c->bytes_filled.assign(L, 0);
   c->ev_copy.assign(L, nullptr);
 
@@ -342,11 +345,14 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   // the gate matrix; it costs a launch, which a short chain of small launches (d < 2048) feels: the host is behind then.
   // MOE_FUSE_BOUNDARY=0 / 1 in the environment overrides the first rule.
   const int64_t records = (int64_t)cfg->top_k * cfg->inter + cfg->shared_inter, streamed = records * c->slot_layout.rec_bytes;
+  // (whichever form is taken: what a wrong x_dev meets depends on the shared expert's share alone)
+  c->x_fixed = 3 * (int64_t)cfg->shared_inter >= records;
   c->fuse_boundary = cfg->weight_fmt != MOE_W_INT4_G128 && 3 * (int64_t)cfg->shared_inter >= records &&
                      streamed >= std::max((int64_t)41000 * cfg->hidden, (int64_t)45000000);
   c->route_everywhere = gate_rows_supported(cfg->hidden, cfg->act_fmt) &&
                         (cfg->hidden >= 2048 || streamed >= (cfg->hidden >= 1024 ? 56000000 : 64000000));
-  if (const char *s = getenv("MOE_FUSE_BOUNDARY")) c->fuse_boundary = atoi(s) != 0;
+  if (const char *s = getenv("MOE_FUSE_BOUNDARY")) c->fuse_boundary = c->x_fixed = atoi(s) != 0;
+  c->x_fixed = c->x_fixed && gemv_fused_supported(cfg->weight_fmt, cfg->act_fmt, cfg->hidden, c->plan);
   if (const char *s = getenv("MOE_ROUTE_EVERYWHERE"))
     c->route_everywhere = atoi(s) != 0 && gate_rows_supported(cfg->hidden, cfg->act_fmt);
   if (const char *s = getenv("MOE_POISON_FILLS")) c->poison_fills = atoi(s) != 0;
@@ -539,6 +545,7 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
   if (c->routed[layer]) return fail(MOE_ESTATE, "layer %d: previous route step not followed by moe_expert_forward", layer);
   if (c->pending_rows) return fail(MOE_ESTATE, "an expert output is pending: the next routing call must be moe_stack_route_step");
   if (c->batch_layer >= 0) return fail(MOE_ESTATE, "a routed batch is pending: call moe_expert_forward_batch first");
+  c->x_given[layer] = nullptr;
   const RouteParams p = make_route_params(c);
   HIP_TRY(launch_route(p, c->gate_w[layer], x_dev, logits_dev, c->state(layer), c->d_route + layer,
                        HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
@@ -555,6 +562,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   // h may be the one another layer's deferred boundary is still to be formed from, d_ss is
   if (c->deferred >= 0)
     if (int rc = settle(c, c->deferred)) return rc;
+  c->x_given[layer] = !out_host && c->x_fixed ? x_dev : nullptr;
   const RouteParams p = make_route_params(c);
   const bool in_launch = !out_host && c->fuse_boundary &&
                          gemv_fused_supported(c->cfg.weight_fmt, c->cfg.act_fmt, c->cfg.hidden, c->plan) && c->cfg.hidden % 64 == 0;
@@ -639,6 +647,8 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   if (!x_dev) return fail(MOE_EINVAL, "x_dev is NULL");
   if (!c->routed[layer]) return fail(MOE_ESTATE, "layer %d: moe_expert_forward without a preceding moe_route_step", layer);
   if (c->pending_rows) return fail(MOE_ESTATE, "an expert output is pending: call moe_stack_route_step first");
+  if (c->x_given[layer] && x_dev != c->x_given[layer])
+    return fail(MOE_EINVAL, "layer %d: x_dev must be the vector moe_stack_route_step wrote", layer);
   const moe_cache_config_t &g = c->cfg;
   GemvParams p{};
   p.slot_pool = static_cast<const uint8_t *>(c->slot_pool[layer]);
@@ -657,8 +667,6 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   p.pass = 0;
   p.row_offset = 0;
   if (c->routed[layer] == 3) {
-    if (x_dev != c->boundary[layer].glue.x_out)
-      return fail(MOE_EINVAL, "layer %d: x_dev must be the vector moe_stack_route_step wrote", layer);
     p.route_in = kRouteBoundary;
     p.b = c->boundary[layer];
   } else if (c->routed[layer] == 4) {

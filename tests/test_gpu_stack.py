@@ -497,3 +497,38 @@ def test_tables_counters_and_snapshots_include_the_step_in_flight(weight, hidden
     assert out[0][0] == out[1][0] and torch.equal(out[0][1], out[1][1])
     # (in one form a workgroup fewer streams records: the rounding of a sum in another order)
     assert (out[0][2] - out[1][2]).abs().max() <= 2 ** -8 * out[0][2].abs().max()
+
+
+@pytest.mark.parametrize("everywhere", ["0", "1"])
+@pytest.mark.parametrize("weight,act,hidden,shared,refused", [("bf16", "bf16", 1024, 64, True), ("int4", "bf16", 2048, 256, True),
+                                                            ("bf16", "bf16", 1024, 0, False), ("fp32", "fp32", 1024, 64, False)])
+def test_another_x_is_refused_whatever_the_form_of_the_boundary(weight, act, hidden, shared, refused, everywhere, monkeypatch):
+    """After a non-blocking boundary moe_expert_forward refuses another vector where the boundary could run inside its launch
+    and the shared expert has a third of the records - whether the size rule leaves it there, to every workgroup or to a
+    launch of its own - and elsewhere computes with the vector it is given; after a blocking one it always does."""
+    import paper_2412_00099_amd as pkg
+
+    monkeypatch.setenv("MOE_ROUTE_EVERYWHERE", everywhere)
+    cfg = CONFIGS["c2_qwen_bf16"].with_(n_layers=1, hidden=hidden, n_experts=8, inter=128 if weight == "int4" else 40,
+                                        shared_inter=shared, top_k=2, capacity=8, weight_fmt=weight, act_fmt=act, seed=6000)
+    store, dec = build(cfg, lam=0.5, initial=[list(range(8))])
+    a = workloads.ar1_stream(cfg, 1).to(DEV)
+    h = torch.zeros(hidden, device=DEV)
+    x = torch.zeros(hidden, dtype=cfg.act_dtype, device=DEV)
+    y, y2 = torch.zeros_like(x), torch.zeros_like(x)
+    torch.cuda.synchronize()
+    dec.stack_route_step(0, h, a[0, 0], 1.0, x, carry=False)
+    other = x.clone()
+    torch.cuda.synchronize()
+    dec.expert_forward(0, other, y)
+    dec.stack_route_step(0, h, a[0, 0], 1.0, x, carry=False, wait=False)
+    if refused:
+        with pytest.raises(pkg.MoEError) as e:
+            dec.expert_forward(0, other, y2)
+        assert e.value.code == pkg.MOE_EINVAL
+        dec.expert_forward(0, x, y2)
+    else:
+        dec.expert_forward(0, other, y2)
+    dec.compute_stream.synchronize()
+    assert torch.equal(y, y2) and y.float().abs().max() > 0
+    dec.close()
