@@ -288,6 +288,10 @@ typedef struct moe_cache_plan {
   int32_t grid, wavefronts, depth, packed_bf16_dot, boundary_in_expert_launch;
 } moe_cache_plan_t;
 int moe_cache_plan(moe_cache_t *ctx, moe_cache_plan_t *out_host);
+/* How a moe_stack_route_step without out_host is run: all of it by launches of its own, x and the routing in the first
+ * workgroup of the layer's expert launch (boundary_in_expert_launch above), or the routing in every workgroup of it. */
+enum { MOE_BOUNDARY_OWN_LAUNCH = 0, MOE_BOUNDARY_IN_FIRST_WORKGROUP = 1, MOE_BOUNDARY_ROUTED_EVERYWHERE = 2 };
+int moe_cache_boundary_form(moe_cache_t *ctx, int32_t *out_host);
 
 /* Average duration in microseconds of the timed expert-GEMV launches that covered a whole layer (no expert missing)
  * since the last call with reset != 0, and their count; measured with start/stop events attached to the launches

@@ -552,6 +552,13 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
   return finish_route_call(c, layer, p.seq, out_host, false);
 }
 
+// how a boundary that nobody waits for is run (see moe_cache_init)
+static int boundary_form(const moe_cache_t *c) {
+  if (c->fuse_boundary && gemv_fused_supported(c->cfg.weight_fmt, c->cfg.act_fmt, c->cfg.hidden, c->plan))
+    return MOE_BOUNDARY_IN_FIRST_WORKGROUP;
+  return c->route_everywhere ? MOE_BOUNDARY_ROUTED_EVERYWHERE : MOE_BOUNDARY_OWN_LAUNCH;
+}
+
 int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const float *a_dev, float perturb,
                          int32_t carry, void *x_dev, void *y_dev, moe_route_out_t *out_host) {
   if (int rc = check_layer(c, layer)) return rc;
@@ -564,15 +571,14 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     if (int rc = settle(c, c->deferred)) return rc;
   c->x_given[layer] = !out_host && c->x_fixed ? x_dev : nullptr;
   const RouteParams p = make_route_params(c);
-  const bool in_launch = !out_host && c->fuse_boundary &&
-                         gemv_fused_supported(c->cfg.weight_fmt, c->cfg.act_fmt, c->cfg.hidden, c->plan) && c->cfg.hidden % 64 == 0;
+  const int form = out_host ? MOE_BOUNDARY_OWN_LAUNCH : boundary_form(c);
   // the pending expert output is summed first (into y_dev if given, else into the library's own buffer)
   void *y = nullptr;
   if (c->pending_rows > 0) y = y_dev ? y_dev : c->d_y;
   FusedParams f{};
   f.h = h_dev;
   f.x_out = x_dev;
-  if (in_launch) {
+  if (form == MOE_BOUNDARY_IN_FIRST_WORKGROUP) {
     // nobody waits for the decision here: the sum of the pending output and the residual glue are one launch, and
     // the rest of the boundary (x, gate GEMV, routing) runs in workgroup 0 of the layer's expert launch
     HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
@@ -599,7 +605,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     c->deferred = layer;
     return MOE_OK;
   }
-  if (!out_host && c->route_everywhere) {
+  if (form == MOE_BOUNDARY_ROUTED_EVERYWHERE) {
     // nobody waits for the decision here: only x and the logits are made by this call (over several compute units), and
     // every wavefront of the layer's expert launch routes for itself
     HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
@@ -1060,8 +1066,13 @@ int moe_cache_plan(moe_cache_t *c, moe_cache_plan_t *out) {
   out->wavefronts = kGemvWaves;
   out->depth = kGemvDepth;
   out->packed_bf16_dot = c->plan.dot2;
-  out->boundary_in_expert_launch = c->fuse_boundary && c->cfg.hidden % 64 == 0 && c->cfg.hidden <= kFusedMaxHidden &&
-                                   gemv_fused_supported(c->cfg.weight_fmt, c->cfg.act_fmt, c->cfg.hidden, c->plan);
+  out->boundary_in_expert_launch = boundary_form(c) == MOE_BOUNDARY_IN_FIRST_WORKGROUP;
+  return MOE_OK;
+}
+
+int moe_cache_boundary_form(moe_cache_t *c, int32_t *out) {
+  if (!c || !out) return fail(MOE_EINVAL, "NULL argument");
+  *out = boundary_form(c);
   return MOE_OK;
 }
 

@@ -166,6 +166,9 @@ class MoEDecoder:
     def plan(self):
         return B.moe_cache_plan(self.ctx)
 
+    def boundary_form(self):
+        return B.moe_cache_boundary_form(self.ctx)
+
     def set_lambda(self, lam):
         B.moe_cache_set_lambda(self.ctx, lam)
 

@@ -263,6 +263,8 @@ def test_routing_in_every_workgroup_equals_the_waiting_path(weight, act, hidden,
     two copies) against the same stack with a blocking boundary (one workgroup routes ahead of the launch): selections,
     states, outputs and residual streams bit for bit, also with two layers' steps in flight, over a snapshot taken and
     restored, and over a reset."""
+    import paper_2412_00099_amd as pkg
+
     cfg = CONFIGS["c3_olmoe_bf16"].with_(n_layers=2, hidden=hidden, n_experts=N, inter=inter, shared_inter=shared, top_k=K,
                                          capacity=C, weight_fmt=weight, act_fmt=act, seed=5300 + hidden + N)
     print(f"case routing everywhere {weight}/{act} d={hidden} N={N} K={K} C={C} mode={mode}", flush=True)
@@ -271,6 +273,7 @@ def test_routing_in_every_workgroup_equals_the_waiting_path(weight, act, hidden,
     store_a, a = build(cfg, **kw)
     store_b, b = build(cfg, **kw)
     assert not b.plan().boundary_in_expert_launch
+    assert b.boundary_form() == pkg.MOE_BOUNDARY_ROUTED_EVERYWHERE
     T, act_dtype = 14, cfg.act_dtype
     stream = workloads.ar1_stream(cfg, T).to(DEV)
     out = []
@@ -313,12 +316,15 @@ def test_routing_in_every_workgroup_equals_the_waiting_path(weight, act, hidden,
 def test_routing_in_every_workgroup_small_hidden(weight, act, hidden, monkeypatch):
     """Hidden sizes whose waiting boundary sums the squares of h in another order: x within one rounding of the waiting
     path's, the same decisions, outputs and residual streams to a few roundings."""
+    import paper_2412_00099_amd as pkg
+
     cfg = CONFIGS["c3_olmoe_bf16"].with_(n_layers=1, hidden=hidden, n_experts=16, inter=40, shared_inter=8, top_k=3, capacity=16,
                                          weight_fmt=weight, act_fmt=act, seed=5400 + hidden)
     monkeypatch.setenv("MOE_ROUTE_EVERYWHERE", "1")
     print(f"case routing everywhere, small hidden {weight}/{act} d={hidden}", flush=True)
     store_a, a = build(cfg, lam=0.5)
     store_b, b = build(cfg, lam=0.5)
+    assert b.boundary_form() == pkg.MOE_BOUNDARY_ROUTED_EVERYWHERE
     T = 8
     stream = workloads.ar1_stream(cfg, T).to(DEV)
     out = []
@@ -349,6 +355,8 @@ def test_routing_in_every_workgroup_without_numbers(weight, N, K, C, lam, shared
     """A token that is not a number (its logits fill no places), finite tokens behind it (with lambda = 0 the bias of the
     resident experts is then 0 times no number, so that places stay empty): the expert launch that routes for itself
     takes an empty place for what the record says, as the waiting path does."""
+    import paper_2412_00099_amd as pkg
+
     hidden, inter = (2048, 128) if weight == "int4" else (1024, 24)
     cfg = CONFIGS["c3_olmoe_bf16"].with_(n_layers=1, hidden=hidden, n_experts=N, inter=inter, shared_inter=shared, top_k=K,
                                          capacity=C, weight_fmt=weight, act_fmt="bf16", seed=5600 + N)
@@ -358,6 +366,7 @@ def test_routing_in_every_workgroup_without_numbers(weight, N, K, C, lam, shared
     initial = [list(range(N))[:C]]
     store_a, a = build(cfg, lam=lam, initial=initial)
     store_b, b = build(cfg, lam=lam, initial=initial)
+    assert b.boundary_form() == pkg.MOE_BOUNDARY_ROUTED_EVERYWHERE
     T = 8
     stream = workloads.ar1_stream(cfg, T)[:, 0].contiguous().to(DEV)
     stream[2, 5] = float("nan")
@@ -426,6 +435,8 @@ def test_blocking_boundary_returns_with_its_outputs(weight, act, hidden, sync, m
 def test_steps_of_two_layers_in_flight(weight, hidden, inter, shared, form, monkeypatch):
     """Both layers are routed, without waiting, before either is computed - with a residual stream of their own and on
     one that the second step goes on from - in either deferred form of the boundary: as with blocking boundaries."""
+    import paper_2412_00099_amd as pkg
+
     cfg = CONFIGS["c2_qwen_bf16"].with_(n_layers=2, hidden=hidden, n_experts=12, inter=inter, shared_inter=shared, top_k=3,
                                         capacity=5, weight_fmt=weight, act_fmt="bf16", seed=5800 + hidden)
     print(f"case two layers in flight {weight} d={hidden} {form}", flush=True)
@@ -436,7 +447,8 @@ def test_steps_of_two_layers_in_flight(weight, hidden, inter, shared, form, monk
     out = []
     for wait in (True, False):
         store, dec = build(cfg, lam=0.5)
-        assert dec.plan().boundary_in_expert_launch == (form == "MOE_FUSE_BOUNDARY")
+        assert dec.boundary_form() == (pkg.MOE_BOUNDARY_IN_FIRST_WORKGROUP if form == "MOE_FUSE_BOUNDARY"
+                                       else pkg.MOE_BOUNDARY_ROUTED_EVERYWHERE)
         h = torch.zeros(2, hidden, device=DEV)
         x = torch.zeros(2, hidden, dtype=cfg.act_dtype, device=DEV)
         y = torch.zeros(T, 2, hidden, dtype=cfg.act_dtype, device=DEV)
@@ -475,6 +487,7 @@ def test_tables_counters_and_snapshots_include_the_step_in_flight(weight, hidden
     out = []
     for wait in (True, False):
         store, dec = build(cfg, lam=0.5)
+        assert dec.boundary_form() == ["neither", "MOE_FUSE_BOUNDARY", "MOE_ROUTE_EVERYWHERE"].index(form)
         h = torch.zeros(hidden, device=DEV)
         x = torch.zeros(hidden, dtype=cfg.act_dtype, device=DEV)
         y = torch.zeros(T, 2, hidden, dtype=cfg.act_dtype, device=DEV)
@@ -512,6 +525,7 @@ def test_another_x_is_refused_whatever_the_form_of_the_boundary(weight, act, hid
     cfg = CONFIGS["c2_qwen_bf16"].with_(n_layers=1, hidden=hidden, n_experts=8, inter=128 if weight == "int4" else 40,
                                         shared_inter=shared, top_k=2, capacity=8, weight_fmt=weight, act_fmt=act, seed=6000)
     store, dec = build(cfg, lam=0.5, initial=[list(range(8))])
+    assert dec.boundary_form() == (pkg.MOE_BOUNDARY_ROUTED_EVERYWHERE if everywhere == "1" else pkg.MOE_BOUNDARY_OWN_LAUNCH)
     a = workloads.ar1_stream(cfg, 1).to(DEV)
     h = torch.zeros(hidden, device=DEV)
     x = torch.zeros(hidden, dtype=cfg.act_dtype, device=DEV)
