@@ -86,6 +86,7 @@ struct moe_cache {
   uint32_t *h_gave_up_dev = nullptr;
   bool fuse_boundary = true;        // run deferred boundaries inside the expert launch (see moe_cache_init)
   bool route_everywhere = false;    // deferred boundaries: gate launch, routing in every workgroup of the expert launch
+  bool everywhere_cumsum = false;   // the same in route mode MOE_ROUTE_CUMSUM
   bool poison_fills = false;        // debugging aid: a slot is overwritten with NaN patterns before its fill (MOE_POISON_FILLS)
   int tag_spins = 1 << 18;          // polls (about a tenth of a second) before a workgroup stops waiting for
                                     // workgroup 0; MOE_TAG_SPINS lowers it so that tests reach the error path
@@ -342,19 +343,36 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   //   int4 d = 2048: 36 MB, 0.25 shared      - / 284 / 351   135 MB, 0.8 shared     - / 457 / 482
   // Inside the launch the boundary hides behind the shared expert's records, but one compute unit does all of it, and the
   // gate matrix alone costs it time in proportion to d: the launch has to be long for that.  Routing everywhere spreads
-  // the gate matrix; it costs a launch, which a short chain of small launches (d < 2048) feels: the host is behind then.
-  // MOE_FUSE_BOUNDARY=0 / 1 in the environment overrides the first rule.
+  // the gate matrix; it costs a launch, which short chains of small launches feel (the host is behind then), and every
+  // wavefront the decision.  Without a shared expert, us per layer-token, one launch of the boundary / routing in every
+  // workgroup, at the sizes around each line:
+  //   d = 512, bf16   64.5 MB 21.9 / 23.2, 89.7 MB 25.2 / 24.2        d = 1024, bf16   56.6 MB 22.3 / 22.1
+  //   d = 2048, bf16  31.5 MB 22.5 / 22.5, 37.7 MB 21.9 / 21.6 (top-2), 23.1 / 23.3 (top-8), 50.3 MB 24.2 / 23.3 (top-8)
+  //   d = 2048, int8  15.7 MB 22.4 / 22.7, 19.7 MB 22.8 / 22.9, 25.2 MB 23.1 / 22.9
+  //   d = 2048, int4  13.0 MB 22.9 / 23.3, 14.2 MB 22.9 / 22.8, 22.7 MB 24.1 / 23.0
+  //   d = 2048, fp32 activations  6.3 MB 22.9 / 21.7                  d = 4096   3.1 MB 23.9 / 21.5
+  // Cumsum-Threshold walks all ranks in every wavefront; only int4, whose launches are the shortest for what they hold
+  // in registers, does not hide that: d = 2048, 64 experts 22.7 MB 27.6 / 30.4, 97 MB 40.0 / 41.6, 32 experts 38.9 MB
+  // 29.1 / 28.8; d = 4096, 60 experts 3.2 MB 28.2 / 29.4, 22.7 MB 31.4 / 31.1.
+  // MOE_FUSE_BOUNDARY=0 / 1 and MOE_ROUTE_EVERYWHERE=0 / 1 in the environment override the two rules.
   const int64_t records = (int64_t)cfg->top_k * cfg->inter + cfg->shared_inter, streamed = records * c->slot_layout.rec_bytes;
   // (whichever form is taken: what a wrong x_dev meets depends on the shared expert's share alone)
   c->x_fixed = 3 * (int64_t)cfg->shared_inter >= records;
   c->fuse_boundary = cfg->weight_fmt != MOE_W_INT4_G128 && 3 * (int64_t)cfg->shared_inter >= records &&
                      streamed >= std::max((int64_t)41000 * cfg->hidden, (int64_t)45000000);
-  c->route_everywhere = gate_rows_supported(cfg->hidden, cfg->act_fmt) &&
-                        (cfg->hidden >= 2048 || streamed >= (cfg->hidden >= 1024 ? 56000000 : 64000000));
+  const bool int4 = cfg->weight_fmt == MOE_W_INT4_G128;
+  int64_t from = 0;  // bytes a layer-token streams
+  if (cfg->hidden < 1024) from = 90000000;
+  else if (cfg->hidden < 2048) from = 56000000;
+  else if (cfg->hidden < 4096 && cfg->act_fmt == MOE_A_BF16)
+    from = int4 ? 14000000 : cfg->weight_fmt == MOE_W_INT8_PC ? 20000000 : 36000000;
+  c->route_everywhere = gate_rows_supported(cfg->hidden, cfg->act_fmt) && streamed >= from;
+  c->everywhere_cumsum = c->route_everywhere && (!int4 || (cfg->hidden < 4096 ? N <= 32 && streamed >= 36000000
+                                                                               : N <= 32 || streamed >= 20000000));
   if (const char *s = getenv("MOE_FUSE_BOUNDARY")) c->fuse_boundary = c->x_fixed = atoi(s) != 0;
   c->x_fixed = c->x_fixed && gemv_fused_supported(cfg->weight_fmt, cfg->act_fmt, cfg->hidden, c->plan);
   if (const char *s = getenv("MOE_ROUTE_EVERYWHERE"))
-    c->route_everywhere = atoi(s) != 0 && gate_rows_supported(cfg->hidden, cfg->act_fmt);
+    c->route_everywhere = c->everywhere_cumsum = atoi(s) != 0 && gate_rows_supported(cfg->hidden, cfg->act_fmt);
   if (const char *s = getenv("MOE_POISON_FILLS")) c->poison_fills = atoi(s) != 0;
   if (const char *s = getenv("MOE_TAG_SPINS")) if (atoi(s) > 0) c->tag_spins = atoi(s);
   HIP_INIT(hipMalloc(&c->d_initial, sizeof(int32_t) * (size_t)L * (b->n_initial > 0 ? b->n_initial : 1)));
@@ -556,7 +574,8 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
 static int boundary_form(const moe_cache_t *c) {
   if (c->fuse_boundary && gemv_fused_supported(c->cfg.weight_fmt, c->cfg.act_fmt, c->cfg.hidden, c->plan))
     return MOE_BOUNDARY_IN_FIRST_WORKGROUP;
-  return c->route_everywhere ? MOE_BOUNDARY_ROUTED_EVERYWHERE : MOE_BOUNDARY_OWN_LAUNCH;
+  return (c->cfg.route_mode == MOE_ROUTE_CUMSUM ? c->everywhere_cumsum : c->route_everywhere) ? MOE_BOUNDARY_ROUTED_EVERYWHERE
+                                                                                             : MOE_BOUNDARY_OWN_LAUNCH;
 }
 
 int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const float *a_dev, float perturb,

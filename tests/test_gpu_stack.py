@@ -546,3 +546,40 @@ def test_another_x_is_refused_whatever_the_form_of_the_boundary(weight, act, hid
     dec.compute_stream.synchronize()
     assert torch.equal(y, y2) and y.float().abs().max() > 0
     dec.close()
+
+
+def test_the_form_of_the_boundary_follows_the_route_mode(monkeypatch):
+    """int4 with many experts: the routing is left to every workgroup, except under Cumsum-Threshold; the mode changes from
+    token to token, with a step of each form in flight, and everything is as with blocking boundaries."""
+    import paper_2412_00099_amd as pkg
+
+    for name in ("MOE_FUSE_BOUNDARY", "MOE_ROUTE_EVERYWHERE"):
+        monkeypatch.delenv(name, raising=False)
+    cfg = CONFIGS["c4_dsv2lite_int4"].with_(n_layers=1, n_experts=40, inter=1152, shared_inter=0, top_k=4, capacity=9, seed=6100)
+    print("case boundary form by route mode", flush=True)
+    modes = [(pkg.MOE_ROUTE_CACHE_PRIOR, 0, 0.0, pkg.MOE_BOUNDARY_ROUTED_EVERYWHERE),
+             (pkg.MOE_ROUTE_CUMSUM, 0, 0.6, pkg.MOE_BOUNDARY_OWN_LAUNCH),
+             (pkg.MOE_ROUTE_MAX_RANK, 8, 0.0, pkg.MOE_BOUNDARY_ROUTED_EVERYWHERE)]
+    T = 9
+    stream = workloads.ar1_stream(cfg, T)[:, 0].contiguous().to(DEV)
+    out = []
+    for wait in (True, False):
+        store, dec = build(cfg, lam=0.5)
+        h = torch.zeros(cfg.hidden, device=DEV)
+        x = torch.zeros(cfg.hidden, dtype=cfg.act_dtype, device=DEV)
+        y = torch.zeros(T, cfg.hidden, dtype=cfg.act_dtype, device=DEV)
+        torch.cuda.synchronize()
+        recs = []
+        for t in range(T):
+            mode, max_rank, p, form = modes[t * t % 3 if t % 2 else t % 3]
+            dec.set_baseline(mode, max_rank, p)
+            assert dec.boundary_form() == form
+            dec.stack_route_step(0, h, stream[t], 1.0 if t == 0 else 0.5, x, carry=t > 0, wait=wait)
+            dec.set_baseline(*modes[(t + 1) % 3][:3])  # (the step in flight keeps its mode)
+            dec.expert_forward(0, x, y[t])
+            recs.append(bytes(dec.last_route(0))[:-16])
+        dec.compute_stream.synchronize()
+        out.append((recs, h.cpu(), y.cpu(), bytes(dec.tables(0)), bytes(dec.stats())))
+        dec.close()
+    for u, v in zip(*out):
+        assert torch.equal(u, v) if isinstance(u, torch.Tensor) else u == v
