@@ -406,7 +406,8 @@ __device__ __forceinline__ void token_list(const BatchParams &p, int slot, int g
 
 // Eight h of one token (A operand: consecutive records) as three bf16 vectors that add up to them exactly (8 + 8 + 8
 // significant bits, truncated): the down projection runs on the bf16 matrix instruction with the precision of a 32-bit h
-// (weights are bf16, products exact, fp32 sums).
+// (weights are bf16, products exact, fp32 sums).  Where nothing is left for a part of an h other than 0 it is 2^-126 with
+// the sign of h, not 0: beside an infinite weight (or of an infinite h) a zero part would make a NaN of the infinity.
 __device__ __forceinline__ void split3(const f32x4 &lo, const f32x4 &hi, u32x4 (&out)[3]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -415,15 +416,18 @@ __device__ __forceinline__ void split3(const f32x4 &lo, const f32x4 &hi, u32x4 (
     for (int j = 0; j < 2; ++j) {
       const float h = i < 2 ? lo[2 * i + j] : hi[2 * i + j - 4];
       const uint32_t u = __float_as_uint(h);
-      // (infinity and NaN have no remainder)
-      const float r1 = __builtin_isfinite(h) ? h - __uint_as_float(u & 0xffff0000u) : 0.f;
+      // magnitudes from here on (what an infinity leaves is not a number, which fmaxf passes over)
+      const float least = __builtin_amdgcn_fmed3f(fabsf(h), 0.f, 0x1p-126f);  // the smaller of |h| and 2^-126
+      const float r1 = fmaxf(fabsf(h) - fabsf(__uint_as_float(u & 0xffff0000u)), least);
       const uint32_t u1 = __float_as_uint(r1);
       part[0][j] = u;
       part[1][j] = u1;
-      part[2][j] = __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u));
+      part[2][j] = __float_as_uint(fmaxf(r1 - __uint_as_float(u1 & 0xffff0000u), least));
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) out[q][i] = __builtin_amdgcn_perm(part[q][1], part[q][0], 0x07060302u);
+#pragma unroll
+    for (int q = 1; q < 3; ++q) out[q][i] |= out[0][i] & 0x80008000u;
   }
 }
 

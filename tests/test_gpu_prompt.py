@@ -410,3 +410,49 @@ def test_one_bad_token_leaves_the_others_alone():
         assert torch.equal(ys[0][others], ys[1][others]) and torch.isfinite(ys[0]).all()
         assert torch.isnan(ys[1][bad].float()).all()
     dec.close()
+
+
+def test_infinite_weights_stay_infinities():
+    """An infinite weight of a down projection - routed or shared - gives infinities of the sign of what it multiplies, as
+    in the single-token steps, whatever the number of significant bits of h: among the tokens are x = 0 and some of a single
+    large power of two, whose h have 16 at most (the SiLU of a large g is g, a product of 8 bits with a power of two)."""
+    cfg = BASE.with_(n_layers=1, hidden=1024, n_experts=6, inter=48, shared_inter=16, top_k=2, capacity=6, seed=7800)
+    inf = float("inf")
+
+    def spoil(w, at):
+        for row, record, value in at:
+            w["down"][row, record] = value
+        return w
+
+    at = [(5, 0, inf), (6, 47, -inf), (700, 20, inf), (1023, 31, -inf)]
+    decs = []
+    for _ in range(2):
+        store, dec = build(cfg, lam=0.5)
+        store.put_expert(0, 3, spoil(workloads.expert_weights(cfg, 0, 3, DEV), at))
+        store.put_shared(0, spoil(workloads.shared_weights(cfg, 0, DEV), [(9, 3, inf), (10, 15, -inf)]))
+        decs.append(dec)
+    one, many = decs
+    T = 40
+    print("case infinite weights", flush=True)
+    zs = workloads.logits_stream(cfg, T, layer=0, scale=1.5).to(DEV)
+    xs = workloads.ar1_stream(cfg, T)[:, 0].to(cfg.act_dtype).to(DEV)
+    xs[7:16] = 0
+    for i in range(8):
+        xs[8 + i, 100 + i] = 4096.0
+    yb, y1 = torch.zeros_like(xs), torch.zeros_like(xs)
+    torch.cuda.synchronize()
+    many.route_batch(0, logits=zs)
+    many.expert_forward_batch(0, xs, yb)
+    for t in range(T):
+        one.route_step(0, logits=zs[t])
+        one.expert_forward(0, xs[t], y1[t])
+    one.compute_stream.synchronize()
+    u, v = y1.float().cpu().numpy(), yb.float().cpu().numpy()
+    assert np.isinf(u[8:16, [9, 10]]).sum() >= 4 and np.isinf(u[:, [9, 10]]).sum() >= 2 * (T - 9) and np.isinf(u[:, [5, 6, 700, 1023]]).any()
+    assert np.array_equal(np.isnan(u), np.isnan(v)) and np.isnan(u[7, 9])  # (0 x infinity)
+    assert np.array_equal(np.where(np.isinf(u), u, 0), np.where(np.isinf(v), v, 0))
+    fin = np.isfinite(u)
+    for t in range(T):
+        assert not u[t][fin[t]].any() and not v[t][fin[t]].any() or oexp.rel_err(v[t][fin[t]], u[t][fin[t]]) <= 1e-2, t
+    one.close()
+    many.close()
