@@ -188,10 +188,6 @@ struct Selected {
   float zp, kth;    // altered logit; the K-th largest of them (Cache-Prior)
   uint64_t taken;   // Cache-Prior: the experts placed
 };
-// Up to this many places are found by rounds of arg-max, a chain of dependent lane exchanges each (0.13 us); counting is
-// 192 instructions for 64 experts whatever K.  A step with K = 1 takes 15.3 / 15.65 us (rounds / counting), a stack with
-// K = 4 339.0 / 341.4; eight rounds take 0.85 - 1.05 us of a boundary launch, counting about 0.3.
-constexpr int kArgMaxRounds = 4;
 __device__ __forceinline__ Selected route_select(const RouteParams &p, float z, bool resident, int t, float dsum_prev, int lane) {
 #pragma clang fp contract(off)
   const int N = p.n_experts, K = p.top_k;
@@ -228,41 +224,16 @@ __device__ __forceinline__ Selected route_select(const RouteParams &p, float z, 
     if (active && (resident || top_j)) s.zp = z + bias;  // one rounding (Eq. 9)
     // only the head of r' matters (one more round, for the margin, follows once the decision has been handed on)
     s.rank = N;
-    if (K <= kArgMaxRounds) {
-      // K rounds of arg-max, ties -> lower index
-      for (int k = 0; k < K; ++k) {
-        const bool cand = active && !((s.taken >> lane) & 1);
-        const float m = wave_max(cand ? s.zp : -INFINITY);
-        const int l = (int)__builtin_ctzll(ballot(cand && s.zp == m));
-        s.taken |= 1ull << l;
-        if (lane == l) s.rank = k;
-        s.kth = m;
-      }
-    } else {
-      // the same by counting how many altered logits are larger, then ties in lane order.  What is not a number has no
-      // place (no arg-max round finds it either): with fewer numbers than places the last ones stay empty
-      const float v = active ? s.zp : -INFINITY;
-      const bool cand = active && v == v;
-      int larger = 0;
-#pragma unroll
-      for (int j0 = 0; j0 < kWave; j0 += 16)
-        if (j0 < N) {
-#pragma unroll
-          for (int j = j0; j < j0 + 16; ++j) larger += readlane_f(v, j) > v;
-        }
-      uint64_t tied = 0;
-      for (int k = 0; k < K; ++k) {
-        if (tied == 0) tied = ballot(cand && larger == k);
-        if (tied == 0) {
-          s.kth = -INFINITY;
-          break;
-        }
-        const int l = (int)__builtin_ctzll(tied);
-        tied &= tied - 1;
-        if (lane == l) s.rank = k;
-        s.kth = readlane_f(v, l);
-        s.taken |= 1ull << l;
-      }
+    // K rounds of arg-max, ties -> lower index; what is not a number has no place.  (Counting the larger ones for
+    // every expert instead, 192 instructions that a launch runs once and has to fetch, made route_kernel 0.4 us longer
+    // from K = 5 to 8 - K = 8 8.04 / 8.44 - and a batch with misses 7 %: route_batch_kernel 238 / 255 us for 64 tokens.)
+    for (int k = 0; k < K; ++k) {
+      const bool cand = active && !((s.taken >> lane) & 1);
+      const float m = wave_max(cand ? s.zp : -INFINITY);
+      const int l = (int)__builtin_ctzll(ballot(cand && s.zp == m));
+      s.taken |= 1ull << l;
+      if (lane == l) s.rank = k;
+      s.kth = m;
     }
   } else {
     // Max-Rank (Eq. 6-7) / Cumsum-Threshold (Eq. 8): two promote() passes = a three-class stable partition

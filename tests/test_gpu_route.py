@@ -407,9 +407,8 @@ def test_pruning_baseline_on_device(h):
 @pytest.mark.parametrize("N,K,C", [(20, 3, 8), (20, 5, 8), (64, 8, 16), (16, 6, 7)])
 @pytest.mark.filterwarnings("ignore::RuntimeWarning")
 def test_experts_without_a_number_are_placed_last(N, K, C, fixed, lam):
-    """Masked experts (-inf), infinities and NaNs among the logits, however the places are found (rounds of arg-max up to
-    four, counting above): an altered logit that is not a number - a NaN, or -inf with an infinite bias - is never taken
-    while numbers are left, as in a sort."""
+    """Masked experts (-inf), infinities and NaNs among the logits: an altered logit that is not a number - a NaN, or -inf
+    with an infinite bias - is never taken while numbers are left, as in a sort."""
     print(f"case odd logits N={N} K={K} C={C} fixed={fixed} lam={lam}", flush=True)
     cfg = TINY.with_(n_experts=N, top_k=K, capacity=C, seed=191 + N)
     store, dec = build(cfg, lam=lam, delta_fixed=fixed)
