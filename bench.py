@@ -43,9 +43,9 @@ PERTURB = 0.5
 # only for the kernel sources it was taken with: reported as null once their hash differs.
 GEMV_TRAFFIC = {
     "workload": "c2_qwen_bf16",
-    "sources_sha256": "e40fa05ac844eb380480d4b9c03a48162916dd8764aa353c21e86d3c46ac49f9",
-    "fetch_kib": 68035.1, "fetch_scale": 2.0,
-    "write_kib": 2054.0, "write_scale": 1.0,
+    "sources_sha256": "054190cf62af1f5bc6e270ef799b94a299ba08d8db565af54e271ab03ac78b4b",
+    "fetch_kib": 68032.2, "fetch_scale": 2.0,
+    "write_kib": 2054.1, "write_scale": 1.0,
 }
 GEMV_SOURCES = ("expert_gemv.hip", "gemv_common.h", "route_device.h", "common.h")
 
@@ -245,7 +245,7 @@ def prompt_phase(pkg, store, cfg, a, dev, n_warm=128, n_timed=256):
                 f"experts {exp_us:.1f} us per layer-batch ({gbs:.0f} GB/s of the distinct experts' bytes)")
         out[f"B{B}"] = res
     out["note"] = (f"{n_warm} warm-up + {n_timed} timed prompt tokens per layer; expert time is the wall time of "
-                   "moe_expert_forward_batch (fills, table upload, expert launches, reduction); decode for comparison: "
+                   "moe_expert_forward_batch (fills, expert launches, reduction); decode for comparison: "
                    "steady_state.per_layer_us per token and layer")
     return out
 
