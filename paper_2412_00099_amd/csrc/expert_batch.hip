@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
 // tokens stay in registers for the unit, no weights are staged through LDS, and no barrier stands in the load
 // stream except one per 16 records of `up`.  A unit finds its tokens itself from the selected slots (1 KB): no tables
 // are made on the host or sent.  Measured (60 experts of 1408, shared 5632, top-4, d = 2048; both kernels): 19 distinct
-// experts, 128 tokens, 399 MB: 62 + 39 us, against 203 us for one fused kernel over tiles of 16 tokens with the down
+// experts, 128 tokens, 399 MB: 62 + 40 us, against 203 us for one fused kernel over tiles of 16 tokens with the down
 // projection on the fp32 matrix instruction; 8 experts, 8 tokens, 208 MB: 28 + 16 us against 47 us.
 // (h written as three bf16 planes instead of fp32, split once by `up`: 63 + 42 us; h costs `down` a third of what W does.)
 constexpr int kBWaves = 4;
