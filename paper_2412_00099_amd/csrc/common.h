@@ -91,6 +91,9 @@ struct GemvParams {
   int32_t pass;        // 0: shared expert + experts that were resident; 1: experts whose slot was just filled
   int32_t row_offset;  // first partial row this launch writes
   int32_t route_in;    // RouteIn
+  // the split of n records over the launch's G streaming workgroups (launch_expert_gemv fills it in): quotient and remainder
+  // of the shared and of the routed records, and ceil(2^32 / G) to divide by G with one multiplication
+  uint32_t shared_q, shared_r, routed_q, routed_r, inv_g;
   uint64_t given_slots;                // kRouteGiven: 8 bits each, in selection order
   float given_weight[MOE_MAX_TOPK];
   BoundaryArgs b;
@@ -138,12 +141,17 @@ hipError_t launch_route(const RouteParams &p, const void *gate_w, const void *x,
                         LayerState *state, moe_route_out_t *out_dev, HostOut host, hipStream_t s);
 // launch shape of the expert GEMV
 constexpr int kGemvWaves = 8;  // wavefronts per workgroup
-constexpr int kGemvDepth = 2;  // records in flight per wavefront (fp32 / bf16 kernels)
+// Records in flight per wavefront, by 16-byte loads per row and lane: about 48 KB per compute unit, at least one record.  What
+// is requested beyond what a compute unit's L1 keeps in flight only lets some wavefronts have all their records before
+// others have their first (static launches, us with 1 / 2 / 3 records: int4 d = 2048, 37 MB - / 12.7 / 13.2; int8 d = 2048, 37 MB
+// 12.1 / 12.1 / 12.2; bf16 d = 2048, 101 MB 20.8 / 20.7; bf16 d = 4096 21.5 / 33.3, where two do not fit the registers).
+constexpr int gemv_depth(int loads_per_row) { return loads_per_row == 1 ? 2 : 1; }
 struct GemvPlan {
   int grid;   // workgroups (= fp32 partial rows written): one per compute unit
+  int depth;  // records in flight per wavefront
   bool dot2;  // packed bf16 dot products (bf16 weights and activations)
 };
-GemvPlan gemv_plan(int n_cus, int total_records, int weight_fmt, int act_fmt);
+GemvPlan gemv_plan(int n_cus, int total_records, int weight_fmt, int act_fmt, int hidden);
 // logits of a layer boundary whose glue launch_reduce_glue has done: x = h / rms to f.x_out, z = W_gate x, one workgroup per
 // four experts (needs gate_rows_supported)
 bool gate_rows_supported(int hidden, int act_fmt);

@@ -9,9 +9,12 @@
 // into its private d/64 outputs: no barrier between the up and the down projection.  Records of all
 // selected experts and of the shared expert form one index space that is split evenly over the workgroups;
 // inside a workgroup records are interleaved over the wavefronts, so a workgroup streams one contiguous span.
-// Each wavefront keeps DEPTH records' loads in flight in a register ring.  The wavefronts' private outputs
+// Each wavefront keeps DEPTH records' loads in flight in a register ring, whose registers are refilled as they become
+// free.  The wavefronts' private outputs
 // are tree-reduced through LDS, each workgroup writes one fp32 partial row, and a second small kernel adds
 // the partial rows in a fixed order (deterministic result).
+#include <type_traits>
+
 #include "common.h"
 #include "gemv_common.h"
 #include "route_device.h"
@@ -148,7 +151,8 @@ struct Chunk<MOE_W_BF16, true> {
 template <int LPR>
 struct RecRegs {
   u32x4 g[LPR], u[LPR], dn[LPR];
-  float wt;
+  float wt, next_wt;
+  bool want;
 };
 
 // FMT: weight format; LPR: 16-byte loads per row per lane (d = LPR*64*VEC); NW: wavefronts per workgroup;
@@ -187,8 +191,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
       return;
     }
   }
-  const int64_t row16 = (int64_t)d / VEC;  // 16-byte chunks per row
-  const int64_t rec_bytes = 3 * row16 * 16;
+  constexpr int kRowBytes = LPR * kWave * 16, kRecBytes = 3 * kRowBytes;
   RecordWalker<NW, IN> walk;
   walk.init(p, wave);
   // FUSED: the operands of x (this lane's columns of the residual stream, its sums of squares per 64 columns) are
@@ -202,60 +205,34 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     __builtin_amdgcn_sched_barrier(0);  // ... and stay ahead of them in the instruction stream
   }
 
-  auto issue = [&](RecRegs<LPR> &R) {
-    R.wt = walk.wt;
-    const u32x4 *q = reinterpret_cast<const u32x4 *>(walk.base + (int64_t)walk.at * rec_bytes) + lane;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.g[c] = stream_load(q + c * kWave);
-    q += row16;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.u[c] = stream_load(q + c * kWave);
-    q += row16;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.dn[c] = stream_load(q + c * kWave);
-  };
-
-  // Pass 0 loads every list entry of the wavefront, also the rare ones whose expert is only being filled (their
-  // arithmetic is skipped): the number of records is then known up front, the steady-state loop below issues
-  // its loads unconditionally, and the compiler can wait for exactly the oldest record in flight instead of for
-  // all loads.  Pass 1 (only the experts just filled) skips the other records without loading them.
-  const bool all = p.pass == 0;
-  int todo = all ? walk.remaining() : 0;  // entries not issued yet (pass 0)
-  if constexpr (IN == kRouteEverywhere) walk.decide_now(p);
-  RecRegs<LPR> ring[DEPTH];
-  bool live[DEPTH], want[DEPTH];
-  auto advance = [&](int j) {  // next record into ring[j], if there is one
-    if (all) {
-      live[j] = todo > 0;
-      if (live[j]) {
-        --todo;
-        want[j] = walk.step(p);
-      }
-    } else {
-      live[j] = walk.next(p);
-      want[j] = true;
-    }
-    if (live[j]) issue(ring[j]);
-  };
-#pragma unroll
-  for (int j = 0; j < DEPTH; ++j) advance(j);  // weights first: they do not depend on x
-
-  // activations: the lane keeps the x entries of its own columns in registers
+  // activations: the lane keeps the x entries of its own columns in registers.  Their few loads go out ahead of the weights
+  // (loads complete in order, and the first record waits for x)
   float xr[LPR * XW];
-  if constexpr (FUSED) {
-    const float scale = 1.0f / sqrtf(blocks.total() / (float)d + 1e-6f);
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) F::make_x(&hraw[c * VEC], scale, p.act_fmt, &xr[c * XW]);
-  } else {
+  if constexpr (!FUSED) {
 #pragma unroll
     for (int c = 0; c < LPR; ++c) F::load_x(p.x, p.act_fmt, (c * kWave + lane) * VEC, &xr[c * XW]);
+    __builtin_amdgcn_sched_barrier(0);
   }
+
+  auto load_up = [&](RecRegs<LPR> &R, bool want) {
+    R.next_wt = walk.wt;
+    const RecBuffer q = record_buffer(walk.base + (int64_t)walk.at * kRecBytes, want ? kRecBytes : 0);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.g[c] = record_load(q, 0, (c * kWave + lane) * 16);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.u[c] = record_load(q, kRowBytes, (c * kWave + lane) * 16);
+    return q;
+  };
+  auto load_down = [&](RecRegs<LPR> &R, RecBuffer q) {
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.dn[c] = record_load(q, 2 * kRowBytes, (c * kWave + lane) * 16);
+    R.wt = R.next_wt;
+  };
 
   float y[CPL];
 #pragma unroll
   for (int j = 0; j < CPL; ++j) y[j] = 0.f;
-
-  auto consume = [&](const RecRegs<LPR> &R) {
+  auto up_part = [&](const RecRegs<LPR> &R) {
     float g0 = 0.f, g1 = 0.f, u0 = 0.f, u1 = 0.f;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -264,34 +241,65 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     }
     float g = g0 + g1, u = u0 + u1;
     wave_sum2(g, u);
-    const float h = g / (1.f + __expf(-g)) * u * R.wt;
+    return g / (1.f + __expf(-g)) * u * R.wt;
+  };
+  auto down_part = [&](const RecRegs<LPR> &R, float h) {
 #pragma unroll
     for (int c = 0; c < LPR; ++c) F::axpy(h, R.dn[c], &y[c * VEC]);
   };
 
-  // steady state of pass 0: all ring entries live and at least DEPTH more entries to fetch
-  if (all && live[DEPTH - 1]) {
-    while (todo >= DEPTH) {
-#pragma unroll
-      for (int j = 0; j < DEPTH; ++j) {
-        if (want[j]) consume(ring[j]);
-        want[j] = walk.step(p);
-        issue(ring[j]);
-      }
-      todo -= DEPTH;
+  // A ring of DEPTH records per wavefront.  A place is refilled as its registers become free: the gate and up rows once
+  // the dot products are done, the down row behind the axpy.  Loads are issued whether or not there is a record
+  // (RecordWalker::step), in blocks of DEPTH places.  What bounds a launch is HBM, and for short launches how
+  // early the arithmetic starts: with loads inside branches and two records in flight no wavefront computed anything before
+  // all its first records were there.  Static launches, us, before / now (both with partial_reduce_kernel): bf16 d = 2048
+  // 101 MB 21.6 / 20.8, 138 MB 26.8 / 26.0; bf16 d = 4096 101 MB 35.4 / 21.5 (no spills); fp32 d = 2048 26.9 / 19.9.
+  RecRegs<LPR> ring[DEPTH];
+  auto turn = [&](RecRegs<LPR> &R, auto refill_tag) {
+    constexpr bool REFILL = decltype(refill_tag)::value;
+    float h = 0.f;
+    if (R.want) h = up_part(R);
+    RecBuffer q;
+    bool want = false;
+    if constexpr (REFILL) {
+      want = walk.step(p);
+      q = load_up(R, want);
     }
-  }
-  // start-up of short lists, tail, and pass 1.  ring[0] is always the oldest record in flight: when it is dead,
-  // all are
-  while (live[0]) {
-#pragma unroll
-    for (int j = 0; j < DEPTH; ++j) {
-      if (live[j]) {
-        if (want[j]) consume(ring[j]);
-        advance(j);
-      }
+    if (R.want) down_part(R, h);
+    if constexpr (REFILL) {
+      load_down(R, q);
+      R.want = want;
     }
+  };
+  auto fetch = [&](RecRegs<LPR> &R, bool any) {
+    R.want = any && walk.step(p);
+    const RecBuffer q = load_up(R, R.want);
+    load_down(R, q);
+  };
+
+  // kRouteEverywhere: the shared records at hand are requested ahead of the decision (the others' places stay empty)
+  if constexpr (IN == kRouteEverywhere) {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], walk.shared_next());
+    walk.decide_now(p);
+  } else {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);
   }
+  const int blocks_left = (walk.remaining() + DEPTH - 1) / DEPTH;
+
+  if constexpr (FUSED) {
+    const float scale = 1.0f / sqrtf(blocks.total() / (float)d + 1e-6f);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) F::make_x(&hraw[c * VEC], scale, p.act_fmt, &xr[c * XW]);
+  }
+
+  for (int b = 0; b < blocks_left; ++b) {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{});
+  }
+#pragma unroll
+  for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{});
 
   reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
                                 tid, lane, wave);
@@ -445,18 +453,18 @@ hipError_t launch_plan(const GemvParams &p, const GemvPlan &plan, hipStream_t s,
   if (p.route_in == kRouteBoundary) {  // the variant with the boundary in workgroup 0 exists for packed bf16 arithmetic, d <= 2048
     if constexpr (LPR <= 4 && DOT2) {
       if (plan.grid < 2) return hipErrorInvalidValue;
-      launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteBoundary>(p, plan.grid, s, e0, e1);
+      launch_one<FMT, LPR, kGemvWaves, gemv_depth(LPR), DOT2, kRouteBoundary>(p, plan.grid, s, e0, e1);
       return hipGetLastError();
     } else {
       return hipErrorInvalidValue;
     }
   }
   if (p.route_in == kRouteEverywhere)
-    launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteEverywhere>(p, plan.grid + 1, s, e0, e1);
+    launch_one<FMT, LPR, kGemvWaves, gemv_depth(LPR), DOT2, kRouteEverywhere>(p, plan.grid + 1, s, e0, e1);
   else if (p.route_in == kRouteGiven)
-    launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteGiven>(p, plan.grid, s, e0, e1);
+    launch_one<FMT, LPR, kGemvWaves, gemv_depth(LPR), DOT2, kRouteGiven>(p, plan.grid, s, e0, e1);
   else
-    launch_one<FMT, LPR, kGemvWaves, kGemvDepth, DOT2, kRouteBefore>(p, plan.grid, s, e0, e1);
+    launch_one<FMT, LPR, kGemvWaves, gemv_depth(LPR), DOT2, kRouteBefore>(p, plan.grid, s, e0, e1);
   return hipGetLastError();
 }
 
@@ -498,14 +506,16 @@ bool gemv_inter_supported(int weight_fmt, int inter) {
   return true;
 }
 
-// Launch shape: one workgroup of 8 wavefronts per compute unit, two records in flight per wavefront
-// (measured best on MI355X among 4/8/16 wavefronts, depths 1-3 and 1-4 workgroups per compute unit).
-GemvPlan gemv_plan(int n_cus, int total_records, int weight_fmt, int act_fmt) {
+// Launch shape: one workgroup of 8 wavefronts per compute unit (measured best on MI355X among 4/8/16 wavefronts and 1-4
+// workgroups per compute unit), gemv_depth records in flight per wavefront.
+GemvPlan gemv_plan(int n_cus, int total_records, int weight_fmt, int act_fmt, int hidden) {
   GemvPlan pl{};
   pl.grid = n_cus < total_records ? n_cus : total_records;
   if (pl.grid < 1) pl.grid = 1;
   if (pl.grid > 1024) pl.grid = 1024;  // (the record split multiplies workgroup index and record count in 32 bits)
   pl.dot2 = weight_fmt == MOE_W_BF16 && act_fmt == MOE_A_BF16;
+  const int vec = weight_fmt == MOE_W_FP32 ? 4 : weight_fmt == MOE_W_BF16 ? 8 : weight_fmt == MOE_W_INT8_PC ? 16 : 32;
+  pl.depth = gemv_depth(hidden / (kWave * vec));
   return pl;
 }
 
@@ -520,9 +530,18 @@ bool gemv_fused_supported(int weight_fmt, int act_fmt, int hidden, const GemvPla
   }
 }
 
-hipError_t launch_expert_gemv(const GemvParams &p, int weight_fmt, const GemvPlan &plan, hipStream_t s,
+hipError_t launch_expert_gemv(const GemvParams &args, int weight_fmt, const GemvPlan &plan, hipStream_t s,
                               hipEvent_t e0, hipEvent_t e1) {
-  if (!gemv_shape_supported(weight_fmt, p.hidden)) return hipErrorInvalidValue;
+  if (!gemv_shape_supported(weight_fmt, args.hidden)) return hipErrorInvalidValue;
+  GemvParams p = args;
+  const uint32_t G = (uint32_t)(plan.grid - (p.route_in == kRouteBoundary));  // workgroups that stream
+  if (G < 1 || G > 1024) return hipErrorInvalidValue;
+  const uint32_t shared = p.pass == 0 ? (uint32_t)p.shared_inter : 0u, routed = (uint32_t)p.top_k * (uint32_t)p.inter;
+  p.shared_q = shared / G;
+  p.shared_r = shared % G;
+  p.routed_q = routed / G;
+  p.routed_r = routed % G;
+  p.inv_g = (uint32_t)(((1ull << 32) + G - 1) / G);  // (G = 1: 0, and nothing is left over)
   switch (weight_fmt) {
     case MOE_W_FP32: return launch_fmt<MOE_W_FP32, false>(p, plan, s, e0, e1);
     case MOE_W_BF16:

@@ -18,6 +18,8 @@
 //  consumed by mixed-precision FMAs; accumulators are unscaled within a group of 128 records and flushed with
 //  the group's per-column scales (and the constant (1024 + 8) * sum(h) removed) when the group or expert
 //  changes and at the end.
+#include <type_traits>
+
 #include "common.h"
 #include "gemv_common.h"
 #include "route_device.h"
@@ -112,9 +114,10 @@ constexpr int boundary_ch(int d) { return d / 512 <= 4 ? d / 512 : 0; }
 template <int LPR>
 struct RecI8 {
   u32x4 g[LPR], u[LPR], dn[LPR];
-  float sg, su, wt;
+  float sg, su, wt, next_wt;
   const uint8_t *base;  // blob of the record's expert (its tail holds the down scales)
   int rows;
+  bool want;
 };
 
 // PRE: the per-column scales of W_down are fetched when the wavefront enters an expert, so that the flush at the
@@ -139,27 +142,36 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
       return;
     }
   }
-  const int64_t row16 = d / VEC;
-  const int64_t rec_bytes = 3 * row16 * 16;
+  constexpr int kRowBytes = LPR * kWave * 16;
+  constexpr int64_t rec_bytes = 3 * kRowBytes;
   RecordWalker<NW, IN> walk;
   walk.init(p, wave);
 
-  auto issue = [&](RecI8<LPR> &R) {
+  // a row's scale, through the scalar data path: its completion is counted apart from the loads of the weights
+  // (the word that holds it: scalar loads are of whole words)
+  auto row_scale = [&](const uint16_t *tail, int i) {
+    typedef const __attribute__((address_space(4))) uint32_t *cword;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(tail + i);
+    return f16_bits((uint16_t)(*(cword)(at & ~(uintptr_t)3) >> (8 * (at & 2))));
+  };
+  auto load_up = [&](RecI8<LPR> &R, bool want) {
     const uint16_t *tail = reinterpret_cast<const uint16_t *>(walk.base + (int64_t)walk.rows * rec_bytes);
-    R.wt = walk.wt;
+    R.next_wt = walk.wt;
+    const RecBuffer q = record_buffer(walk.base + (int64_t)walk.at * rec_bytes, want ? (int)rec_bytes : 0);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.g[c] = record_load(q, 0, (c * kWave + lane) * 16);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.u[c] = record_load(q, kRowBytes, (c * kWave + lane) * 16);
+    R.sg = row_scale(tail, walk.at);              // gate scales [rows]
+    R.su = row_scale(tail, walk.rows + walk.at);  // up scales [rows]
+    return q;
+  };
+  auto load_down = [&](RecI8<LPR> &R, RecBuffer q) {
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.dn[c] = record_load(q, 2 * kRowBytes, (c * kWave + lane) * 16);
+    R.wt = R.next_wt;
     R.base = walk.base;
     R.rows = walk.rows;
-    const u32x4 *q = reinterpret_cast<const u32x4 *>(walk.base + (int64_t)walk.at * rec_bytes) + lane;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.g[c] = stream_load(q + c * kWave);
-    q += row16;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.u[c] = stream_load(q + c * kWave);
-    q += row16;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.dn[c] = stream_load(q + c * kWave);
-    R.sg = f16_bits(tail[walk.at]);              // gate scales [rows]
-    R.su = f16_bits(tail[walk.rows + walk.at]);  // up scales [rows]
   };
 
   // the activations' few loads go out ahead of the weights (loads complete in order, and the first routed record
@@ -177,33 +189,22 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     for (int c = 0; c < LPR; ++c) fetch_x<VEC>(p.x, p.act_fmt, (c * kWave + lane) * VEC, xraw[c]);
   }
 
-  if constexpr (IN == kRouteEverywhere) walk.decide_now(p);
-  // pass 0 loads every list entry, see expert_gemv_int4_kernel; for an expert that is only being filled its first record
-  // over and over, from the caches (four experts of 1408 records, d = 2048, one of them missing: 9.5 us, 10.1 with its
-  // records as they are)
-  const bool all = p.pass == 0;
-  int todo = all ? walk.remaining() : 0;
   RecI8<LPR> ring[DEPTH];
-  bool live[DEPTH], want[DEPTH];
-  auto step = [&](int j) {
-    want[j] = walk.step(p);
-    walk.at = want[j] ? walk.at : 0;
+  auto fetch = [&](RecI8<LPR> &R, bool any) {
+    R.want = any && walk.step(p);
+    const RecBuffer q = load_up(R, R.want);
+    load_down(R, q);
   };
-  auto advance = [&](int j) {
-    if (all) {
-      live[j] = todo > 0;
-      if (live[j]) {
-        --todo;
-        step(j);
-      }
-    } else {
-      live[j] = walk.next(p);
-      want[j] = true;
-    }
-    if (live[j]) issue(ring[j]);
-  };
+  // kRouteEverywhere: the shared records at hand are requested ahead of the decision (the others' places stay empty)
+  if constexpr (IN == kRouteEverywhere) {
 #pragma unroll
-  for (int j = 0; j < DEPTH; ++j) advance(j);
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], walk.shared_next());
+    walk.decide_now(p);
+  } else {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);
+  }
+  const int blocks_left = (walk.remaining() + DEPTH - 1) / DEPTH;
 
   // activations as packed fp16 pairs in column order, and their sum over this lane's columns
   uint32_t xh[CPL / 2];
@@ -262,13 +263,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     hsum = 0.f;
   };
 
-  auto consume = [&](const RecI8<LPR> &R) {
-    if (R.base != cur_base) {
-      if (cur_base) flush(cur_base, cur_rows);
-      cur_base = R.base;
-      cur_rows = R.rows;
-      load_scales(cur_base, cur_rows);
-    }
+  auto up_part = [&](const RecI8<LPR> &R) {
     float g0 = 0.f, g1 = 0.f, u0 = 0.f, u1 = 0.f;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -291,7 +286,15 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     wave_sum2(g, u);
     g *= R.sg;
     u *= R.su;
-    const float h = g / (1.f + __expf(-g)) * u * R.wt;
+    return g / (1.f + __expf(-g)) * u * R.wt;
+  };
+  auto down_part = [&](const RecI8<LPR> &R, float h) {
+    if (R.base != cur_base) {
+      if (cur_base) flush(cur_base, cur_rows);
+      cur_base = R.base;
+      cur_rows = R.rows;
+      load_scales(cur_base, cur_rows);
+    }
     hsum += h;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -307,27 +310,29 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     }
   };
 
-  // steady state of pass 0: all ring entries live and at least DEPTH more entries to fetch
-  if (all && live[DEPTH - 1]) {
-    while (todo >= DEPTH) {
-#pragma unroll
-      for (int j = 0; j < DEPTH; ++j) {
-        if (want[j]) consume(ring[j]);
-        step(j);
-        issue(ring[j]);
-      }
-      todo -= DEPTH;
+  // A ring of DEPTH records, refilled in two parts (see expert_gemv_kernel).  37 MB at d = 2048: 13.1 -> 12.1 us
+  auto turn = [&](RecI8<LPR> &R, auto refill_tag) {
+    constexpr bool REFILL = decltype(refill_tag)::value;
+    float h = 0.f;
+    if (R.want) h = up_part(R);
+    RecBuffer q;
+    bool want = false;
+    if constexpr (REFILL) {
+      want = walk.step(p);
+      q = load_up(R, want);
     }
-  }
-  while (live[0]) {
-#pragma unroll
-    for (int j = 0; j < DEPTH; ++j) {
-      if (live[j]) {
-        if (want[j]) consume(ring[j]);
-        advance(j);
-      }
+    if (R.want) down_part(R, h);
+    if constexpr (REFILL) {
+      load_down(R, q);
+      R.want = want;
     }
+  };
+  for (int b = 0; b < blocks_left; ++b) {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{});
   }
+#pragma unroll
+  for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{});
   if (cur_base) flush(cur_base, cur_rows);
   reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
                                 tid, lane, wave);
@@ -355,9 +360,10 @@ template <int LPR>
 struct RecI4 {
   u32x4 g[LPR], u[LPR], dn[LPR];
   uint32_t sc[LPR];  // (gate scale, up scale) fp16 pair of this lane's group, per chunk
-  float wt;
+  float wt, next_wt;
   const uint8_t *base;  // blob of the record's expert (its tail holds the down scales)
   int rows, grp;
+  bool want;
 };
 
 template <int LPR, int NW, int DEPTH, bool PRE, int IN>
@@ -380,29 +386,30 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
       return;
     }
   }
-  const int64_t row16 = d / VEC;                             // 16-byte chunks per row of nibbles
-  const int64_t rec_bytes = int4_record_bytes(d);            // three rows + (gate, up) scale pairs, padded
+  constexpr int kRowBytes = LPR * kWave * 16;
+  constexpr int64_t rec_bytes = int4_record_bytes(CPL * kWave);  // three rows + (gate, up) scale pairs, padded
   RecordWalker<NW, IN, 1> walk;  // a contiguous block of records per wavefront: few changes of scale group
   walk.init(p, wave);
 
-  auto issue = [&](RecI4<LPR> &R) {
-    const uint8_t *rec = walk.base + (int64_t)walk.at * rec_bytes;
-    R.wt = walk.wt;
+  auto load_up = [&](RecI4<LPR> &R, bool want) {
+    R.next_wt = walk.wt;
+    const RecBuffer q = record_buffer(walk.base + (int64_t)walk.at * rec_bytes, want ? (int)rec_bytes : 0);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c)  // 4 lanes (128 columns) per group
+      R.sc[c] = __builtin_amdgcn_raw_buffer_load_b32(q, (c * kWave + lane) / 4 * 4, 3 * kRowBytes, 0);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.g[c] = record_load(q, 0, (c * kWave + lane) * 16);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.u[c] = record_load(q, kRowBytes, (c * kWave + lane) * 16);
+    return q;
+  };
+  auto load_down = [&](RecI4<LPR> &R, RecBuffer q) {
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) R.dn[c] = record_load(q, 2 * kRowBytes, (c * kWave + lane) * 16);
+    R.wt = R.next_wt;
     R.base = walk.base;
     R.rows = walk.rows;
     R.grp = walk.at >> 7;
-    const u32x4 *q = reinterpret_cast<const u32x4 *>(rec) + lane;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.g[c] = stream_load(q + c * kWave);
-    q += row16;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.u[c] = stream_load(q + c * kWave);
-    q += row16;
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.dn[c] = stream_load(q + c * kWave);
-    const uint32_t *sc = reinterpret_cast<const uint32_t *>(rec + 3 * row16 * 16);
-#pragma unroll
-    for (int c = 0; c < LPR; ++c) R.sc[c] = sc[(c * kWave + lane) >> 2];  // 4 lanes (128 columns) per group
   };
 
   XRaw<VEC> xraw[FUSED ? 1 : LPR];  // fetched ahead of the weights, converted after the ring has been filled
@@ -418,30 +425,22 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     for (int c = 0; c < LPR; ++c) fetch_x<VEC>(p.x, p.act_fmt, (c * kWave + lane) * VEC, xraw[c]);
   }
 
-  // Pass 0 loads every list entry of the wavefront, also the rare ones whose expert is only being filled (their
-  // arithmetic is skipped), so that the steady-state loop issues its loads unconditionally and each use waits for
-  // the oldest record only.  Pass 1 (the experts just filled) skips the other records without loading them.
-  const bool all = p.pass == 0;
-  int todo = all ? walk.remaining() : 0;
-  if constexpr (IN == kRouteEverywhere) walk.decide_now(p);
   RecI4<LPR> ring[DEPTH];
-  bool live[DEPTH], want[DEPTH];
-  auto advance = [&](int j) {
-    if (all) {
-      live[j] = todo > 0;
-      if (live[j]) {
-        --todo;
-        want[j] = walk.step(p);
-      }
-    } else {
-      live[j] = walk.next(p);
-      want[j] = true;
-    }
-    if (live[j]) issue(ring[j]);
+  auto fetch = [&](RecI4<LPR> &R, bool any) {
+    R.want = any && walk.step(p);
+    const RecBuffer q = load_up(R, R.want);
+    load_down(R, q);
   };
+  // kRouteEverywhere: the shared records at hand are requested ahead of the decision (the others' places stay empty)
+  if constexpr (IN == kRouteEverywhere) {
 #pragma unroll
-  for (int j = 0; j < DEPTH; ++j) advance(j);
-  // the down scales of the first record's group travel with the first records
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], walk.shared_next());
+    walk.decide_now(p);
+  } else {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);
+  }
+  const int blocks_left = (walk.remaining() + DEPTH - 1) / DEPTH;
   const uint8_t *cur_base = nullptr;
   int cur_rows = 0, cur_grp = -1;
   u32x4 dsc[PRE ? 4 * LPR : 1];
@@ -454,13 +453,6 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
       for (int q4 = 0; q4 < 4; ++q4) dsc[4 * c + q4] = sp[q4];
     }
   };
-  if (live[0]) {
-    cur_base = ring[0].base;
-    cur_rows = ring[0].rows;
-    cur_grp = ring[0].grp;
-    load_scales(cur_base, cur_rows, cur_grp);
-  }
-
   // mask and bias of the nibble unpacking as register values (see and_or)
   uint32_t mask_lo = kNibMaskLo, mask_hi = kNibMaskHi, bias = kF16Bias;
   asm volatile("" : "+s"(mask_lo), "+s"(mask_hi));
@@ -524,14 +516,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     dirty = false;
   };
 
-  auto consume = [&](const RecI4<LPR> &R) {
-    if (R.base != cur_base || R.grp != cur_grp) {
-      if (dirty) flush(cur_base, cur_rows, cur_grp);
-      cur_base = R.base;
-      cur_rows = R.rows;
-      cur_grp = R.grp;
-      load_scales(cur_base, cur_rows, cur_grp);
-    }
+  auto up_part = [&](const RecI4<LPR> &R) {
     float g = 0.f, u = 0.f;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -555,7 +540,16 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
       u = __builtin_fmaf((u0 + u1) + xoff[c], f16_hi(R.sc[c]), u);
     }
     wave_sum2(g, u);
-    const float h = g / (1.f + __expf(-g)) * u * R.wt;
+    return g / (1.f + __expf(-g)) * u * R.wt;
+  };
+  auto down_part = [&](const RecI4<LPR> &R, float h) {
+    if (R.base != cur_base || R.grp != cur_grp) {
+      if (dirty) flush(cur_base, cur_rows, cur_grp);
+      cur_base = R.base;
+      cur_rows = R.rows;
+      cur_grp = R.grp;
+      load_scales(cur_base, cur_rows, cur_grp);
+    }
     hsum += h;
     dirty = true;
 #pragma unroll
@@ -577,28 +571,31 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     }
   };
 
-  // steady state of pass 0: all ring entries live and at least DEPTH more entries to fetch
-  if (all && live[DEPTH - 1]) {
-    while (todo >= DEPTH) {
-#pragma unroll
-      for (int j = 0; j < DEPTH; ++j) {
-        if (want[j]) consume(ring[j]);
-        want[j] = walk.step(p);
-        issue(ring[j]);
-      }
-      todo -= DEPTH;
+  // A ring of DEPTH records, refilled in two parts (see expert_gemv_kernel).  37 MB at d = 2048, a quarter of it shared, in a
+  // static launch: 16.3 -> 12.7 us; inside the launch (clocks of its wavefronts) the first record is multiplied at 2.0 us
+  // instead of 6.9, and the last wavefront has stored its row at 8.9 instead of 13.2.
+  auto turn = [&](RecI4<LPR> &R, auto refill_tag) {
+    constexpr bool REFILL = decltype(refill_tag)::value;
+    float h = 0.f;
+    if (R.want) h = up_part(R);
+    RecBuffer q;
+    bool want = false;
+    if constexpr (REFILL) {
+      want = walk.step(p);
+      q = load_up(R, want);
     }
-  }
-  // start-up of short lists, tail, and pass 1.  ring[0] is always the oldest record in flight
-  while (live[0]) {
-#pragma unroll
-    for (int j = 0; j < DEPTH; ++j) {
-      if (live[j]) {
-        if (want[j]) consume(ring[j]);
-        advance(j);
-      }
+    if (R.want) down_part(R, h);
+    if constexpr (REFILL) {
+      load_down(R, q);
+      R.want = want;
     }
+  };
+  for (int b = 0; b < blocks_left; ++b) {
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{});
   }
+#pragma unroll
+  for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{});
   if (dirty) flush(cur_base, cur_rows, cur_grp);
   reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
                                 tid, lane, wave);
@@ -623,15 +620,15 @@ hipError_t launch_expert_gemv_quant(const GemvParams &p, int weight_fmt, const G
   if (p.route_in == kRouteBoundary && (plan.grid < 2 || p.act_fmt != MOE_A_BF16)) return hipErrorInvalidValue;
   if (weight_fmt == MOE_W_INT8_PC) {
     switch (p.hidden / (kWave * 16)) {
-      case 1: MOE_Q(expert_gemv_int8_kernel, 1, 8, 2, true); break;
-      case 2: MOE_Q(expert_gemv_int8_kernel, 2, 8, 2, false); break;
-      case 4: MOE_Q(expert_gemv_int8_kernel, 4, 8, 1, false); break;
+      case 1: MOE_Q(expert_gemv_int8_kernel, 1, 8, gemv_depth(1), true); break;
+      case 2: MOE_Q(expert_gemv_int8_kernel, 2, 8, gemv_depth(2), false); break;
+      case 4: MOE_Q(expert_gemv_int8_kernel, 4, 8, gemv_depth(4), false); break;
       default: return hipErrorInvalidValue;
     }
   } else if (weight_fmt == MOE_W_INT4_G128) {
     switch (p.hidden / (kWave * 32)) {
-      case 1: MOE_Q(expert_gemv_int4_kernel, 1, 8, 6, true); break;
-      case 2: MOE_Q(expert_gemv_int4_kernel, 2, 8, 2, false); break;
+      case 1: MOE_Q(expert_gemv_int4_kernel, 1, 8, gemv_depth(1), true); break;
+      case 2: MOE_Q(expert_gemv_int4_kernel, 2, 8, gemv_depth(2), false); break;
       default: return hipErrorInvalidValue;
     }
   } else {

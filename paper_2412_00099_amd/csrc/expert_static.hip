@@ -62,7 +62,7 @@ hipError_t launch_expert_forward_static(int weight_fmt, int act_fmt, int hidden,
   e = static_scratch_setup(dev, &base, &cus);
   if (e != hipSuccess) return e;
   float *partial = static_cast<float *>(base);
-  GemvPlan plan = gemv_plan(cus, top_k * inter + shared_inter, weight_fmt, act_fmt);
+  GemvPlan plan = gemv_plan(cus, top_k * inter + shared_inter, weight_fmt, act_fmt, hidden);
   if (plan.grid > kStaticMaxGrid) plan.grid = kStaticMaxGrid;
   GemvParams p{};
   p.slot_pool = static_cast<const uint8_t *>(slot_pool);

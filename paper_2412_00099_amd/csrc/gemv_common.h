@@ -14,6 +14,19 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // weights are read once: mark the loads non-temporal so they do not displace x and the partial rows in L2
 __device__ __forceinline__ u32x4 stream_load(const u32x4 *p) { return __builtin_nontemporal_load(p); }
 
+// One record of a blob as a buffer resource.  bytes = 0 makes it an empty one: loads from it return zeros and touch no
+// memory, so that a place of a list that holds nothing is loaded by the same instructions as any other (no branch
+// around loads, see RecordWalker::step).  base has to be the same in every lane.
+typedef __amdgpu_buffer_rsrc_t RecBuffer;
+__device__ __forceinline__ RecBuffer record_buffer(const uint8_t *base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base), 0, bytes, 0x00020000);
+}
+// weights are read once: non-temporal (aux 2), so that they do not displace x and the partial rows in L2.  at: the same in
+// every lane, off: this lane's offset
+__device__ __forceinline__ u32x4 record_load(RecBuffer r, uint32_t at, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, off, at, 2);
+}
+
 __device__ __forceinline__ float dot2_bf16(uint32_t w, uint32_t x, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, x), acc, false);
 }
@@ -65,9 +78,10 @@ __device__ __forceinline__ u32x2 ld64(const void *p) { return *static_cast<const
 // workgroups 1..G-1 and the decision is fetched only when the first routed entry comes up, once workgroup 0 has handed it
 // over.  kRouteEverywhere: the same split, and every wavefront with routed entries works the decision out before its first
 // load of weights (decide_now: one place in the kernel, where few registers are in use).
-// STEP: distance between a wavefront's consecutive list entries.  NW (the default) interleaves the wavefronts over
+// STEP: distance between a wavefront's consecutive routed entries.  NW (the default) interleaves the wavefronts over
 // the workgroup's list; 1 gives every wavefront one contiguous block of it, so that its records stay inside one
-// expert and, for int4, inside one scale group of 128 records as far as possible.
+// expert and, for int4, inside one scale group of 128 records as far as possible.  Shared records are dealt out in turn
+// in both cases: every wavefront then has something to load while the decision is on its way.
 //
 // The walk is organised in runs - consecutive entries of the wavefront inside one blob (the shared expert, or one
 // selected expert) - so that the per-record work is an increment and a decrement; slot, weight and the split of the
@@ -83,7 +97,9 @@ struct RecordWalker {
   int r, n_rt;       // its routed entries: next index into the K*I routed records, how many are left to start
   int left;          // records left in the current run
   int next_at;       // row of the current run's next record
+  int run_step;      // distance between its records
   bool run_wanted;   // the pass covers the current run's expert
+  bool run_shared;   // the current run is of shared records
   bool decided;      // the routing decision has been unpacked
   // the routing record: loaded at kernel start, unpacked when the first routed run comes up
   u32x4 rw0, rw1, rd;  // sel_weight[0..3], sel_weight[4..7], {tag, slots lo, slots hi, miss mask}
@@ -91,14 +107,15 @@ struct RecordWalker {
   uint32_t miss_mask;
   float z, dsum;       // kRouteEverywhere: lane's logit, Eq. 10's sum so far
   int my_slot, count;  // lane's expert's slot, tokens so far
-  // the record found by step() / next()
+  // the record found by step()
   const uint8_t *base;  // blob of the record's expert
   int rows, at;
   float wt;
 
-  // start of part b of n records split into G parts (b * n < 2^32: the host limits n to 2^22 and G to 2^10)
-  static __device__ __forceinline__ int bound(int b, int n, int G) {
-    return (int)((uint32_t)b * (uint32_t)n / (uint32_t)G);
+  // start of part b of n = q G + r records split into G parts: floor(b n / G).  b r < 2^20 (the host limits G to 2^10), so
+  // that the product with ceil(2^32 / G) has the exact quotient in its upper half
+  static __device__ __forceinline__ int bound(int b, uint32_t q, uint32_t r, uint32_t inv_g) {
+    return (int)((uint32_t)b * q + __umulhi((uint32_t)b * r, inv_g));
   }
 
   // The record is the same for every lane and was written by an earlier launch: it is read through the scalar data
@@ -154,7 +171,7 @@ struct RecordWalker {
 
   __device__ __forceinline__ void init(const GemvParams &p, int wave) {
     constexpr int kFirst = IN == kRouteBefore || IN == kRouteGiven ? 0 : 1;  // workgroups that stream nothing
-    const int G = (int)gridDim.x - kFirst, b = (int)blockIdx.x - kFirst;
+    const int b = (int)blockIdx.x - kFirst;
     // the routing record, or what it is worked out from, first: it is on its way while the shared records are set up
     if constexpr (IN == kRouteBefore) load_record(p);
     if constexpr (IN == kRouteEverywhere) {
@@ -165,29 +182,33 @@ struct RecordWalker {
       count = p.b.state->count;
       __builtin_amdgcn_sched_barrier(0);
     }
-    const int routed = p.top_k * p.inter;
-    const int shared = p.pass == 0 ? p.shared_inter : 0;
     // the workgroup's list: ns shared records from row s0, then nr routed entries from q0
-    const int s0 = bound(b, shared, G), ns = bound(b + 1, shared, G) - s0;
-    const int q0 = bound(b, routed, G), nl = ns + bound(b + 1, routed, G) - q0;
-    int first_sh, first_rt;  // list indices
+    const int s0 = bound(b, p.shared_q, p.shared_r, p.inv_g), ns = bound(b + 1, p.shared_q, p.shared_r, p.inv_g) - s0;
+    const int q0 = bound(b, p.routed_q, p.routed_r, p.inv_g), nr = bound(b + 1, p.routed_q, p.routed_r, p.inv_g) - q0;
+    // the shared records are dealt to the wavefronts in turn
+    n_sh = wave < ns ? (ns - wave + NW - 1) / NW : 0;
+    const int first_sh = wave;
+    int first_rt;  // among the workgroup's routed entries
     if constexpr (STEP == 1) {
-      const int lb = wave * nl / NW, le = (wave + 1) * nl / NW;
-      first_sh = lb;
-      n_sh = max(0, min(le, ns) - lb);
-      first_rt = max(lb, ns);
-      n_rt = max(0, le - first_rt);
+      // blocks of equal length; what is left over goes to the last wavefronts, as that of the shared records to the first
+      const int more = nr % NW, from = wave - (NW - more);
+      n_rt = nr / NW + (from >= 0);
+      first_rt = wave * (nr / NW) + max(0, from);
     } else {
-      first_sh = wave;
-      n_sh = wave < ns ? (ns - wave + NW - 1) / NW : 0;
-      first_rt = wave + n_sh * NW;
-      n_rt = first_rt < nl ? (nl - first_rt + NW - 1) / NW : 0;
+      first_rt = wave + n_sh * NW - ns;
+      n_rt = first_rt < nr ? (nr - first_rt + NW - 1) / NW : 0;
     }
     sh_at = s0 + first_sh;
-    r = q0 + (first_rt - ns);
+    r = q0 + first_rt;
     left = 0;
     next_at = 0;
+    run_step = STEP;
+    at = 0;
+    base = p.slot_pool;
+    rows = p.inter;
+    wt = 0.f;
     run_wanted = true;
+    run_shared = false;
     decided = false;
     if constexpr (IN == kRouteGiven) {
       const float *w = p.given_weight;
@@ -226,6 +247,8 @@ struct RecordWalker {
 
   // list entries this wavefront still owns
   __device__ __forceinline__ int remaining() const { return left + n_sh + n_rt; }
+  // its next entry is a shared record, which needs no decision
+  __device__ __forceinline__ bool shared_next() const { return n_sh > 0 || (left > 0 && run_shared); }
 
   // the wavefront's next run (there must be one): its shared records first, then its routed entries expert by expert
   __device__ __forceinline__ void start_run(const GemvParams &p) {
@@ -233,6 +256,8 @@ struct RecordWalker {
       base = p.shared_blob;
       rows = p.shared_inter;
       next_at = sh_at;
+      run_step = NW;
+      run_shared = true;
       left = n_sh;
       n_sh = 0;
       wt = 1.f;
@@ -258,7 +283,12 @@ struct RecordWalker {
       decided = true;
     }
     const int I = p.inter;
-    const int seg = (int)((uint32_t)r / (uint32_t)I), row = r - seg * I;
+    int seg = 0;  // r / I, of at most MOE_MAX_TOPK values
+#pragma unroll
+    for (int k = 1; k < MOE_MAX_TOPK; ++k) seg += r >= k * I;
+    const int row = r - seg * I;
+    run_step = STEP;
+    run_shared = false;
     const int in_seg = (I - row + STEP - 1) / STEP;  // this wavefront's entries inside expert `seg` from here on
     left = min(in_seg, n_rt);
     n_rt -= left;
@@ -270,32 +300,20 @@ struct RecordWalker {
     run_wanted = (((miss_mask >> seg) & 1u) != 0) == (p.pass == 1);
   }
 
-  // Move to this wavefront's next list entry (there must be one: see remaining()) and describe its record, whether
-  // the pass covers it or not; returns whether it does.  The caller loads the record in any case, so that the
-  // number of loads in flight does not depend on the routing decision, and only skips the arithmetic.
+  // Move to this wavefront's next list entry and describe its record; whether there is one and the pass covers it.  The
+  // caller issues the same loads in any case, from an empty resource where the answer is no (record_buffer): the number
+  // of loads in flight then depends on nothing, and the compiler can wait for exactly the oldest record.  (Loads inside
+  // branches make a wait cover all loads in flight: the wavefronts then did no arithmetic before the last of their first
+  // records had arrived.)
   __device__ __forceinline__ bool step(const GemvParams &p) {
-    if (left == 0) start_run(p);
+    if (left == 0) {
+      if (n_sh + n_rt == 0) return false;
+      start_run(p);
+    }
     at = next_at;
-    next_at += STEP;
+    next_at += run_step;
     --left;
     return run_wanted;
-  }
-
-  // advance to this wavefront's next record of the pass, skipping the others; false when the list is exhausted
-  __device__ __forceinline__ bool next(const GemvParams &p) {
-    for (;;) {
-      if (left == 0) {
-        if (n_sh + n_rt == 0) return false;
-        start_run(p);
-      }
-      if (run_wanted) {
-        at = next_at;
-        next_at += STEP;
-        --left;
-        return true;
-      }
-      left = 0;  // the pass does not cover this expert: drop the whole run
-    }
   }
 };
 

@@ -307,7 +307,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   HIP_INIT(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   HIP_INIT(static_scratch_setup(dev, nullptr, nullptr));  // moe_expert_forward_static's scratch array on this device
   c->n_cus = cus;
-  c->plan = gemv_plan(cus, cfg->top_k * cfg->inter + cfg->shared_inter, cfg->weight_fmt, cfg->act_fmt);
+  c->plan = gemv_plan(cus, cfg->top_k * cfg->inter + cfg->shared_inter, cfg->weight_fmt, cfg->act_fmt, cfg->hidden);
   // the host learns a routing decision by polling the three self-tagged words the router stores into mapped host
   // memory (each complete in itself, no ordering between them); MOE_HOST_SYNC=event waits on a stream event instead
   c->poll = true;
@@ -1083,7 +1083,7 @@ int moe_cache_plan(moe_cache_t *c, moe_cache_plan_t *out) {
   if (!c || !out) return fail(MOE_EINVAL, "NULL argument");
   out->grid = c->plan.grid;
   out->wavefronts = kGemvWaves;
-  out->depth = kGemvDepth;
+  out->depth = c->plan.depth;
   out->packed_bf16_dot = c->plan.dot2;
   out->boundary_in_expert_launch = boundary_form(c) == MOE_BOUNDARY_IN_FIRST_WORKGROUP;
   return MOE_OK;

@@ -459,7 +459,7 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
 }
 
 // What a streaming wavefront needs of the decision (see RecordWalker): slots 8 bits each, weights, miss flags, all in
-// selection order.  The experts that miss have no slot yet: slot 0, whose records are loaded and not used.
+// selection order.  The experts that miss have no slot yet: slot 0, whose records are not loaded.
 __device__ __forceinline__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane,
                                        uint64_t &slots, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]) {
   const Selected pick = route_select(p, lane < p.n_experts ? z : -INFINITY, my_slot >= 0, t, dsum_prev, lane);
