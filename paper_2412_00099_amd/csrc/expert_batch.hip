@@ -117,8 +117,7 @@ __device__ __forceinline__ void store_sel(const uint32_t *rec, int K, int lane, 
   }
 }
 
-// barrier that waits for LDS only: the records on their way to host memory are not waited for
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+using rt::lds_barrier;
 
 constexpr int kAheadWaves = 4;
 constexpr int kZStride = MOE_MAX_EXPERTS + 1;  // (a thread walks a row: rows start in different banks)

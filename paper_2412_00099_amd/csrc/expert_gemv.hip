@@ -281,7 +281,8 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
   if constexpr (IN == kRouteEverywhere) {
 #pragma unroll
     for (int j = 0; j < DEPTH; ++j) fetch(ring[j], walk.shared_next());
-    walk.decide_now(p);
+    __shared__ __attribute__((aligned(16))) rt::DecideLds decide_s;
+    walk.decide_now(p, wave, decide_s);
   } else {
 #pragma unroll
     for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);

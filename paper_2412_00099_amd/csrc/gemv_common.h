@@ -76,8 +76,8 @@ __device__ __forceinline__ u32x2 ld64(const void *p) { return *static_cast<const
 
 // IN (RouteIn) = kRouteBoundary: workgroup 0 of the launch runs the layer boundary; the records are shared among
 // workgroups 1..G-1 and the decision is fetched only when the first routed entry comes up, once workgroup 0 has handed it
-// over.  kRouteEverywhere: the same split, and every wavefront with routed entries works the decision out before its first
-// load of weights (decide_now: one place in the kernel, where few registers are in use).
+// over.  kRouteEverywhere: the same split, and the wavefronts of every workgroup work the decision out ahead of their first
+// routed record (decide_now: one place in the kernel, where few registers are in use).
 // STEP: distance between a wavefront's consecutive routed entries.  NW (the default) interleaves the wavefronts over
 // the workgroup's list; 1 gives every wavefront one contiguous block of it, so that its records stay inside one
 // expert and, for int4, inside one scale group of 128 records as far as possible.  Shared records are dealt out in turn
@@ -87,8 +87,10 @@ __device__ __forceinline__ u32x2 ld64(const void *p) { return *static_cast<const
 // selected expert) - so that the per-record work is an increment and a decrement; slot, weight and the split of the
 // routed index into (expert, row) are worked out once per run.  All of it is wavefront-uniform (scalar registers).
 namespace rt {
-__device__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane, uint64_t &slots,
-                       uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]);
+struct DecideLds;
+template <int NW>
+__device__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane, int wave, DecideLds &lds,
+                       uint64_t &slots, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]);
 }
 template <int NW, int IN = kRouteBefore, int STEP = NW>
 struct RecordWalker {
@@ -220,11 +222,15 @@ struct RecordWalker {
     }
   }
 
-  // kRouteEverywhere, after init() and the loads that are wanted ahead of the weights
-  __device__ __forceinline__ void decide_now(const GemvParams &p) {
-    if (n_rt == 0) return;
+  // kRouteEverywhere, after init() and the loads that are wanted ahead of the weights; by all wavefronts of the workgroup
+  __device__ __forceinline__ void decide_now(const GemvParams &p, int wave, rt::DecideLds &lds) {
+    // (what the decision reads through the scalar data path is wanted here, not where it is used: the compiler moves such
+    // loads into the branches behind, one trip to memory each)
+    const RouteParams &q = p.b.route;
+    asm volatile("" ::"s"(dsum), "s"(count), "s"(q.lambda), "s"(q.delta_fixed), "s"(q.cumsum_p), "s"(q.n_experts), "s"(q.top_k),
+                 "s"(q.top_j), "s"(q.renormalize), "s"(q.delta_mode), "s"(q.route_mode), "s"(q.max_rank));
     float w[MOE_MAX_TOPK];
-    rt::decide(p.b.route, z, my_slot, dsum, count, (int)(threadIdx.x & 63), slots, miss_mask, w);
+    rt::decide<NW>(p.b.route, z, my_slot, dsum, count, (int)(threadIdx.x & 63), wave, lds, slots, miss_mask, w);
     rw0 = u32x4{__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
     rw1 = u32x4{__float_as_uint(w[4]), __float_as_uint(w[5]), __float_as_uint(w[6]), __float_as_uint(w[7])};
     decided = true;

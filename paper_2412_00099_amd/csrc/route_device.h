@@ -55,6 +55,34 @@ __device__ __forceinline__ uint32_t sortable(float f) {
   const uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+// the same for a ranking by maxima: 0, which every number beats, for what is not a number
+__device__ __forceinline__ uint32_t number_key(float f, bool active) {
+  const uint32_t u = __float_as_uint(f + 0.f);
+  return active && f == f ? u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u) : 0u;
+}
+__device__ __forceinline__ float key_number(uint32_t k) {
+  return __uint_as_float(k ^ (~(uint32_t)((int32_t)k >> 31) | 0x80000000u));
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t dppu(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+// (left to the compiler the three maxima become one vector operation, with moves in front and lane reads behind)
+__device__ __forceinline__ uint32_t smax(uint32_t a, uint32_t b) {
+  uint32_t r;
+  asm("s_max_u32 %0, %1, %2" : "=s"(r) : "s"(a), "s"(b) : "scc");
+  return r;
+}
+// the largest of 64 unsigned values, in a scalar register (whole numbers need no canonical forms: one instruction a step)
+__device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
+  v = max(v, dppu<0x128>(v));
+  v = max(v, dppu<0x124>(v));
+  v = max(v, dppu<0x122>(v));
+  v = max(v, dppu<0x121>(v));
+  const uint32_t r0 = (uint32_t)readlane_i((int)v, 0), r1 = (uint32_t)readlane_i((int)v, 16);
+  const uint32_t r2 = (uint32_t)readlane_i((int)v, 32), r3 = (uint32_t)readlane_i((int)v, 48);
+  return smax(smax(r0, r1), smax(r2, r3));
+}
 // key: larger = earlier in a descending ranking; equal values rank the lower lane first
 __device__ __forceinline__ uint64_t rank_key(float v, int lane, bool active) {
   return active ? (((uint64_t)sortable(v + 0.f) << 32) | (uint32_t)(63 - lane)) : 0ull;
@@ -67,6 +95,24 @@ __device__ __forceinline__ int rank_of(uint64_t key) {
   for (int j = 0; j < kWave; ++j) r += readlane_u64(key, j) > key;
   return r;
 }
+
+// The same by NW wavefronts that hold the same keys: each counts for 64 / NW lanes (a few instructions a lane, no lane's
+// waiting for another's) and gets the ranks of those; owns_lane tells which they are.
+template <int NW>
+__device__ __forceinline__ bool owns_lane(int lane, int wave) { return lane / (kWave / NW) == wave; }
+template <int NW>
+__device__ __forceinline__ int rank_share(uint64_t key, int lane, int wave) {
+  int mine = 0;
+#pragma unroll
+  for (int i = 0; i < kWave / NW; ++i) {
+    const int e = wave * (kWave / NW) + i;
+    const int above = (int)__builtin_popcountll(ballot(key > readlane_u64(key, e)));
+    mine = lane == e ? above : mine;
+  }
+  return mine;
+}
+// workgroup barrier that waits for LDS only, not for loads from memory in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __device__ __forceinline__ float dot2(uint32_t w, uint32_t x, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, x), acc, false);
@@ -181,6 +227,65 @@ static_assert(kHandoverCopies * 8 == kWave, "one lane per word of every copy");
 
 // The part of a routing step that decides which experts a token takes and with which weights (Eq. 3 softmax, Eq. 10,
 // Eq. 9, Eq. 2), by one wavefront: lane e <-> expert e.  z: this lane's logit (-inf in lanes past the last expert).
+struct Scores {
+  float w;          // softmax of the unmodified logits
+  float delta, dsum;
+  bool top_j;       // one of the router's own top-J
+};
+__device__ __forceinline__ Scores route_scores(const RouteParams &p, float z, int t, float dsum_prev, int lane) {
+#pragma clang fp contract(off)
+  const bool active = lane < p.n_experts;
+  Scores s;
+  // softmax of the unmodified logits (Eq. 3); feeds only the expert weights.  Largest and smallest among the numbers (lanes
+  // past the last expert: -inf and +inf; where 64 logits are none, it is none either)
+  const uint32_t zkey = number_key(z, true);
+  const float zmax = key_number(wave_umax(zkey));
+  const float zmin = key_number(~wave_umax(!active ? ~0xff800000u : zkey != 0u ? ~zkey : 0u));
+  const float pe = active ? expf(z - zmax) : 0.f;
+  const float psum = wave_sum(pe);
+  s.w = pe / psum;
+
+  // Delta_avg (Eq. 10): cumulative mean of the logit range, current token included
+  const float range = zmax - zmin;
+  s.dsum = dsum_prev + range;
+  const float mean = s.dsum / (float)(t + 1);
+  s.delta = p.delta_mode == MOE_DELTA_FIXED ? p.delta_fixed : p.delta_mode == MOE_DELTA_TOKEN ? range : mean;
+
+  // router's own top-J (Sec. 3.3): J rounds of arg-max, ties -> lower index
+  uint64_t topj_mask = 0;
+  for (int j = 0; j < p.top_j; ++j) {
+    const uint32_t key = !active || (topj_mask >> lane) & 1 ? 0u : zkey, m = wave_umax(key);
+    if (m != 0u) topj_mask |= 1ull << __builtin_ctzll(ballot(key == m));
+  }
+  s.top_j = (topj_mask >> lane) & 1;
+  return s;
+}
+// altered logit of Cache-Prior (Eq. 9)
+__device__ __forceinline__ float prior_logit(const RouteParams &p, const Scores &s, float z, bool resident, int lane) {
+#pragma clang fp contract(off)
+  const float bias = p.lambda * s.delta;                                  // one rounding
+  return lane < p.n_experts && (resident || s.top_j) ? z + bias : z;      // one rounding
+}
+// Max-Rank (Eq. 6-7) / Cumsum-Threshold (Eq. 8): two promote() passes = a three-class stable partition.  rank_z: position
+// in the ranking by logit; the result is the key of the altered ranking
+__device__ __forceinline__ uint64_t baseline_key(const RouteParams &p, const Scores &s, int rank_z, bool resident, int lane) {
+#pragma clang fp contract(off)
+  const int N = p.n_experts;
+  const bool active = lane < N;
+  int M = p.max_rank;
+  if (p.route_mode == MOE_ROUTE_CUMSUM) {
+    // mass ranked before me; M = number of experts whose preceding mass is still below p
+    float before = 0.f;
+    for (int r = 0; r < N; ++r) {
+      const float wr = readlane_f(s.w, (int)__builtin_ctzll(ballot(active && rank_z == r)));
+      if (rank_z > r) before += wr;
+    }
+    M = (int)__builtin_popcountll(ballot(active && before < p.cumsum_p));
+  }
+  const int cls = s.top_j ? 0 : ((resident && rank_z < M) ? 1 : 2);
+  return active ? (((uint64_t)(2 - cls) << 32) | (uint32_t)(63 - rank_z)) : 0ull;
+}
+
 struct Selected {
   int rank;         // position in the altered ranking r' (exact for the first K positions, >= K otherwise)
   float w;          // softmax of the unmodified logits, renormalised over the selected experts if asked
@@ -192,65 +297,34 @@ __device__ __forceinline__ Selected route_select(const RouteParams &p, float z, 
 #pragma clang fp contract(off)
   const int N = p.n_experts, K = p.top_k;
   const bool active = lane < N;
+  const Scores sc = route_scores(p, z, t, dsum_prev, lane);
   Selected s;
-  // softmax of the unmodified logits (Eq. 3); feeds only the expert weights
-  const float zmax = wave_max(z);
-  const float zmin = wave_min(active ? z : INFINITY);
-  const float pe = active ? expf(z - zmax) : 0.f;
-  const float psum = wave_sum(pe);
-  s.w = pe / psum;
-
-  // Delta_avg (Eq. 10): cumulative mean of the logit range, current token included
-  const float range = zmax - zmin;
-  s.dsum = dsum_prev + range;
-  s.delta = p.delta_mode == MOE_DELTA_FIXED ? p.delta_fixed
-            : p.delta_mode == MOE_DELTA_TOKEN ? range
-                                              : s.dsum / (float)(t + 1);
-
-  // router's own top-J (Sec. 3.3): J rounds of arg-max, ties -> lower index
-  uint64_t topj_mask = 0;
-  for (int j = 0; j < p.top_j; ++j) {
-    const bool cand = active && !((topj_mask >> lane) & 1);
-    const float m = wave_max(cand ? z : -INFINITY);
-    topj_mask |= 1ull << __builtin_ctzll(ballot(cand && z == m));
-  }
-  const bool top_j = (topj_mask >> lane) & 1;
-
+  s.w = sc.w;
+  s.delta = sc.delta;
+  s.dsum = sc.dsum;
   s.zp = z;
   s.taken = 0;
   s.kth = 0.f;
-  if (p.route_mode == MOE_ROUTE_CACHE_PRIOR) {
-    const float bias = p.lambda * s.delta;               // one rounding
-    if (active && (resident || top_j)) s.zp = z + bias;  // one rounding (Eq. 9)
+  if (__builtin_expect(p.route_mode == MOE_ROUTE_CACHE_PRIOR, 1)) {
+    s.zp = prior_logit(p, sc, z, resident, lane);
     // only the head of r' matters (one more round, for the margin, follows once the decision has been handed on)
     s.rank = N;
-    // K rounds of arg-max, ties -> lower index; what is not a number has no place.  (Counting the larger ones for
-    // every expert instead, 192 instructions that a launch runs once and has to fetch, made route_kernel 0.4 us longer
-    // from K = 5 to 8 - K = 8 8.04 / 8.44 - and a batch with misses 7 %: route_batch_kernel 238 / 255 us for 64 tokens.)
+    // K rounds of arg-max over whole-number keys, ties -> lower index; what is not a number has no place.  (Counting the
+    // larger ones for every expert instead, 192 instructions that a launch runs once and has to fetch, made route_kernel
+    // 0.4 us longer from K = 5 to 8 - K = 8 8.04 / 8.44 - and a batch with misses 7 %: route_batch_kernel 238 / 255 us for
+    // 64 tokens.)
+    uint32_t key = number_key(s.zp, active);
     for (int k = 0; k < K; ++k) {
-      const bool cand = active && !((s.taken >> lane) & 1);
-      const float m = wave_max(cand ? s.zp : -INFINITY);
-      const int l = (int)__builtin_ctzll(ballot(cand && s.zp == m));
-      s.taken |= 1ull << l;
-      if (lane == l) s.rank = k;
-      s.kth = m;
+      const uint32_t m = wave_umax(key);
+      const uint64_t at = ballot(key == m) & (m != 0u ? ~0ull : 0ull);
+      const bool here = at != 0 && lane == (int)__builtin_ctzll(at);
+      s.rank = here ? k : s.rank;
+      key = here ? 0u : key;
+      s.taken |= at & (0ull - at);
+      s.kth = m != 0u ? key_number(m) : -INFINITY;
     }
   } else {
-    // Max-Rank (Eq. 6-7) / Cumsum-Threshold (Eq. 8): two promote() passes = a three-class stable partition
-    const int rank_z = rank_of(rank_key(z, lane, active));
-    int M = p.max_rank;
-    if (p.route_mode == MOE_ROUTE_CUMSUM) {
-      // mass ranked before me; M = number of experts whose preceding mass is still below p
-      float before = 0.f;
-      for (int r = 0; r < N; ++r) {
-        const float wr = readlane_f(s.w, (int)__builtin_ctzll(ballot(active && rank_z == r)));
-        if (rank_z > r) before += wr;
-      }
-      M = (int)__builtin_popcountll(ballot(active && before < p.cumsum_p));
-    }
-    const int cls = top_j ? 0 : ((resident && rank_z < M) ? 1 : 2);
-    const uint64_t key = active ? (((uint64_t)(2 - cls) << 32) | (uint32_t)(63 - rank_z)) : 0ull;
-    s.rank = rank_of(key);
+    s.rank = rank_of(baseline_key(p, sc, rank_of(rank_key(z, lane, active)), resident, lane));
   }
   // expert weights from the unmodified logits (Sec. 3.3), optional renormalisation (Sec. 2.1)
   if (p.renormalize) {
@@ -459,25 +533,58 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
 }
 
 // What a streaming wavefront needs of the decision (see RecordWalker): slots 8 bits each, weights, miss flags, all in
-// selection order.  The experts that miss have no slot yet: slot 0, whose records are not loaded.
-__device__ __forceinline__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane,
-                                       uint64_t &slots, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]) {
-  const Selected pick = route_select(p, lane < p.n_experts ? z : -INFINITY, my_slot >= 0, t, dsum_prev, lane);
-  slots = 0;
-  miss_mask = 0;
-#pragma unroll
-  for (int k = 0; k < MOE_MAX_TOPK; ++k) {
-    weight[k] = 0.f;
-    if (k < p.top_k) {
-      // (a place that nothing fills - logits that are not numbers - is slot 0 with weight 0, as in the record)
-      const uint64_t at = ballot(lane < p.n_experts && pick.rank == k);
-      const int l = (int)__builtin_ctzll(at | (1ull << 63));
-      const int slot = at != 0 ? readlane_i(my_slot, l) : 0;
-      weight[k] = at != 0 ? readlane_f(pick.w, l) : 0.f;
-      if (slot >= 0) slots |= (uint64_t)(uint32_t)(slot & 0xff) << (8 * k);
-      else miss_mask |= 1u << k;
-    }
+// selection order.  The experts that miss have no slot yet: slot 0, whose records are not loaded.  Run once per launch by
+// all NW wavefronts of a workgroup together: a chain of dependent instructions with the memory idle.  Every wavefront
+// ranks its share of the experts, and those among the first K are gathered through LDS (six of 64 experts, inside the
+// launch: 2.1 us with rounds of arg-max in every wavefront and lane reads by position, 1.2 us like this).
+struct DecideLds {
+  float weight[MOE_MAX_TOPK];
+  uint8_t slot[MOE_MAX_TOPK], miss[MOE_MAX_TOPK];
+  int rank[kWave], rank_z[kWave];
+};
+template <int NW>
+__device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_slot, float dsum_prev, int t, int lane, int wave,
+                                       DecideLds &lds, uint64_t &slots, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]) {
+#pragma clang fp contract(off)
+  const int N = p.n_experts, K = p.top_k;
+  const bool active = lane < N, own = owns_lane<NW>(lane, wave), resident = my_slot >= 0;
+  const float z = active ? z_in : -INFINITY;
+  const Scores sc = route_scores(p, z, t, dsum_prev, lane);
+  uint64_t key;
+  if (__builtin_expect(p.route_mode == MOE_ROUTE_CACHE_PRIOR, 1)) {
+    const uint32_t k32 = number_key(prior_logit(p, sc, z, resident, lane), active);
+    key = k32 != 0u ? ((uint64_t)k32 << 32) | (uint32_t)(63 - lane) : 0ull;  // ties -> lower index; no number: no place
+  } else {
+    const int r = rank_share<NW>(rank_key(z, lane, active), lane, wave);
+    if (own) lds.rank_z[lane] = r;
+    lds_barrier();
+    key = baseline_key(p, sc, lds.rank_z[lane], resident, lane);
+    if (active) key += 1;  // (the least key of an expert may be 0, which here says that there is none)
   }
+  const int places = min(K, (int)__builtin_popcountll(ballot(key != 0)));
+  const int rank = rank_share<NW>(key, lane, wave);
+  if (own && key != 0 && rank < K) {
+    lds.weight[rank] = sc.w;
+    lds.slot[rank] = (uint8_t)max(my_slot, 0);
+    lds.miss[rank] = (uint8_t)!resident;
+  }
+  if (p.renormalize && own) lds.rank[lane] = key != 0 ? rank : kWave;
+  lds_barrier();
+  float w = lds.weight[lane & (MOE_MAX_TOPK - 1)];
+  const bool filled = lane < places;  // (a place that nothing fills is slot 0 with weight 0, as in the record)
+  const bool miss = filled && lds.miss[lane & (MOE_MAX_TOPK - 1)] != 0;
+  const uint64_t all_slots = *reinterpret_cast<const uint64_t *>(lds.slot);
+  if (p.renormalize) {  // Sec. 2.1
+    const float sum = wave_sum(active && lds.rank[lane] < K ? sc.w : 0.f);
+    w = w / sum;
+  }
+  w = filled ? w : 0.f;
+  miss_mask = (uint32_t)ballot(miss);
+#pragma unroll
+  for (int k = 0; k < MOE_MAX_TOPK; ++k) weight[k] = readlane_f(w, k);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)all_slots);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(all_slots >> 32));
+  slots = (((uint64_t)hi << 32) | lo) & (places >= 8 ? ~0ull : (1ull << (8 * places)) - 1ull);
 }
 
 // Workgroup 0 of an expert launch in which every wavefront routes for itself: does the same step with everything that
