@@ -152,16 +152,19 @@ void moe_cache_destroy(moe_cache_t *ctx);
  * non-NULL; the buffer must stay unchanged until the layer's moe_expert_forward has been called.
  * With out_host non-NULL the call returns once the decision is known on the host (written to *out_host)
  * and the copies filling missed experts' slots are enqueued on copy_stream.  With out_host NULL the call
- * only enqueues the router kernel; the decision is collected, and the fills enqueued, inside
- * moe_expert_forward.  MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
+ * only enqueues the router kernel, and moe_expert_forward takes care of the fills (see there).  MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
 int moe_route_step(moe_cache_t *ctx, int32_t layer, const void *x_dev, const float *logits_dev,
                    moe_route_out_t *out_host);
 
 /* Eq. 1 for the layer's last routing step: y = sum_k w_k E_k(x) + shared(x); x_dev (the vector given to
- * moe_route_step), y_dev device [d] in act_fmt.  The kernels are asynchronous on compute_stream: a first
- * launch covers the shared expert and the experts that were resident, a second one (after the fills) the
- * experts that were missing.  The call returns once the routing decision has reached the host (it is needed
- * to enqueue the fills), not when y is ready.  MOE_ESTATE without a preceding moe_route_step.
+ * moe_route_step), y_dev device [d] in act_fmt.  The kernels are asynchronous on compute_stream.
+ * After a routing step that was waited for, a first launch covers the shared expert and the experts that were
+ * resident, a second one (behind the fills) the experts that were missing.
+ * After one that was not (out_host NULL), one launch covers everything: it reads the experts that miss from the host
+ * blobs itself, computes with them and puts them into their slots on the way; the call returns at once.  That needs all
+ * host blobs in pinned memory that the device can read; where some are not (or with MOE_DEVICE_FILLS=0 in the environment
+ * at moe_cache_init) the call waits for the decision, enqueues the fills on copy_stream and proceeds as above.
+ * A step cannot be captured into a graph (MOE_EHIP).  MOE_ESTATE without a preceding moe_route_step.
  * y_dev may be NULL: the output then stays inside the library as fp32 partial sums and is finished by the next
  * moe_stack_route_step (of any layer), which must follow before another moe_expert_forward. */
 int moe_expert_forward(moe_cache_t *ctx, int32_t layer, const void *x_dev, void *y_dev);

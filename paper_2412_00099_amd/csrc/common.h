@@ -88,8 +88,12 @@ struct GemvParams {
   float *partial;                // [grid][d] fp32
   int32_t hidden, inter, shared_inter, top_k, act_fmt;
   int64_t slot_bytes;
+  // the layer's experts in the host tier as the device sees them [N], or nullptr.  Given: one launch covers everything (pass
+  // 0), the experts that miss are streamed from there and put into their slots on the way.  nullptr: see pass
+  const uint8_t *const *host_blob;
   int32_t pass;        // 0: shared expert + experts that were resident; 1: experts whose slot was just filled
   int32_t row_offset;  // first partial row this launch writes
+  int32_t missing_row; // with host_blob: how many rows further on the sums over the experts that missed are written, if any did
   int32_t route_in;    // RouteIn
   // the split of n records over the launch's G streaming workgroups (launch_expert_gemv fills it in): quotient and remainder
   // of the shared and of the routed records, and ceil(2^32 / G) to divide by G with one multiplication
@@ -163,11 +167,12 @@ hipError_t launch_fused_route(const RouteParams &p, const FusedParams &f, const 
                               moe_route_out_t *out_dev, HostOut host, hipStream_t s);
 hipError_t launch_expert_gemv(const GemvParams &p, int weight_fmt, const GemvPlan &plan, hipStream_t s,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-hipError_t launch_partial_reduce(const float *partial, int n_partial, void *y, int hidden, int act_fmt,
+// n_miss: nullptr, or the number of misses of the step (device): if there are any, n_partial rows more
+hipError_t launch_partial_reduce(const float *partial, int n_partial, const int32_t *n_miss, void *y, int hidden, int act_fmt,
                                  hipStream_t s);
 // the same plus the residual glue: h = (carry ? h + y : 0) + perturb * a in place, ss[b] = sum of h^2 over columns
 // 64b .. 64b+63 (y may be NULL: not stored; n_partial may be 0: y = nothing)
-hipError_t launch_reduce_glue(const float *partial, int n_partial, void *y, int hidden, int act_fmt, float *h,
+hipError_t launch_reduce_glue(const float *partial, int n_partial, const int32_t *n_miss, void *y, int hidden, int act_fmt, float *h,
                               const float *a, float perturb, int carry, float *ss, hipStream_t s);
 hipError_t launch_pack(int fmt, int hidden, int inter, const void *gate, const void *up, const void *down,
                        const void *gs, const void *us, const void *ds, void *blob, hipStream_t s);

@@ -152,6 +152,7 @@ template <int LPR>
 struct RecRegs {
   u32x4 g[LPR], u[LPR], dn[LPR];
   float wt, next_wt;
+  uint8_t *fill, *next_fill;  // where the record goes in a slot that is being filled, else nullptr
   bool want;
 };
 
@@ -214,8 +215,9 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  auto load_up = [&](RecRegs<LPR> &R, bool want) {
+  auto load_up = [&](RecRegs<LPR> &R, bool want) MOE_INLINE {
     R.next_wt = walk.wt;
+    if constexpr (IN != kRouteGiven) R.next_fill = walk.fill != nullptr ? walk.fill + (int64_t)walk.at * kRecBytes : nullptr;
     const RecBuffer q = record_buffer(walk.base + (int64_t)walk.at * kRecBytes, want ? kRecBytes : 0);
 #pragma unroll
     for (int c = 0; c < LPR; ++c) R.g[c] = record_load(q, 0, (c * kWave + lane) * 16);
@@ -223,16 +225,17 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     for (int c = 0; c < LPR; ++c) R.u[c] = record_load(q, kRowBytes, (c * kWave + lane) * 16);
     return q;
   };
-  auto load_down = [&](RecRegs<LPR> &R, RecBuffer q) {
+  auto load_down = [&](RecRegs<LPR> &R, RecBuffer q) MOE_INLINE {
 #pragma unroll
     for (int c = 0; c < LPR; ++c) R.dn[c] = record_load(q, 2 * kRowBytes, (c * kWave + lane) * 16);
     R.wt = R.next_wt;
+    if constexpr (IN != kRouteGiven) R.fill = R.next_fill;
   };
 
   float y[CPL];
 #pragma unroll
   for (int j = 0; j < CPL; ++j) y[j] = 0.f;
-  auto up_part = [&](const RecRegs<LPR> &R) {
+  auto up_part = [&](const RecRegs<LPR> &R) MOE_INLINE {
     float g0 = 0.f, g1 = 0.f, u0 = 0.f, u1 = 0.f;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -243,9 +246,16 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     wave_sum2(g, u);
     return g / (1.f + __expf(-g)) * u * R.wt;
   };
-  auto down_part = [&](const RecRegs<LPR> &R, float h) {
+  auto down_part = [&](const RecRegs<LPR> &R, float h) MOE_INLINE {
 #pragma unroll
     for (int c = 0; c < LPR; ++c) F::axpy(h, R.dn[c], &y[c * VEC]);
+  };
+
+  // a row of a record on its way into a slot
+  auto put = [&](uint8_t *at, const u32x4 (&row)[LPR]) MOE_INLINE {
+    const RecBuffer to = record_buffer(at, kRowBytes);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) record_store(to, (c * kWave + lane) * 16, row[c]);
   };
 
   // A ring of DEPTH records per wavefront.  A place is refilled as its registers become free: the gate and up rows once
@@ -255,23 +265,32 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
   // all its first records were there.  Static launches, us, before / now (both with partial_reduce_kernel): bf16 d = 2048
   // 101 MB 21.6 / 20.8, 138 MB 26.8 / 26.0; bf16 d = 4096 101 MB 35.4 / 21.5 (no spills); fp32 d = 2048 26.9 / 19.9.
   RecRegs<LPR> ring[DEPTH];
-  auto turn = [&](RecRegs<LPR> &R, auto refill_tag) {
-    constexpr bool REFILL = decltype(refill_tag)::value;
+  auto turn = [&](RecRegs<LPR> &R, auto refill_tag, auto fill_tag) MOE_INLINE {
+    constexpr bool REFILL = decltype(refill_tag)::value, FILL = decltype(fill_tag)::value;  // FILL: into a slot on the way
     float h = 0.f;
-    if (R.want) h = up_part(R);
+    if (R.want) {
+      h = up_part(R);
+      if constexpr (FILL) {
+        put(R.fill, R.g);
+        put(R.fill + kRowBytes, R.u);
+      }
+    }
     RecBuffer q;
     bool want = false;
     if constexpr (REFILL) {
       want = walk.step(p);
       q = load_up(R, want);
     }
-    if (R.want) down_part(R, h);
+    if (R.want) {
+      down_part(R, h);
+      if constexpr (FILL) put(R.fill + 2 * kRowBytes, R.dn);
+    }
     if constexpr (REFILL) {
       load_down(R, q);
       R.want = want;
     }
   };
-  auto fetch = [&](RecRegs<LPR> &R, bool any) {
+  auto fetch = [&](RecRegs<LPR> &R, bool any) MOE_INLINE {
     R.want = any && walk.step(p);
     const RecBuffer q = load_up(R, R.want);
     load_down(R, q);
@@ -295,28 +314,65 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     for (int c = 0; c < LPR; ++c) F::make_x(&hraw[c * VEC], scale, p.act_fmt, &xr[c * XW]);
   }
 
-  for (int b = 0; b < blocks_left; ++b) {
+  auto walk_list = [&](int blocks_left, auto fill_tag) MOE_INLINE {
+    for (int b = 0; b < blocks_left; ++b) {
 #pragma unroll
-    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{});
+      for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{}, fill_tag);
+    }
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{}, fill_tag);
+  };
+  walk_list(blocks_left, std::false_type{});
+  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d;
+  if constexpr (IN == kRouteGiven) {
+    reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
+  } else {
+    // experts that missed: a second walk over them, into a second row (one launch does then what a first and a second pass
+    // do, in the same order)
+    __shared__ int missing_s[NW];
+    missing_s[wave] = walk.any_missing(p);
+    reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
+    int missing = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) missing |= missing_s[w];
+    if (missing == 0) return;
+    __syncthreads();
+    walk.start_missing();
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) y[j] = 0.f;
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);
+    walk_list((walk.remaining() + DEPTH - 1) / DEPTH, std::true_type{});
+    reduce_and_store<NW, VEC, LPR>(y, red, row + (int64_t)p.missing_row * d, tid, lane, wave);
   }
-#pragma unroll
-  for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{});
-
-  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
-                                tid, lane, wave);
 }
 
 // y[j] = sum over partial rows in index order, rounded to the activation type.
 // Block: 256 threads = 16 row groups x 16 lanes, each lane 4 columns (64 columns per block).
-__global__ __launch_bounds__(256) void partial_reduce_kernel(const float *partial, int n_partial, void *y, int d,
-                                                             int act_fmt) {
-  __shared__ float4 acc_s[16][16];
-  const int tid = threadIdx.x, cl = tid & 15, rg = tid >> 4;
-  const int col = blockIdx.x * 64 + cl * 4;
+// rows in all: where experts may have missed, the launch that wrote the rows has left a second set if any did (n_miss of its
+// record).  The rows of the usual case are requested before that is known.
+constexpr int kSumRows = 16;  // rows per thread then: one partial row per compute unit of a 256-unit device
+__device__ __forceinline__ float4 sum_rows(const float *partial, int n_partial, const int32_t *n_miss, int d, int rg, int col) {
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int32_t misses = n_miss != nullptr ? *n_miss : 0;
+  if (n_partial == 16 * kSumRows) {
+    float4 t[kSumRows];
+#pragma unroll
+    for (int i = 0; i < kSumRows; ++i) t[i] = *reinterpret_cast<const float4 *>(partial + (int64_t)(rg * kSumRows + i) * d + col);
+    if (misses <= 0) {
+#pragma unroll
+      for (int i = 0; i < kSumRows; ++i) {
+        acc.x += t[i].x;
+        acc.y += t[i].y;
+        acc.z += t[i].z;
+        acc.w += t[i].w;
+      }
+      return acc;
+    }
+  }
+  const int rows = misses > 0 ? 2 * n_partial : n_partial;
   // rows rg*chunk .. (rg+1)*chunk: contiguous chunks keep the overall order a fixed left-to-right tree
-  const int chunk = (n_partial + 15) / 16;
-  const int b0 = rg * chunk, b1 = min(n_partial, b0 + chunk);
+  const int chunk = (rows + 15) / 16, b0 = rg * chunk, b1 = min(rows, b0 + chunk);
 #pragma unroll 8
   for (int b = b0; b < b1; ++b) {
     const float4 t = *reinterpret_cast<const float4 *>(partial + (int64_t)b * d + col);
@@ -325,6 +381,15 @@ __global__ __launch_bounds__(256) void partial_reduce_kernel(const float *partia
     acc.z += t.z;
     acc.w += t.w;
   }
+  return acc;
+}
+
+__global__ __launch_bounds__(256) void partial_reduce_kernel(const float *partial, int n_partial, void *y, int d,
+                                                             int act_fmt, const int32_t *n_miss) {
+  __shared__ float4 acc_s[16][16];
+  const int tid = threadIdx.x, cl = tid & 15, rg = tid >> 4;
+  const int col = blockIdx.x * 64 + cl * 4;
+  const float4 acc = sum_rows(partial, n_partial, n_miss, d, rg, col);
   acc_s[rg][cl] = acc;
   __syncthreads();
   if (rg == 0) {
@@ -354,7 +419,7 @@ __global__ __launch_bounds__(256) void partial_reduce_kernel(const float *partia
 //   ss[block] = sum of h^2 over the block's 64 columns, in a fixed order
 __global__ __launch_bounds__(256) void reduce_glue_kernel(const float *partial, int n_partial, void *y, int d,
                                                           int act_fmt, float *h, const float *a, float perturb,
-                                                          int carry, float *ss) {
+                                                          int carry, float *ss, const int32_t *n_miss) {
   __shared__ float4 acc_s[16][16];
   __shared__ float sq_s[16];
   const int tid = threadIdx.x, cl = tid & 15, rg = tid >> 4;
@@ -363,32 +428,7 @@ __global__ __launch_bounds__(256) void reduce_glue_kernel(const float *partial, 
   // that they are there when the sum is: only the threads of the first row group use them
   const float4 hv = *reinterpret_cast<const float4 *>(h + col);
   const float4 av = *reinterpret_cast<const float4 *>((a != nullptr ? a : h) + col);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  const int chunk = (n_partial + 15) / 16;
-  const int b0 = rg * chunk, b1 = min(n_partial, b0 + chunk);
-  if (chunk == 16 && b1 - b0 == 16) {
-    // the usual case (one partial row per compute unit of a 256-unit device): all sixteen rows requested at once,
-    // added in the same order as below
-    float4 t[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) t[i] = *reinterpret_cast<const float4 *>(partial + (int64_t)(b0 + i) * d + col);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      acc.x += t[i].x;
-      acc.y += t[i].y;
-      acc.z += t[i].z;
-      acc.w += t[i].w;
-    }
-  } else {
-#pragma unroll 8
-    for (int b = b0; b < b1; ++b) {
-      const float4 t = *reinterpret_cast<const float4 *>(partial + (int64_t)b * d + col);
-      acc.x += t.x;
-      acc.y += t.y;
-      acc.z += t.z;
-      acc.w += t.w;
-    }
-  }
+  const float4 acc = sum_rows(partial, n_partial, n_miss, d, rg, col);
   // (keeps the two early loads where they are: without a use here they are moved into the branch below)
   asm volatile("" ::"v"(hv.x), "v"(hv.y), "v"(hv.z), "v"(hv.w), "v"(av.x), "v"(av.y), "v"(av.z), "v"(av.w));
   acc_s[rg][cl] = acc;
@@ -554,19 +594,19 @@ hipError_t launch_expert_gemv(const GemvParams &args, int weight_fmt, const Gemv
   }
 }
 
-hipError_t launch_partial_reduce(const float *partial, int n_partial, void *y, int hidden, int act_fmt,
+hipError_t launch_partial_reduce(const float *partial, int n_partial, const int32_t *n_miss, void *y, int hidden, int act_fmt,
                                  hipStream_t s) {
   if (hidden % 64 != 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(partial_reduce_kernel, dim3(hidden / 64), dim3(256), 0, s, partial, n_partial, y, hidden,
-                     act_fmt);
+                     act_fmt, n_miss);
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_glue(const float *partial, int n_partial, void *y, int hidden, int act_fmt, float *h,
+hipError_t launch_reduce_glue(const float *partial, int n_partial, const int32_t *n_miss, void *y, int hidden, int act_fmt, float *h,
                               const float *a, float perturb, int carry, float *ss, hipStream_t s) {
   if (hidden % 64 != 0 || hidden / 64 > 128) return hipErrorInvalidValue;
   hipLaunchKernelGGL(reduce_glue_kernel, dim3(hidden / 64), dim3(256), 0, s, partial, n_partial, y, hidden, act_fmt, h,
-                     a, perturb, carry, ss);
+                     a, perturb, carry, ss, n_miss);
   return hipGetLastError();
 }
 

@@ -116,7 +116,8 @@ struct RecI8 {
   u32x4 g[LPR], u[LPR], dn[LPR];
   float sg, su, wt, next_wt;
   const uint8_t *base;  // blob of the record's expert (its tail holds the down scales)
-  int rows;
+  uint8_t *fill, *next_fill;  // the slot that is being filled with the expert, else nullptr
+  int rows, at, next_at;
   bool want;
 };
 
@@ -149,14 +150,16 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
 
   // a row's scale, through the scalar data path: its completion is counted apart from the loads of the weights
   // (the word that holds it: scalar loads are of whole words)
-  auto row_scale = [&](const uint16_t *tail, int i) {
+  auto row_scale = [&](const uint16_t *tail, int i) MOE_INLINE {
     typedef const __attribute__((address_space(4))) uint32_t *cword;
     const uintptr_t at = reinterpret_cast<uintptr_t>(tail + i);
     return f16_bits((uint16_t)(*(cword)(at & ~(uintptr_t)3) >> (8 * (at & 2))));
   };
-  auto load_up = [&](RecI8<LPR> &R, bool want) {
+  auto load_up = [&](RecI8<LPR> &R, bool want) MOE_INLINE {
     const uint16_t *tail = reinterpret_cast<const uint16_t *>(walk.base + (int64_t)walk.rows * rec_bytes);
     R.next_wt = walk.wt;
+    R.next_at = walk.at;
+    if constexpr (IN != kRouteGiven) R.next_fill = walk.fill;
     const RecBuffer q = record_buffer(walk.base + (int64_t)walk.at * rec_bytes, want ? (int)rec_bytes : 0);
 #pragma unroll
     for (int c = 0; c < LPR; ++c) R.g[c] = record_load(q, 0, (c * kWave + lane) * 16);
@@ -166,10 +169,12 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     R.su = row_scale(tail, walk.rows + walk.at);  // up scales [rows]
     return q;
   };
-  auto load_down = [&](RecI8<LPR> &R, RecBuffer q) {
+  auto load_down = [&](RecI8<LPR> &R, RecBuffer q) MOE_INLINE {
 #pragma unroll
     for (int c = 0; c < LPR; ++c) R.dn[c] = record_load(q, 2 * kRowBytes, (c * kWave + lane) * 16);
     R.wt = R.next_wt;
+    R.at = R.next_at;
+    if constexpr (IN != kRouteGiven) R.fill = R.next_fill;
     R.base = walk.base;
     R.rows = walk.rows;
   };
@@ -190,7 +195,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
   }
 
   RecI8<LPR> ring[DEPTH];
-  auto fetch = [&](RecI8<LPR> &R, bool any) {
+  auto fetch = [&](RecI8<LPR> &R, bool any) MOE_INLINE {
     R.want = any && walk.step(p);
     const RecBuffer q = load_up(R, R.want);
     load_down(R, q);
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
   int cur_rows = 0;
 
   u32x4 dsc[PRE ? 2 * LPR : 1];
-  auto load_scales = [&](const uint8_t *base, int rows) {
+  auto load_scales = [&](const uint8_t *base, int rows) MOE_INLINE {
     const uint16_t *sd = reinterpret_cast<const uint16_t *>(base + (int64_t)rows * rec_bytes) + 2 * rows;
 #pragma unroll
     for (int c = 0; c < (PRE ? LPR : 0); ++c) {
@@ -245,7 +250,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
   };
 
   // y += scale_col * (acc - 128*hsum) with the per-column scales of the expert whose blob is `base`
-  auto flush = [&](const uint8_t *base, int rows) {
+  auto flush = [&](const uint8_t *base, int rows) MOE_INLINE {
     const uint16_t *sd = reinterpret_cast<const uint16_t *>(base + (int64_t)rows * rec_bytes) + 2 * rows;
     const float off = 128.f * hsum;
 #pragma unroll
@@ -264,7 +269,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     hsum = 0.f;
   };
 
-  auto up_part = [&](const RecI8<LPR> &R) {
+  auto up_part = [&](const RecI8<LPR> &R) MOE_INLINE {
     float g0 = 0.f, g1 = 0.f, u0 = 0.f, u1 = 0.f;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -289,7 +294,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     u *= R.su;
     return g / (1.f + __expf(-g)) * u * R.wt;
   };
-  auto down_part = [&](const RecI8<LPR> &R, float h) {
+  auto down_part = [&](const RecI8<LPR> &R, float h) MOE_INLINE {
     if (R.base != cur_base) {
       if (cur_base) flush(cur_base, cur_rows);
       cur_base = R.base;
@@ -311,32 +316,81 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     }
   };
 
+  // a row of a record on its way into a slot
+  auto put = [&](uint8_t *at, const u32x4 (&row)[LPR]) MOE_INLINE {
+    const RecBuffer to = record_buffer(at, kRowBytes);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) record_store(to, (c * kWave + lane) * 16, row[c]);
+  };
   // A ring of DEPTH records, refilled in two parts (see expert_gemv_kernel).  37 MB at d = 2048: 13.1 -> 12.1 us
-  auto turn = [&](RecI8<LPR> &R, auto refill_tag) {
-    constexpr bool REFILL = decltype(refill_tag)::value;
+  auto turn = [&](RecI8<LPR> &R, auto refill_tag, auto fill_tag) MOE_INLINE {
+    constexpr bool REFILL = decltype(refill_tag)::value, FILL = decltype(fill_tag)::value;  // FILL: into a slot on the way
     float h = 0.f;
-    if (R.want) h = up_part(R);
+    if (R.want) {
+      h = up_part(R);
+      if constexpr (FILL) {
+        uint8_t *to = R.fill + (int64_t)R.at * rec_bytes;
+        put(to, R.g);
+        put(to + kRowBytes, R.u);
+      }
+    }
     RecBuffer q;
     bool want = false;
     if constexpr (REFILL) {
       want = walk.step(p);
       q = load_up(R, want);
     }
-    if (R.want) down_part(R, h);
+    if (R.want) {
+      down_part(R, h);
+      if constexpr (FILL) {
+        put(R.fill + (int64_t)R.at * rec_bytes + 2 * kRowBytes, R.dn);
+        const int64_t tail = (int64_t)R.rows * rec_bytes;
+        // the record's share of what stands behind the records: the row scales of four records by every fourth one, and
+        // the down scales in pieces of 16 bytes by record 0, 1, ..., 0, 1, ...
+        const int bytes = 4 * R.rows + CPL * kWave * 2;
+        copy_tail16(R.base + tail, R.fill + tail, bytes, lane == 0 && R.at % 4 == 0 ? (uint32_t)R.at * 4u : ~0u);
+        const int piece = R.at + lane * R.rows;
+        copy_tail16(R.base + tail, R.fill + tail, bytes, piece < CPL * kWave / 8 ? (uint32_t)(4 * R.rows + piece * 16) : ~0u);
+      }
+    }
     if constexpr (REFILL) {
       load_down(R, q);
       R.want = want;
     }
   };
-  for (int b = 0; b < blocks_left; ++b) {
+  auto walk_list = [&](int blocks_left, auto fill_tag) MOE_INLINE {
+    for (int b = 0; b < blocks_left; ++b) {
 #pragma unroll
-    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{});
+      for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{}, fill_tag);
+    }
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{}, fill_tag);
+    if (cur_base) flush(cur_base, cur_rows);
+    cur_base = nullptr;
+  };
+  walk_list(blocks_left, std::false_type{});
+  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d;
+  if constexpr (IN == kRouteGiven) {
+    reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
+  } else {
+    // experts that missed: a second walk over them, into a second row (one launch does then what a first and a second pass
+    // do, in the same order)
+    __shared__ int missing_s[NW];
+    missing_s[wave] = walk.any_missing(p);
+    reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
+    int missing = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) missing |= missing_s[w];
+    if (missing == 0) return;
+    __syncthreads();
+    walk.start_missing();
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) y[j] = acc[j] = 0.f;
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);
+    walk_list((walk.remaining() + DEPTH - 1) / DEPTH, std::true_type{});
+    reduce_and_store<NW, VEC, LPR>(y, red, row + (int64_t)p.missing_row * d, tid, lane, wave);
   }
-#pragma unroll
-  for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{});
-  if (cur_base) flush(cur_base, cur_rows);
-  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
-                                tid, lane, wave);
 }
 
 // =================================================================================================
@@ -363,7 +417,8 @@ struct RecI4 {
   uint32_t sc[LPR];  // (gate scale, up scale) fp16 pair of this lane's group, per chunk
   float wt, next_wt;
   const uint8_t *base;  // blob of the record's expert (its tail holds the down scales)
-  int rows, grp;
+  uint8_t *fill, *next_fill;  // the slot that is being filled with the expert, else nullptr
+  int rows, at, next_at;
   bool want;
 };
 
@@ -392,8 +447,10 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   RecordWalker<NW, IN, 1> walk;  // a contiguous block of records per wavefront: few changes of scale group
   walk.init(p, wave);
 
-  auto load_up = [&](RecI4<LPR> &R, bool want) {
+  auto load_up = [&](RecI4<LPR> &R, bool want) MOE_INLINE {
     R.next_wt = walk.wt;
+    R.next_at = walk.at;
+    if constexpr (IN != kRouteGiven) R.next_fill = walk.fill;
     const RecBuffer q = record_buffer(walk.base + (int64_t)walk.at * rec_bytes, want ? (int)rec_bytes : 0);
 #pragma unroll
     for (int c = 0; c < LPR; ++c)  // 4 lanes (128 columns) per group
@@ -404,13 +461,14 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     for (int c = 0; c < LPR; ++c) R.u[c] = record_load(q, kRowBytes, (c * kWave + lane) * 16);
     return q;
   };
-  auto load_down = [&](RecI4<LPR> &R, RecBuffer q) {
+  auto load_down = [&](RecI4<LPR> &R, RecBuffer q) MOE_INLINE {
 #pragma unroll
     for (int c = 0; c < LPR; ++c) R.dn[c] = record_load(q, 2 * kRowBytes, (c * kWave + lane) * 16);
     R.wt = R.next_wt;
+    R.at = R.next_at;
+    if constexpr (IN != kRouteGiven) R.fill = R.next_fill;
     R.base = walk.base;
     R.rows = walk.rows;
-    R.grp = walk.at >> 7;
   };
 
   XRaw<VEC> xraw[FUSED ? 1 : LPR];  // fetched ahead of the weights, converted after the ring has been filled
@@ -427,7 +485,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   }
 
   RecI4<LPR> ring[DEPTH];
-  auto fetch = [&](RecI4<LPR> &R, bool any) {
+  auto fetch = [&](RecI4<LPR> &R, bool any) MOE_INLINE {
     R.want = any && walk.step(p);
     const RecBuffer q = load_up(R, R.want);
     load_down(R, q);
@@ -446,7 +504,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   const uint8_t *cur_base = nullptr;
   int cur_rows = 0, cur_grp = -1;
   u32x4 dsc[PRE ? 4 * LPR : 1];
-  auto load_scales = [&](const uint8_t *base, int rows, int grp) {
+  auto load_scales = [&](const uint8_t *base, int rows, int grp) MOE_INLINE {
     const uint16_t *sd = reinterpret_cast<const uint16_t *>(base + (int64_t)rows * rec_bytes) + (int64_t)grp * d;
 #pragma unroll
     for (int c = 0; c < (PRE ? LPR : 0); ++c) {
@@ -495,7 +553,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
 
   // even columns: y += s * (acc - (1024 + 8) * hsum);  odd columns (weights taken 16-fold):
   // y += (s / 16) * (acc - (1024 + 128) * hsum)
-  auto flush = [&](const uint8_t *base, int rows, int grp) {
+  auto flush = [&](const uint8_t *base, int rows, int grp) MOE_INLINE {
     const uint16_t *sd = reinterpret_cast<const uint16_t *>(base + (int64_t)rows * rec_bytes) + (int64_t)grp * d;
     const float off_even = (1024.f + 8.f) * hsum, off_odd = (1024.f + 128.f) * hsum;
 #pragma unroll
@@ -518,7 +576,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     dirty = false;
   };
 
-  auto up_part = [&](const RecI4<LPR> &R) {
+  auto up_part = [&](const RecI4<LPR> &R) MOE_INLINE {
     float g = 0.f, u = 0.f;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -544,12 +602,12 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     wave_sum2(g, u);
     return g / (1.f + __expf(-g)) * u * R.wt;
   };
-  auto down_part = [&](const RecI4<LPR> &R, float h) {
-    if (R.base != cur_base || R.grp != cur_grp) {
+  auto down_part = [&](const RecI4<LPR> &R, float h) MOE_INLINE {
+    if (R.base != cur_base || (R.at >> 7) != cur_grp) {
       if (dirty) flush(cur_base, cur_rows, cur_grp);
       cur_base = R.base;
       cur_rows = R.rows;
-      cur_grp = R.grp;
+      cur_grp = (R.at >> 7);
       load_scales(cur_base, cur_rows, cur_grp);
     }
     hsum += h;
@@ -573,34 +631,84 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     }
   };
 
+  // a row of a record on its way into a slot
+  auto put = [&](uint8_t *at, const u32x4 (&row)[LPR]) MOE_INLINE {
+    const RecBuffer to = record_buffer(at, kRowBytes);
+#pragma unroll
+    for (int c = 0; c < LPR; ++c) record_store(to, (c * kWave + lane) * 16, row[c]);
+  };
   // A ring of DEPTH records, refilled in two parts (see expert_gemv_kernel).  37 MB at d = 2048, a quarter of it shared, in a
   // static launch: 16.3 -> 12.7 us; inside the launch (clocks of its wavefronts) the first record is multiplied at 2.0 us
   // instead of 6.9, and the last wavefront has stored its row at 8.9 instead of 13.2.
-  auto turn = [&](RecI4<LPR> &R, auto refill_tag) {
-    constexpr bool REFILL = decltype(refill_tag)::value;
+  auto turn = [&](RecI4<LPR> &R, auto refill_tag, auto fill_tag) MOE_INLINE {
+    constexpr bool REFILL = decltype(refill_tag)::value, FILL = decltype(fill_tag)::value;  // FILL: into a slot on the way
     float h = 0.f;
-    if (R.want) h = up_part(R);
+    if (R.want) {
+      h = up_part(R);
+      if constexpr (FILL) {
+        uint8_t *to = R.fill + (int64_t)R.at * rec_bytes;
+        put(to, R.g);
+        put(to + kRowBytes, R.u);
+#pragma unroll
+        for (int c = 0; c < LPR; ++c)
+          __builtin_amdgcn_raw_buffer_store_b32(R.sc[c], record_buffer(to + 3 * kRowBytes, (int)rec_bytes - 3 * kRowBytes),
+                                                (c * kWave + lane) / 4 * 4, 0, 0);
+      }
+    }
     RecBuffer q;
     bool want = false;
     if constexpr (REFILL) {
       want = walk.step(p);
       q = load_up(R, want);
     }
-    if (R.want) down_part(R, h);
+    if (R.want) {
+      down_part(R, h);
+      if constexpr (FILL) {
+        put(R.fill + (int64_t)R.at * rec_bytes + 2 * kRowBytes, R.dn);
+        const int64_t tail = (int64_t)R.rows * rec_bytes;
+        // the record's share of what stands behind the records: d / 1024 times 16 bytes of down scales
+        const uint32_t off = lane < CPL * kWave / 1024 ? (uint32_t)(R.at * (CPL * kWave / 1024) + lane) * 16u : ~0u;
+        copy_tail16(R.base + tail, R.fill + tail, R.rows / 128 * (CPL * kWave * 2), off);
+      }
+    }
     if constexpr (REFILL) {
       load_down(R, q);
       R.want = want;
     }
   };
-  for (int b = 0; b < blocks_left; ++b) {
+  auto walk_list = [&](int blocks_left, auto fill_tag) MOE_INLINE {
+    for (int b = 0; b < blocks_left; ++b) {
 #pragma unroll
-    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{});
+      for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::true_type{}, fill_tag);
+    }
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{}, fill_tag);
+    if (dirty) flush(cur_base, cur_rows, cur_grp);
+    cur_base = nullptr;
+  };
+  walk_list(blocks_left, std::false_type{});
+  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d;
+  if constexpr (IN == kRouteGiven) {
+    reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
+  } else {
+    // experts that missed: a second walk over them, into a second row (one launch does then what a first and a second pass
+    // do, in the same order)
+    __shared__ int missing_s[NW];
+    missing_s[wave] = walk.any_missing(p);
+    reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
+    int missing = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) missing |= missing_s[w];
+    if (missing == 0) return;
+    __syncthreads();
+    walk.start_missing();
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) y[j] = acc[j] = 0.f;
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);
+    walk_list((walk.remaining() + DEPTH - 1) / DEPTH, std::true_type{});
+    reduce_and_store<NW, VEC, LPR>(y, red, row + (int64_t)p.missing_row * d, tid, lane, wave);
   }
-#pragma unroll
-  for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{});
-  if (dirty) flush(cur_base, cur_rows, cur_grp);
-  reduce_and_store<NW, VEC, LPR>(y, red, p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d,
-                                tid, lane, wave);
 }
 
 }  // namespace

@@ -84,7 +84,7 @@ hipError_t launch_expert_forward_static(int weight_fmt, int act_fmt, int hidden,
   }
   e = launch_expert_gemv(p, weight_fmt, plan, s);
   if (e != hipSuccess) return e;
-  return launch_partial_reduce(partial, plan.grid, y, hidden, act_fmt, s);
+  return launch_partial_reduce(partial, plan.grid, nullptr, y, hidden, act_fmt, s);
 }
 
 int static_max_hidden() { return kStaticMaxHidden; }

@@ -7,6 +7,9 @@ namespace moe {
 
 constexpr int kRedFloats = 16384;  // LDS floats (64 KB) shared by the wavefronts' rows in the final reduction
 
+// for lambdas that are called in several places: as calls they would keep their captures in memory
+#define MOE_INLINE __attribute__((always_inline))
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -25,6 +28,12 @@ __device__ __forceinline__ RecBuffer record_buffer(const uint8_t *base, int byte
 // every lane, off: this lane's offset
 __device__ __forceinline__ u32x4 record_load(RecBuffer r, uint32_t at, uint32_t off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, off, at, 2);
+}
+
+// (no scalar offset: behind a 16-byte store that has one the compiler lets the next vector instruction write the registers
+// that hold the data, and the last lanes then store what that instruction wrote - seen in one record of 500)
+__device__ __forceinline__ void record_store(RecBuffer r, uint32_t off, u32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
 }
 
 __device__ __forceinline__ float dot2_bf16(uint32_t w, uint32_t x, float acc) {
@@ -90,7 +99,7 @@ namespace rt {
 struct DecideLds;
 template <int NW>
 __device__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane, int wave, DecideLds &lds,
-                       uint64_t &slots, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]);
+                       uint64_t &slots, uint64_t &experts, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]);
 }
 template <int NW, int IN = kRouteBefore, int STEP = NW>
 struct RecordWalker {
@@ -106,13 +115,19 @@ struct RecordWalker {
   // the routing record: loaded at kernel start, unpacked when the first routed run comes up
   u32x4 rw0, rw1, rd;  // sel_weight[0..3], sel_weight[4..7], {tag, slots lo, slots hi, miss mask}
   uint64_t slots;
+  uint64_t experts;    // 8 bits each, like slots (kRouteBoundary, kRouteEverywhere)
   uint32_t miss_mask;
+  bool no_decision;    // the hand-over did not come
+  int r0, n_rt0;       // r and n_rt at the start
+  bool missing_only;   // the walk covers the experts that missed, not the others
+  uint8_t *fill_blob;  // the current run's expert comes from the host tier: the slot it is put into, else nullptr
   float z, dsum;       // kRouteEverywhere: lane's logit, Eq. 10's sum so far
   int my_slot, count;  // lane's expert's slot, tokens so far
   // the record found by step()
   const uint8_t *base;  // blob of the record's expert
   int rows, at;
   float wt;
+  uint8_t *fill;        // nullptr, or the slot that the record (with its part of the tail) has to be put into
 
   // start of part b of n = q G + r records split into G parts: floor(b n / G).  b r < 2^20 (the host limits G to 2^10), so
   // that the product with ceil(2^32 / G) has the exact quotient in its upper half
@@ -164,6 +179,10 @@ struct RecordWalker {
         rw1.y = (uint32_t)(q[5] >> 16);
         rw1.z = (uint32_t)q[6];
         rw1.w = (uint32_t)(q[6] >> 32) | ((uint32_t)q[7] << 16);
+        experts = 0;
+        const uint64_t e48 = ((q[1] >> 24) & 0xffffffu) | (((q[7] >> 16) & 0xffffffu) << 24);
+#pragma unroll
+        for (int k = 0; k < MOE_MAX_TOPK; ++k) experts |= ((e48 >> (6 * k)) & 63u) << (8 * k);
         return true;
       }
       __builtin_amdgcn_s_sleep(2);
@@ -212,6 +231,11 @@ struct RecordWalker {
     run_wanted = true;
     run_shared = false;
     decided = false;
+    no_decision = false;
+    fill_blob = fill = nullptr;
+    r0 = r;
+    n_rt0 = n_rt;
+    missing_only = p.pass == 1;
     if constexpr (IN == kRouteGiven) {
       const float *w = p.given_weight;
       slots = p.given_slots;
@@ -230,7 +254,7 @@ struct RecordWalker {
     asm volatile("" ::"s"(dsum), "s"(count), "s"(q.lambda), "s"(q.delta_fixed), "s"(q.cumsum_p), "s"(q.n_experts), "s"(q.top_k),
                  "s"(q.top_j), "s"(q.renormalize), "s"(q.delta_mode), "s"(q.route_mode), "s"(q.max_rank));
     float w[MOE_MAX_TOPK];
-    rt::decide<NW>(p.b.route, z, my_slot, dsum, count, (int)(threadIdx.x & 63), wave, lds, slots, miss_mask, w);
+    rt::decide<NW>(p.b.route, z, my_slot, dsum, count, (int)(threadIdx.x & 63), wave, lds, slots, experts, miss_mask, w);
     rw0 = u32x4{__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
     rw1 = u32x4{__float_as_uint(w[4]), __float_as_uint(w[5]), __float_as_uint(w[6]), __float_as_uint(w[7])};
     decided = true;
@@ -256,6 +280,42 @@ struct RecordWalker {
   // its next entry is a shared record, which needs no decision
   __device__ __forceinline__ bool shared_next() const { return n_sh > 0 || (left > 0 && run_shared); }
 
+  // the routing record is unpacked when the first routed run comes up
+  __device__ __forceinline__ void ensure_decided(const GemvParams &p) {
+    if (decided) return;
+    bool ok = true;
+    if constexpr (IN == kRouteBoundary) {
+      // (one wavefront per workgroup fetching for all eight through LDS was measured: no faster)
+      ok = load_handover(p.b.handover + 8 * ((int)blockIdx.x % 8), p.b.hand_tag, p.b.spin_limit);
+    }
+    if constexpr (IN != kRouteEverywhere && IN != kRouteGiven) {
+      slots = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.y) |
+              ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.z) << 32);
+      miss_mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)rd.w);
+    }
+    if (!ok) {  // no record: use nothing
+      slots = 0;
+      miss_mask = 0;
+      no_decision = true;
+      *p.b.gave_up = 1u;
+    }
+    decided = true;
+  }
+
+  // One launch for everything (p.host_blob): whether a second walk is needed, over the experts that missed, and its start.
+  // The first walk has gone over the others as a first pass does, and the second one adds what a second pass would.
+  __device__ __forceinline__ bool any_missing(const GemvParams &p) {
+    if (IN == kRouteGiven || p.host_blob == nullptr) return false;
+    ensure_decided(p);
+    return miss_mask != 0;
+  }
+  __device__ __forceinline__ void start_missing() {
+    r = r0;
+    n_rt = n_rt0;
+    n_sh = left = 0;
+    missing_only = true;
+  }
+
   // the wavefront's next run (there must be one): its shared records first, then its routed entries expert by expert
   __device__ __forceinline__ void start_run(const GemvParams &p) {
     if (n_sh > 0) {
@@ -268,26 +328,10 @@ struct RecordWalker {
       n_sh = 0;
       wt = 1.f;
       run_wanted = true;
+      fill_blob = nullptr;
       return;
     }
-    if (!decided) {  // first routed run: unpack the routing record
-      bool ok = true;
-      if constexpr (IN == kRouteBoundary) {
-        // (one wavefront per workgroup fetching for all eight through LDS was measured: no faster)
-        ok = load_handover(p.b.handover + 8 * ((int)blockIdx.x % 8), p.b.hand_tag, p.b.spin_limit);
-      }
-      if constexpr (IN != kRouteEverywhere && IN != kRouteGiven) {
-        slots = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.y) |
-                ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.z) << 32);
-        miss_mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)rd.w);
-      }
-      if (!ok) {  // no record: read slot 0 and use nothing of it
-        slots = 0;
-        miss_mask = p.pass == 1 ? 0u : ~0u;
-        *p.b.gave_up = 1u;
-      }
-      decided = true;
-    }
+    ensure_decided(p);
     const int I = p.inter;
     int seg = 0;  // r / I, of at most MOE_MAX_TOPK values
 #pragma unroll
@@ -303,7 +347,38 @@ struct RecordWalker {
     rows = I;
     next_at = row;
     wt = pick_weight(seg);
-    run_wanted = (((miss_mask >> seg) & 1u) != 0) == (p.pass == 1);
+    const bool missing = ((miss_mask >> seg) & 1u) != 0;
+    run_wanted = missing == missing_only && !no_decision;
+    fill_blob = nullptr;
+    if (IN != kRouteGiven && run_wanted && missing && p.host_blob != nullptr) from_host_tier(p, seg);
+  }
+
+  // The run's expert was not resident: it is read from the host tier and put into its slot on the way (a rare case, kept out
+  // of line of the others).  Which slot that is is the routing workgroup's to say where every workgroup routes.
+  __device__ __forceinline__ void from_host_tier(const GemvParams &p, int seg) {
+    typedef const __attribute__((address_space(4))) int32_t *cint;
+    typedef const __attribute__((address_space(4))) uint64_t *caddr;
+    uint32_t slot = (uint32_t)(slots >> (8 * seg)) & 0xffu, expert;
+    if constexpr (IN == kRouteBefore) {
+      expert = (uint32_t)((cint)(reinterpret_cast<uintptr_t>(p.route)))[seg];
+      static_assert(offsetof(moe_route_out_t, sel_expert) == 0, "record layout");
+    } else {
+      expert = (uint32_t)(experts >> (8 * seg)) & 0xffu;
+      if constexpr (IN == kRouteEverywhere) {
+        if (!load_handover(p.b.handover + 8 * ((int)blockIdx.x % 8), p.b.hand_tag, p.b.spin_limit)) {
+          no_decision = true;
+          run_wanted = false;
+          *p.b.gave_up = 1u;
+          return;
+        }
+        const uint64_t placed = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.y) |
+                                ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.z) << 32);
+        slot = (uint32_t)(placed >> (8 * seg)) & 0xffu;
+      }
+    }
+    base = reinterpret_cast<const uint8_t *>(((caddr)(reinterpret_cast<uintptr_t>(p.host_blob)))[expert]);
+    fill_blob = const_cast<uint8_t *>(p.slot_pool) + (int64_t)slot * p.slot_bytes;
+    run_wanted = true;
   }
 
   // Move to this wavefront's next list entry and describe its record; whether there is one and the pass covers it.  The
@@ -313,15 +388,25 @@ struct RecordWalker {
   // records had arrived.)
   __device__ __forceinline__ bool step(const GemvParams &p) {
     if (left == 0) {
-      if (n_sh + n_rt == 0) return false;
+      if (n_sh + n_rt == 0) {
+        fill = nullptr;
+        return false;
+      }
       start_run(p);
     }
+    fill = fill_blob;
     at = next_at;
     next_at += run_step;
     --left;
     return run_wanted;
   }
 };
+
+// The 16 bytes at each lane's offset from one blob's tail to another's (offsets past the end: nothing is read or written)
+__device__ __forceinline__ void copy_tail16(const uint8_t *from, uint8_t *to, int bytes, uint32_t off) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_amdgcn_raw_buffer_load_b128(record_buffer(from, bytes), off, 0, 0),
+                                         record_buffer(to, bytes), off, 0, 0);
+}
 
 // Sum the wavefronts' private outputs through LDS (one barrier per pass) and write the workgroup's fp32
 // partial row.  y holds, for load index c and v < VEC, column (c*64 + lane)*VEC + v at y[c*VEC + v].

@@ -93,6 +93,7 @@ struct moe_cache {
   int32_t *d_initial = nullptr;
   float *d_partial = nullptr;
   int pending_rows = 0;            // partial rows of an expert output not reduced yet (y_dev was NULL)
+  const int32_t *pending_miss = nullptr;  // see launch_partial_reduce
   void *d_y = nullptr;             // [d] act_fmt: a pending expert output once summed, when the caller gave no y_dev
   GemvPlan plan{};
   hipEvent_t ev_route = nullptr;
@@ -105,7 +106,10 @@ struct moe_cache {
   int deferred = -1;                  // the layer in state 3: its launch forms x from the caller's h and d_ss
   std::vector<uint32_t> route_seq;    // per layer: completion tag of the pending route step
   std::vector<uint32_t> hand_count;   // per layer: hand-overs inside an expert launch so far
-  std::vector<int64_t> bytes_filled;
+  std::vector<int64_t> bytes_filled;  // per layer: what had been filled when the misses stood at miss_base
+  std::vector<int64_t> miss_base;
+  const uint8_t **d_host_blob = nullptr;  // [n_layers][N] the host tier as the device sees it, or nullptr: some of it is not
+                                          // mapped there, and every fill is a copy that the host enqueues
   uint32_t seq = 0;
   bool poll = false;
 
@@ -180,6 +184,7 @@ int do_reset(moe_cache_t *c) {
     }
     c->routed[l] = 0;
     c->bytes_filled[l] = 0;
+    c->miss_base[l] = 0;
   }
   HIP_TRY(hipStreamSynchronize(c->compute));
   return MOE_OK;
@@ -286,6 +291,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   c->boundary.assign(L, BoundaryArgs{});
   c->x_given.assign(L, nullptr);
   c->bytes_filled.assign(L, 0);
+  c->miss_base.assign(L, 0);
   c->ev_copy.assign(L, nullptr);
 
   auto bail = [&](int code) {
@@ -375,6 +381,25 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
     c->route_everywhere = c->everywhere_cumsum = atoi(s) != 0 && gate_rows_supported(cfg->hidden, cfg->act_fmt);
   if (const char *s = getenv("MOE_POISON_FILLS")) c->poison_fills = atoi(s) != 0;
   if (const char *s = getenv("MOE_TAG_SPINS")) if (atoi(s) > 0) c->tag_spins = atoi(s);
+  // The host tier as the device sees it, for launches that bring in the experts that miss: only if all of it is pinned
+  // memory (MOE_DEVICE_FILLS=0: the host enqueues every fill)
+  bool mapped = !c->poison_fills;
+  if (const char *s = getenv("MOE_DEVICE_FILLS")) mapped = mapped && atoi(s) != 0;
+  std::vector<const uint8_t *> dev_blob((size_t)L * N);
+  for (size_t i = 0; mapped && i < dev_blob.size(); ++i) {
+    void *first = nullptr, *last = nullptr;
+    uint8_t *host = static_cast<uint8_t *>(const_cast<void *>(c->host_blob[i]));
+    const size_t end = (size_t)c->slot_layout.total - 1;
+    mapped = hipHostGetDevicePointer(&first, host, 0) == hipSuccess && hipHostGetDevicePointer(&last, host + end, 0) == hipSuccess &&
+             static_cast<uint8_t *>(last) == static_cast<uint8_t *>(first) + end && reinterpret_cast<uintptr_t>(first) % 16 == 0;
+    dev_blob[i] = static_cast<const uint8_t *>(first);
+  }
+  if (mapped) {
+    HIP_INIT(hipMalloc(&c->d_host_blob, sizeof(void *) * dev_blob.size()));
+    HIP_INIT(hipMemcpy(c->d_host_blob, dev_blob.data(), sizeof(void *) * dev_blob.size(), hipMemcpyHostToDevice));
+  } else {
+    (void)hipGetLastError();  // (memory that is not pinned is no error)
+  }
   HIP_INIT(hipMalloc(&c->d_initial, sizeof(int32_t) * (size_t)L * (b->n_initial > 0 ? b->n_initial : 1)));
   HIP_INIT(hipMalloc(&c->d_partial, sizeof(float) * 2 * (size_t)c->plan.grid * cfg->hidden));
   HIP_INIT(hipMalloc(&c->d_y, sizeof(float) * (size_t)cfg->hidden));
@@ -419,6 +444,7 @@ void moe_cache_destroy(moe_cache_t *c) {
   if (c->d_ss) (void)hipFree(c->d_ss);
   if (c->h_gave_up) (void)hipHostFree(c->h_gave_up);
   if (c->d_initial) (void)hipFree(c->d_initial);
+  if (c->d_host_blob) (void)hipFree(c->d_host_blob);
   if (c->d_partial) (void)hipFree(c->d_partial);
   if (c->d_y) (void)hipFree(c->d_y);
   if (c->d_logits_batch) (void)hipFree(c->d_logits_batch);
@@ -438,9 +464,8 @@ void moe_cache_destroy(moe_cache_t *c) {
   delete c;
 }
 
-// Wait until the routing decision of `layer` (tag `seq`) is visible on the host, decode it, then enqueue the fills
-// of the missed experts on the copy stream.  Returns the number of misses through *n_miss.
-static int collect_route(moe_cache_t *c, int32_t layer, uint32_t seq, int *n_miss) {
+// Wait until the routing decision of `layer` (tag `seq`) is visible on the host and decode it into decided[layer].
+static int read_note(moe_cache_t *c, int32_t layer, uint32_t seq) {
   const moe_cache_config_t &g = c->cfg;
   const HostNote *h = c->h_note + layer;
   const uint64_t tag = seq & 0xffffu;
@@ -461,6 +486,14 @@ static int collect_route(moe_cache_t *c, int32_t layer, uint32_t seq, int *n_mis
     d.expert[k] = (uint8_t)((w1 >> (16 + 6 * k)) & 63);
     d.slot[k] = (uint8_t)((w2 >> (16 + 6 * k)) & 63);
   }
+  return MOE_OK;
+}
+
+// The same, then the fills of the missed experts are enqueued on the copy stream.  Returns the number of misses.
+static int collect_route(moe_cache_t *c, int32_t layer, uint32_t seq, int *n_miss) {
+  if (int rc = read_note(c, layer, seq)) return rc;
+  const moe_cache_config_t &g = c->cfg;
+  const moe_cache::Decision &d = c->decided[layer];
   const size_t slot_bytes = (size_t)c->slot_layout.total;
   if (d.n_miss > 0) {
     for (int k = 0; k < g.top_k; ++k) {
@@ -475,7 +508,6 @@ static int collect_route(moe_cache_t *c, int32_t layer, uint32_t seq, int *n_mis
       HIP_TRY(hipMemcpyAsync(static_cast<uint8_t *>(c->slot_pool[layer]) + (size_t)s * slot_bytes,
                              c->host_blob[(size_t)layer * g.n_experts + e], slot_bytes, hipMemcpyHostToDevice,
                              c->copy));
-      c->bytes_filled[layer] += (int64_t)slot_bytes;
     }
     HIP_TRY(hipEventRecord(c->ev_copy[layer], c->copy));
   }
@@ -600,7 +632,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   if (form == MOE_BOUNDARY_IN_FIRST_WORKGROUP) {
     // nobody waits for the decision here: the sum of the pending output and the residual glue are one launch, and
     // the rest of the boundary (x, gate GEMV, routing) runs in workgroup 0 of the layer's expert launch
-    HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
+    HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, c->pending_miss, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
                                carry, c->d_ss, c->compute));
     c->pending_rows = 0;
     f.ss = c->d_ss;
@@ -627,7 +659,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   if (form == MOE_BOUNDARY_ROUTED_EVERYWHERE) {
     // nobody waits for the decision here: only x and the logits are made by this call (over several compute units), and
     // every wavefront of the layer's expert launch routes for itself
-    HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
+    HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, c->pending_miss, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
                                carry, c->d_ss, c->compute));
     c->pending_rows = 0;
     f.ss = c->d_ss;
@@ -642,6 +674,10 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
     b.logits = logits;
     b.out_dev = c->d_route + layer;
     b.note = c->h_note_dev + layer;
+    b.handover = c->d_handover + 64 * (size_t)layer;  // (read where an expert misses: the slot it is put into)
+    b.hand_tag = ++c->hand_count[layer] & 0xffffu;
+    b.gave_up = c->h_gave_up_dev;
+    b.spin_limit = c->tag_spins;
     c->route_seq[layer] = p.seq;
     c->routed[layer] = 4;
     return MOE_OK;
@@ -649,13 +685,13 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   if (fused_route_pre_supported(c->cfg.hidden)) {
     // the sum of the pending output and the residual glue spread over d / 64 workgroups; the single-workgroup
     // boundary launch then starts from h and the sums of squares
-    HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
+    HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, c->pending_miss, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
                                carry, c->d_ss, c->compute));
     f.ss = c->d_ss;
     f.n_ss = c->cfg.hidden / 64;
   } else {
     if (c->pending_rows > 0)
-      HIP_TRY(launch_partial_reduce(c->d_partial, c->pending_rows, y, c->cfg.hidden, c->cfg.act_fmt, c->compute));
+      HIP_TRY(launch_partial_reduce(c->d_partial, c->pending_rows, c->pending_miss, y, c->cfg.hidden, c->cfg.act_fmt, c->compute));
     f.y = y;
     f.a = a_dev;
     f.perturb = perturb;
@@ -687,8 +723,20 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   p.top_k = g.top_k;
   p.act_fmt = g.act_fmt;
   p.slot_bytes = c->slot_layout.total;
-  // pass 0: the shared expert and the experts that were resident; it reads slots, weights and miss flags from
-  // the device record, so it is launched before the host knows the decision
+  // A step that nobody waited for: the launch itself brings in what misses, and the host, which need not know the decision,
+  // is free to go on (with a wait in each layer it was what bounded a stack of small layers: 36 MB of int4 a layer-token 20.6 us
+  // a layer, 12.9 without; 101 MB of bf16 26.4 / 20.9).  Otherwise, and where the host tier is not mapped on the device, a
+  // first pass covers the shared expert and the experts that were resident, the host enqueues the fills, and a second pass
+  // covers the experts filled.
+  const bool on_device = c->d_host_blob != nullptr && c->routed[layer] >= 2;
+  if (on_device) {
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(c->compute, &capturing));
+    if (capturing != hipStreamCaptureStatusNone)  // (a replay would repeat this step's tags and state)
+      return fail(MOE_EHIP, "layer %d: a routed step cannot be captured into a graph", layer);
+    p.host_blob = c->d_host_blob + (size_t)layer * g.n_experts;
+    p.missing_row = c->plan.grid;
+  }
   p.pass = 0;
   p.row_offset = 0;
   if (c->routed[layer] == 3) {
@@ -711,10 +759,16 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   if (p.route_in == kRouteEverywhere) c->cur[layer] ^= 1;  // the launch writes the other copy of the state
   p.route_in = kRouteBefore;
   int n_miss = c->decided[layer].n_miss;
-  if (c->routed[layer] >= 2) {
+  if (on_device) {
+    n_miss = 0;
+    if (prof) {
+      if (int rc = read_note(c, layer, c->route_seq[layer])) return rc;
+      c->prof_full[c->prof_used++] = c->decided[layer].n_miss == 0;
+    }
+  } else if (c->routed[layer] >= 2) {
     if (int rc = collect_route(c, layer, c->route_seq[layer], &n_miss)) return rc;
   }
-  if (prof) c->prof_full[c->prof_used++] = n_miss == 0;
+  if (prof && !on_device) c->prof_full[c->prof_used++] = n_miss == 0;
   int rows = c->plan.grid;
   if (n_miss > 0) {
     // pass 1: the experts whose slots are being filled, once the fills have landed
@@ -724,10 +778,13 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
     HIP_TRY(launch_expert_gemv(p, g.weight_fmt, c->plan, c->compute));
     rows = 2 * c->plan.grid;
   }
-  if (y_dev)
-    HIP_TRY(launch_partial_reduce(c->d_partial, rows, y_dev, g.hidden, g.act_fmt, c->compute));
-  else
+  const int32_t *misses = on_device ? &c->d_route[layer].n_miss : nullptr;
+  if (y_dev) {
+    HIP_TRY(launch_partial_reduce(c->d_partial, rows, misses, y_dev, g.hidden, g.act_fmt, c->compute));
+  } else {
     c->pending_rows = rows;  // finished by the next moe_stack_route_step
+    c->pending_miss = misses;
+  }
   c->routed[layer] = 0;
   return MOE_OK;
 }
@@ -876,7 +933,6 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
         HIP_TRY(hipMemcpyAsync(static_cast<uint8_t *>(c->slot_pool[layer]) + (size_t)r.sel_slot[k] * slot_bytes,
                                c->host_blob[(size_t)layer * g.n_experts + r.sel_expert[k]], slot_bytes,
                                hipMemcpyHostToDevice, c->copy));
-        c->bytes_filled[layer] += (int64_t)slot_bytes;
       }
     }
     if (n_fill > 0) HIP_TRY(hipEventRecord(c->ev_copy[layer], c->copy));
@@ -962,7 +1018,11 @@ int moe_cache_stats(moe_cache_t *c, int32_t layer, moe_cache_stats_t *out) {
     out->cold_misses += st.cold_misses;
     out->evictions += st.evictions;
     out->lifetime_sum += st.lifetime_sum;
-    out->bytes_filled += c->bytes_filled[l];
+    // a miss is a fill, except that those of a step whose moe_expert_forward has not been called are still to come
+    int32_t to_come = 0;
+    if (c->routed[l] >= 2)
+      HIP_TRY(hipMemcpy(&to_come, &c->d_route[l].n_miss, sizeof to_come, hipMemcpyDeviceToHost));
+    out->bytes_filled += c->bytes_filled[l] + (st.misses - c->miss_base[l] - to_come) * c->slot_layout.total;
   }
   return MOE_OK;
 }
@@ -1035,7 +1095,11 @@ int moe_cache_restore(moe_cache_t *c, int32_t layer, const void *buf, size_t byt
   if (st.count < 0 || st.selections < 0 || st.misses < 0) return fail(MOE_EINVAL, "snapshot counters negative");
   HIP_TRY(hipStreamSynchronize(c->compute));
   HIP_TRY(hipStreamSynchronize(c->copy));
+  int64_t misses = 0;
+  HIP_TRY(hipMemcpy(&misses, &c->state(layer)->misses, sizeof misses, hipMemcpyDeviceToHost));
   HIP_TRY(hipMemcpy(c->state(layer), &st, sizeof st, hipMemcpyHostToDevice));
+  c->bytes_filled[layer] += (misses - c->miss_base[layer]) * c->slot_layout.total;
+  c->miss_base[layer] = st.misses;
   const size_t slot_bytes = (size_t)c->slot_layout.total;
   for (int s = 0; s < g.capacity; ++s) {
     const int e = st.slot_expert[s];

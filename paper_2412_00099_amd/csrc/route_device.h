@@ -212,8 +212,10 @@ __device__ __forceinline__ CacheRegs load_cache_regs(const LayerState *st, int l
 // run the boundary in their first workgroup): what they need - the K slots, the miss flags and the K weights - as
 // eight 8-byte words, each complete in itself: bits 0..15 = the tag of this hand-over (a per-layer count, so the
 // words' previous content never carries it), bits 16..63 = 48 bits of payload
-//     word 0: slots of positions 0..5 (8 bits each)      word 1: slots of positions 6, 7 | miss flags << 16
-//     words 2..7: the eight fp32 weights as one 256-bit string, 48 bits per word
+//     word 0: slots of positions 0..5 (8 bits each)      word 1: slots of positions 6, 7 | miss flags << 16 | experts of
+//     positions 0..3 << 24 (6 bits each)
+//     words 2..7: the eight fp32 weights as one 256-bit string, 48 bits per word; behind it, in word 7, the experts of
+//     positions 4..7 << 16
 // A reader accepts the eight words only when all carry the tag it waits for, so no order between the stores is
 // assumed: 8-byte atomic stores and loads, no fence.  The block is written kHandoverCopies times, 64 bytes apart,
 // by one store instruction; workgroup b reads copy b % kHandoverCopies (hundreds of wavefronts polling one line
@@ -460,12 +462,13 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
     if (word == 0) {
       payload = ((uint64_t)lo | ((uint64_t)hi << 32)) & 0xffffffffffffull;
     } else if (word == 1) {
-      payload = (uint64_t)(hi >> 16) | ((uint64_t)(mm & 0xffu) << 16);
+      payload = (uint64_t)(hi >> 16) | ((uint64_t)(mm & 0xffu) << 16) | (((ew >> 16) & 0xffffffu) << 24);
     } else {
       const int bit = 48 * (word - 2), i = bit >> 5, sh = bit & 31;  // position in the 256-bit weight string
       const uint32_t next = i + 1 < MOE_MAX_TOPK ? rec_s[W_WEIGHT + i + 1] : 0u;  // (the string ends with weight 7)
       const uint64_t two = (uint64_t)rec_s[W_WEIGHT + i] | ((uint64_t)next << 32);
       payload = (two >> sh) & 0xffffffffffffull;
+      if (word == 7) payload = (payload & 0xffffu) | (((ew >> 40) & 0xffffffu) << 16);
     }
     __hip_atomic_store(flags.handover + lane, (payload << 16) | (uint64_t)(flags.tag & 0xffffu), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
@@ -539,12 +542,13 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
 // launch: 2.1 us with rounds of arg-max in every wavefront and lane reads by position, 1.2 us like this).
 struct DecideLds {
   float weight[MOE_MAX_TOPK];
-  uint8_t slot[MOE_MAX_TOPK], miss[MOE_MAX_TOPK];
+  uint8_t slot[MOE_MAX_TOPK], expert[MOE_MAX_TOPK], miss[MOE_MAX_TOPK];
   int rank[kWave], rank_z[kWave];
 };
 template <int NW>
 __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_slot, float dsum_prev, int t, int lane, int wave,
-                                       DecideLds &lds, uint64_t &slots, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]) {
+                                       DecideLds &lds, uint64_t &slots, uint64_t &experts, uint32_t &miss_mask,
+                                       float (&weight)[MOE_MAX_TOPK]) {
 #pragma clang fp contract(off)
   const int N = p.n_experts, K = p.top_k;
   const bool active = lane < N, own = owns_lane<NW>(lane, wave), resident = my_slot >= 0;
@@ -566,6 +570,7 @@ __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_
   if (own && key != 0 && rank < K) {
     lds.weight[rank] = sc.w;
     lds.slot[rank] = (uint8_t)max(my_slot, 0);
+    lds.expert[rank] = (uint8_t)lane;
     lds.miss[rank] = (uint8_t)!resident;
   }
   if (p.renormalize && own) lds.rank[lane] = key != 0 ? rank : kWave;
@@ -573,7 +578,7 @@ __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_
   float w = lds.weight[lane & (MOE_MAX_TOPK - 1)];
   const bool filled = lane < places;  // (a place that nothing fills is slot 0 with weight 0, as in the record)
   const bool miss = filled && lds.miss[lane & (MOE_MAX_TOPK - 1)] != 0;
-  const uint64_t all_slots = *reinterpret_cast<const uint64_t *>(lds.slot);
+  const uint64_t all_slots = *reinterpret_cast<const uint64_t *>(lds.slot), all_experts = *reinterpret_cast<const uint64_t *>(lds.expert);
   if (p.renormalize) {  // Sec. 2.1
     const float sum = wave_sum(active && lds.rank[lane] < K ? sc.w : 0.f);
     w = w / sum;
@@ -585,6 +590,8 @@ __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)all_slots);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(all_slots >> 32));
   slots = (((uint64_t)hi << 32) | lo) & (places >= 8 ? ~0ull : (1ull << (8 * places)) - 1ull);
+  experts = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(all_experts >> 32)) << 32) |
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)all_experts);
 }
 
 // Workgroup 0 of an expert launch in which every wavefront routes for itself: does the same step with everything that
@@ -594,7 +601,7 @@ __device__ __forceinline__ void routing_workgroup(const GemvParams &p, float *re
   const int lane = threadIdx.x;
   const CacheRegs cr = load_cache_regs(p.b.state, lane, p.b.route.n_experts, p.b.route.capacity);
   route_wave(p.b.route, p.b.logits, cr, p.b.state_out, p.b.out_dev, HostOut{p.b.note, nullptr}, reinterpret_cast<uint32_t *>(red),
-             lane);
+             lane, BoundaryFlags{p.b.handover, p.b.hand_tag});
 }
 
 // Gate rows of one wavefront held in registers: loaded before x exists, used once x is in LDS.
@@ -901,7 +908,10 @@ __device__ __forceinline__ void boundary_workgroup(const GemvParams &p, float *r
                                     BoundaryFlags{p.b.handover, p.b.hand_tag},
                                     carve_boundary_lds(reinterpret_cast<uint32_t *>(red)));
   float *row = p.partial + (int64_t)p.row_offset * d;  // this workgroup's partial row: nothing to add
-  for (int j = tid; j < d; j += NW * kWave) row[j] = 0.f;
+  for (int j = tid; j < d; j += NW * kWave) {
+    row[j] = 0.f;
+    if (p.host_blob != nullptr) row[(int64_t)p.missing_row * d + j] = 0.f;  // (whether or not anything misses)
+  }
   if (p.b.next_gate_w != nullptr) {
     // this compute unit is idle for the rest of the launch: pull what the next boundary reads first towards it
     const u32x4 *g = static_cast<const u32x4 *>(p.b.next_gate_w);
