@@ -285,8 +285,8 @@ int moe_trace_misses(const int32_t *trace, int64_t n_tokens, int32_t top_k, int3
 
 /* The launch shape the context chose for the expert kernels, and whether a moe_stack_route_step without out_host
  * runs x and its routing in the first workgroup of the layer's expert launch (bf16 activations, a supported shape, and,
- * other than int4, a shared expert of at least a third of the layer's records in a layer-token of at least 45 MB and 41 KB
- * per hidden column; MOE_FUSE_BOUNDARY=0 or 1 in the environment at moe_cache_init overrides the last condition). */
+ * other than int4, a shared expert of at least a third of the layer's records and 20 KB of them per hidden column;
+ * MOE_FUSE_BOUNDARY=0 or 1 in the environment at moe_cache_init overrides the last condition). */
 typedef struct moe_cache_plan {
   int32_t grid, wavefronts, depth, packed_bf16_dot, boundary_in_expert_launch;
 } moe_cache_plan_t;

@@ -338,41 +338,30 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
                          hipHostMallocMapped | hipHostMallocCoherent));
   *c->h_gave_up = 0;
   HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->h_gave_up_dev), c->h_gave_up, 0));
-  // Three ways to run a boundary that nobody waits for, by what a layer-token streams (measured, us for 12 layer-tokens;
-  // 60 experts, top-4; one launch of the boundary before the experts / routing in every workgroup behind a gate launch /
-  // boundary inside the expert launch):
-  //   bf16 d = 512:  34.6 MB, half shared  222 / 246 / 236    57.7 MB, 0.7 shared  249 / 248 / 236    69 MB  278 / 262
-  //   bf16 d = 1024: 34.4 MB, half shared  230 / 239 / 240    53.2 MB, 0.35 shared 251 / 241 / 242    69 MB  281 / 259 / 243
-  //   bf16 d = 2048: 12 MB, 0.35 shared    236 / 235 / 257    68.8 MB, half shared 301 / 267 / 274   115 MB  375 / 345 / 303
-  //   int8 d = 2048: 34.6 MB, half shared  266 / 238 / 268    98 MB, 0.65 shared     - / 338 / 325
-  //   int8 d = 4096: 34.6 MB, half shared  315 / 252 / 356   138 MB, half shared    - / 428 / 426   197 MB   - / 529 / 502
-  //   int4 d = 2048: 36 MB, 0.25 shared      - / 284 / 351   135 MB, 0.8 shared     - / 457 / 482
+  // Three ways to run a boundary that nobody waits for (measured with nobody waiting in the expert launch either, us per
+  // layer-token, 60 experts, 3 layers; one launch of the boundary before the experts / routing in every workgroup behind a gate
+  // launch / boundary inside the expert launch; MB a layer-token, of them the shared expert's):
+  //   d = 512, bf16   3.1, 0    12.5 / 13.7 / -      17.3, 0    13.8 / 13.2 / -      26, 8.7  14.6 / 13.6 / 14.2   69, 34.6  20.6 / 18.7 / 17.0
+  //   d = 1024, bf16  12.6, 0   14.6 / 13.3 / -      51.9, 17.3 19.6 / 16.7 / 17.7   69, 34.6 21.9 / 18.8 / 17.8
+  //   d = 2048, bf16  6.3, 0    15.8 / 14.1 / -      75.5, 25   24.7 / 20.5 / 22.0   104, 34.6 28.8 / 24.6 / 25.1  75.5, 50  24.5 / 20.5 / 18.9
+  //   d = 2048, int8  12.6, 0   17.1 / 15.2 / -      52, 17.3   23.0 / 20.1 / 20.5   86.5, 52 27.9 / 25.0 / 22.5
+  //   d = 2048, int4  3.2, 0    16.5 / 15.9 / -      35.7, 9    24.9 / 22.9 / 26.0   62.4, 36 31.9 / 29.1 / 27.4
+  //   d = 4096        6.5, 0 (int4) 22.3 / 19.4 / -  138, 69 (int8) 39.2 / 35.9 / 35.9          277, 138 (int8) 58.8 / 55.5 / 52.4
+  //   d = 256, fp32   3.1, 0    12.0 / 12.9 / -      d = 1024, fp32 25, 0 17.0 / 14.4 / -       25, 12.6 16.3 / 14.1 / -
   // Inside the launch the boundary hides behind the shared expert's records, but one compute unit does all of it, and the
-  // gate matrix alone costs it time in proportion to d: the launch has to be long for that.  Routing everywhere spreads
-  // the gate matrix; it costs a launch, which short chains of small launches feel (the host is behind then), and every
-  // wavefront the decision.  Without a shared expert, us per layer-token, one launch of the boundary / routing in every
-  // workgroup, at the sizes around each line:
-  //   d = 512, bf16   64.5 MB 21.9 / 23.2, 89.7 MB 25.2 / 24.2        d = 1024, bf16   56.6 MB 22.3 / 22.1
-  //   d = 2048, bf16  31.5 MB 22.5 / 22.5, 37.7 MB 21.9 / 21.6 (top-2), 23.1 / 23.3 (top-8), 50.3 MB 24.2 / 23.3 (top-8)
-  //   d = 2048, int8  15.7 MB 22.4 / 22.7, 19.7 MB 22.8 / 22.9, 25.2 MB 23.1 / 22.9
-  //   d = 2048, int4  13.0 MB 22.9 / 23.3, 14.2 MB 22.9 / 22.8, 22.7 MB 24.1 / 23.0
-  //   d = 2048, fp32 activations  6.3 MB 22.9 / 21.7                  d = 4096   3.1 MB 23.9 / 21.5
+  // gate matrix alone costs it time in proportion to d: about 20 KB of shared records per hidden column are wanted for that.
+  // Routing everywhere spreads the gate matrix; against that, the launch of its own sums the pending output and does the glue
+  // of small hidden sizes in one launch less where a token begins, which only the smallest layers feel.
   // Cumsum-Threshold walks all ranks in every wavefront; only int4, whose launches are the shortest for what they hold
-  // in registers, does not hide that: d = 2048, 64 experts 22.7 MB 27.6 / 30.4, 97 MB 40.0 / 41.6, 32 experts 38.9 MB
-  // 29.1 / 28.8; d = 4096, 60 experts 3.2 MB 28.2 / 29.4, 22.7 MB 31.4 / 31.1.
+  // in registers, does not hide that: d = 2048, 60 experts 3.2 MB 20.7 / 23.4, 35.7 MB 28.5 / 30.5; d = 4096, 6.5 MB 26.4 /
+  // 27.0 (bf16 d = 2048, 6.3 MB 20.0 / 16.9; int8 12.6 MB 21.2 / 18.8).
   // MOE_FUSE_BOUNDARY=0 / 1 and MOE_ROUTE_EVERYWHERE=0 / 1 in the environment override the two rules.
   const int64_t records = (int64_t)cfg->top_k * cfg->inter + cfg->shared_inter, streamed = records * c->slot_layout.rec_bytes;
   // (whichever form is taken: what a wrong x_dev meets depends on the shared expert's share alone)
   c->x_fixed = 3 * (int64_t)cfg->shared_inter >= records;
-  c->fuse_boundary = cfg->weight_fmt != MOE_W_INT4_G128 && 3 * (int64_t)cfg->shared_inter >= records &&
-                     streamed >= std::max((int64_t)41000 * cfg->hidden, (int64_t)45000000);
   const bool int4 = cfg->weight_fmt == MOE_W_INT4_G128;
-  int64_t from = 0;  // bytes a layer-token streams
-  if (cfg->hidden < 1024) from = 90000000;
-  else if (cfg->hidden < 2048) from = 56000000;
-  else if (cfg->hidden < 4096 && cfg->act_fmt == MOE_A_BF16)
-    from = int4 ? 14000000 : cfg->weight_fmt == MOE_W_INT8_PC ? 20000000 : 36000000;
-  c->route_everywhere = gate_rows_supported(cfg->hidden, cfg->act_fmt) && streamed >= from;
+  c->fuse_boundary = !int4 && c->x_fixed && cfg->shared_inter * c->slot_layout.rec_bytes >= (int64_t)20000 * cfg->hidden;
+  c->route_everywhere = gate_rows_supported(cfg->hidden, cfg->act_fmt) && (cfg->hidden >= 1024 || streamed >= 10000000);
   c->everywhere_cumsum = c->route_everywhere && (!int4 || (cfg->hidden < 4096 ? N <= 32 && streamed >= 36000000
                                                                                : N <= 32 || streamed >= 20000000));
   if (const char *s = getenv("MOE_FUSE_BOUNDARY")) c->fuse_boundary = c->x_fixed = atoi(s) != 0;
