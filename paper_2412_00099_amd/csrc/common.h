@@ -203,7 +203,7 @@ struct BatchEntry {
 };
 constexpr int kMaxEntries = MOE_MAX_EXPERTS + 1;
 constexpr int kMaxPartialRows = 4096;  // rows of P of a segment (P: [rows][hidden] fp32)
-struct BatchParams {
+struct BatchArgs {
   const uint8_t *slot_pool, *shared_blob;
   const uint16_t *x;    // [B, d] bf16
   const BatchSel *sel;
@@ -216,15 +216,70 @@ struct BatchParams {
   int32_t down_groups;  // groups of 32 records per unit of down_batch_kernel
   int32_t shared_row0;  // first row of the shared expert in P
   int32_t n_entries;
+};
+struct BatchParams : BatchArgs {
   BatchEntry e[kMaxEntries];
 };
+// The same list made on the device (route_batch_kernel), for a batch in which nothing misses: the expert kernels are then
+// enqueued behind the routing before the host knows the decisions.
+struct BatchPlan {
+  int32_t n_up, n_down;  // units of the two expert kernels; 0: something misses, the host sees to the batch
+  int32_t up_records, down_groups, n_rc, n_rc_shared, shared_row0, n_entries;
+  BatchEntry e[kMaxEntries];
+};
+// what route_batch_kernel needs for it (plan = nullptr: not wanted)
+constexpr int kPlanRounds = 2;  // its launches have that many workgroups per compute unit; a longer list is the host's
+struct BatchPlanFor {
+  BatchPlan *plan;
+  int32_t hidden, inter, shared_inter, n_cus;
+};
+// Sizes of the units of the two expert kernels.  A unit costs a start-up of about 3 us and then what its compute unit's L1
+// takes in (about 23 KB per us: 8 KB a record in `up`, 16 KB a group of 32 records in `down`), and a launch runs in rounds of
+// one workgroup per compute unit: the sizes with the smallest rounds x unit time are taken, the larger ones where two are equal.
+// The same on the host and on the device (whole numbers).
+__host__ __device__ inline int batch_parts(int n, int by) { return (n + by - 1) / by; }
+constexpr int64_t kNoCandidate = INT64_MAX;
+__host__ __device__ inline int64_t batch_up_estimate(int cand, int groups, int inter, int shared_groups, int shared_inter, int hidden, int n_cus) {
+  const int units = groups * batch_parts(inter, cand) + shared_groups * batch_parts(shared_inter, cand);
+  return (int64_t)batch_parts(units, n_cus) * (300 * 2048 + (int64_t)36 * hidden * cand);  // 3 us + 0.36 us a record at d = 2048
+}
+__host__ __device__ inline int batch_up_candidates(int inter, int shared_inter) {  // 32, 64, .. times 1 .. this
+  const int longest = inter > shared_inter ? inter : shared_inter, n = batch_parts(longest, 32);
+  return n < 32 ? n : 32;
+}
+// P has to hold the rows: a candidate that makes too many is none
+__host__ __device__ inline int64_t batch_down_estimate(int cand, int groups, int inter, int shared_groups, int shared_inter, int hidden, int n_seg,
+                                                      int top_k, int n_cus) {
+  const int n32 = batch_parts(inter, 32), n32s = shared_groups ? batch_parts(shared_inter, 32) : 0;
+  const int rc = batch_parts(n32, cand), rcs = batch_parts(n32s, cand);
+  if ((int64_t)n_seg * (top_k * rc + rcs) > kMaxPartialRows) return kNoCandidate;
+  const int units = (groups * rc + shared_groups * rcs) * (hidden / 256);
+  return (int64_t)batch_parts(units, n_cus) * (40 + 7 * cand);  // 4 us + 0.7 us a group
+}
+__host__ __device__ inline int batch_down_candidates(int inter, int shared_inter) {  // 4, 8, .. times 1 .. this
+  const int longest = inter > shared_inter ? inter : shared_inter;
+  return batch_parts(batch_parts(longest, 32), 4);
+}
+// units of one expert with n_tok tokens and `rows` records in the two kernels (several token groups: see group_pos)
+__host__ __device__ inline void batch_entry_units(int n_tok, int rows, int up_records, int down_groups, int hidden, int *up, int *down) {
+  const int groups = batch_parts(n_tok, 64);
+  *up = batch_parts(rows, up_records);
+  *down = batch_parts(batch_parts(rows, 32), down_groups) * (hidden / 256);
+  if (groups > 1) {
+    *up = (*up + 7) / 8 * 8 * groups;
+    *down = (*down + 7) / 8 * 8 * groups;
+  }
+}
 bool batch_shape_supported(int weight_fmt, int act_fmt, int hidden, int inter, int shared_inter);
 hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, int B, int N, int hidden, hipStream_t s);
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              BatchSel *sel, BatchAhead *ahead, uint32_t *done, hipStream_t s);
+                              BatchSel *sel, BatchAhead *ahead, uint32_t *done, const BatchPlanFor &planned, hipStream_t s);
 hipError_t launch_up_batch(const BatchParams &p, int n_units, hipStream_t s);
 hipError_t launch_down_batch(const BatchParams &p, int n_units, hipStream_t s);
-hipError_t launch_reduce_batch(const BatchParams &p, void *y, int n_rc, int n_rc_shared, hipStream_t s);
+hipError_t launch_reduce_batch(const BatchArgs &p, void *y, int n_rc, int n_rc_shared, hipStream_t s);
+// with the list that route_batch_kernel leaves
+hipError_t launch_planned_experts(const BatchArgs &p, const BatchPlan *plan, int n_cus, hipStream_t s);
+hipError_t launch_planned_reduce(const BatchArgs &p, const BatchPlan *plan, void *y, hipStream_t s);
 
 // the allocation-free entry point (expert_static.hip): device address of its fixed scratch array and the compute-unit
 // count of device `dev` (which must be current), looked up once per device

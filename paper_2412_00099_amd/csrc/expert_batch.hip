@@ -173,10 +173,100 @@ __global__ __launch_bounds__(kAheadWaves *kWave) void route_ahead_kernel(RoutePa
   }
 }
 
+// The list of experts for the expert kernels (BatchPlan), by one wavefront: lane s <-> slot s with count[s] places.  The order
+// and the numbers are those the host makes: experts with several groups of 64 tokens first, the shared one ahead of its kind.
+__device__ __forceinline__ int wave_sum_i(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+__device__ __forceinline__ int wave_before_i(int v, int lane) {  // sum over the lanes below
+  int s = v;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int t = __shfl_up(s, o);
+    if (lane >= o) s += t;
+  }
+  return s - v;
+}
+__device__ __forceinline__ int64_t wave_min_i64(int64_t v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = min(v, (int64_t)__shfl_xor((long long)v, o));
+  return v;
+}
+__device__ __forceinline__ int wave_max_i(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
+  return v;
+}
+__device__ __forceinline__ void make_plan(const BatchPlanFor &f, int B, int top_k, const int *count, uint32_t *order_s, int lane) {
+  const int n = count[lane], groups = wave_sum_i(batch_parts(n, 64));
+  const int sg = f.shared_inter > 0 ? batch_parts(B, 64) : 0, sh = sg ? f.shared_inter : 0;
+  // the best candidate, the largest where several are equal
+  int64_t best = kNoCandidate;
+  int cand = 0;
+  if (lane < batch_up_candidates(f.inter, sh)) {
+    cand = 32 * (lane + 1);
+    best = batch_up_estimate(cand, groups, f.inter, sg, sh, f.hidden, f.n_cus);
+  }
+  const int up_records = wave_max_i(best == wave_min_i64(best) ? cand : 0);
+  best = kNoCandidate;
+  cand = 4;
+  for (int c = lane; c < batch_down_candidates(f.inter, sh); c += kWave) {
+    const int64_t est = batch_down_estimate(4 * (c + 1), groups, f.inter, sg, sh, f.hidden, B, top_k, f.n_cus);
+    if (est <= best) best = est, cand = 4 * (c + 1);
+  }
+  const int down_groups = wave_max_i(best == wave_min_i64(best) ? cand : 0);
+  const int n32 = batch_parts(f.inter, 32), n32s = sg ? batch_parts(f.shared_inter, 32) : 0;
+  const int rc = batch_parts(n32, down_groups), rcs = batch_parts(n32s, down_groups);
+  // the experts in list order, one per lane
+  const uint64_t several = rt::ballot(n > 64), others = rt::ballot(n > 0 && n <= 64), below = (1ull << lane) - 1ull;
+  const int n_several = (int)__builtin_popcountll(several), n_slots = n_several + (int)__builtin_popcountll(others);
+  if (n > 64) order_s[__builtin_popcountll(several & below)] = (uint32_t)lane | ((uint32_t)n << 8);
+  else if (n > 0) order_s[n_several + __builtin_popcountll(others & below)] = (uint32_t)lane | ((uint32_t)n << 8);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const uint32_t mine = lane < n_slots ? order_s[lane] : 0u;
+  const int n_tok = (int)(mine >> 8);
+  int up = 0, down = 0, h = 0, sh_up = 0, sh_down = 0, sh_h = 0;
+  if (lane < n_slots) {
+    batch_entry_units(n_tok, f.inter, up_records, down_groups, f.hidden, &up, &down);
+    h = batch_parts(n_tok, 16) * n32;
+  }
+  if (sg) {
+    batch_entry_units(B, f.shared_inter, up_records, down_groups, f.hidden, &sh_up, &sh_down);
+    sh_h = batch_parts(B, 16) * n32s;
+  }
+  const int up0 = wave_before_i(up, lane), down0 = wave_before_i(down, lane), h0 = wave_before_i(h, lane);
+  const int sh_at = B > 64 ? 0 : n_several;  // the shared expert's place
+  const bool after = sg && lane >= sh_at;
+  BatchPlan *o = f.plan;
+  if (lane < n_slots)
+    o->e[lane + after] = BatchEntry{(int16_t)(mine & 0xffu), (uint16_t)n_tok, (uint32_t)(h0 + (after ? sh_h : 0)),
+                                    (uint32_t)(up0 + (after ? sh_up : 0)), (uint32_t)(down0 + (after ? sh_down : 0))};
+  const int up_all = wave_sum_i(up) + sh_up, down_all = wave_sum_i(down) + sh_down, h_all = wave_sum_i(h);
+  // (n_slots = 64 and the shared expert behind them all: there is no lane at its place)
+  const int su0 = sh_at < kWave ? __shfl(up0, sh_at & 63) : up_all - sh_up, sd0 = sh_at < kWave ? __shfl(down0, sh_at & 63) : down_all - sh_down;
+  const int h_at = sh_at < kWave ? __shfl(h0, sh_at & 63) : h_all;
+  if (lane == 0) {
+    if (sg) o->e[sh_at] = BatchEntry{(int16_t)-1, (uint16_t)B, (uint32_t)h_at, (uint32_t)su0, (uint32_t)sd0};
+    const bool fits = max(up_all, down_all) <= kPlanRounds * f.n_cus;
+    o->n_up = fits ? up_all : 0;
+    o->n_down = fits ? down_all : 0;
+    o->up_records = up_records;
+    o->down_groups = down_groups;
+    o->n_rc = rc;
+    o->n_rc_shared = rcs;
+    o->shared_row0 = B * top_k * rc;
+    o->n_entries = n_slots + (sg ? 1 : 0);
+  }
+}
+
 __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RouteParams p, const float *logits, int B,
                                                                          LayerState *st, moe_route_out_t *out,
                                                                          BatchSel *sel, const BatchAhead *ahead,
-                                                                         uint32_t *done) {
+                                                                         uint32_t *done, BatchPlanFor planned) {
   __shared__ float z_all[kMaxBatch * MOE_MAX_EXPERTS];
   __shared__ float range_s[kMaxBatch];
   __shared__ float dsum_s[kMaxBatch + 1];  // Eq. 10's sum before token t
@@ -184,8 +274,12 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
   __shared__ __attribute__((aligned(16))) uint32_t stage_s[kRouteWaves][rt::kRecWords];  // a wavefront's record
   __shared__ BatchCacheState cs;
   __shared__ int first_miss_s;
+  __shared__ int count_s[MOE_MAX_EXPERTS];  // places that name the slot
+  __shared__ uint32_t order_s[MOE_MAX_EXPERTS];
   const int tid = threadIdx.x, lane = tid & 63, N = p.n_experts, K = p.top_k;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  bool missed = false;  // (the same in every thread)
+  if (tid < MOE_MAX_EXPERTS) count_s[tid] = 0;
 
   if (wave == 0) {
     const rt::CacheRegs cr = rt::load_cache_regs(st, lane, N, p.capacity);
@@ -212,6 +306,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
       const int t = i / K, pos = i - t * K;
       const int e = ahead->touched[t][pos];
       if (e < MOE_MAX_EXPERTS) atomicMax(&cs.stamp[e], (long long)(cs.count0 + t) * K + pos);
+      atomicAdd(&count_s[sel->slot[t][pos] & (MOE_MAX_EXPERTS - 1)], 1);
     }
   }
   if (ahead == nullptr || fm < B) {
@@ -262,6 +357,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
           reinterpret_cast<u32x4 *>(out + t)[lane] = reinterpret_cast<const u32x4 *>(stage_s[wave])[lane];
         if (lane < N && next.stamp != cr.stamp) atomicMax(&cs.stamp[lane], (long long)next.stamp);
         store_sel(stage_s[wave], K, lane, t, sel);
+        if (lane < K) atomicAdd(&count_s[stage_s[wave][rt::W_SLOT + lane] & (MOE_MAX_EXPERTS - 1)], 1);
       }
     }
     routed_ahead = false;
@@ -270,6 +366,7 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
     t0 = fm;
     if (fm < window_end) {
       // token fm misses at least one expert: routed against the merged state, which it updates
+      missed = true;
       if (wave == 0) {
         cr = batch_cache_regs(cs, lane, fm, dsum_s[fm]);
         rt::route_wave(p, z_all + fm * MOE_MAX_EXPERTS, cr, st, out + fm, HostOut{nullptr, nullptr}, asm_s[0], lane,
@@ -293,6 +390,13 @@ __global__ __launch_bounds__(kRouteWaves *kWave) void route_batch_kernel(RoutePa
   if (tid == 0) {
     __threadfence_system();
     __hip_atomic_store(done, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  if (wave == 1 && planned.plan != nullptr) {
+    if (missed) {
+      if (lane == 0) planned.plan->n_up = planned.plan->n_down = 0;
+    } else {
+      make_plan(planned, B, K, count_s, order_s, lane);
+    }
   }
   if (wave == 0) {
     if (lane < N) {
@@ -334,8 +438,12 @@ struct UnitPos {
   int entry, unit;  // index into BatchParams::e, and the unit's place inside that entry
 };
 // the entry a workgroup belongs to: the last one whose first unit is not beyond it
-template <bool DOWN>
-__device__ __forceinline__ UnitPos find_unit(const BatchParams &p, int block, int lane) {
+// (P: BatchParams, or BatchPlanned with the list in memory)
+struct BatchPlanned : BatchArgs {
+  const BatchEntry *e;
+};
+template <bool DOWN, typename P>
+__device__ __forceinline__ UnitPos find_unit(const P &p, int block, int lane) {
   int at = 0;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -363,7 +471,7 @@ __device__ __forceinline__ GroupPos group_pos(int unit, int groups) {
 // selection), by one wavefront into LDS of its own.  list has 64 entries; unused ones name the segment's first token.
 // Every place that names the slot is listed, as the host counts them: a token whose logits are not numbers leaves places
 // that nothing filled, whose record reads slot 0 with weight 0, so that it may name slot 0 several times.
-__device__ __forceinline__ void token_list(const BatchParams &p, int slot, int group, int n, int lane, uint16_t *list) {
+__device__ __forceinline__ void token_list(const BatchArgs &p, int slot, int group, int n, int lane, uint16_t *list) {
   if (slot < 0) {
     const int t = p.t0 + group * 64 + lane;
     list[lane] = (uint16_t)((lane < n ? t : p.t0 + group * 64) * 8);
@@ -437,7 +545,7 @@ __device__ __forceinline__ void split3(const f32x4 &lo, const f32x4 &hi, u32x4 (
 // reads it, per (token tile, 32 records) two blocks of [lane][4] fp32, lane = 16 (record / 8) + token: records 0..3 and
 // 4..7 of the lane's eight.
 template <int D, int NT>
-__device__ __forceinline__ void up_unit(const BatchParams &p, const BatchEntry &e, int part, int group, int lane, int wave,
+__device__ __forceinline__ void up_unit(const BatchArgs &p, const BatchEntry &e, int part, int group, int lane, int wave,
                                         f32x4 *red, uint16_t *list) {
   constexpr int KQ = D / kBWaves, KS = KQ / 32, HS = KS / 2;
   const int rows = e.slot < 0 ? p.shared_inter : p.inter;
@@ -529,21 +637,46 @@ __device__ __forceinline__ void up_unit(const BatchParams &p, const BatchEntry &
   block(n_blk - 1, std::false_type{});
 }
 
-template <int D>
-__global__ __launch_bounds__(kBWaves *kWave, 1) void up_batch_kernel(BatchParams p) {
-  __shared__ f32x4 red[2 * kBWaves * 2 * kGroupTiles * 64];
-  __shared__ uint16_t list_s[kBWaves][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const UnitPos up = find_unit<false>(p, blockIdx.x, lane);
-  const BatchEntry e = p.e[up.entry];
+template <int D, typename P>
+__device__ __forceinline__ void up_block(const P &list_in, int block, int lane, int wave, f32x4 *red, uint16_t *list) {
+  const UnitPos up = find_unit<false>(list_in, block, lane);
+  const BatchEntry e = list_in.e[up.entry];
+  const BatchArgs p = list_in;  // (a copy: a reference into the launch's arguments puts them all into scratch)
   const int groups = (e.n_tok + 63) / 64;
   const GroupPos gp = group_pos(up.unit, groups);
   if (gp.part * p.up_records >= (e.slot < 0 ? p.shared_inter : p.inter)) return;  // padding of the unit grid
   const int tiles = (min((int)e.n_tok - 64 * gp.group, 64) + 15) / 16;
-  if (tiles == 1) up_unit<D, 1>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
-  else if (tiles == 2) up_unit<D, 2>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
-  else up_unit<D, 4>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+  if (tiles == 1) up_unit<D, 1>(p, e, gp.part, gp.group, lane, wave, red, list);
+  else if (tiles == 2) up_unit<D, 2>(p, e, gp.part, gp.group, lane, wave, red, list);
+  else up_unit<D, 4>(p, e, gp.part, gp.group, lane, wave, red, list);
+}
+template <int D>
+__global__ __launch_bounds__(kBWaves *kWave, 1) void up_batch_kernel(BatchParams p) {
+  __shared__ f32x4 red[2 * kBWaves * 2 * kGroupTiles * 64];
+  __shared__ uint16_t list_s[kBWaves][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  up_block<D>(p, blockIdx.x, threadIdx.x & 63, wave, red, list_s[wave]);
+}
+// the batch's arguments with what the device decided
+__device__ __forceinline__ BatchPlanned planned_args(const BatchArgs &p, const BatchPlan *plan) {
+  BatchPlanned a;
+  static_cast<BatchArgs &>(a) = p;
+  a.up_records = plan->up_records;
+  a.down_groups = plan->down_groups;
+  a.shared_row0 = plan->shared_row0;
+  a.n_entries = plan->n_entries;
+  a.e = plan->e;
+  return a;
+}
+// Workgroups past the last unit end at once.  (One workgroup per compute unit that walks the units: the loop costs `down`, which
+// fills the register file, spills: 8 tokens 20.1 us instead of 15.9.)
+template <int D>
+__global__ __launch_bounds__(kBWaves *kWave, 1) void up_planned_kernel(BatchArgs p, const BatchPlan *plan) {
+  __shared__ f32x4 red[2 * kBWaves * 2 * kGroupTiles * 64];
+  __shared__ uint16_t list_s[kBWaves][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x >= plan->n_up) return;
+  up_block<D>(planned_args(p, plan), blockIdx.x, threadIdx.x & 63, wave, red, list_s[wave]);
 }
 
 // Eight rows of eight bf16 columns -> eight columns of eight rows, inside a lane: the record layout keeps the columns of
@@ -561,7 +694,7 @@ __device__ __forceinline__ void transpose8(const u32x4 (&r)[8], u32x4 (&c)[8]) {
 // columns] tile over them in registers; the four tiles are added through LDS at the end.  Lane l loads columns
 // 8 (l % 16) .. + 8 of records 8 (l / 16) + i: full 128-byte lines, each lane an 8 x 8 block that it transposes.
 template <int D, int NT>
-__device__ __forceinline__ void down_unit(const BatchParams &p, const BatchEntry &e, int part, int group, int lane, int wave,
+__device__ __forceinline__ void down_unit(const BatchArgs &p, const BatchEntry &e, int part, int group, int lane, int wave,
                                           float *red, uint16_t *list) {
   constexpr int CBLKS = D / 256;
   const int rows = e.slot < 0 ? p.shared_inter : p.inter;
@@ -677,29 +810,46 @@ __device__ __forceinline__ void down_unit(const BatchParams &p, const BatchEntry
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(kBWaves *kWave, 1) void down_batch_kernel(BatchParams p) {
-  __shared__ __attribute__((aligned(16))) float red[kBWaves * 4096];
-  __shared__ uint16_t list_s[kBWaves][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const UnitPos up = find_unit<true>(p, blockIdx.x, lane);
-  const BatchEntry e = p.e[up.entry];
+template <int D, typename P>
+__device__ __forceinline__ void down_block(const P &list_in, int block, int lane, int wave, float *red, uint16_t *list) {
+  const UnitPos up = find_unit<true>(list_in, block, lane);
+  const BatchEntry e = list_in.e[up.entry];
+  const BatchArgs p = list_in;  // (a copy: a reference into the launch's arguments puts them all into scratch)
   const int groups = (e.n_tok + 63) / 64;
   const GroupPos gp = group_pos(up.unit, groups);
   const int rows = e.slot < 0 ? p.shared_inter : p.inter;
   if (gp.part / (D / 256) * p.down_groups * 32 >= rows) return;  // padding of the unit grid
   const int tiles = (min((int)e.n_tok - 64 * gp.group, 64) + 15) / 16;
-  if (tiles == 1) down_unit<D, 1>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
-  else if (tiles == 2) down_unit<D, 2>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
-  else down_unit<D, 4>(p, e, gp.part, gp.group, lane, wave, red, list_s[wave]);
+  if (tiles == 1) down_unit<D, 1>(p, e, gp.part, gp.group, lane, wave, red, list);
+  else if (tiles == 2) down_unit<D, 2>(p, e, gp.part, gp.group, lane, wave, red, list);
+  else down_unit<D, 4>(p, e, gp.part, gp.group, lane, wave, red, list);
+}
+template <int D>
+__global__ __launch_bounds__(kBWaves *kWave, 1) void down_batch_kernel(BatchParams p) {
+  __shared__ __attribute__((aligned(16))) float red[kBWaves * 4096];
+  __shared__ uint16_t list_s[kBWaves][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  down_block<D>(p, blockIdx.x, threadIdx.x & 63, wave, red, list_s[wave]);
+}
+template <int D>
+__global__ __launch_bounds__(kBWaves *kWave, 1) void down_planned_kernel(BatchArgs p, const BatchPlan *plan) {
+  __shared__ __attribute__((aligned(16))) float red[kBWaves * 4096];
+  __shared__ uint16_t list_s[kBWaves][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x >= plan->n_down) return;
+  down_block<D>(planned_args(p, plan), blockIdx.x, threadIdx.x & 63, wave, red, list_s[wave]);
 }
 
 // y[t] = the sum of token t's rows of P - its experts in selection order, each block of records in turn, then the
 // shared expert's blocks - rounded to bf16.  grid = (tokens, d / 256), one wavefront: all of a token's rows are
 // requested eight at a time.
 __global__ __launch_bounds__(kWave) void reduce_batch_kernel(const float *partial, uint16_t *y, int d, int t0, int n_seg, int top_k,
-                                                             int n_rc, int shared_row0, int n_rc_shared) {
+                                                             int n_rc, int shared_row0, int n_rc_shared, const BatchPlan *plan) {
+  if (plan != nullptr) {
+    n_rc = plan->n_rc;
+    n_rc_shared = plan->n_rc_shared;
+    shared_row0 = plan->shared_row0;
+  }
   const int t = blockIdx.x, col = blockIdx.y * 256 + threadIdx.x * 4;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
   for (int rc = 0; rc < n_rc; ++rc) {
@@ -742,7 +892,7 @@ hipError_t launch_gate_gemm(const void *x, const void *gate_w, float *logits, in
 constexpr int kAheadMinTokens = kRouteWaves;
 
 hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, LayerState *state, moe_route_out_t *out,
-                              BatchSel *sel, BatchAhead *ahead, uint32_t *done, hipStream_t s) {
+                              BatchSel *sel, BatchAhead *ahead, uint32_t *done, const BatchPlanFor &planned, hipStream_t s) {
   if (B <= 0 || B > kMaxBatch) return hipErrorInvalidValue;
   const bool use_ahead = B > kAheadMinTokens;
   if (use_ahead) {
@@ -752,7 +902,7 @@ hipError_t launch_route_batch(const RouteParams &p, const float *logits, int B, 
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(route_batch_kernel, dim3(1), dim3(kRouteWaves * kWave), 0, s, p, logits, B, state, out, sel,
-                     use_ahead ? ahead : nullptr, done);
+                     use_ahead ? ahead : nullptr, done, planned);
   return hipGetLastError();
 }
 
@@ -772,11 +922,30 @@ hipError_t launch_down_batch(const BatchParams &p, int n_units, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_batch(const BatchParams &p, void *y, int n_rc, int n_rc_shared, hipStream_t s) {
+hipError_t launch_reduce_batch(const BatchArgs &p, void *y, int n_rc, int n_rc_shared, hipStream_t s) {
   const int n_seg = p.t1 - p.t0;
   if (n_seg <= 0) return hipSuccess;
   hipLaunchKernelGGL(reduce_batch_kernel, dim3(n_seg, p.hidden / 256), dim3(kWave), 0, s, p.partial, static_cast<uint16_t *>(y),
-                     p.hidden, p.t0, n_seg, p.top_k, n_rc, p.shared_row0, n_rc_shared);
+                     p.hidden, p.t0, n_seg, p.top_k, n_rc, p.shared_row0, n_rc_shared, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_planned_experts(const BatchArgs &p, const BatchPlan *plan, int n_cus, hipStream_t s) {
+  if (n_cus < 1 || (p.hidden != 2048 && p.hidden != 1024)) return hipErrorInvalidValue;
+  const dim3 g(kPlanRounds * n_cus), b(kBWaves * kWave);
+  if (p.hidden == 2048) hipLaunchKernelGGL(up_planned_kernel<2048>, g, b, 0, s, p, plan);
+  else hipLaunchKernelGGL(up_planned_kernel<1024>, g, b, 0, s, p, plan);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (p.hidden == 2048) hipLaunchKernelGGL(down_planned_kernel<2048>, g, b, 0, s, p, plan);
+  else hipLaunchKernelGGL(down_planned_kernel<1024>, g, b, 0, s, p, plan);
+  return hipGetLastError();
+}
+
+hipError_t launch_planned_reduce(const BatchArgs &p, const BatchPlan *plan, void *y, hipStream_t s) {
+  const int n_seg = p.t1 - p.t0;
+  hipLaunchKernelGGL(reduce_batch_kernel, dim3(n_seg, p.hidden / 256), dim3(kWave), 0, s, p.partial, static_cast<uint16_t *>(y), p.hidden,
+                     p.t0, n_seg, p.top_k, 0, 0, 0, plan);
   return hipGetLastError();
 }
 

@@ -120,6 +120,8 @@ struct moe_cache {
   moe_route_out_t *batch_rec_dev = nullptr;  // the routing kernel's view of it (the records go straight to the host)
   BatchSel *d_bsel = nullptr;               // the same selection as the expert kernels read it
   BatchAhead *d_bahead = nullptr;           // between the two routing kernels of a long batch
+  BatchPlan *d_bplan = nullptr;             // units of a batch whose expert kernels were enqueued behind its routing
+  const void *batch_x = nullptr;            // x_dev of that batch, until moe_expert_forward_batch; nullptr: they were not
   uint8_t *d_bh = nullptr;                  // h of a segment (see up_batch_kernel)
   float *d_bpartial = nullptr;              // P of a segment: [kMaxPartialRows][hidden]
   int n_cus = 0;
@@ -175,6 +177,7 @@ int do_reset(moe_cache_t *c) {
   c->deferred = -1;
   c->batch_layer = -1;
   c->batch_n = 0;
+  c->batch_x = nullptr;
   const int N = c->cfg.n_experts;
   for (int l = 0; l < c->cfg.n_layers; ++l) {
     for (int i = 0; i < c->n_initial; ++i) {
@@ -406,6 +409,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
     HIP_INIT(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->h_done_dev), c->h_done, 0));
     HIP_INIT(hipMalloc(&c->d_bsel, sizeof(BatchSel)));
     HIP_INIT(hipMalloc(&c->d_bahead, sizeof(BatchAhead)));
+    HIP_INIT(hipMalloc(&c->d_bplan, sizeof(BatchPlan)));
     HIP_INIT(hipMalloc(&c->d_bh, (size_t)h_blocks * 2048));
     HIP_INIT(hipMalloc(&c->d_bpartial, sizeof(float) * (size_t)kMaxPartialRows * cfg->hidden));
     HIP_INIT(hipEventCreateWithFlags(&c->ev_batch, hipEventDisableTiming));
@@ -441,6 +445,7 @@ void moe_cache_destroy(moe_cache_t *c) {
   if (c->d_bpartial) (void)hipFree(c->d_bpartial);
   if (c->d_bsel) (void)hipFree(c->d_bsel);
   if (c->d_bahead) (void)hipFree(c->d_bahead);
+  if (c->d_bplan) (void)hipFree(c->d_bplan);
   if (c->d_bh) (void)hipFree(c->d_bh);
   if (c->ev_batch) (void)hipEventDestroy(c->ev_batch);
   if (c->ev_route) (void)hipEventDestroy(c->ev_route);
@@ -805,6 +810,51 @@ int moe_expert_forward_static(int32_t weight_fmt, int32_t act_fmt, int32_t hidde
   return MOE_OK;
 }
 
+namespace {
+struct BatchUnits {
+  int up_records, down_groups;  // records per unit of up_batch_kernel, groups of 32 records per unit of down_batch_kernel
+  int n_rc, n_rc_shared;        // blocks of records of down_batch_kernel per routed expert / of the shared expert
+};
+BatchUnits batch_units(int groups, int inter, int shared_groups, int shared_inter, int hidden, int n_seg, int top_k, int n_cus) {
+  BatchUnits u{};
+  const int sh = shared_groups ? shared_inter : 0;
+  int64_t best = kNoCandidate;
+  for (int cand = 32; cand <= 32 * batch_up_candidates(inter, sh); cand += 32) {
+    const int64_t est = batch_up_estimate(cand, groups, inter, shared_groups, sh, hidden, n_cus);
+    if (est <= best) best = est, u.up_records = cand;
+  }
+  best = kNoCandidate;
+  u.down_groups = 4;
+  for (int cand = 4; cand <= 4 * batch_down_candidates(inter, sh); cand += 4) {
+    const int64_t est = batch_down_estimate(cand, groups, inter, shared_groups, sh, hidden, n_seg, top_k, n_cus);
+    if (est <= best) best = est, u.down_groups = cand;
+  }
+  u.n_rc = batch_parts(batch_parts(inter, 32), u.down_groups);
+  u.n_rc_shared = batch_parts(batch_parts(sh, 32), u.down_groups);
+  return u;
+}
+}  // namespace
+
+// what the expert kernels of a batch of the layer take, but for the list of experts
+static BatchArgs batch_args(const moe_cache_t *c, int32_t layer, const void *x_dev, int n_tokens) {
+  const moe_cache_config_t &g = c->cfg;
+  BatchArgs a{};
+  a.slot_pool = static_cast<const uint8_t *>(c->slot_pool[layer]);
+  a.shared_blob = g.shared_inter > 0 ? static_cast<const uint8_t *>(c->shared_blob[layer]) : nullptr;
+  a.x = static_cast<const uint16_t *>(x_dev);
+  a.sel = c->d_bsel;
+  a.h = c->d_bh;
+  a.partial = c->d_bpartial;
+  a.slot_bytes = (int64_t)c->slot_layout.total;
+  a.hidden = g.hidden;
+  a.inter = g.inter;
+  a.shared_inter = g.shared_inter;
+  a.top_k = g.top_k;
+  a.t0 = 0;
+  a.t1 = n_tokens;
+  return a;
+}
+
 int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const float *logits_dev, int32_t n_tokens,
                     moe_route_out_t *out_host) {
   if (int rc = check_layer(c, layer)) return rc;
@@ -819,53 +869,49 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
     z = c->d_logits_batch;
   }
   const RouteParams p = make_route_params(c);
-  HIP_TRY(launch_route_batch(p, z, n_tokens, c->state(layer), c->batch_rec_dev, c->d_bsel, c->d_bahead, c->h_done_dev, c->compute));
+  // x_dev is what moe_expert_forward_batch will be given: the expert kernels follow the routing at once, with a list of experts
+  // made there (it is empty if something misses), and run while the host takes its turn (15 us between the two calls' launches).
+  // What is left for moe_expert_forward_batch is the sum per token.
+  const BatchPlanFor planned{x_dev ? c->d_bplan : nullptr, c->cfg.hidden, c->cfg.inter, c->cfg.shared_inter, c->n_cus};
+  c->batch_x = nullptr;
+  HIP_TRY(launch_route_batch(p, z, n_tokens, c->state(layer), c->batch_rec_dev, c->d_bsel, c->d_bahead, c->h_done_dev, planned, c->compute));
+  if (x_dev) {
+    HIP_TRY(launch_planned_experts(batch_args(c, layer, x_dev, n_tokens), c->d_bplan, c->n_cus, c->compute));
+    c->batch_x = x_dev;
+  }
   bool ok;
   if (int rc = wait_for(c, [&]() { return __atomic_load_n(c->h_done, __ATOMIC_ACQUIRE) == p.seq; }, &ok)) return rc;
   if (!ok) return fail(MOE_EHIP, "batch routing of layer %d did not publish its records", layer);
   const moe_cache_config_t &g = c->cfg;
+  int n_of_slot[MOE_MAX_EXPERTS] = {};
   for (int t = 0; t < n_tokens; ++t)
     for (int k = 0; k < g.top_k; ++k) {
       const moe_route_out_t &r = c->batch_rec[t];
+      if (r.miss[k]) c->batch_x = nullptr;
+      else ++n_of_slot[r.sel_slot[k]];
       if (r.sel_expert[k] < 0 || r.sel_expert[k] >= g.n_experts || r.sel_slot[k] < 0 || r.sel_slot[k] >= g.capacity)
         return fail(MOE_EHIP, "batch routing returned expert %d slot %d out of range", r.sel_expert[k], r.sel_slot[k]);
     }
+  if (c->batch_x) {  // the device's list has to fit its launches (see make_plan)
+    const int sg = g.shared_inter > 0 ? batch_parts(n_tokens, 64) : 0;
+    int groups = 0, n_up = 0, n_down = 0, up, down;
+    for (int n : n_of_slot) groups += batch_parts(n, 64);
+    const BatchUnits bu = batch_units(groups, g.inter, sg, g.shared_inter, g.hidden, n_tokens, g.top_k, c->n_cus);
+    const auto add = [&](int n, int rows) {
+      batch_entry_units(n, rows, bu.up_records, bu.down_groups, g.hidden, &up, &down);
+      n_up += up;
+      n_down += down;
+    };
+    for (int n : n_of_slot)
+      if (n > 0) add(n, g.inter);
+    if (sg) add(n_tokens, g.shared_inter);
+    if (std::max(n_up, n_down) > kPlanRounds * c->n_cus) c->batch_x = nullptr;
+  }
   if (out_host) memcpy(out_host, c->batch_rec, sizeof(moe_route_out_t) * n_tokens);
   c->batch_layer = layer;
   c->batch_n = n_tokens;
   return MOE_OK;
 }
-
-namespace {
-struct BatchUnits {
-  int up_records, down_groups;  // records per unit of up_batch_kernel, groups of 32 records per unit of down_batch_kernel
-  int n_rc, n_rc_shared;        // blocks of records of down_batch_kernel per routed expert / of the shared expert
-};
-// A unit costs a start-up of about 3 us and then what its compute unit's L1 takes in (about 23 KB per us: 8 KB a
-// record in `up`, 16 KB a group of 32 records in `down`), and a launch runs in rounds of one workgroup per compute unit:
-// take the sizes with the smallest rounds x unit time, the larger ones where two are equal.  P has to hold the rows.
-BatchUnits batch_units(int groups, int inter, int shared_groups, int shared_inter, int hidden, int n_seg, int top_k, int n_cus) {
-  BatchUnits u{};
-  const auto parts = [](int n, int by) { return (n + by - 1) / by; };
-  const int longest = std::max(inter, shared_groups ? shared_inter : 0);
-  double best = 1e30;
-  for (int cand = 32; cand <= std::min(1024, parts(longest, 32) * 32); cand += 32) {
-    const int units = groups * parts(inter, cand) + shared_groups * parts(shared_inter, cand);
-    const double est = parts(units, n_cus) * (3.0 + 0.36 * hidden / 2048.0 * cand);
-    if (est <= best) best = est, u.up_records = cand;
-  }
-  const int n32 = parts(inter, 32), n32s = shared_groups ? parts(shared_inter, 32) : 0;
-  best = 1e30;
-  for (int cand = 4; cand <= parts(std::max(n32, n32s), 4) * 4; cand += 4) {
-    const int rc = parts(n32, cand), rcs = parts(n32s, cand);
-    if ((int64_t)n_seg * (top_k * rc + rcs) > kMaxPartialRows) continue;
-    const int units = (groups * rc + shared_groups * rcs) * (hidden / 256);
-    const double est = parts(units, n_cus) * (4.0 + 0.7 * cand);
-    if (est <= best) best = est, u.down_groups = cand, u.n_rc = rc, u.n_rc_shared = rcs;
-  }
-  return u;
-}
-}  // namespace
 
 int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, void *y_dev, int32_t n_tokens) {
   if (int rc = check_layer(c, layer)) return rc;
@@ -876,17 +922,15 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
   const int K = g.top_k, d = g.hidden;
   const size_t slot_bytes = (size_t)c->slot_layout.total;
   BatchParams bp{};
-  bp.slot_pool = static_cast<const uint8_t *>(c->slot_pool[layer]);
-  bp.shared_blob = g.shared_inter > 0 ? static_cast<const uint8_t *>(c->shared_blob[layer]) : nullptr;
-  bp.x = static_cast<const uint16_t *>(x_dev);
-  bp.sel = c->d_bsel;
-  bp.h = c->d_bh;
-  bp.partial = c->d_bpartial;
-  bp.slot_bytes = (int64_t)slot_bytes;
-  bp.hidden = d;
-  bp.inter = g.inter;
-  bp.shared_inter = g.shared_inter;
-  bp.top_k = K;
+  static_cast<BatchArgs &>(bp) = batch_args(c, layer, x_dev, n_tokens);
+  if (c->batch_x == x_dev) {  // the expert kernels are on their way
+    HIP_TRY(launch_planned_reduce(bp, c->d_bplan, y_dev, c->compute));
+    HIP_TRY(hipStreamSynchronize(c->compute));
+    c->batch_layer = -1;
+    c->batch_n = 0;
+    c->batch_x = nullptr;
+    return MOE_OK;
+  }
   // Segments: maximal runs of tokens during which no slot is refilled after a token of the run has read it, so that
   // all experts a segment needs are in their slots at once.
   int t0 = 0;
@@ -948,14 +992,10 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
       int n_up = 0, n_down = 0;
       bp.n_entries = 0;
       auto add = [&](int slot, int n_tok, int rows) {
-        const int groups = (n_tok + 63) / 64, n32 = (rows + 31) / 32;
-        int up = (rows + bu.up_records - 1) / bu.up_records, down = (n32 + bu.down_groups - 1) / bu.down_groups * (d / 256);
-        if (groups > 1) {
-          up = (up + 7) / 8 * 8 * groups;
-          down = (down + 7) / 8 * 8 * groups;
-        }
+        int up, down;
+        batch_entry_units(n_tok, rows, bu.up_records, bu.down_groups, d, &up, &down);
         bp.e[bp.n_entries++] = BatchEntry{(int16_t)slot, (uint16_t)n_tok, h_base, (uint32_t)n_up, (uint32_t)n_down};
-        h_base += (uint32_t)((n_tok + 15) / 16) * (uint32_t)n32;
+        h_base += (uint32_t)batch_parts(n_tok, 16) * (uint32_t)batch_parts(rows, 32);
         n_up += up;
         n_down += down;
       };
@@ -977,6 +1017,7 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
   HIP_TRY(hipStreamSynchronize(c->compute));
   c->batch_layer = -1;
   c->batch_n = 0;
+  c->batch_x = nullptr;
   return MOE_OK;
 }
 
@@ -1084,6 +1125,7 @@ int moe_cache_restore(moe_cache_t *c, int32_t layer, const void *buf, size_t byt
   if (st.count < 0 || st.selections < 0 || st.misses < 0) return fail(MOE_EINVAL, "snapshot counters negative");
   HIP_TRY(hipStreamSynchronize(c->compute));
   HIP_TRY(hipStreamSynchronize(c->copy));
+  c->batch_x = nullptr;  // (a batch routed before this is computed with what the slots hold after it)
   int64_t misses = 0;
   HIP_TRY(hipMemcpy(&misses, &c->state(layer)->misses, sizeof misses, hipMemcpyDeviceToHost));
   HIP_TRY(hipMemcpy(c->state(layer), &st, sizeof st, hipMemcpyHostToDevice));
