@@ -716,8 +716,8 @@ __device__ __forceinline__ void down_unit(const BatchArgs &p, const BatchEntry &
 #pragma unroll
     for (int i = 0; i < 8; ++i) w[i] = stream_load(reinterpret_cast<const u32x4 *>(q + i * rec_bytes + off));
   };
-  f32x4 ha[NT][2], hb[NT][2];
-  auto load_h = [&](int g, int i, f32x4 (&h)[NT][2]) {
+  f32x4 h[NT][2];
+  auto load_h = [&](int g, int i) {
 #pragma unroll
     for (int q = 0; q < 2; ++q)  // (tiles past the last repeat it; their rows are not stored)
       h[i][q] = *reinterpret_cast<const f32x4 *>(hbase + ((int64_t)min(i, tiles - 1) * n32 + g) * kHBlock + q * (kHBlock / 2) +
@@ -730,17 +730,19 @@ __device__ __forceinline__ void down_unit(const BatchArgs &p, const BatchEntry &
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[i][c][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // One group of 32 records; NEXT: there is a group after it, whose loads are requested as registers become free: its h
-  // into a second set ahead of its weights (loads complete in order, and h is wanted first).  With four token tiles
-  // everything but the accumulators lives in 256 registers: the order below is kept as written, or loads and splits of
-  // later tiles are moved up and spill.
-  auto step = [&](int g, const f32x4 (&h)[NT][2], f32x4 (&h_next)[NT][2], auto next_tag) {
+  // One group of 32 records; NEXT: there is a group after it, whose loads are requested as registers become free.  h is split
+  // first, once for both halves of the columns; its registers then take the next group's (requested ahead of its weights:
+  // loads complete in order, and h is wanted first).  With four token tiles everything but the accumulators lives in 256
+  // registers: the order below is kept as written, or loads of later tiles are moved up and spill.
+  auto step = [&](int g, auto next_tag) {
     constexpr bool NEXT = decltype(next_tag)::value;
-    if constexpr (NEXT) {
+    u32x4 a[NT][3];
 #pragma unroll
-      for (int i = 0; i < NT; ++i) load_h(g + kBWaves, i, h_next);
+    for (int i = 0; i < NT; ++i) {
+      split3(h[i][0], h[i][1], a[i]);
+      if constexpr (NEXT) load_h(g + kBWaves, i);
+      if constexpr (NT > 2) __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (NT > 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       u32x4 (&w)[8] = c == 0 ? w0 : w1;
@@ -754,29 +756,21 @@ __device__ __forceinline__ void down_unit(const BatchArgs &p, const BatchEntry &
       if constexpr (NEXT) load_w(g + kBWaves, c, w);
       if constexpr (NT > 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        u32x4 a[3];
-        split3(h[i][0], h[i][1], a);
-        if constexpr (NT > 2) __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < NT; ++i)
 #pragma unroll
         for (int q = 2; q >= 0; --q)  // the small parts first
 #pragma unroll
-          for (int j = 0; j < 8; ++j) acc[i][c][j] = mfma_bf16(a[q], col[j], acc[i][c][j]);
-      }
+          for (int j = 0; j < 8; ++j) acc[i][c][j] = mfma_bf16(a[i][q], col[j], acc[i][c][j]);
     }
   };
   int g = g_begin + wave, left = g < g_end ? (g_end - g + kBWaves - 1) / kBWaves : 0;
   if (left > 0) {
 #pragma unroll
-    for (int i = 0; i < NT; ++i) load_h(g, i, ha);
+    for (int i = 0; i < NT; ++i) load_h(g, i);
     load_w(g, 0, w0);
     load_w(g, 1, w1);
-    for (; left > 1; --left, g += kBWaves) {
-      step(g, ha, hb, std::true_type{});
-#pragma unroll
-      for (int i = 0; i < NT; ++i) ha[i][0] = hb[i][0], ha[i][1] = hb[i][1];
-    }
-    step(g, ha, hb, std::false_type{});
+    for (; left > 1; --left, g += kBWaves) step(g, std::true_type{});
+    step(g, std::false_type{});
   }
   // the tiles of the four wavefronts, one token tile at a time: [wave][16 rows][256 columns]
   token_list(p, e.slot, group, n_tok, lane, list);
