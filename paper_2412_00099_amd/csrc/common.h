@@ -160,6 +160,8 @@ GemvPlan gemv_plan(int n_cus, int total_records, int weight_fmt, int act_fmt, in
 // four experts (needs gate_rows_supported)
 bool gate_rows_supported(int hidden, int act_fmt);
 hipError_t launch_gate_rows(const RouteParams &p, const FusedParams &f, const void *gate_w, float *logits, hipStream_t s);
+// logits of a step on a given x, spread the same way
+hipError_t launch_gate_x(const RouteParams &p, const void *x, const void *gate_w, float *logits, hipStream_t s);
 bool gemv_fused_supported(int weight_fmt, int act_fmt, int hidden, const GemvPlan &plan);  // a launch variant with the boundary in workgroup 0
 // f.ss != nullptr: the glue has been done by launch_reduce_glue (needs fused_route_pre_supported(hidden))
 bool fused_route_pre_supported(int hidden);

@@ -582,6 +582,29 @@ static int finish_route_call(moe_cache_t *c, int32_t layer, uint32_t seq, moe_ro
   return MOE_OK;
 }
 
+// the routing of a step is left to every workgroup of its expert launch, which starts from the logits
+static void defer_routing(moe_cache_t *c, int32_t layer, const RouteParams &p, const float *logits) {
+  BoundaryArgs &b = c->boundary[layer];
+  b = BoundaryArgs{};
+  b.route = p;
+  b.state = c->state(layer);
+  b.state_out = c->d_state + (size_t)(1 - c->cur[layer]) * c->cfg.n_layers + layer;
+  b.logits = logits;
+  b.out_dev = c->d_route + layer;
+  b.note = c->h_note_dev + layer;
+  b.handover = c->d_handover + 64 * (size_t)layer;  // (read where an expert misses: the slot it is put into)
+  b.hand_tag = ++c->hand_count[layer] & 0xffffu;
+  b.gave_up = c->h_gave_up_dev;
+  b.spin_limit = c->tag_spins;
+  c->route_seq[layer] = p.seq;
+  c->routed[layer] = 4;
+}
+
+// whether that is the better way (see moe_cache_init)
+static bool routed_everywhere(const moe_cache_t *c) {
+  return c->cfg.route_mode == MOE_ROUTE_CUMSUM ? c->everywhere_cumsum : c->route_everywhere;
+}
+
 int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float *logits_dev,
                    moe_route_out_t *out_host) {
   if (int rc = check_layer(c, layer)) return rc;
@@ -591,6 +614,14 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
   if (c->batch_layer >= 0) return fail(MOE_ESTATE, "a routed batch is pending: call moe_expert_forward_batch first");
   c->x_given[layer] = nullptr;
   const RouteParams p = make_route_params(c);
+  if (!out_host && x_dev && routed_everywhere(c)) {
+    // nobody waits: only the logits are made by this call, over several compute units (route_kernel takes 8.9 us for 8 experts
+    // of d = 4096 or 64 of d = 2048, the logits alone 3)
+    float *logits = c->d_logits + (size_t)layer * MOE_MAX_EXPERTS;
+    HIP_TRY(launch_gate_x(p, x_dev, c->gate_w[layer], logits, c->compute));
+    defer_routing(c, layer, p, logits);
+    return MOE_OK;
+  }
   HIP_TRY(launch_route(p, c->gate_w[layer], x_dev, logits_dev, c->state(layer), c->d_route + layer,
                        HostOut{c->h_note_dev + layer, out_host ? c->h_rec_dev : nullptr}, c->compute));
   return finish_route_call(c, layer, p.seq, out_host, false);
@@ -600,8 +631,7 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
 static int boundary_form(const moe_cache_t *c) {
   if (c->fuse_boundary && gemv_fused_supported(c->cfg.weight_fmt, c->cfg.act_fmt, c->cfg.hidden, c->plan))
     return MOE_BOUNDARY_IN_FIRST_WORKGROUP;
-  return (c->cfg.route_mode == MOE_ROUTE_CUMSUM ? c->everywhere_cumsum : c->route_everywhere) ? MOE_BOUNDARY_ROUTED_EVERYWHERE
-                                                                                             : MOE_BOUNDARY_OWN_LAUNCH;
+  return routed_everywhere(c) ? MOE_BOUNDARY_ROUTED_EVERYWHERE : MOE_BOUNDARY_OWN_LAUNCH;
 }
 
 int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const float *a_dev, float perturb,
@@ -652,28 +682,16 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   }
   if (form == MOE_BOUNDARY_ROUTED_EVERYWHERE) {
     // nobody waits for the decision here: only x and the logits are made by this call (over several compute units), and
-    // every wavefront of the layer's expert launch routes for itself
+    // every workgroup of the layer's expert launch routes for itself.  (Doing the glue in the gate launch where a token begins
+    // saves a launch a token: 272 -> 266 us for 12 layer-tokens in stacks of 3 layers, less than 1 % in deeper ones; not done.)
     HIP_TRY(launch_reduce_glue(c->d_partial, c->pending_rows, c->pending_miss, y, c->cfg.hidden, c->cfg.act_fmt, h_dev, a_dev, perturb,
                                carry, c->d_ss, c->compute));
-    c->pending_rows = 0;
     f.ss = c->d_ss;
     f.n_ss = c->cfg.hidden / 64;
+    c->pending_rows = 0;
     float *logits = c->d_logits + (size_t)layer * MOE_MAX_EXPERTS;
     HIP_TRY(launch_gate_rows(p, f, c->gate_w[layer], logits, c->compute));
-    BoundaryArgs &b = c->boundary[layer];
-    b = BoundaryArgs{};
-    b.route = p;
-    b.state = c->state(layer);
-    b.state_out = c->d_state + (size_t)(1 - c->cur[layer]) * c->cfg.n_layers + layer;
-    b.logits = logits;
-    b.out_dev = c->d_route + layer;
-    b.note = c->h_note_dev + layer;
-    b.handover = c->d_handover + 64 * (size_t)layer;  // (read where an expert misses: the slot it is put into)
-    b.hand_tag = ++c->hand_count[layer] & 0xffffu;
-    b.gave_up = c->h_gave_up_dev;
-    b.spin_limit = c->tag_spins;
-    c->route_seq[layer] = p.seq;
-    c->routed[layer] = 4;
+    defer_routing(c, layer, p, logits);
     return MOE_OK;
   }
   if (fused_route_pre_supported(c->cfg.hidden)) {

@@ -61,33 +61,48 @@ __global__ __launch_bounds__(1024) void fused_route_kernel(RouteParams p, FusedP
 // the same operations in the same order as fused_boundary; the first writes it to memory.  The routing is left to the
 // expert launch (kRouteEverywhere).
 constexpr int kGateRowWaves = 4;
+// (scalar arguments: they arrive in registers)
 template <int D, bool BF16>
-__global__ __launch_bounds__(kGateRowWaves *kWave) void gate_rows_kernel(RouteParams p, FusedParams f, const void *gate_w, float *logits) {
+__global__ __launch_bounds__(kGateRowWaves *kWave) void gate_rows_kernel(const float *h, const float *ss, const void *gate_w, int n_experts,
+                                                                         void *x_out, float *logits) {
   constexpr int PER = D / (kGateRowWaves * kWave), CH = D / (kWave * (BF16 ? 8 : 4));
   __shared__ __attribute__((aligned(16))) uint32_t x_s[BF16 ? D / 2 : D];
   const int tid = threadIdx.x, lane = tid & 63;
   const int e = (int)blockIdx.x * kGateRowWaves + __builtin_amdgcn_readfirstlane(tid >> 6);
   float hv[PER];
-  load_f32<PER>(f.h + tid * PER, hv);
   OrderedSum<D / 64> blocks;
-  blocks.fetch(f.ss, lane);
+  load_f32<PER>(h + tid * PER, hv);
+  blocks.fetch(ss, lane);
   __builtin_amdgcn_sched_barrier(0);  // the small loads stay ahead of the gate row
   GateRegs<1, CH> g;
-  gate_prefetch<1, CH>(gate_w, min(e, p.n_experts - 1), 1, lane, g);
+  gate_prefetch<1, CH>(gate_w, min(e, n_experts - 1), 1, lane, g);
   const float scale = 1.0f / sqrtf(blocks.total() / (float)D + 1e-6f);
 #pragma unroll
   for (int i = 0; i < PER; ++i) hv[i] *= scale;
   if constexpr (BF16) {
     store_bf16<PER>(reinterpret_cast<uint16_t *>(x_s) + tid * PER, hv);
-    if (blockIdx.x == 0) store_bf16<PER>(static_cast<uint16_t *>(f.x_out) + tid * PER, hv);
+    if (blockIdx.x == 0) store_bf16<PER>(static_cast<uint16_t *>(x_out) + tid * PER, hv);
   } else {
     store_f32<PER>(reinterpret_cast<float *>(x_s) + tid * PER, hv);
-    if (blockIdx.x == 0) store_f32<PER>(static_cast<float *>(f.x_out) + tid * PER, hv);
+    if (blockIdx.x == 0) store_f32<PER>(static_cast<float *>(x_out) + tid * PER, hv);
   }
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  lds_barrier();
   float z[1];
   gate_dot<1, CH>(g, x_s, BF16 ? MOE_A_BF16 : MOE_A_FP32, lane, z);
-  if (lane == 0 && e < p.n_experts) logits[e] = z[0];
+  if (lane == 0 && e < n_experts) logits[e] = z[0];
+}
+
+// The logits of a step on a given x the same way (one row per wavefront, the sums in the order of gate_rows).
+template <int D, bool BF16>
+__global__ __launch_bounds__(kGateRowWaves *kWave) void gate_x_kernel(const void *x, const void *gate_w, int n_experts, float *logits) {
+  constexpr int CH = D / (kWave * (BF16 ? 8 : 4));
+  const int lane = threadIdx.x & 63;
+  const int e = (int)blockIdx.x * kGateRowWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  GateRegs<1, CH> g;
+  gate_prefetch<1, CH>(gate_w, min(e, n_experts - 1), 1, lane, g);
+  float z[1];
+  gate_dot<1, CH>(g, static_cast<const uint32_t *>(x), BF16 ? MOE_A_BF16 : MOE_A_FP32, lane, z);
+  if (lane == 0 && e < n_experts) logits[e] = z[0];
 }
 
 __global__ void state_init_kernel(LayerState *state, int n_layers, const int32_t *initial, int n_initial) {
@@ -177,13 +192,37 @@ hipError_t launch_gate_rows(const RouteParams &p, const FusedParams &f, const vo
   const dim3 g((p.n_experts + kGateRowWaves - 1) / kGateRowWaves), b(kGateRowWaves * kWave);
   const bool bf16 = p.act_fmt == MOE_A_BF16;
   if (!gate_rows_supported(p.hidden, p.act_fmt)) return hipErrorInvalidValue;
-#define MOE_GATE(D)                                                                                            \
-  do {                                                                                                         \
-    if (bf16) hipLaunchKernelGGL((gate_rows_kernel<D, true>), g, b, 0, s, p, f, gate_w, logits);               \
-    else hipLaunchKernelGGL((gate_rows_kernel<D, false>), g, b, 0, s, p, f, gate_w, logits);                   \
+#define MOE_GATE1(D, BF16)                                                                                       \
+  hipLaunchKernelGGL((gate_rows_kernel<D, BF16>), g, b, 0, s, f.h, f.ss, gate_w, p.n_experts, f.x_out, logits)
+#define MOE_GATE(D)                                                                                              \
+  do {                                                                                                           \
+    if (bf16) MOE_GATE1(D, true);                                                                                \
+    else MOE_GATE1(D, false);                                                                                    \
   } while (0)
   switch (p.hidden) {
-    case 256: hipLaunchKernelGGL((gate_rows_kernel<256, false>), g, b, 0, s, p, f, gate_w, logits); break;
+    case 256: MOE_GATE1(256, false); break;
+    case 512: MOE_GATE(512); break;
+    case 1024: MOE_GATE(1024); break;
+    case 2048: MOE_GATE(2048); break;
+    case 4096: MOE_GATE(4096); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef MOE_GATE
+#undef MOE_GATE1
+  return hipGetLastError();
+}
+
+hipError_t launch_gate_x(const RouteParams &p, const void *x, const void *gate_w, float *logits, hipStream_t s) {
+  const dim3 g((p.n_experts + kGateRowWaves - 1) / kGateRowWaves), b(kGateRowWaves * kWave);
+  const bool bf16 = p.act_fmt == MOE_A_BF16;
+  if (!gate_rows_supported(p.hidden, p.act_fmt)) return hipErrorInvalidValue;
+#define MOE_GATE(D)                                                                                              \
+  do {                                                                                                           \
+    if (bf16) hipLaunchKernelGGL((gate_x_kernel<D, true>), g, b, 0, s, x, gate_w, p.n_experts, logits);          \
+    else hipLaunchKernelGGL((gate_x_kernel<D, false>), g, b, 0, s, x, gate_w, p.n_experts, logits);              \
+  } while (0)
+  switch (p.hidden) {
+    case 256: hipLaunchKernelGGL((gate_x_kernel<256, false>), g, b, 0, s, x, gate_w, p.n_experts, logits); break;
     case 512: MOE_GATE(512); break;
     case 1024: MOE_GATE(1024); break;
     case 2048: MOE_GATE(2048); break;
