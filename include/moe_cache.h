@@ -152,7 +152,8 @@ void moe_cache_destroy(moe_cache_t *ctx);
  * non-NULL; the buffer must stay unchanged until the layer's moe_expert_forward has been called.
  * With out_host non-NULL the call returns once the decision is known on the host (written to *out_host)
  * and the copies filling missed experts' slots are enqueued on copy_stream.  With out_host NULL the call
- * only enqueues the router kernel, and moe_expert_forward takes care of the fills (see there).  MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
+ * only enqueues the gate logits or the router kernel (from large layers on the expert launch routes by itself), and
+ * moe_expert_forward takes care of the fills (see there).  MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
 int moe_route_step(moe_cache_t *ctx, int32_t layer, const void *x_dev, const float *logits_dev,
                    moe_route_out_t *out_host);
 
@@ -176,7 +177,8 @@ int moe_expert_forward(moe_cache_t *ctx, int32_t layer, const void *x_dev, void 
  * moe_route_step in the same order; only the arithmetic is batched (matrix cores).
  * moe_route_batch: exactly one of x_dev (device [n_tokens, d], act_fmt: the gate logits are computed) and logits_dev
  *   (device [n_tokens, N] fp32) is non-NULL.  Returns once all decisions are on the host; out_host (may be NULL)
- *   receives n_tokens records.  x_dev must stay unchanged until moe_expert_forward_batch.
+ *   receives n_tokens records.  x_dev must stay unchanged until moe_expert_forward_batch: with x_dev the expert kernels of a
+ *   batch that nothing misses in are enqueued behind the routing by this call already, and the other only adds the sum.
  * moe_expert_forward_batch: y[t] = sum_k w_k E_k(x[t]) + shared(x[t]) (Eq. 1) for every token of the batch routed
  *   last; x_dev as given to moe_route_batch, y_dev device [n_tokens, d] in act_fmt.  Tokens are grouped per expert;
  *   where a slot is refilled inside the batch after an earlier token has read it, the batch is cut there and the

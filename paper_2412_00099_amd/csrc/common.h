@@ -66,7 +66,7 @@ struct BoundaryArgs {
   const void *next_gate_w;
   const LayerState *next_state;
   int64_t gate_bytes;
-  // routing in every workgroup: the logits, and the copy of the state that receives the step (every wavefront of the
+  // routing in every workgroup: the logits, and the copy of the state that receives the step (every workgroup of the
   // launch reads the old one)
   const float *logits;
   LayerState *state_out;
@@ -76,7 +76,7 @@ enum RouteIn {
   kRouteBefore = 0,     // from the record an earlier launch wrote
   kRouteBoundary = 1,   // workgroup 0 runs the layer boundary `b`, hands the decision over and writes a zero partial row
   kRouteGiven = 3,      // from the launch's own arguments (given_slots, given_weight): all experts are in their slots
-  kRouteEverywhere = 2  // every wavefront routes for itself from b.logits and b.state; one workgroup more than plan.grid,
+  kRouteEverywhere = 2  // every workgroup routes for itself from b.logits and b.state; one workgroup more than plan.grid,
                         // the first, does the bookkeeping
 };
 

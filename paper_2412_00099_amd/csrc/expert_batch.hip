@@ -13,6 +13,9 @@
 //  up_batch_kernel, down_batch_kernel, reduce_batch_kernel
 //                      the experts as two weights-stationary products over the tokens routed to them, and the sum per
 //                      token in a fixed order (deterministic y).
+//  up_planned_kernel, down_planned_kernel
+//                      the same products where nobody waits between routing and experts: the units of work are listed on
+//                      the device by route_batch_kernel (make_plan), the grids are a few workgroups per compute unit.
 #include <type_traits>
 
 #include "common.h"

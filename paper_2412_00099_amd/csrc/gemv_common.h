@@ -70,7 +70,8 @@ __device__ __forceinline__ void wave_sum2(float &a, float &b) {
 // records need nothing from the routing step, so streaming starts at once while the loads of the routing
 // record are in flight; the record is unpacked when the first routed entry comes up.  Pass 0 covers the
 // shared expert and the experts that were resident; pass 1 covers only the experts whose slots were filled
-// for this token, so the first pass can run while the fills stream.
+// for this token, so the first pass can run while the fills stream.  With the host tier at hand (host_blob) the launch walks
+// twice instead: like pass 0, then over the experts that missed, straight from there (start_missing).
 //
 // Shares are equal and fixed.  With equal shares the workgroups do not finish together: the mean finish time of
 // a workgroup depends on its XCD (about 1.4 us between the fastest and the slowest of 8, the same from launch to

@@ -594,7 +594,7 @@ __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_
             (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)all_experts);
 }
 
-// Workgroup 0 of an expert launch in which every wavefront routes for itself: does the same step with everything that
+// Workgroup 0 of an expert launch in which every workgroup routes for itself: does the same step with everything that
 // goes with it - cache update, record, the host's note - from the old state to the new one.
 __device__ __forceinline__ void routing_workgroup(const GemvParams &p, float *red) {
   if (threadIdx.x >= kWave) return;
