@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "deal.h"
 
 namespace moe {
 
@@ -88,10 +89,7 @@ __device__ __forceinline__ u32x2 ld64(const void *p) { return *static_cast<const
 // workgroups 1..G-1 and the decision is fetched only when the first routed entry comes up, once workgroup 0 has handed it
 // over.  kRouteEverywhere: the same split, and the wavefronts of every workgroup work the decision out ahead of their first
 // routed record (decide_now: one place in the kernel, where few registers are in use).
-// STEP: distance between a wavefront's consecutive routed entries.  NW (the default) interleaves the wavefronts over
-// the workgroup's list; 1 gives every wavefront one contiguous block of it, so that its records stay inside one
-// expert and, for int4, inside one scale group of 128 records as far as possible.  Shared records are dealt out in turn
-// in both cases: every wavefront then has something to load while the decision is on its way.
+// STEP: distance between a wavefront's consecutive list entries (see deal).
 //
 // The walk is organised in runs - consecutive entries of the wavefront inside one blob (the shared expert, or one
 // selected expert) - so that the per-record work is an increment and a decrement; slot, weight and the split of the
@@ -104,12 +102,10 @@ __device__ void decide(const RouteParams &p, float z, int my_slot, float dsum_pr
 }
 template <int NW, int IN = kRouteBefore, int STEP = NW>
 struct RecordWalker {
-  static_assert(STEP == NW || STEP == 1, "interleaved or blocked");
   int sh_at, n_sh;   // the wavefront's shared records: first row, how many (not yet started)
   int r, n_rt;       // its routed entries: next index into the K*I routed records, how many are left to start
   int left;          // records left in the current run
   int next_at;       // row of the current run's next record
-  int run_step;      // distance between its records
   bool run_wanted;   // the pass covers the current run's expert
   bool run_shared;   // the current run is of shared records
   bool decided;      // the routing decision has been unpacked
@@ -207,24 +203,13 @@ struct RecordWalker {
     // the workgroup's list: ns shared records from row s0, then nr routed entries from q0
     const int s0 = bound(b, p.shared_q, p.shared_r, p.inv_g), ns = bound(b + 1, p.shared_q, p.shared_r, p.inv_g) - s0;
     const int q0 = bound(b, p.routed_q, p.routed_r, p.inv_g), nr = bound(b + 1, p.routed_q, p.routed_r, p.inv_g) - q0;
-    // the shared records are dealt to the wavefronts in turn
-    n_sh = wave < ns ? (ns - wave + NW - 1) / NW : 0;
-    const int first_sh = wave;
-    int first_rt;  // among the workgroup's routed entries
-    if constexpr (STEP == 1) {
-      // blocks of equal length; what is left over goes to the last wavefronts, as that of the shared records to the first
-      const int more = nr % NW, from = wave - (NW - more);
-      n_rt = nr / NW + (from >= 0);
-      first_rt = wave * (nr / NW) + max(0, from);
-    } else {
-      first_rt = wave + n_sh * NW - ns;
-      n_rt = first_rt < nr ? (nr - first_rt + NW - 1) / NW : 0;
-    }
-    sh_at = s0 + first_sh;
-    r = q0 + first_rt;
+    const Deal mine = deal<NW, STEP>(ns, nr, wave);
+    n_sh = mine.n_sh;
+    n_rt = mine.n_rt;
+    sh_at = s0 + mine.first_sh;
+    r = q0 + mine.first_rt;
     left = 0;
     next_at = 0;
-    run_step = STEP;
     at = 0;
     base = p.slot_pool;
     rows = p.inter;
@@ -323,7 +308,6 @@ struct RecordWalker {
       base = p.shared_blob;
       rows = p.shared_inter;
       next_at = sh_at;
-      run_step = NW;
       run_shared = true;
       left = n_sh;
       n_sh = 0;
@@ -338,7 +322,6 @@ struct RecordWalker {
 #pragma unroll
     for (int k = 1; k < MOE_MAX_TOPK; ++k) seg += r >= k * I;
     const int row = r - seg * I;
-    run_step = STEP;
     run_shared = false;
     const int in_seg = (I - row + STEP - 1) / STEP;  // this wavefront's entries inside expert `seg` from here on
     left = min(in_seg, n_rt);
@@ -397,7 +380,7 @@ struct RecordWalker {
     }
     fill = fill_blob;
     at = next_at;
-    next_at += run_step;
+    next_at += STEP;
     --left;
     return run_wanted;
   }
