@@ -373,8 +373,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
   if constexpr (IN == kRouteGiven) {
     reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
   } else {
-    // experts that missed: a second walk over them, into a second row (one launch does then what a first and a second pass
-    // do, in the same order)
+    // experts that missed: a second walk over them, into a second row (see RecordWalker::any_missing)
     __shared__ int missing_s[NW];
     missing_s[wave] = walk.any_missing(p);
     reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
@@ -383,7 +382,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     for (int w = 0; w < NW; ++w) missing |= missing_s[w];
     if (missing == 0) return;
     __syncthreads();
-    walk.start_missing();
+    walk.start_missing(wave);
 #pragma unroll
     for (int j = 0; j < CPL; ++j) y[j] = acc[j] = 0.f;
 #pragma unroll
@@ -691,8 +690,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   if constexpr (IN == kRouteGiven) {
     reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
   } else {
-    // experts that missed: a second walk over them, into a second row (one launch does then what a first and a second pass
-    // do, in the same order)
+    // experts that missed: a second walk over them, into a second row (see RecordWalker::any_missing)
     __shared__ int missing_s[NW];
     missing_s[wave] = walk.any_missing(p);
     reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
@@ -701,7 +699,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     for (int w = 0; w < NW; ++w) missing |= missing_s[w];
     if (missing == 0) return;
     __syncthreads();
-    walk.start_missing();
+    walk.start_missing(wave);
 #pragma unroll
     for (int j = 0; j < CPL; ++j) y[j] = acc[j] = 0.f;
 #pragma unroll

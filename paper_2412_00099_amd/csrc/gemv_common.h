@@ -115,7 +115,7 @@ struct RecordWalker {
   uint64_t experts;    // 8 bits each, like slots (kRouteBoundary, kRouteEverywhere)
   uint32_t miss_mask;
   bool no_decision;    // the hand-over did not come
-  int r0, n_rt0;       // r and n_rt at the start
+  int q0, nr;          // the workgroup's routed entries: the first one, how many
   bool missing_only;   // the walk covers the experts that missed, not the others
   uint8_t *fill_blob;  // the current run's expert comes from the host tier: the slot it is put into, else nullptr
   float z, dsum;       // kRouteEverywhere: lane's logit, Eq. 10's sum so far
@@ -202,7 +202,8 @@ struct RecordWalker {
     }
     // the workgroup's list: ns shared records from row s0, then nr routed entries from q0
     const int s0 = bound(b, p.shared_q, p.shared_r, p.inv_g), ns = bound(b + 1, p.shared_q, p.shared_r, p.inv_g) - s0;
-    const int q0 = bound(b, p.routed_q, p.routed_r, p.inv_g), nr = bound(b + 1, p.routed_q, p.routed_r, p.inv_g) - q0;
+    q0 = bound(b, p.routed_q, p.routed_r, p.inv_g);
+    nr = bound(b + 1, p.routed_q, p.routed_r, p.inv_g) - q0;
     const Deal mine = deal<NW, STEP>(ns, nr, wave);
     n_sh = mine.n_sh;
     n_rt = mine.n_rt;
@@ -219,8 +220,6 @@ struct RecordWalker {
     decided = false;
     no_decision = false;
     fill_blob = fill = nullptr;
-    r0 = r;
-    n_rt0 = n_rt;
     missing_only = p.pass == 1;
     if constexpr (IN == kRouteGiven) {
       const float *w = p.given_weight;
@@ -289,15 +288,18 @@ struct RecordWalker {
   }
 
   // One launch for everything (p.host_blob): whether a second walk is needed, over the experts that missed, and its start.
-  // The first walk has gone over the others as a first pass does, and the second one adds what a second pass would.
+  // The first walk has gone over the others as a first pass does; the second one is dealt to the wavefronts as a second pass
+  // deals its records, which has no shared ones, so that it adds the same in the same order.  (kRouteBoundary: a second pass
+  // streams with one workgroup more, so there the order is another.)
   __device__ __forceinline__ bool any_missing(const GemvParams &p) {
     if (IN == kRouteGiven || p.host_blob == nullptr) return false;
     ensure_decided(p);
     return miss_mask != 0;
   }
-  __device__ __forceinline__ void start_missing() {
-    r = r0;
-    n_rt = n_rt0;
+  __device__ __forceinline__ void start_missing(int wave) {
+    const Deal mine = deal<NW, STEP>(0, nr, wave);
+    r = q0 + mine.first_rt;
+    n_rt = mine.n_rt;
     n_sh = left = 0;
     missing_only = true;
   }

@@ -108,6 +108,36 @@ def test_same_outputs_as_with_fills_by_the_host(fmt, env, monkeypatch):
     assert float(((out[0][0] - out[1][0]).abs() / scale).max()) <= 2.0 ** -7  # two roundings to bf16
 
 
+@pytest.mark.parametrize("everywhere", ["0", "1"])
+@pytest.mark.parametrize("fmt,shared,inter", [("fp32", 200, 300), ("bf16", 520, 384), ("int8", 264, 1016), ("int4", 640, 1152)])
+def test_bit_for_bit_as_with_fills_by_the_host(fmt, shared, inter, everywhere, monkeypatch):
+    """With the boundary ahead of the expert launch the launch's second walk adds the same products in the same order as the
+    second launch behind fills by the host, beside a shared expert too."""
+    cfg = C2.with_(n_layers=2, hidden=2048, inter=inter, shared_inter=shared, n_experts=12, capacity=5, top_k=4, weight_fmt=fmt,
+                   act_fmt="fp32", seed=8300 + inter)
+    print(f"case device fills bit for bit {fmt} everywhere={everywhere}", flush=True)
+    monkeypatch.setenv("MOE_FUSE_BOUNDARY", "0")
+    monkeypatch.setenv("MOE_ROUTE_EVERYWHERE", everywhere)
+    out = []
+    for on in ("1", "0"):
+        monkeypatch.setenv("MOE_DEVICE_FILLS", on)
+        store, dec = build(cfg, lam=0.0)
+        h = torch.zeros(cfg.hidden, device=DEV)
+        x = torch.zeros(cfg.hidden, dtype=cfg.act_dtype, device=DEV)
+        a = workloads.ar1_stream(cfg, 8).to(DEV)
+        ys = torch.zeros(8, 2, cfg.hidden, dtype=cfg.act_dtype, device=DEV)
+        torch.cuda.synchronize()
+        for t in range(8):
+            for l in range(2):
+                dec.stack_route_step(l, h, a[t, l], 1.0 if l == 0 else 0.5, x, carry=l > 0, wait=False)
+                dec.expert_forward(l, x, ys[t, l])
+        st = dec.stats()
+        assert st.misses > 3 * cfg.top_k
+        out.append((ys.cpu(), bytes(st)))
+        dec.close()
+    assert torch.equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
+
+
 def test_host_tier_that_is_not_pinned(monkeypatch):
     """The launch cannot read such memory: the host enqueues the fills, as it does where it waits for the decision."""
     import paper_2412_00099_amd as pkg
