@@ -97,8 +97,8 @@ __device__ __forceinline__ u32x2 ld64(const void *p) { return *static_cast<const
 namespace rt {
 struct DecideLds;
 template <int NW>
-__device__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane, int wave, DecideLds &lds,
-                       uint64_t &slots, uint64_t &experts, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]);
+__device__ void decide(const RouteParams &p, float z, int my_slot, float dsum_prev, int t, int lane, int wave, const LayerState *fills,
+                       DecideLds &lds, uint64_t &slots, uint64_t &experts, uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]);
 }
 template <int NW, int IN = kRouteBefore, int STEP = NW>
 struct RecordWalker {
@@ -239,7 +239,8 @@ struct RecordWalker {
     asm volatile("" ::"s"(dsum), "s"(count), "s"(q.lambda), "s"(q.delta_fixed), "s"(q.cumsum_p), "s"(q.n_experts), "s"(q.top_k),
                  "s"(q.top_j), "s"(q.renormalize), "s"(q.delta_mode), "s"(q.route_mode), "s"(q.max_rank));
     float w[MOE_MAX_TOPK];
-    rt::decide<NW>(p.b.route, z, my_slot, dsum, count, (int)(threadIdx.x & 63), wave, lds, slots, experts, miss_mask, w);
+    rt::decide<NW>(p.b.route, z, my_slot, dsum, count, (int)(threadIdx.x & 63), wave, p.host_blob != nullptr ? p.b.state : nullptr,
+                   lds, slots, experts, miss_mask, w);
     rw0 = u32x4{__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
     rw1 = u32x4{__float_as_uint(w[4]), __float_as_uint(w[5]), __float_as_uint(w[6]), __float_as_uint(w[7])};
     decided = true;
@@ -340,31 +341,19 @@ struct RecordWalker {
   }
 
   // The run's expert was not resident: it is read from the host tier and put into its slot on the way (a rare case, kept out
-  // of line of the others).  Which slot that is is the routing workgroup's to say where every workgroup routes.
+  // of line of the others).
   __device__ __forceinline__ void from_host_tier(const GemvParams &p, int seg) {
     typedef const __attribute__((address_space(4))) int32_t *cint;
     typedef const __attribute__((address_space(4))) uint64_t *caddr;
-    uint32_t slot = (uint32_t)(slots >> (8 * seg)) & 0xffu, expert;
+    uint32_t expert;
     if constexpr (IN == kRouteBefore) {
       expert = (uint32_t)((cint)(reinterpret_cast<uintptr_t>(p.route)))[seg];
       static_assert(offsetof(moe_route_out_t, sel_expert) == 0, "record layout");
     } else {
       expert = (uint32_t)(experts >> (8 * seg)) & 0xffu;
-      if constexpr (IN == kRouteEverywhere) {
-        if (!load_handover(p.b.handover + 8 * ((int)blockIdx.x % 8), p.b.hand_tag, p.b.spin_limit)) {
-          no_decision = true;
-          run_wanted = false;
-          *p.b.gave_up = 1u;
-          return;
-        }
-        const uint64_t placed = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.y) |
-                                ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)rd.z) << 32);
-        slot = (uint32_t)(placed >> (8 * seg)) & 0xffu;
-      }
     }
+    fill_blob = const_cast<uint8_t *>(base);
     base = reinterpret_cast<const uint8_t *>(((caddr)(reinterpret_cast<uintptr_t>(p.host_blob)))[expert]);
-    fill_blob = const_cast<uint8_t *>(p.slot_pool) + (int64_t)slot * p.slot_bytes;
-    run_wanted = true;
   }
 
   // Move to this wavefront's next list entry and describe its record; whether there is one and the pass covers it.  The

@@ -592,10 +592,6 @@ static void defer_routing(moe_cache_t *c, int32_t layer, const RouteParams &p, c
   b.logits = logits;
   b.out_dev = c->d_route + layer;
   b.note = c->h_note_dev + layer;
-  b.handover = c->d_handover + 64 * (size_t)layer;  // (read where an expert misses: the slot it is put into)
-  b.hand_tag = ++c->hand_count[layer] & 0xffffu;
-  b.gave_up = c->h_gave_up_dev;
-  b.spin_limit = c->tag_spins;
   c->route_seq[layer] = p.seq;
   c->routed[layer] = 4;
 }

@@ -336,6 +336,38 @@ __device__ __forceinline__ Selected route_select(const RouteParams &p, float z, 
   return s;
 }
 
+// Where the experts that miss are put (Sec. 4.2): empty slots first, lowest index first, then those of the experts that were
+// touched longest ago and are not selected.  lane e <-> expert e, lane s <-> slot s.
+struct Places {
+  uint64_t empty;  // slots that hold nothing
+  int n_empty;
+  bool eligible;   // the lane's expert may lose its slot
+  int vrank;       // its position among those, oldest first
+};
+__device__ __forceinline__ Places lru_places(bool resident, bool sel, int slot_exp, int64_t stamp, int C, int n_miss, int lane) {
+  Places p;
+  p.empty = ballot(lane < C && slot_exp < 0);
+  p.n_empty = (int)__builtin_popcountll(p.empty);
+  p.eligible = resident && !sel;  // selected experts are never victims
+  p.vrank = 0;
+  if (n_miss > p.n_empty) {
+    for (uint64_t m = ballot(p.eligible); m; m &= m - 1)
+      p.vrank += (int64_t)readlane_u64((uint64_t)stamp, (int)__builtin_ctzll(m)) < stamp;
+  }
+  return p;
+}
+// the slot of the q-th miss in touch order (called for q = 0, 1, ... in turn), and the expert that loses it (-1: none)
+__device__ __forceinline__ int next_place(Places &p, int q, int my_slot, int &victim) {
+  victim = -1;
+  if (q < p.n_empty) {
+    const int s = (int)__builtin_ctzll(p.empty);
+    p.empty &= p.empty - 1;
+    return s;
+  }
+  victim = (int)__builtin_ctzll(ballot(p.eligible && p.vrank == q - p.n_empty));
+  return readlane_i(my_slot, victim);
+}
+
 // Everything after the logits (Eq. 3 softmax, Eq. 10, Eq. 9, Eq. 2, Eq. 4, Sec. 4.2), run by one wavefront.
 // host.note == nullptr: nobody on the host waits for this step (a token inside a batch).  host.rec: see HostRecord.  carry != nullptr: receives the
 // cache state as this step leaves it, so that a batch continues from registers; store_state = false then leaves the
@@ -379,28 +411,17 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
   int ordinal = 0;  // among the misses, in touch order
   for (uint64_t m = miss_mask; m; m &= m - 1) ordinal += readlane_i(pos, (int)__builtin_ctzll(m)) < pos;
 
-  uint64_t empty_mask = ballot(lane < C && slot_exp < 0);
-  const int n_empty = (int)__builtin_popcountll(empty_mask);
-  const bool eligible = resident && !sel;  // selected experts are never victims
-  const uint64_t elig_mask = ballot(eligible);
-  int vrank = 0;  // eligible experts ordered by stamp, oldest first
-  if (n_miss > n_empty) {
-    for (uint64_t m = elig_mask; m; m &= m - 1)
-      vrank += (int64_t)readlane_u64((uint64_t)stamp, (int)__builtin_ctzll(m)) < stamp;
-  }
+  Places places = lru_places(resident, sel, slot_exp, stamp, C, n_miss, lane);
   int my_evicted = -1;
   int born = cr.born;
   int cold = 0, evictions = 0, lifetime = 0;  // lifetime: tokens the evicted experts had stayed (Sec. 4.6)
   for (int q = 0; q < n_miss; ++q) {
     const int ml = (int)__builtin_ctzll(ballot(miss && ordinal == q));
-    int s, victim = -1;
-    if (q < n_empty) {
-      s = (int)__builtin_ctzll(empty_mask);
-      empty_mask &= empty_mask - 1;
+    int victim;
+    const int s = next_place(places, q, my_slot, victim);
+    if (victim < 0) {
       cold += !((ever_used >> s) & 1);
     } else {
-      victim = (int)__builtin_ctzll(ballot(eligible && vrank == q - n_empty));
-      s = readlane_i(my_slot, victim);
       lifetime += t - readlane_i(born, victim);
       if (lane == victim) my_slot = -1;
       ++evictions;
@@ -536,7 +557,9 @@ __device__ __forceinline__ void route_wave(const RouteParams &p, const float *z_
 }
 
 // What a streaming wavefront needs of the decision (see RecordWalker): slots 8 bits each, weights, miss flags, all in
-// selection order.  The experts that miss have no slot yet: slot 0, whose records are not loaded.  Run once per launch by
+// selection order.  For the experts that miss the slots that they are put into, worked out from the state `fills` (nullptr:
+// the launch does not fill, slot 0, whose records are not loaded): no workgroup has to learn them from another, which may not
+// be running yet where launches of several contexts share the device.  Run once per launch by
 // all NW wavefronts of a workgroup together: a chain of dependent instructions with the memory idle.  Every wavefront
 // ranks its share of the experts, and those among the first K are gathered through LDS (six of 64 experts, inside the
 // launch: 2.1 us with rounds of arg-max in every wavefront and lane reads by position, 1.2 us like this).
@@ -547,8 +570,8 @@ struct DecideLds {
 };
 template <int NW>
 __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_slot, float dsum_prev, int t, int lane, int wave,
-                                       DecideLds &lds, uint64_t &slots, uint64_t &experts, uint32_t &miss_mask,
-                                       float (&weight)[MOE_MAX_TOPK]) {
+                                       const LayerState *fills, DecideLds &lds, uint64_t &slots, uint64_t &experts,
+                                       uint32_t &miss_mask, float (&weight)[MOE_MAX_TOPK]) {
 #pragma clang fp contract(off)
   const int N = p.n_experts, K = p.top_k;
   const bool active = lane < N, own = owns_lane<NW>(lane, wave), resident = my_slot >= 0;
@@ -592,6 +615,26 @@ __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_
   slots = (((uint64_t)hi << 32) | lo) & (places >= 8 ? ~0ull : (1ull << (8 * places)) - 1ull);
   experts = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(all_experts >> 32)) << 32) |
             (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)all_experts);
+  if (fills != nullptr && miss_mask != 0) {
+    uint64_t sel_mask = 0;
+#pragma unroll
+    for (int k = 0; k < MOE_MAX_TOPK; ++k) sel_mask |= k < places ? 1ull << ((experts >> (8 * k)) & 63u) : 0ull;
+    const bool sel = ((sel_mask >> lane) & 1) != 0, missing = sel && !resident;
+    const uint64_t missing_mask = ballot(missing), touch = rank_key(z, lane, active);
+    const int n_miss = (int)__builtin_popcountll(missing_mask);
+    int ordinal = 0;  // among the misses, in touch order (descending logit)
+    for (uint64_t m = missing_mask; m; m &= m - 1) ordinal += readlane_u64(touch, (int)__builtin_ctzll(m)) > touch;
+    // (lanes past the last expert hold a copy of its slot)
+    Places at = lru_places(active && resident, sel, fills->slot_expert[lane], fills->stamp[lane], p.capacity, n_miss, lane);
+    for (int q = 0; q < n_miss; ++q) {
+      const uint32_t e = (uint32_t)__builtin_ctzll(ballot(missing && ordinal == q));
+      int victim;
+      const uint64_t s = (uint64_t)(uint32_t)next_place(at, q, my_slot, victim);
+#pragma unroll
+      for (int k = 0; k < MOE_MAX_TOPK; ++k)
+        if (k < places && (uint32_t)((experts >> (8 * k)) & 0xffu) == e) slots |= s << (8 * k);  // (slot 0 so far)
+    }
+  }
 }
 
 // Workgroup 0 of an expert launch in which every workgroup routes for itself: does the same step with everything that
@@ -601,7 +644,7 @@ __device__ __forceinline__ void routing_workgroup(const GemvParams &p, float *re
   const int lane = threadIdx.x;
   const CacheRegs cr = load_cache_regs(p.b.state, lane, p.b.route.n_experts, p.b.route.capacity);
   route_wave(p.b.route, p.b.logits, cr, p.b.state_out, p.b.out_dev, HostOut{p.b.note, nullptr}, reinterpret_cast<uint32_t *>(red),
-             lane, BoundaryFlags{p.b.handover, p.b.hand_tag});
+             lane);
 }
 
 // Gate rows of one wavefront held in registers: loaded before x exists, used once x is in LDS.

@@ -70,6 +70,39 @@ def test_slots_hold_the_host_tiers_bytes(fmt, hidden, inter, shared, everywhere,
     dec.close()
 
 
+@pytest.mark.parametrize("N,K,C,n_initial,mode,top_j", [(64, 8, 8, 0, 0, 0), (64, 8, 13, 5, 0, 2), (61, 7, 9, 9, 1, 1),
+                                                      (60, 8, 11, 4, 2, 0), (8, 1, 1, 0, 0, 0), (64, 5, 64, 20, 0, 0)])
+def test_every_workgroup_finds_the_slots_by_itself(N, K, C, n_initial, mode, top_j, monkeypatch):
+    """Where the routing is left to every workgroup, each works out into which slots the missing experts go; it does not wait
+    for the first one to say so (a limit of one poll changes nothing).  Empty slots, evictions and both at once, in every
+    routing mode: pools as the first workgroup's tables say, outputs and counters as with fills by the host."""
+    cfg = C2.with_(n_layers=1, hidden=512, inter=24, shared_inter=0, n_experts=N, capacity=C, top_k=K, seed=8500 + N + C)
+    print(f"case slots found in every workgroup N={N} K={K} C={C} initial={n_initial} mode={mode}", flush=True)
+    monkeypatch.setenv("MOE_FUSE_BOUNDARY", "0")
+    monkeypatch.setenv("MOE_ROUTE_EVERYWHERE", "1")
+    monkeypatch.setenv("MOE_TAG_SPINS", "1")
+    out = []
+    for on in ("1", "0"):
+        monkeypatch.setenv("MOE_DEVICE_FILLS", on)
+        store, dec = build(cfg, lam=0.1, top_j=top_j, initial=[list(range(N))[N - n_initial:]] if n_initial else None,
+                           route_mode=mode, max_rank=min(2 * K, N), cumsum_p=0.5)
+        xs = workloads.ar1_stream(cfg, 24)[:, 0].to(cfg.act_dtype).to(DEV)
+        ys = torch.zeros_like(xs)
+        torch.cuda.synchronize()
+        for t in range(24):
+            dec.route_step(0, x=xs[t], wait=False)
+            dec.expert_forward(0, xs[t], ys[t])
+        tables, st = dec.tables(0), dec.stats(0)
+        assert st.misses >= 5
+        pool = store.pools[0].cpu().numpy().reshape(C, store.blob_bytes)
+        for s in range(C):
+            e = tables.slot_expert[s]
+            assert e < 0 or np.array_equal(pool[s], store.host[0, e].numpy()), (s, e)
+        out.append((ys.cpu(), bytes(tables), bytes(st)))
+        dec.close()
+    assert torch.equal(out[0][0], out[1][0]) and out[0][1:] == out[1][1:]
+
+
 @pytest.mark.parametrize("fmt,hidden,inter,shared", SHAPES)
 def test_outputs(fmt, hidden, inter, shared):
     cfg = config(fmt, hidden, inter, shared)
