@@ -74,10 +74,11 @@ struct BoundaryArgs {
 // how an expert launch comes by the routing decision
 enum RouteIn {
   kRouteBefore = 0,     // from the record an earlier launch wrote
-  kRouteBoundary = 1,   // workgroup 0 runs the layer boundary `b`, hands the decision over and writes a zero partial row
+  kRouteBoundary = 1,   // workgroup 0 runs the layer boundary `b`, hands the decision over and writes a zero partial row; the
+                        // others wait for it (see WaitingTurn)
   kRouteGiven = 3,      // from the launch's own arguments (given_slots, given_weight): all experts are in their slots
-  kRouteEverywhere = 2  // every workgroup routes for itself from b.logits and b.state; one workgroup more than plan.grid,
-                        // the first, does the bookkeeping
+  kRouteEverywhere = 2  // every workgroup routes for itself from b.logits and b.state; the first does the bookkeeping: one
+                        // more than plan.grid, or (idle_row) one of them, whose partial row is then zero
 };
 
 struct GemvParams {
@@ -95,6 +96,7 @@ struct GemvParams {
   int32_t row_offset;  // first partial row this launch writes
   int32_t missing_row; // with host_blob: how many rows further on the sums over the experts that missed are written, if any did
   int32_t route_in;    // RouteIn
+  int32_t idle_row;    // kRouteEverywhere: 1 = plan.grid workgroups with the first one, which writes a zero row
   // the split of n records over the launch's G streaming workgroups (launch_expert_gemv fills it in): quotient and remainder
   // of the shared and of the routed records, and ceil(2^32 / G) to divide by G with one multiplication
   uint32_t shared_q, shared_r, routed_q, routed_r, inv_g;

@@ -323,7 +323,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_kernel(GemvParams p) {
     for (int j = 0; j < DEPTH; ++j) turn(ring[j], std::false_type{}, fill_tag);
   };
   walk_list(blocks_left, std::false_type{});
-  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d;
+  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere ? 1 - p.idle_row : 0)) * d;
   if constexpr (IN == kRouteGiven) {
     reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
   } else {
@@ -500,7 +500,7 @@ hipError_t launch_plan(const GemvParams &p, const GemvPlan &plan, hipStream_t s,
     }
   }
   if (p.route_in == kRouteEverywhere)
-    launch_one<FMT, LPR, kGemvWaves, gemv_depth(LPR), DOT2, kRouteEverywhere>(p, plan.grid + 1, s, e0, e1);
+    launch_one<FMT, LPR, kGemvWaves, gemv_depth(LPR), DOT2, kRouteEverywhere>(p, plan.grid + 1 - p.idle_row, s, e0, e1);
   else if (p.route_in == kRouteGiven)
     launch_one<FMT, LPR, kGemvWaves, gemv_depth(LPR), DOT2, kRouteGiven>(p, plan.grid, s, e0, e1);
   else
@@ -574,7 +574,8 @@ hipError_t launch_expert_gemv(const GemvParams &args, int weight_fmt, const Gemv
                               hipEvent_t e0, hipEvent_t e1) {
   if (!gemv_shape_supported(weight_fmt, args.hidden)) return hipErrorInvalidValue;
   GemvParams p = args;
-  const uint32_t G = (uint32_t)(plan.grid - (p.route_in == kRouteBoundary));  // workgroups that stream
+  if (p.route_in != kRouteEverywhere) p.idle_row = 0;
+  const uint32_t G = (uint32_t)(plan.grid - (p.route_in == kRouteBoundary) - p.idle_row);  // workgroups that stream
   if (G < 1 || G > 1024) return hipErrorInvalidValue;
   const uint32_t shared = p.pass == 0 ? (uint32_t)p.shared_inter : 0u, routed = (uint32_t)p.top_k * (uint32_t)p.inter;
   p.shared_q = shared / G;

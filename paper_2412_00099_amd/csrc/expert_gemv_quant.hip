@@ -369,7 +369,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     cur_base = nullptr;
   };
   walk_list(blocks_left, std::false_type{});
-  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d;
+  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere ? 1 - p.idle_row : 0)) * d;
   if constexpr (IN == kRouteGiven) {
     reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
   } else {
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     cur_base = nullptr;
   };
   walk_list(blocks_left, std::false_type{});
-  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere)) * d;
+  float *row = p.partial + (int64_t)(p.row_offset + (int)blockIdx.x - (IN == kRouteEverywhere ? 1 - p.idle_row : 0)) * d;
   if constexpr (IN == kRouteGiven) {
     reduce_and_store<NW, VEC, LPR>(y, red, row, tid, lane, wave);
   } else {
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
 
 hipError_t launch_expert_gemv_quant(const GemvParams &p, int weight_fmt, const GemvPlan &plan, hipStream_t s,
                                     hipEvent_t e0, hipEvent_t e1) {
-  const dim3 g(plan.grid + (p.route_in == kRouteEverywhere)), b(8 * kWave);
+  const dim3 g(plan.grid + (p.route_in == kRouteEverywhere ? 1 - p.idle_row : 0)), b(8 * kWave);
 #define MOE_Q(KERNEL, ...)                                                                      \
   do {                                                                                          \
     if (p.route_in == kRouteBoundary)                                                           \

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "common.h"
+#include "waiting_turn.h"
 
 using namespace moe;
 
@@ -44,6 +45,10 @@ __global__ void hold_stream_kernel(uint64_t ticks) {
   const uint64_t t0 = wall_clock64();
   for (int i = 0; i < 4096 && wall_clock64() - t0 < ticks; ++i) __builtin_amdgcn_s_sleep(8);
 }
+
+// per device: whose launches may wait for their first workgroup
+constexpr int kMaxDevices = 64;
+WaitingTurn g_turn[kMaxDevices];
 
 bool valid_wfmt(int f) { return f >= MOE_W_FP32 && f <= MOE_W_INT4_G128; }
 bool valid_afmt(int f) { return f == MOE_A_FP32 || f == MOE_A_BF16; }
@@ -125,6 +130,7 @@ struct moe_cache {
   uint8_t *d_bh = nullptr;                  // h of a segment (see up_batch_kernel)
   float *d_bpartial = nullptr;              // P of a segment: [kMaxPartialRows][hidden]
   int n_cus = 0;
+  int dev = 0;
   int batch_layer = -1, batch_n = 0;
   hipEvent_t ev_batch = nullptr;            // compute stream has finished reading the slots (before fills overwrite them)
 
@@ -172,6 +178,7 @@ int do_reset(moe_cache_t *c) {
   for (int copy = 0; copy < 2; ++copy)
     HIP_TRY(launch_state_init(c->d_state + (size_t)copy * c->cfg.n_layers, c->cfg.n_layers, c->d_initial, c->n_initial, c->compute));
   std::fill(c->cur.begin(), c->cur.end(), 0);
+  g_turn[c->dev].give_back(c);
   if (c->h_gave_up) __atomic_store_n(c->h_gave_up, 0u, __ATOMIC_RELAXED);
   c->pending_rows = 0;
   c->deferred = -1;
@@ -312,6 +319,8 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
 
   int dev = 0;
   HIP_INIT(hipGetDevice(&dev));
+  if (dev < 0 || dev >= kMaxDevices) HIP_INIT(hipErrorInvalidDevice);
+  c->dev = dev;
   int cus = 0;
   HIP_INIT(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   HIP_INIT(static_scratch_setup(dev, nullptr, nullptr));  // moe_expert_forward_static's scratch array on this device
@@ -427,6 +436,7 @@ void moe_cache_destroy(moe_cache_t *c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->compute);
   (void)hipStreamSynchronize(c->copy);
+  g_turn[c->dev].give_back(c);
   if (c->d_state) (void)hipFree(c->d_state);
   if (c->d_logits) (void)hipFree(c->d_logits);
   if (c->d_route) (void)hipFree(c->d_route);
@@ -747,6 +757,16 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   }
   p.pass = 0;
   p.row_offset = 0;
+  if (c->routed[layer] == 3 && !g_turn[c->dev].take(c, &c->h_note[layer].w[0], c->route_seq[layer])) {
+    // another context's launch may still be waiting for its first workgroup: the boundary ahead of the launch, the routing in
+    // every workgroup.  (The first workgroup still streams nothing, so that the sums are those of the other form.)
+    BoundaryArgs &b = c->boundary[layer];
+    float *logits = c->d_logits + (size_t)layer * MOE_MAX_EXPERTS;
+    HIP_TRY(launch_gate_rows(b.route, b.glue, c->gate_w[layer], logits, c->compute));
+    if (c->deferred == layer) c->deferred = -1;
+    defer_routing(c, layer, RouteParams(b.route), logits);
+    p.idle_row = 1;
+  }
   if (c->routed[layer] == 3) {
     p.route_in = kRouteBoundary;
     p.b = c->boundary[layer];
@@ -758,10 +778,12 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
   if (prof) {
     hipLaunchKernelGGL(hold_stream_kernel, dim3(1), dim3(64), 0, c->compute, (uint64_t)5000);  // 50 us
     HIP_TRY(hipGetLastError());
-    HIP_TRY(launch_expert_gemv(p, g.weight_fmt, c->plan, c->compute, c->prof_events[c->prof_used].first,
-                               c->prof_events[c->prof_used].second));
-  } else {
-    HIP_TRY(launch_expert_gemv(p, g.weight_fmt, c->plan, c->compute));
+  }
+  const hipError_t launched = launch_expert_gemv(p, g.weight_fmt, c->plan, c->compute, prof ? c->prof_events[c->prof_used].first : nullptr,
+                                                 prof ? c->prof_events[c->prof_used].second : nullptr);
+  if (launched != hipSuccess) {
+    g_turn[c->dev].give_back(c);
+    return fail(MOE_EHIP, "expert launch of layer %d: %s", layer, hipGetErrorString(launched));
   }
   if (c->deferred == layer) c->deferred = -1;
   if (p.route_in == kRouteEverywhere) c->cur[layer] ^= 1;  // the launch writes the other copy of the state

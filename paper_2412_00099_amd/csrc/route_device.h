@@ -640,7 +640,16 @@ __device__ __forceinline__ void decide(const RouteParams &p, float z_in, int my_
 // Workgroup 0 of an expert launch in which every workgroup routes for itself: does the same step with everything that
 // goes with it - cache update, record, the host's note - from the old state to the new one.
 __device__ __forceinline__ void routing_workgroup(const GemvParams &p, float *red) {
-  if (threadIdx.x >= kWave) return;
+  if (threadIdx.x >= kWave) {
+    if (p.idle_row != 0) {
+      float *row = p.partial + (int64_t)p.row_offset * p.hidden;
+      for (int j = (int)threadIdx.x - kWave; j < p.hidden; j += (int)blockDim.x - kWave) {
+        row[j] = 0.f;
+        if (p.host_blob != nullptr) row[(int64_t)p.missing_row * p.hidden + j] = 0.f;  // (whether or not anything misses)
+      }
+    }
+    return;
+  }
   const int lane = threadIdx.x;
   const CacheRegs cr = load_cache_regs(p.b.state, lane, p.b.route.n_experts, p.b.route.capacity);
   route_wave(p.b.route, p.b.logits, cr, p.b.state_out, p.b.out_dev, HostOut{p.b.note, nullptr}, reinterpret_cast<uint32_t *>(red),

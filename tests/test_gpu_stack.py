@@ -583,3 +583,69 @@ def test_the_form_of_the_boundary_follows_the_route_mode(monkeypatch):
         dec.close()
     for u, v in zip(*out):
         assert torch.equal(u, v) if isinstance(u, torch.Tensor) else u == v
+
+
+@pytest.mark.parametrize("weight,hidden,inter,shared", [("bf16", 2048, 24, 72), ("bf16", 512, 64, 0), ("int8", 4096, 24, 16),
+                                                       ("int4", 2048, 128, 128)])
+def test_contexts_in_flight_together(weight, hidden, inter, shared, monkeypatch):
+    """The boundary in the first workgroup of the expert launch has the others wait: only one context at a time may have such
+    launches on the device.  A decoder whose stream is held up has the turn; a second one (which would give up at its first
+    poll) goes through all of its tokens meanwhile, with the same bits as alone, misses among them; then the first one does."""
+    import paper_2412_00099_amd as pkg
+
+    cfg = CONFIGS["c2_qwen_bf16"].with_(n_layers=2, hidden=hidden, n_experts=12, inter=inter, shared_inter=shared, top_k=3,
+                                        capacity=5, weight_fmt=weight, act_fmt="bf16", seed=6200 + hidden)
+    print(f"case contexts in flight together {weight} d={hidden}", flush=True)
+    monkeypatch.setenv("MOE_FUSE_BOUNDARY", "1")
+    T = 8
+    stream = workloads.ar1_stream(cfg, T).to(DEV)
+
+    def run(dec, bufs):
+        h, x, y = bufs
+        for t in range(T):
+            for l in range(2):
+                dec.stack_route_step(l, h[t], stream[t, l], 1.0 if l == 0 else 0.5, x[t, l], carry=l > 0, wait=False)
+                dec.expert_forward(l, x[t, l], y[t] if l else None)
+
+    def buffers():
+        return (torch.zeros(T, hidden, device=DEV), torch.zeros(T, 2, hidden, dtype=cfg.act_dtype, device=DEV),
+                torch.zeros(T, hidden, dtype=cfg.act_dtype, device=DEV))
+
+    def result(dec, bufs):
+        dec.compute_stream.synchronize()
+        return [v.cpu() for v in bufs], [bytes(dec.tables(l)) for l in range(2)], bytes(dec.stats())
+
+    def same(u, v):
+        return all(torch.equal(p, q) for p, q in zip(u[0], v[0])) and u[1:] == v[1:]
+
+    _, alone = build(cfg, lam=0.5)
+    assert alone.boundary_form() == pkg.MOE_BOUNDARY_IN_FIRST_WORKGROUP
+    bufs = [buffers() for _ in range(4)]
+    torch.cuda.synchronize()
+    run(alone, bufs[0])
+    ref = result(alone, bufs[0])
+    alone.close()
+    assert alone.ctx is None and ref[0][2].float().abs().max() > 0
+
+    _, a = build(cfg, lam=0.5)
+    monkeypatch.setenv("MOE_TAG_SPINS", "1")
+    _, b = build(cfg, lam=0.5)
+    torch.cuda.synchronize()
+    held = torch.cuda.Event()
+    with torch.cuda.stream(a.compute_stream):
+        torch.cuda._sleep(400_000_000)  # a good part of a second
+        held.record()
+    run(a, bufs[1])
+    run(b, bufs[2])
+    assert not held.query()  # (all of b's steps were enqueued while none of a's were decided)
+    assert same(result(b, bufs[2]), ref)
+    assert same(result(a, bufs[1]), ref)
+    b.close()
+    # ... and once a's decisions are known the turn is free again
+    monkeypatch.delenv("MOE_TAG_SPINS")
+    _, c = build(cfg, lam=0.5)
+    torch.cuda.synchronize()
+    run(c, bufs[3])
+    assert same(result(c, bufs[3]), ref)
+    a.close()
+    c.close()
