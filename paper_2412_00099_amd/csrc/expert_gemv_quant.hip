@@ -292,16 +292,19 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     wave_sum2(g, u);
     g *= R.sg;
     u *= R.su;
-    return g / (1.f + __expf(-g)) * u * R.wt;
+    return g / (1.f + __expf(-g)) * u;
   };
-  auto down_part = [&](const RecI8<LPR> &R, float h) MOE_INLINE {
+  // (a: the record's activation, before its weight.  h enters its sum unrounded, whichever copy of the walk adds it: left to
+  // the compiler that depends on whether product and sum end up in one block)
+  auto down_part = [&](const RecI8<LPR> &R, float a) MOE_INLINE {
     if (R.base != cur_base) {
       if (cur_base) flush(cur_base, cur_rows);
       cur_base = R.base;
       cur_rows = R.rows;
       load_scales(cur_base, cur_rows);
     }
-    hsum += h;
+    const float h = a * R.wt;
+    hsum = __builtin_fmaf(a, R.wt, hsum);
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
       const uint32_t dw[4] = {R.dn[c].x, R.dn[c].y, R.dn[c].z, R.dn[c].w};
@@ -325,9 +328,9 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
   // A ring of DEPTH records, refilled in two parts (see expert_gemv_kernel).  37 MB at d = 2048: 13.1 -> 12.1 us
   auto turn = [&](RecI8<LPR> &R, auto refill_tag, auto fill_tag) MOE_INLINE {
     constexpr bool REFILL = decltype(refill_tag)::value, FILL = decltype(fill_tag)::value;  // FILL: into a slot on the way
-    float h = 0.f;
+    float a = 0.f;
     if (R.want) {
-      h = up_part(R);
+      a = up_part(R);
       if constexpr (FILL) {
         uint8_t *to = R.fill + (int64_t)R.at * rec_bytes;
         put(to, R.g);
@@ -341,7 +344,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
       q = load_up(R, want);
     }
     if (R.want) {
-      down_part(R, h);
+      down_part(R, a);
       if constexpr (FILL) {
         put(R.fill + (int64_t)R.at * rec_bytes + 2 * kRowBytes, R.dn);
         const int64_t tail = (int64_t)R.rows * rec_bytes;
@@ -599,9 +602,9 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
       u = __builtin_fmaf((u0 + u1) + xoff[c], f16_hi(R.sc[c]), u);
     }
     wave_sum2(g, u);
-    return g / (1.f + __expf(-g)) * u * R.wt;
+    return g / (1.f + __expf(-g)) * u;
   };
-  auto down_part = [&](const RecI4<LPR> &R, float h) MOE_INLINE {
+  auto down_part = [&](const RecI4<LPR> &R, float a) MOE_INLINE {  // (see expert_gemv_int8_kernel)
     if (R.base != cur_base || (R.at >> 7) != cur_grp) {
       if (dirty) flush(cur_base, cur_rows, cur_grp);
       cur_base = R.base;
@@ -609,7 +612,8 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
       cur_grp = (R.at >> 7);
       load_scales(cur_base, cur_rows, cur_grp);
     }
-    hsum += h;
+    const float h = a * R.wt;
+    hsum = __builtin_fmaf(a, R.wt, hsum);
     dirty = true;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
@@ -641,9 +645,9 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   // instead of 6.9, and the last wavefront has stored its row at 8.9 instead of 13.2.
   auto turn = [&](RecI4<LPR> &R, auto refill_tag, auto fill_tag) MOE_INLINE {
     constexpr bool REFILL = decltype(refill_tag)::value, FILL = decltype(fill_tag)::value;  // FILL: into a slot on the way
-    float h = 0.f;
+    float a = 0.f;
     if (R.want) {
-      h = up_part(R);
+      a = up_part(R);
       if constexpr (FILL) {
         uint8_t *to = R.fill + (int64_t)R.at * rec_bytes;
         put(to, R.g);
@@ -661,7 +665,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
       q = load_up(R, want);
     }
     if (R.want) {
-      down_part(R, h);
+      down_part(R, a);
       if constexpr (FILL) {
         put(R.fill + (int64_t)R.at * rec_bytes + 2 * kRowBytes, R.dn);
         const int64_t tail = (int64_t)R.rows * rec_bytes;
