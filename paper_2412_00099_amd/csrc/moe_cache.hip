@@ -144,12 +144,23 @@ struct moe_cache {
 
 namespace {
 
+int check_waits(const moe_cache_t *ctx) {
+  if (ctx->h_gave_up && __atomic_load_n(ctx->h_gave_up, __ATOMIC_ACQUIRE) != 0)
+    return fail(MOE_EHIP, "an expert kernel gave up waiting for the layer boundary of its own launch: outputs since then are invalid");
+  return MOE_OK;
+}
+
 int check_layer(const moe_cache_t *ctx, int32_t layer) {
   if (!ctx) return fail(MOE_EINVAL, "context is NULL");
   if (layer < 0 || layer >= ctx->cfg.n_layers) return fail(MOE_EINVAL, "layer %d out of range [0,%d)", layer, ctx->cfg.n_layers);
-  if (ctx->h_gave_up && __atomic_load_n(ctx->h_gave_up, __ATOMIC_RELAXED) != 0)
-    return fail(MOE_EHIP, "an expert kernel gave up waiting for the layer boundary of its own launch: outputs since then are invalid");
-  return MOE_OK;
+  return check_waits(ctx);
+}
+
+// Everything enqueued on the compute stream has run.  The host may be many tokens ahead when it asks, so a wait that ran out
+// in one of the launches that were still queued is known only now.
+int sync_compute(const moe_cache_t *ctx) {
+  HIP_TRY(hipStreamSynchronize(ctx->compute));
+  return check_waits(ctx);
 }
 
 // Polls until arrived() or, after 200 ms (or at once without polling: MOE_HOST_SYNC=event), the end of what has been
@@ -522,8 +533,7 @@ static int collect_route(moe_cache_t *c, int32_t layer, uint32_t seq, int *n_mis
 // the full decision record of a layer, from device memory (waits for the compute stream)
 static int fetch_record(moe_cache_t *c, int32_t layer, moe_route_out_t *out) {
   HIP_TRY(hipMemcpyAsync(out, c->d_route + layer, sizeof *out, hipMemcpyDeviceToHost, c->compute));
-  HIP_TRY(hipStreamSynchronize(c->compute));
-  return MOE_OK;
+  return sync_compute(c);
 }
 
 static RouteParams make_route_params(moe_cache_t *c) {
@@ -1070,7 +1080,7 @@ int moe_cache_stats(moe_cache_t *c, int32_t layer, moe_cache_stats_t *out) {
   for (int l = 0; l < c->cfg.n_layers; ++l)
     if (layer == -1 || l == layer)
       if (int rc = settle(c, l)) return rc;
-  HIP_TRY(hipStreamSynchronize(c->compute));
+  if (int rc = sync_compute(c)) return rc;
   std::vector<LayerState> both(2 * (size_t)c->cfg.n_layers);
   HIP_TRY(hipMemcpy(both.data(), c->d_state, sizeof(LayerState) * both.size(), hipMemcpyDeviceToHost));
   memset(out, 0, sizeof *out);
@@ -1097,7 +1107,7 @@ int moe_cache_tables(moe_cache_t *c, int32_t layer, moe_cache_tables_t *out) {
   if (int rc = check_layer(c, layer)) return rc;
   if (!out) return fail(MOE_EINVAL, "out is NULL");
   if (int rc = settle(c, layer)) return rc;
-  HIP_TRY(hipStreamSynchronize(c->compute));
+  if (int rc = sync_compute(c)) return rc;
   LayerState st;
   HIP_TRY(hipMemcpy(&st, c->state(layer), sizeof st, hipMemcpyDeviceToHost));
   memcpy(out->expert_slot, st.expert_slot, sizeof out->expert_slot);
@@ -1125,7 +1135,7 @@ int moe_cache_snapshot(moe_cache_t *c, int32_t layer, void *buf, size_t *bytes) 
   if (!buf) return MOE_OK;
   if (have < kSnapBytes) return fail(MOE_EINVAL, "snapshot needs %zu bytes, buffer has %zu", kSnapBytes, have);
   if (int rc = settle(c, layer)) return rc;
-  HIP_TRY(hipStreamSynchronize(c->compute));
+  if (int rc = sync_compute(c)) return rc;
   SnapshotHeader hd{kSnapMagic, kSnapVersion, c->cfg.n_experts, c->cfg.capacity, c->cfg.top_k, 0};
   memcpy(buf, &hd, sizeof hd);
   HIP_TRY(hipMemcpy(static_cast<uint8_t *>(buf) + sizeof hd, c->state(layer), sizeof(LayerState),
@@ -1159,7 +1169,7 @@ int moe_cache_restore(moe_cache_t *c, int32_t layer, const void *buf, size_t byt
     if (!ok) return fail(MOE_EINVAL, "snapshot tables inconsistent at slot %d", s);
   }
   if (st.count < 0 || st.selections < 0 || st.misses < 0) return fail(MOE_EINVAL, "snapshot counters negative");
-  HIP_TRY(hipStreamSynchronize(c->compute));
+  if (int rc = sync_compute(c)) return rc;
   HIP_TRY(hipStreamSynchronize(c->copy));
   c->batch_x = nullptr;  // (a batch routed before this is computed with what the slots hold after it)
   int64_t misses = 0;

@@ -216,6 +216,34 @@ def test_bounded_wait_error_path_and_reset(monkeypatch):
     dec.close()
 
 
+@pytest.mark.parametrize("ask", ["stats", "tables", "snapshot", "last_route"])
+def test_a_wait_that_runs_out_in_a_queued_launch_is_reported(ask, monkeypatch):
+    """The host is ahead of the device: the launch whose workgroups stop waiting is still queued when the caller asks.  The
+    call that waits for the stream reports it, not the one behind it.  (The stream is held by a kernel of a fixed length.)"""
+    import paper_2412_00099_amd as pkg
+
+    cfg = CONFIGS["c2_qwen_bf16"].with_(n_layers=1, hidden=512, n_experts=12, inter=64, shared_inter=0, capacity=5,
+                                        top_k=4, seed=77)
+    monkeypatch.setenv("MOE_FUSE_BOUNDARY", "1")
+    monkeypatch.setenv("MOE_TAG_SPINS", "1")
+    store, dec = build(cfg, lam=0.5)
+    a = workloads.ar1_stream(cfg, 1).to(DEV)
+    h = torch.zeros(cfg.hidden, device=DEV)
+    x = torch.zeros(cfg.hidden, dtype=cfg.act_dtype, device=DEV)
+    torch.cuda.synchronize()
+    print(f"case bounded wait in a queued launch: {ask}", flush=True)
+    with torch.cuda.stream(dec.compute_stream):
+        torch.cuda._sleep(20_000_000)  # some 10 ms
+    dec.stack_route_step(0, h, a[0, 0], 1.0, x, carry=False, y=None, wait=False)
+    dec.expert_forward(0, x, None)
+    with pytest.raises(pkg.MoEError) as e:
+        getattr(dec, ask)(0)
+    assert e.value.code == pkg.MOE_EHIP
+    dec.reset()
+    assert dec.stats(0).tokens == 0
+    dec.close()
+
+
 def test_launch_timing_counts_and_strides():
     """moe_cache_profile: events on every n-th first-pass expert launch; only launches that covered a whole layer
     (no expert missing) are averaged."""
