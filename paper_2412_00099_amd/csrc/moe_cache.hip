@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "batch_places.h"
 #include "common.h"
 #include "waiting_turn.h"
 
@@ -929,26 +930,23 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
   if (int rc = wait_for(c, [&]() { return __atomic_load_n(c->h_done, __ATOMIC_ACQUIRE) == p.seq; }, &ok)) return rc;
   if (!ok) return fail(MOE_EHIP, "batch routing of layer %d did not publish its records", layer);
   const moe_cache_config_t &g = c->cfg;
-  int n_of_slot[MOE_MAX_EXPERTS] = {};
-  for (int t = 0; t < n_tokens; ++t)
-    for (int k = 0; k < g.top_k; ++k) {
-      const moe_route_out_t &r = c->batch_rec[t];
-      if (r.miss[k]) c->batch_x = nullptr;
-      else ++n_of_slot[r.sel_slot[k]];
-      if (r.sel_expert[k] < 0 || r.sel_expert[k] >= g.n_experts || r.sel_slot[k] < 0 || r.sel_slot[k] >= g.capacity)
-        return fail(MOE_EHIP, "batch routing returned expert %d slot %d out of range", r.sel_expert[k], r.sel_slot[k]);
-    }
+  BatchPlaces places;
+  if (const moe_route_out_t *r = places.count(c->batch_rec, n_tokens, g.top_k, g.n_experts, g.capacity)) {
+    c->batch_x = nullptr;
+    return fail(MOE_EHIP, "batch routing returned an expert or a slot out of range (token %d)", r->token);
+  }
+  if (places.misses > 0) c->batch_x = nullptr;
   if (c->batch_x) {  // the device's list has to fit its launches (see make_plan)
     const int sg = g.shared_inter > 0 ? batch_parts(n_tokens, 64) : 0;
     int groups = 0, n_up = 0, n_down = 0, up, down;
-    for (int n : n_of_slot) groups += batch_parts(n, 64);
+    for (int n : places.of_slot) groups += batch_parts(n, 64);
     const BatchUnits bu = batch_units(groups, g.inter, sg, g.shared_inter, g.hidden, n_tokens, g.top_k, c->n_cus);
     const auto add = [&](int n, int rows) {
       batch_entry_units(n, rows, bu.up_records, bu.down_groups, g.hidden, &up, &down);
       n_up += up;
       n_down += down;
     };
-    for (int n : n_of_slot)
+    for (int n : places.of_slot)
       if (n > 0) add(n, g.inter);
     if (sg) add(n_tokens, g.shared_inter);
     if (std::max(n_up, n_down) > kPlanRounds * c->n_cus) c->batch_x = nullptr;
