@@ -133,6 +133,7 @@ struct moe_cache {
   int n_cus = 0;
   int dev = 0;
   int batch_layer = -1, batch_n = 0;
+  int batch_misses = 0;                     // fills that moe_expert_forward_batch has not enqueued yet
   hipEvent_t ev_batch = nullptr;            // compute stream has finished reading the slots (before fills overwrite them)
 
   // optional timing of the expert GEMV launches
@@ -954,6 +955,7 @@ int moe_route_batch(moe_cache_t *c, int32_t layer, const void *x_dev, const floa
   if (out_host) memcpy(out_host, c->batch_rec, sizeof(moe_route_out_t) * n_tokens);
   c->batch_layer = layer;
   c->batch_n = n_tokens;
+  c->batch_misses = places.misses;
   return MOE_OK;
 }
 
@@ -1012,6 +1014,7 @@ int moe_expert_forward_batch(moe_cache_t *c, int32_t layer, const void *x_dev, v
                                hipMemcpyHostToDevice, c->copy));
       }
     }
+    c->batch_misses -= n_fill;
     if (n_fill > 0) HIP_TRY(hipEventRecord(c->ev_copy[layer], c->copy));
     // Sizes of the units of the two expert kernels (see batch_units): chosen for the whole segment
     const int n_seg = t1 - t0;
@@ -1092,8 +1095,9 @@ int moe_cache_stats(moe_cache_t *c, int32_t layer, moe_cache_stats_t *out) {
     out->cold_misses += st.cold_misses;
     out->evictions += st.evictions;
     out->lifetime_sum += st.lifetime_sum;
-    // a miss is a fill, except that those of a step whose moe_expert_forward has not been called are still to come
-    int32_t to_come = 0;
+    // a miss is a fill, except that those of a step or batch whose moe_expert_forward(_batch) has not been called are still
+    // to come
+    int32_t to_come = l == c->batch_layer ? c->batch_misses : 0;
     if (c->routed[l] >= 2)
       HIP_TRY(hipMemcpy(&to_come, &c->d_route[l].n_miss, sizeof to_come, hipMemcpyDeviceToHost));
     out->bytes_filled += c->bytes_filled[l] + (st.misses - c->miss_base[l] - to_come) * c->slot_layout.total;

@@ -456,3 +456,24 @@ def test_infinite_weights_stay_infinities():
         assert not u[t][fin[t]].any() and not v[t][fin[t]].any() or oexp.rel_err(v[t][fin[t]], u[t][fin[t]]) <= 1e-2, t
     one.close()
     many.close()
+
+
+def test_bytes_filled_of_a_batch_that_is_still_to_be_computed():
+    """Between moe_route_batch and moe_expert_forward_batch the counters have the batch's misses, and bytes_filled has what
+    has been filled: nothing of it yet."""
+    cfg = BASE.with_(n_layers=2, hidden=1024, n_experts=12, inter=32, shared_inter=32, top_k=3, capacity=5, seed=640)
+    print("case prompt bytes filled", flush=True)
+    store, dec = build(cfg, lam=0.0)
+    xs = workloads.ar1_stream(cfg, 40)[:, 0].to(cfg.act_dtype).to(DEV)
+    ys = torch.zeros_like(xs)
+    torch.cuda.synchronize()
+    filled = 0
+    for t0, n in ((0, 5), (5, 35)):
+        dec.route_batch(1, x=xs[t0:t0 + n])
+        for layer in (1, -1):
+            st = dec.stats(layer)
+            assert st.bytes_filled == filled and st.misses * store.blob_bytes > filled
+        dec.expert_forward_batch(1, xs[t0:t0 + n], ys[t0:t0 + n])
+        filled = st.misses * store.blob_bytes
+        assert dec.stats(1).bytes_filled == filled and dec.stats(0).bytes_filled == 0
+    dec.close()
