@@ -149,11 +149,12 @@ void moe_cache_destroy(moe_cache_t *ctx);
 
 /* Routing step of one layer for one token (Eq. 3, Eq. 9-10, Eq. 4, Sec. 4.2): exactly one of x_dev
  * (device [d], act_fmt: the router GEMV is computed) and logits_dev (device [N] fp32: used as z) is
- * non-NULL; the buffer must stay unchanged until the layer's moe_expert_forward has been called.
+ * non-NULL.  logits_dev must stay unchanged until this call (out_host given) or the layer's moe_expert_forward has
+ * returned.  x_dev is read by kernels of both calls and must stay unchanged until compute_stream has run them.
  * With out_host non-NULL the call returns once the decision is known on the host (written to *out_host)
  * and the copies filling missed experts' slots are enqueued on copy_stream.  With out_host NULL the call
- * only enqueues the gate logits or the router kernel (from large layers on the expert launch routes by itself), and
- * moe_expert_forward takes care of the fills (see there).  MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
+ * only enqueues the router kernel or, with x_dev and from d = 1024 on, the gate logits alone (the expert launch then
+ * routes by itself; smaller d: from 10 MB a layer-token on), and moe_expert_forward takes care of the fills (see there).  MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
 int moe_route_step(moe_cache_t *ctx, int32_t layer, const void *x_dev, const float *logits_dev,
                    moe_route_out_t *out_host);
 
@@ -162,8 +163,10 @@ int moe_route_step(moe_cache_t *ctx, int32_t layer, const void *x_dev, const flo
  * After a routing step that was waited for, a first launch covers the shared expert and the experts that were
  * resident, a second one (behind the fills) the experts that were missing.
  * After one that was not (out_host NULL), one launch covers everything: it reads the experts that miss from the host
- * blobs itself, computes with them and puts them into their slots on the way; the call returns at once.  That needs all
- * host blobs in pinned memory that the device can read; where some are not (or with MOE_DEVICE_FILLS=0 in the environment
+ * blobs itself, computes with them and puts them into their slots on the way; the call returns at once (after a step
+ * on given logits: once these have been read).  Whatever its kernels read - x_dev, h_dev and a_dev of a
+ * moe_stack_route_step, the host blobs - then has to stay valid and unchanged until compute_stream has run them, not only
+ * until the call returns.  That needs all host blobs in pinned memory that the device can read; where some are not (or with MOE_DEVICE_FILLS=0 in the environment
  * at moe_cache_init) the call waits for the decision, enqueues the fills on copy_stream and proceeds as above.
  * A step cannot be captured into a graph (MOE_EHIP).  MOE_ESTATE without a preceding moe_route_step.
  * y_dev may be NULL: the output then stays inside the library as fp32 partial sums and is finished by the next
@@ -222,7 +225,8 @@ int moe_expert_forward_static(int32_t weight_fmt, int32_t act_fmt, int32_t hidde
  * does them while the others already stream the shared expert; see moe_cache_plan), or the routing alone (every
  * workgroup then works the decision out from the logits): x_dev and the routing record may then be written by the kernels
  * moe_expert_forward enqueues, not by this call's, so nothing but moe_expert_forward(ctx, layer, x_dev, ...) and
- * further calls of moe_stack_route_step may use h_dev and x_dev in between, and that call must be given the same x_dev
+ * further calls of moe_stack_route_step may use h_dev and x_dev in between (a_dev is read by a kernel that this call
+ * enqueues and must stay unchanged until compute_stream has run it), and that call must be given the same x_dev
  * (another one is refused with MOE_EINVAL where the shape has the first form and a third of a layer's records or more are
  * the shared expert's).  Counters, tables and snapshots taken in between include the step.
  * The other workgroups' wait for the first one is bounded; should it ever run out, they finish without the routed

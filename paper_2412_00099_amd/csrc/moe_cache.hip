@@ -109,6 +109,7 @@ struct moe_cache {
                                       // 4 routing deferred into every workgroup of it
   bool x_fixed = false;               // a non-blocking boundary's x_dev is the only one its moe_expert_forward takes
   std::vector<const void *> x_given;  // per layer: that x_dev, or nullptr
+  std::vector<uint8_t> logits_given;  // per layer: the pending step reads the caller's logits
   int deferred = -1;                  // the layer in state 3: its launch forms x from the caller's h and d_ss
   std::vector<uint32_t> route_seq;    // per layer: completion tag of the pending route step
   std::vector<uint32_t> hand_count;   // per layer: hand-overs inside an expert launch so far
@@ -313,6 +314,7 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   c->decided.assign(L, {});
   c->boundary.assign(L, BoundaryArgs{});
   c->x_given.assign(L, nullptr);
+  c->logits_given.assign(L, 0);
   c->bytes_filled.assign(L, 0);
   c->miss_base.assign(L, 0);
   c->ev_copy.assign(L, nullptr);
@@ -631,6 +633,7 @@ int moe_route_step(moe_cache_t *c, int32_t layer, const void *x_dev, const float
   if (c->pending_rows) return fail(MOE_ESTATE, "an expert output is pending: the next routing call must be moe_stack_route_step");
   if (c->batch_layer >= 0) return fail(MOE_ESTATE, "a routed batch is pending: call moe_expert_forward_batch first");
   c->x_given[layer] = nullptr;
+  c->logits_given[layer] = logits_dev != nullptr;
   const RouteParams p = make_route_params(c);
   if (!out_host && x_dev && routed_everywhere(c)) {
     // nobody waits: only the logits are made by this call, over several compute units (route_kernel takes 8.9 us for 8 experts
@@ -663,6 +666,7 @@ int moe_stack_route_step(moe_cache_t *c, int32_t layer, float *h_dev, const floa
   if (c->deferred >= 0)
     if (int rc = settle(c, c->deferred)) return rc;
   c->x_given[layer] = !out_host && c->x_fixed ? x_dev : nullptr;
+  c->logits_given[layer] = 0;
   const RouteParams p = make_route_params(c);
   const int form = out_host ? MOE_BOUNDARY_OWN_LAUNCH : boundary_form(c);
   // the pending expert output is summed first (into y_dev if given, else into the library's own buffer)
@@ -828,6 +832,8 @@ int moe_expert_forward(moe_cache_t *c, int32_t layer, const void *x_dev, void *y
     c->pending_miss = misses;
   }
   c->routed[layer] = 0;
+  // the caller's logits are the caller's again when this call returns: the decision says that they have been read
+  if (on_device && c->logits_given[layer]) return read_note(c, layer, c->route_seq[layer]);
   return MOE_OK;
 }
 

@@ -219,3 +219,27 @@ def test_a_step_is_not_captured():
     dec.compute_stream.synchronize()
     assert float(y.float().abs().max()) > 0
     dec.close()
+
+
+def test_the_callers_logits_are_the_callers_again():
+    """A step on given logits that nobody waits for: moe_expert_forward returns once they have been read, so a caller may
+    put the next token's into the same buffer, from any stream.  (The stream is held by a kernel of a fixed length.)"""
+    cfg = config("bf16", 1024, 96, 32)
+    print("case logits refilled behind moe_expert_forward", flush=True)
+    store, dec = build(cfg, lam=0.0)
+    zs = workloads.logits_stream(cfg, 5, layer=0, scale=2.0).to(DEV)
+    z = torch.zeros_like(zs[0])
+    x = torch.randn(1024, device=DEV).to(torch.bfloat16)
+    y = torch.zeros_like(x)
+    for t in range(5):
+        z.copy_(zs[t])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(dec.compute_stream):
+            torch.cuda._sleep(20_000_000)
+        dec.route_step(0, logits=z, wait=False)
+        dec.expert_forward(0, x, y)
+        z.fill_(-1.0)
+        torch.cuda.current_stream().synchronize()
+        want = torch.sort(zs[t], descending=True).indices[:cfg.top_k].tolist()
+        assert list(dec.last_route(0).sel_expert[:cfg.top_k]) == want
+    dec.close()
