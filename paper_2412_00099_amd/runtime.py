@@ -79,7 +79,11 @@ class ExpertStore:
 
 
 class MoEDecoder:
-    """One library context over an ExpertStore."""
+    """One library context over an ExpertStore.
+
+    The kernels run on compute_stream.  Without waiting (wait=False) the calls return before they have run: x, h and y
+    then belong to the library until compute_stream has passed the call's work, whatever stream they were made on.
+    """
 
     def __init__(self, store: ExpertStore, *, top_k, top_j=0, lam=0.0, renormalize=False, initial=None,
                  delta_fixed=None, delta_per_token=False, route_mode=B.MOE_ROUTE_CACHE_PRIOR, max_rank=0,
@@ -136,6 +140,8 @@ class MoEDecoder:
         return B.moe_route_step(self.ctx, layer, _ptr(x), _ptr(logits), out, wait)
 
     def stack_route_step(self, layer, h, a, perturb, x, carry=True, y=None, out=None, wait=True):
+        if a is not None and not wait:  # (often a temporary: its memory must not be given out again before it has been read)
+            a.record_stream(self.compute_stream)
         return B.moe_stack_route_step(self.ctx, layer, _ptr(h), _ptr(a), perturb, int(carry), _ptr(x), _ptr(y), out, wait)
 
     def expert_forward(self, layer, x, y):

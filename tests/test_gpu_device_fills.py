@@ -243,3 +243,32 @@ def test_the_callers_logits_are_the_callers_again():
         want = torch.sort(zs[t], descending=True).indices[:cfg.top_k].tolist()
         assert list(dec.last_route(0).sel_expert[:cfg.top_k]) == want
     dec.close()
+
+
+def test_a_temporary_a_is_not_given_out_again():
+    """The residual input of a boundary that nobody waits for is a temporary of the caller's: its memory stays its own until
+    the kernel that reads it has run."""
+    cfg = config("bf16", 1024, 96, 32)
+    print("case temporary a", flush=True)
+    a = workloads.ar1_stream(cfg, 1).to(DEV)[0, 0]
+    out = []
+    for hold in (False, True):
+        store, dec = build(cfg, lam=0.0)
+        h = torch.zeros(1024, device=DEV)
+        x = torch.zeros(1024, dtype=torch.bfloat16, device=DEV)
+        y = torch.zeros_like(x)
+        torch.cuda.synchronize()
+        temporary = a * 2.0
+        torch.cuda.synchronize()
+        if hold:
+            with torch.cuda.stream(dec.compute_stream):
+                torch.cuda._sleep(20_000_000)
+        dec.stack_route_step(0, h, temporary, 1.0, x, carry=False, wait=False)
+        dec.expert_forward(0, x, y)
+        del temporary
+        others = [torch.full((1024,), 7.0, device=DEV) for _ in range(64)]
+        torch.cuda.synchronize()
+        out.append((h.cpu(), y.cpu()))
+        del others
+        dec.close()
+    assert torch.equal(out[0][0], (a * 2.0).cpu()) and torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
