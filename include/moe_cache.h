@@ -301,6 +301,10 @@ int moe_cache_plan(moe_cache_t *ctx, moe_cache_plan_t *out_host);
  * workgroup of the layer's expert launch (boundary_in_expert_launch above), or the routing in every workgroup of it. */
 enum { MOE_BOUNDARY_OWN_LAUNCH = 0, MOE_BOUNDARY_IN_FIRST_WORKGROUP = 1, MOE_BOUNDARY_ROUTED_EVERYWHERE = 2 };
 int moe_cache_boundary_form(moe_cache_t *ctx, int32_t *out_host);
+/* Who brings in the experts that miss in a step that nobody waits for (see moe_expert_forward): the host, with copies that
+ * it enqueues once it knows the decision, or the expert launch. */
+enum { MOE_FILLS_BY_HOST = 0, MOE_FILLS_IN_EXPERT_LAUNCH = 1 };
+int moe_cache_fill_form(moe_cache_t *ctx, int32_t *out_host);
 
 /* Average duration in microseconds of the timed expert-GEMV launches that covered a whole layer (no expert missing)
  * since the last call with reset != 0, and their count; measured with start/stop events attached to the launches

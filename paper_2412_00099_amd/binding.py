@@ -21,6 +21,7 @@ MOE_DELTA_RUNNING_MEAN, MOE_DELTA_FIXED, MOE_DELTA_TOKEN = 0, 1, 2
 MOE_ROUTE_CACHE_PRIOR, MOE_ROUTE_MAX_RANK, MOE_ROUTE_CUMSUM = 0, 1, 2
 MOE_POLICY_LRU, MOE_POLICY_FARTHEST = 0, 1
 MOE_BOUNDARY_OWN_LAUNCH, MOE_BOUNDARY_IN_FIRST_WORKGROUP, MOE_BOUNDARY_ROUTED_EVERYWHERE = 0, 1, 2
+MOE_FILLS_BY_HOST, MOE_FILLS_IN_EXPERT_LAUNCH = 0, 1
 
 WEIGHT_FMT = {"fp32": MOE_W_FP32, "bf16": MOE_W_BF16, "int8": MOE_W_INT8_PC, "int4": MOE_W_INT4_G128}
 ACT_FMT = {"fp32": MOE_A_FP32, "bf16": MOE_A_BF16}
@@ -141,6 +142,8 @@ lib.moe_cache_plan.restype = C.c_int
 lib.moe_cache_plan.argtypes = [_vp, C.POINTER(moe_cache_plan_t)]
 lib.moe_cache_boundary_form.restype = C.c_int
 lib.moe_cache_boundary_form.argtypes = [_vp, C.POINTER(C.c_int32)]
+lib.moe_cache_fill_form.restype = C.c_int
+lib.moe_cache_fill_form.argtypes = [_vp, C.POINTER(C.c_int32)]
 lib.moe_cache_set_lambda.restype = C.c_int
 lib.moe_cache_set_lambda.argtypes = [_vp, C.c_float]
 lib.moe_cache_set_baseline.restype = C.c_int
@@ -157,7 +160,7 @@ lib.moe_last_error.argtypes = []
 EXPORTS = [
     "moe_blob_bytes", "moe_slot_bytes", "moe_pack_expert", "moe_cache_init", "moe_cache_destroy", "moe_route_step", "moe_stack_route_step",
     "moe_expert_forward", "moe_route_batch", "moe_expert_forward_batch", "moe_expert_forward_static", "moe_cache_last_route", "moe_cache_stats", "moe_cache_tables", "moe_cache_snapshot",
-    "moe_cache_restore", "moe_trace_misses", "moe_cache_plan", "moe_cache_boundary_form", "moe_cache_set_lambda",
+    "moe_cache_restore", "moe_trace_misses", "moe_cache_plan", "moe_cache_boundary_form", "moe_cache_fill_form", "moe_cache_set_lambda",
     "moe_cache_set_baseline", "moe_cache_reset", "moe_residual_rmsnorm", "moe_cache_profile", "moe_last_error",
 ]
 
@@ -300,6 +303,12 @@ def moe_cache_plan(ctx) -> moe_cache_plan_t:
 def moe_cache_boundary_form(ctx) -> int:
     out = C.c_int32()
     _check(lib.moe_cache_boundary_form(ctx, C.byref(out)), "moe_cache_boundary_form")
+    return out.value
+
+
+def moe_cache_fill_form(ctx) -> int:
+    out = C.c_int32()
+    _check(lib.moe_cache_fill_form(ctx, C.byref(out)), "moe_cache_fill_form")
     return out.value
 
 

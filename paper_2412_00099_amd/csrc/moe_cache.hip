@@ -1244,6 +1244,12 @@ int moe_cache_boundary_form(moe_cache_t *c, int32_t *out) {
   return MOE_OK;
 }
 
+int moe_cache_fill_form(moe_cache_t *c, int32_t *out) {
+  if (!c || !out) return fail(MOE_EINVAL, "NULL argument");
+  *out = c->d_host_blob != nullptr ? MOE_FILLS_IN_EXPERT_LAUNCH : MOE_FILLS_BY_HOST;
+  return MOE_OK;
+}
+
 namespace {
 constexpr size_t kProfEvents = 1u << 15;  // launches timed between two resets
 }

@@ -175,6 +175,9 @@ class MoEDecoder:
     def boundary_form(self):
         return B.moe_cache_boundary_form(self.ctx)
 
+    def fill_form(self):
+        return B.moe_cache_fill_form(self.ctx)
+
     def set_lambda(self, lam):
         B.moe_cache_set_lambda(self.ctx, lam)
 

@@ -6,10 +6,13 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2412_00099_amd as pkg
 from synth import workloads
 from synth.workloads import CONFIGS
 
+import test_gpu_route
 from _gpu_common import DEV, build
+from test_gpu_poison import poisoned_slots
 from test_gpu_route import free_run
 
 pytestmark = pytest.mark.gpu
@@ -48,6 +51,7 @@ def test_slots_hold_the_host_tiers_bytes(fmt, hidden, inter, shared, everywhere,
     cfg = config(fmt, hidden, inter, shared)
     print(f"case device fills {fmt} hidden={hidden} inter={inter} everywhere={everywhere}", flush=True)
     store, dec = build(cfg, lam=0.0)
+    assert dec.fill_form() == pkg.MOE_FILLS_IN_EXPERT_LAUNCH
     h = torch.zeros(hidden, device=DEV)
     x = torch.zeros(hidden, dtype=cfg.act_dtype, device=DEV)
     y = torch.zeros_like(x)
@@ -86,6 +90,7 @@ def test_every_workgroup_finds_the_slots_by_itself(N, K, C, n_initial, mode, top
         monkeypatch.setenv("MOE_DEVICE_FILLS", on)
         store, dec = build(cfg, lam=0.1, top_j=top_j, initial=[list(range(N))[N - n_initial:]] if n_initial else None,
                            route_mode=mode, max_rank=min(2 * K, N), cumsum_p=0.5)
+        assert dec.fill_form() == int(on)
         xs = workloads.ar1_stream(cfg, 24)[:, 0].to(cfg.act_dtype).to(DEV)
         ys = torch.zeros_like(xs)
         torch.cuda.synchronize()
@@ -104,9 +109,11 @@ def test_every_workgroup_finds_the_slots_by_itself(N, K, C, n_initial, mode, top
 
 
 @pytest.mark.parametrize("fmt,hidden,inter,shared", SHAPES)
-def test_outputs(fmt, hidden, inter, shared):
+def test_outputs(fmt, hidden, inter, shared, monkeypatch):
+    """(What the slots hold at first would make y NaN: an expert's record is used before it is in its slot by nobody.)"""
     cfg = config(fmt, hidden, inter, shared)
     print(f"case device fills outputs {fmt} hidden={hidden} inter={inter}", flush=True)
+    poisoned_slots(monkeypatch, test_gpu_route)
     free_run(cfg, 0.0, 10, deferred=True)
 
 
@@ -114,7 +121,8 @@ def test_outputs(fmt, hidden, inter, shared):
                                  dict(MOE_FUSE_BOUNDARY="0", MOE_ROUTE_EVERYWHERE="0")])
 @pytest.mark.parametrize("fmt", ["bf16", "int8", "int4"])
 def test_same_outputs_as_with_fills_by_the_host(fmt, env, monkeypatch):
-    """The two ways add the same products in another order: outputs to bf16 rounding, decisions the same."""
+    """In every form of the boundary: outputs to bf16 rounding (with the boundary in the first workgroup the two ways split the
+    records that missed over 255 and over 256 workgroups; the other two forms are bit for bit, see below), decisions the same."""
     cfg = (C4 if fmt == "int4" else C2).with_(n_layers=2, hidden=2048, inter=384, shared_inter=512, n_experts=12, capacity=5,
                                               top_k=4, weight_fmt=fmt, seed=8200)
     print(f"case device fills against host fills {fmt} {env}", flush=True)
@@ -124,6 +132,7 @@ def test_same_outputs_as_with_fills_by_the_host(fmt, env, monkeypatch):
     for on in ("1", "0"):
         monkeypatch.setenv("MOE_DEVICE_FILLS", on)
         store, dec = build(cfg, lam=0.0)
+        assert dec.fill_form() == int(on)
         h = torch.zeros(cfg.hidden, device=DEV)
         x = torch.zeros(cfg.hidden, dtype=cfg.act_dtype, device=DEV)
         a = workloads.ar1_stream(cfg, 8).to(DEV)
@@ -155,6 +164,7 @@ def test_bit_for_bit_as_with_fills_by_the_host(fmt, shared, inter, everywhere, m
     for on in ("1", "0"):
         monkeypatch.setenv("MOE_DEVICE_FILLS", on)
         store, dec = build(cfg, lam=0.0)
+        assert dec.fill_form() == int(on)
         h = torch.zeros(cfg.hidden, device=DEV)
         x = torch.zeros(cfg.hidden, dtype=cfg.act_dtype, device=DEV)
         a = workloads.ar1_stream(cfg, 8).to(DEV)
@@ -173,8 +183,6 @@ def test_bit_for_bit_as_with_fills_by_the_host(fmt, shared, inter, everywhere, m
 
 def test_host_tier_that_is_not_pinned(monkeypatch):
     """The launch cannot read such memory: the host enqueues the fills, as it does where it waits for the decision."""
-    import paper_2412_00099_amd as pkg
-
     cfg = config("bf16", 1024, 96, 32)
     print("case host tier not pinned", flush=True)
     out = []
@@ -185,6 +193,7 @@ def test_host_tier_that_is_not_pinned(monkeypatch):
             store.host = store.host.clone()
             assert not store.host.is_pinned()
             dec = pkg.MoEDecoder(store, top_k=cfg.top_k)
+        assert dec.fill_form() == (pkg.MOE_FILLS_IN_EXPERT_LAUNCH if pinned else pkg.MOE_FILLS_BY_HOST)
         xs = workloads.ar1_stream(cfg, 8)[:, 0].to(cfg.act_dtype).to(DEV)
         ys = torch.zeros_like(xs)
         torch.cuda.synchronize()
@@ -198,11 +207,10 @@ def test_host_tier_that_is_not_pinned(monkeypatch):
 
 
 def test_a_step_is_not_captured():
-    import paper_2412_00099_amd as pkg
-
     cfg = config("bf16", 1024, 96, 32)
     print("case capture refused", flush=True)
     store, dec = build(cfg, lam=0.0)
+    assert dec.fill_form() == pkg.MOE_FILLS_IN_EXPERT_LAUNCH
     x = torch.randn(1024, device=DEV).to(torch.bfloat16)
     y = torch.zeros_like(x)
     torch.cuda.synchronize()
