@@ -325,7 +325,12 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
 #pragma unroll
     for (int c = 0; c < LPR; ++c) record_store(to, (c * kWave + lane) * 16, row[c]);
   };
-  // A ring of DEPTH records, refilled in two parts (see expert_gemv_kernel).  37 MB at d = 2048: 13.1 -> 12.1 us
+  // A ring of DEPTH records, refilled in two parts (see expert_gemv_kernel).  37 MB at d = 2048: 13.1 -> 12.1 us.  Records of
+  // 12 KB (d = 4096) are refilled whole, behind the axpy: the launches are long and their loads queue anyway, and the next
+  // record's two thirds ahead of the rest of this one's arithmetic only delay it.  352 MB, refilled in two parts / whole: stack
+  // 66.7 / 65.5 us a layer-token, launch by events 60.6 / 59.2; static 58.6 / 57.9 (13 to 201 MB the same; d = 2048 static 37 MB
+  // 11.64 / 11.74).
+  constexpr bool kInParts = LPR < 4;
   auto turn = [&](RecI8<LPR> &R, auto refill_tag, auto fill_tag) MOE_INLINE {
     constexpr bool REFILL = decltype(refill_tag)::value, FILL = decltype(fill_tag)::value;  // FILL: into a slot on the way
     float a = 0.f;
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
     }
     RecBuffer q;
     bool want = false;
-    if constexpr (REFILL) {
+    if constexpr (REFILL && kInParts) {
       want = walk.step(p);
       q = load_up(R, want);
     }
@@ -357,6 +362,10 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int8_kernel(GemvParams 
       }
     }
     if constexpr (REFILL) {
+      if constexpr (!kInParts) {
+        want = walk.step(p);
+        q = load_up(R, want);
+      }
       load_down(R, q);
       R.want = want;
     }
