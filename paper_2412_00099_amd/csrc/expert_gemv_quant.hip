@@ -552,8 +552,9 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
         xp[c * 16 + w * 4 + t] = pr;
         if (t & 1) s_odd += f16_lo(pr) + f16_hi(pr); else s_even += f16_lo(pr) + f16_hi(pr);
       }
-    // odd entries hold x / 16: 1024 * (x / 16) = 64 x of bias, and 8 x = 128 * (x / 16) of zero point
-    xoff[c] = -((1024.f + 8.f) * s_even + (1024.f + 128.f) * s_odd);
+    // odd entries hold x / 16: 1024 * (x / 16) = 64 x of bias, and 8 x = 128 * (x / 16) of zero point.  (Which of the two
+    // products is rounded is said here: left to the compiler it changed with code far away, and the bits of y with it.)
+    xoff[c] = -__builtin_fmaf(1024.f + 8.f, s_even, (1024.f + 128.f) * s_odd);
   }
 
   float y[CPL], acc[CPL];
@@ -563,10 +564,9 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
   bool dirty = false;  // acc holds something (scales of a group nothing was taken from are never applied)
 
   // even columns: y += s * (acc - (1024 + 8) * hsum);  odd columns (weights taken 16-fold):
-  // y += (s / 16) * (acc - (1024 + 128) * hsum)
+  // y += (s / 16) * (acc - (1024 + 128) * hsum), both differences rounded once
   auto flush = [&](const uint8_t *base, int rows, int grp) MOE_INLINE {
     const uint16_t *sd = reinterpret_cast<const uint16_t *>(base + (int64_t)rows * rec_bytes) + (int64_t)grp * d;
-    const float off_even = (1024.f + 8.f) * hsum, off_odd = (1024.f + 128.f) * hsum;
 #pragma unroll
     for (int c = 0; c < LPR; ++c) {
       const u32x4 *sp = reinterpret_cast<const u32x4 *>(sd + (c * kWave + lane) * VEC);
@@ -577,8 +577,8 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int j = c * VEC + q4 * 8 + t * 2;
-          y[j] = __builtin_fmaf(f16_lo(sw[t]), acc[j] - off_even, y[j]);
-          y[j + 1] = __builtin_fmaf(f16_hi(sw[t]) * 0.0625f, acc[j + 1] - off_odd, y[j + 1]);
+          y[j] = __builtin_fmaf(f16_lo(sw[t]), __builtin_fmaf(-(1024.f + 8.f), hsum, acc[j]), y[j]);
+          y[j + 1] = __builtin_fmaf(f16_hi(sw[t]) * 0.0625f, __builtin_fmaf(-(1024.f + 128.f), hsum, acc[j + 1]), y[j + 1]);
           acc[j] = acc[j + 1] = 0.f;
         }
       }
@@ -675,13 +675,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     }
     if (R.want) {
       down_part(R, a);
-      if constexpr (FILL) {
-        put(R.fill + (int64_t)R.at * rec_bytes + 2 * kRowBytes, R.dn);
-        const int64_t tail = (int64_t)R.rows * rec_bytes;
-        // the record's share of what stands behind the records: d / 1024 times 16 bytes of down scales
-        const uint32_t off = lane < CPL * kWave / 1024 ? (uint32_t)(R.at * (CPL * kWave / 1024) + lane) * 16u : ~0u;
-        copy_tail16(R.base + tail, R.fill + tail, R.rows / 128 * (CPL * kWave * 2), off);
-      }
+      if constexpr (FILL) put(R.fill + (int64_t)R.at * rec_bytes + 2 * kRowBytes, R.dn);
     }
     if constexpr (REFILL) {
       load_down(R, q);
@@ -719,6 +713,20 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     for (int j = 0; j < DEPTH; ++j) fetch(ring[j], true);
     walk_list((walk.remaining() + DEPTH - 1) / DEPTH, std::true_type{});
     reduce_and_store<NW, VEC, LPR>(y, red, row + (int64_t)p.missing_row * d, tid, lane, wave);
+    // What stands behind the records, d / 1024 times 16 bytes of down scales a record: the workgroup's records' share of it,
+    // here, where the ring and the sums are no longer needed.  (Record by record in the walk it took the kernel from 135 to 216
+    // registers at d = 2048, now 141.  Above 168 a compute unit holds one workgroup, and in a launch that routes in every workgroup
+    // the last one to stream then started behind the one that does the cache update: 18.4 -> 16.9 us by events, 36 MB, a third
+    // of it shared.)
+    constexpr int kTail = CPL * kWave / 64;  // bytes
+    for (int seg = 0; seg < p.top_k; ++seg) {
+      int first, last;
+      if (!walk.missing_rows(p, seg, first, last)) continue;
+      const int64_t at = (int64_t)p.inter * rec_bytes;
+      const int bytes = p.inter * kTail;
+      for (int off = first * kTail + tid * 16; off < last * kTail; off += NW * kWave * 16)
+        copy_tail16(walk.base + at, walk.fill_blob + at, bytes, (uint32_t)off);
+    }
   }
 }
 

@@ -356,6 +356,18 @@ struct RecordWalker {
     base = reinterpret_cast<const uint8_t *>(((caddr)(reinterpret_cast<uintptr_t>(p.host_blob)))[expert]);
   }
 
+  // Whether selected expert `seg` missed and the workgroup owns some of its records: which (up to last), and base and
+  // fill_blob set as for a run of it.  For what is put into the slot apart from the records.
+  __device__ __forceinline__ bool missing_rows(const GemvParams &p, int seg, int &first, int &last) {
+    const int I = p.inter;
+    first = max(q0 - seg * I, 0);
+    last = min(q0 + nr - seg * I, I);
+    if (((miss_mask >> seg) & 1u) == 0 || first >= last) return false;
+    base = p.slot_pool + (int64_t)((slots >> (8 * seg)) & 0xffu) * p.slot_bytes;
+    from_host_tier(p, seg);
+    return true;
+  }
+
   // Move to this wavefront's next list entry and describe its record; whether there is one and the pass covers it.  The
   // caller issues the same loads in any case, from an empty resource where the answer is no (record_buffer): the number
   // of loads in flight then depends on nothing, and the compiler can wait for exactly the oldest record.  (Loads inside

@@ -1,6 +1,6 @@
 """The same inputs give the same bits from version to version: digests of fp32 outputs of the allocation-free entry point, for
 every weight format, hidden size and enough records that a wavefront walks several (whichever copy of its loop adds a record,
-the sums are rounded alike).  Parity unpinned: the digests are those of an earlier build of this library, whose outputs the other
+the sums are rounded alike); and routed steps, whose kernels are compiled apart, give the bits of that entry point.  Parity unpinned: the digests are those of an earlier build of this library, whose outputs the other
 tests hold against the oracle; they belong to 256 compute units, which is what the records are split over."""
 import ctypes as C
 import hashlib
@@ -78,3 +78,34 @@ def test_bits(case):
         pytest.skip("the digests are for 256 compute units")
     print("case bits", case, flush=True)
     assert digest(*case) == BITS[case]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("way", ["waited for", "routed ahead", "routed everywhere"])
+@pytest.mark.parametrize("case", [c for c in sorted(BITS) if c[1] >= 1024])
+def test_routed_steps_give_the_same_bits(case, way, monkeypatch):
+    fmt, hidden, inter, shared, top_k = case
+    print("case routed bits", case, way, flush=True)
+    monkeypatch.setenv("MOE_ROUTE_EVERYWHERE", "1" if way == "routed everywhere" else "0")
+    rng, n = np.random.default_rng([hidden, inter, shared, top_k, 1]), top_k + 1
+    store = moe.ExpertStore(n_layers=1, hidden=hidden, n_experts=n, inter=inter, shared_inter=shared, capacity=n, weight_fmt=fmt,
+                            act_fmt="fp32", device=DEV)
+    for e in range(n):
+        store.host[0, e].copy_(_blob(fmt, hidden, inter, rng))
+    if shared:
+        store.shared[0].copy_(_blob(fmt, hidden, shared, rng))
+    store.put_gate(0, torch.from_numpy(rng.standard_normal((n, hidden), dtype=np.float32) * np.float32(0.02)))
+    x = torch.from_numpy(rng.standard_normal(hidden, dtype=np.float32)).to(DEV)
+    y, y_static = torch.zeros_like(x), torch.zeros_like(x)
+    dec = moe.MoEDecoder(store, top_k=top_k, lam=0.0, initial=[list(range(n))])
+    dec.route_step(0, x=x, wait=way == "waited for")
+    dec.expert_forward(0, x, y)
+    rec = dec.last_route(0)
+    moe.moe_expert_forward_static(moe.WEIGHT_FMT[fmt], moe.ACT_FMT["fp32"], hidden, inter, shared, top_k,
+                                  C.c_void_p(store.pools[0].data_ptr()), n, C.c_void_p(store.shared[0].data_ptr()) if shared else None,
+                                  list(rec.sel_slot)[:top_k], list(rec.sel_weight)[:top_k], C.c_void_p(x.data_ptr()),
+                                  C.c_void_p(y_static.data_ptr()), C.c_void_p(dec.compute_stream.cuda_stream))
+    torch.cuda.synchronize()
+    dec.close()
+    assert not any(list(rec.miss)[:top_k]) and float(y.abs().max()) > 0
+    assert torch.equal(y, y_static)
