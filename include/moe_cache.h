@@ -153,8 +153,10 @@ void moe_cache_destroy(moe_cache_t *ctx);
  * returned.  x_dev is read by kernels of both calls and must stay unchanged until compute_stream has run them.
  * With out_host non-NULL the call returns once the decision is known on the host (written to *out_host)
  * and the copies filling missed experts' slots are enqueued on copy_stream.  With out_host NULL the call
- * only enqueues the router kernel or, with x_dev and from d = 1024 on, the gate logits alone (the expert launch then
- * routes by itself; smaller d: from 10 MB a layer-token on), and moe_expert_forward takes care of the fills (see there).  MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
+ * only enqueues the router kernel or, with x_dev and where the rule for MOE_BOUNDARY_ROUTED_EVERYWHERE holds (any size from
+ * d = 1024 on, below that 10 MB a layer-token; Cumsum-Threshold with int4 later), the gate logits alone: the expert launch
+ * then routes by itself.  moe_expert_forward takes care of the fills (see there).
+ * MOE_ESTATE if the layer's previous step has not been followed by moe_expert_forward. */
 int moe_route_step(moe_cache_t *ctx, int32_t layer, const void *x_dev, const float *logits_dev,
                    moe_route_out_t *out_host);
 
@@ -166,8 +168,9 @@ int moe_route_step(moe_cache_t *ctx, int32_t layer, const void *x_dev, const flo
  * blobs itself, computes with them and puts them into their slots on the way; the call returns at once (after a step
  * on given logits: once these have been read).  Whatever its kernels read - x_dev, h_dev and a_dev of a
  * moe_stack_route_step, the host blobs - then has to stay valid and unchanged until compute_stream has run them, not only
- * until the call returns.  That needs all host blobs in pinned memory that the device can read; where some are not (or with MOE_DEVICE_FILLS=0 in the environment
- * at moe_cache_init) the call waits for the decision, enqueues the fills on copy_stream and proceeds as above.
+ * until the call returns.  That needs all host blobs in pinned memory that the device can read; where some are not (or with
+ * MOE_DEVICE_FILLS=0 in the environment at moe_cache_init) the call waits for the decision, enqueues the fills on
+ * copy_stream and proceeds as above.
  * A step cannot be captured into a graph (MOE_EHIP).  MOE_ESTATE without a preceding moe_route_step.
  * y_dev may be NULL: the output then stays inside the library as fp32 partial sums and is finished by the next
  * moe_stack_route_step (of any layer), which must follow before another moe_expert_forward. */

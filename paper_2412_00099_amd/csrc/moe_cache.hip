@@ -1,5 +1,6 @@
-// Host side of libmoe_cache: argument checking, the context, the per-layer step sequence
-// (route kernel -> host learns the misses -> fills on the copy stream -> expert kernels) and statistics.
+// Host side of libmoe_cache: argument checking, the context, the per-layer step sequence and statistics.  A step that nobody
+// waits for is enqueued and left alone: routing, the experts and what misses run on the device.  Only one that is waited for
+// goes route kernel -> host learns the misses -> fills on the copy stream -> expert kernels.
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -379,9 +380,13 @@ int moe_cache_init(const moe_cache_config_t *cfg, const moe_cache_buffers_t *b, 
   // gate matrix alone costs it time in proportion to d: about 20 KB of shared records per hidden column are wanted for that.
   // Routing everywhere spreads the gate matrix; against that, the launch of its own sums the pending output and does the glue
   // of small hidden sizes in one launch less where a token begins, which only the smallest layers feel.
-  // Cumsum-Threshold walks all ranks in every wavefront; only int4, whose launches are the shortest for what they hold
-  // in registers, does not hide that: d = 2048, 60 experts 3.2 MB 20.7 / 23.4, 35.7 MB 28.5 / 30.5; d = 4096, 6.5 MB 26.4 /
-  // 27.0 (bf16 d = 2048, 6.3 MB 20.0 / 16.9; int8 12.6 MB 21.2 / 18.8).
+  // Cumsum-Threshold walks all ranks in every wavefront (bf16 d = 2048, 6.3 MB 20.0 / 16.9; int8 12.6 MB 21.2 / 18.8).  The lines
+  // for int4 were drawn when its launch was longer by what its registers cost (see expert_gemv_int4_kernel): own launch / every
+  // workgroup then, d = 2048, 64 experts 22.7 MB 27.6 / 30.4, 97 MB 40.0 / 41.6, 32 experts 38.9 MB 29.1 / 28.8; d = 4096, 60
+  // experts 3.2 MB 28.2 / 29.4, 22.7 MB 31.4 / 31.1.  Now: d = 2048, 60 experts 1.6 MB 20.5 / 18.4, 35 MB 27.0 / 24.6, 64 experts
+  // 95 MB 42.5 / 39.7, 32 experts 20 MB 21.6 / 19.4, 38 MB 26.1 / 24.0; d = 4096, 60 experts 6.4 MB 26.2 / 26.2, 22.5 MB 28.4 /
+  // 28.4, 45 MB 31.3 / 30.9, 32 experts 3.2 MB 24.8 / 23.4.  So d = 2048 has no reason for a line any more; which form a context
+  // takes is something callers can ask for, and it is left as it was.
   // MOE_FUSE_BOUNDARY=0 / 1 and MOE_ROUTE_EVERYWHERE=0 / 1 in the environment override the two rules.
   const int64_t records = (int64_t)cfg->top_k * cfg->inter + cfg->shared_inter, streamed = records * c->slot_layout.rec_bytes;
   // (whichever form is taken: what a wrong x_dev meets depends on the shared expert's share alone)
