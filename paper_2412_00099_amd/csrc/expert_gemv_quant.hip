@@ -716,7 +716,7 @@ __global__ __launch_bounds__(NW *kWave) void expert_gemv_int4_kernel(GemvParams 
     // What stands behind the records, d / 1024 times 16 bytes of down scales a record: the workgroup's records' share of it,
     // here, where the ring and the sums are no longer needed.  (Record by record in the walk it took the kernel from 135 to 216
     // registers at d = 2048, now 141.  Above 168 a compute unit holds one workgroup, and in a launch that routes in every workgroup
-    // the last one to stream then started behind the one that does the cache update: 18.4 -> 16.9 us by events, 36 MB, a third
+    // the last one to stream then started behind the one that does the cache update: 18.4 -> 16.9 us by events, 36 MB, a quarter
     // of it shared.)
     constexpr int kTail = CPL * kWave / 64;  // bytes
     for (int seg = 0; seg < p.top_k; ++seg) {
